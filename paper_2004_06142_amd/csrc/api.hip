@@ -183,6 +183,8 @@ struct Plan {
   int nbf, nact, naux, npairs, ncwo, nsingle, functional, prec, ints;
   int pc, ns2, ns3, xv, yv;
   int ldk, ldx, ldxx, ldw, nact32;
+  int ldb;      // bf16 family: row length of B as X reads it (nbf rounded up to 16 bytes)
+  bool packb;   // bf16 B whose rows are not 16-byte aligned: X reads a padded copy of the chunk
   bool split;   // bf16 family
   bool f32;     // PNOF_FP32: the float64 path's kernels in float32
   int terms;    // 1 or 3
@@ -209,6 +211,8 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   pl.ldxx = (int)round_up(pl.nact, 32);
   pl.ldw = (int)round_up(pl.nact, 32);
   pl.nact32 = (int)round_up(pl.nact, 32);
+  pl.ldb = (int)round_up(pl.nbf, 8);
+  pl.packb = pl.split && p->ints == PNOF_INTS_DF_BF16 && pl.ldb != pl.nbf;
   if (!is_df(p->ints)) { pl.pc = pl.ns2 = pl.ns3 = 1; pl.xv = pl.yv = 1; return pl; }
   // block tiles of the split contractions: the 256 x 256 tile (variant 3) halves the LDS and operand
   // traffic per product, and is the automatic choice when it pads the output no more than the 128
@@ -318,8 +322,10 @@ Bufs carve(const Plan& pl, char* base) {
       }
       b.Ypart32 = a.take<float>((long long)pl.ns3 * ny);
       if (pl.ints == PNOF_INTS_DF_F64) {
-        b.bh = a.take<u16>((long long)pl.pc * pl.nbf * pl.nbf);
-        b.bl = a.take<u16>((long long)pl.pc * pl.nbf * pl.nbf);
+        b.bh = a.take<u16>((long long)pl.pc * pl.nbf * pl.ldb);
+        b.bl = a.take<u16>((long long)pl.pc * pl.nbf * pl.ldb);
+      } else if (pl.packb) {
+        b.bh = a.take<u16>((long long)pl.pc * pl.nbf * pl.ldb);
       }
     }
   } else {
@@ -400,13 +406,24 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
   char* ws = nullptr;
   pnof_status st = PNOF_OK;
   if (r.ws) {
-    // fit the caller's region: fewer rows of B per chunk until the plan's workspace fits
+    // fit the caller's region: fewer rows of B per chunk until the plan's workspace fits.  The padded
+    // rows of B are not counted (they are an option: X also reads unaligned rows, more slowly), and
+    // used when there is room for them at that chunk length.
+    auto plain = [&](Plan q) {
+      q.packb = false;
+      q.ldb = q.nbf;
+      return q;
+    };
     pnof_tuning tu = ctx->tune;
+    b = carve(plain(pl), nullptr);
     while (b.bytes > r.ws_bytes && pl.pc > 1) {
       tu.pchunk = std::max(1, pl.pc / 2);
       pl = make_plan(prob, tu);
-      b = carve(pl, nullptr);
+      b = carve(plain(pl), nullptr);
     }
+    const Bufs padded = carve(pl, nullptr);
+    if (padded.bytes <= r.ws_bytes) b = padded;
+    else pl = plain(pl);
     if (b.bytes > r.ws_bytes)
       return fail(ctx, PNOF_E_UNSUPPORTED,
                   "the problem needs " + std::to_string(b.bytes) + " bytes of workspace, more than the " +
@@ -562,14 +579,17 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
       auto chunk_rows = [&](int c) { return (int)std::min<long long>(pl.pc, pl.naux - (long long)c * pl.pc); };
       // row bounds of every chunk of B in one pass before the first X (beside the contractions it
       // would take their compute units: measured slower)
+      bool raise = false;
       if (split) {
         const auto& bd = ctx->bound;
         if (bd.ints && bd.ints == ints && bd.nbf == nbf && bd.naux == pl.naux && bd.kind == pl.ints && bd.pc == pl.pc)
           DEV_CHECK(ctx, hipMemcpyAsync(b.bnd + SCL_CALL, bd.words, bd.nwords * sizeof(uint32_t),
                                         hipMemcpyDeviceToDevice, s));   // bound integrals: kept bounds
-        else
-          DEV_CHECK(ctx, b_bounds(s, ints, pl.ints == PNOF_INTS_DF_F64, (long long)pl.naux * nbf, nbf, nbf,
+        else if (!pl.packb)   // with padded rows the copy of a chunk forms its bounds
+          DEV_CHECK(ctx, b_bounds(s, ints, pl.ints == PNOF_INTS_DF_F64, (long long)pl.naux * nbf, nbf,
                                   (long long)pl.pc * nbf, b.bnd + SCL_CALL));
+        else
+          raise = true;
       }
       auto run_x = [&](int c) -> pnof_status {
         const long long p0 = (long long)c * pl.pc;
@@ -577,19 +597,30 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         SplitPtr Bp;
         SplitPtr A = Ct;
         long long b_bytes;
+        int ldb = pl.ldb;
+        const long long nrows = (long long)np * nbf;
         if (pl.ints == PNOF_INTS_DF_BF16) {
-          Bp.hi = static_cast<const u16*>(ints) + p0 * bsz;
+          const u16* src = static_cast<const u16*>(ints) + p0 * bsz;
           Bp.lo = nullptr;
-          b_bytes = 2LL * (pl.naux - p0) * bsz;
+          if (pl.packb) {
+            b_bytes = 2LL * nrows * ldb;
+            DEV_CHECK(ctx, pack_b(s, nrows, nbf, src, b.bh, ldb, raise ? b.bnd + SCL_CALL + 2 * c : nullptr));
+            Bp.hi = b.bh;
+          } else {
+            ldb = nbf;
+            b_bytes = 2LL * (pl.naux - p0) * bsz;
+            Bp.hi = src;
+          }
         } else {
-          b_bytes = 2LL * np * bsz;
-          DEV_CHECK(ctx, split_b(s, np * bsz, static_cast<const double*>(ints) + p0 * bsz, b.bh, b.bl,
+          b_bytes = 2LL * nrows * ldb;
+          DEV_CHECK(ctx, split_b(s, nrows, nbf, static_cast<const double*>(ints) + p0 * bsz, b.bh, b.bl, ldb,
                                  split ? b.bnd : nullptr, c));
           Bp.hi = b.bh;
           Bp.lo = split ? b.bl : nullptr;
           if (split) A = C16;
         }
-        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_bf16_gemm1(s, nbf, nact, np, pl.terms, A, pl.ldk, Bp, bsz, nbf, b_bytes,
+        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_bf16_gemm1(s, nbf, nact, np, pl.terms, A, pl.ldk, Bp,
+                                                               (long long)nbf * ldb, ldb, b_bytes,
                                                                xth_[c & 1], xtl_[c & 1], pl.ldx, pl.xv, wd, b.bnd, c)));
         return PNOF_OK;
       };
@@ -1267,7 +1298,7 @@ pnof_status pnof_bind_integrals(pnof_ctx ctx, const pnof_problem* prob, const vo
   }
   hipStream_t s = ctx->stream;
   DEV_CHECK(ctx, hipMemsetAsync(bd.words, 0, nw * sizeof(uint32_t), s));   // the bounds are raised from zero
-  DEV_CHECK(ctx, b_bounds(s, ints, pl.ints == PNOF_INTS_DF_F64, (long long)pl.naux * pl.nbf, pl.nbf, pl.nbf,
+  DEV_CHECK(ctx, b_bounds(s, ints, pl.ints == PNOF_INTS_DF_F64, (long long)pl.naux * pl.nbf, pl.nbf,
                           (long long)pl.pc * pl.nbf, bd.words));
   bd.ints = ints;
   bd.nbf = pl.nbf;

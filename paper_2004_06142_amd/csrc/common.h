@@ -558,16 +558,21 @@ hipError_t add_diag_f32(hipStream_t s, int nact, int np, const double* Dchunk, c
 // (h16, l16) of the same value times sC (bnd: call-level words already formed).
 hipError_t split_ca(hipStream_t s, int nbf, int nact, int terms, const double* C, u16* Ct_hi,
                     u16* Ct_lo, u16* Ct_h16, u16* Ct_l16, int ldk, const uint32_t* bnd);
-// float64 B rows of one chunk as the fp16 pair of B sB.
-hipError_t split_b(hipStream_t s, long long n, const double* B, u16* hi, u16* lo, const uint32_t* bnd, int chunk);
+// float64 B rows of one chunk (nrows rows of n) as the fp16 pair of B sB, in rows of ldo (a multiple of
+// 8, zeros from n on; or ldo == n).
+hipError_t split_b(hipStream_t s, long long nrows, int n, const double* B, u16* hi, u16* lo, int ldo, const uint32_t* bnd,
+                   int chunk);
+// bf16 B rows of one chunk (nrows rows of n) copied to rows of ldo (a multiple of 8, zeros from n on);
+// with slot, the chunk's bounds (see b_bounds) raised into slot[0], slot[1] in the same pass.
+hipError_t pack_b(hipStream_t s, long long nrows, int n, const u16* B, u16* out, int ldo, uint32_t* slot);
 // Call-level scale bounds from C_A and n (col: 4 nact floats of scratch) into bnd[0..SCL_CALL), and
 // the nclear per-chunk words after them cleared.
 hipError_t scale_bounds(hipStream_t s, int nbf, int nact, const double* C, const double* n, int npairs, int ncwo,
                         int nsingle, int functional, float* col, uint32_t* bnd, int nclear);
-// Per chunk of rows_per_chunk rows of B (nrows rows, ncols used of ld): the largest row 1-norm and the
-// largest |B|, raised into slot[2c], slot[2c + 1] (the words must start at zero).
-hipError_t b_bounds(hipStream_t s, const void* B, int is_f64, long long nrows, int ncols, long long ld,
-                    long long rows_per_chunk, uint32_t* slot);
+// Per chunk of rows_per_chunk rows of B (nrows rows of n): the largest row 1-norm and the largest |B|,
+// raised into slot[2c], slot[2c + 1] (the words must start at zero).
+hipError_t b_bounds(hipStream_t s, const void* B, int is_f64, long long nrows, int n, long long rows_per_chunk,
+                    uint32_t* slot);
 hipError_t widen_bf16(hipStream_t s, long long n, const u16* src, double* dst);
 hipError_t hpp_from_hc(hipStream_t s, int nbf, int nact, const double* C, const double* HC, double* Hpp);
 // Split-K float64 product for few output tiles: ks (<= F64_KSPLIT_MAX) dense M x N partial slabs in

@@ -578,24 +578,28 @@ __device__ __forceinline__ int find_instance(const int* __restrict__ off, int ni
   return lo;
 }
 
-// gemm1: XT_P[p][mu] = sum_nu Ct[p][nu] B_P[mu][nu], written as a hi/lo pair.  Tile G1M (p) x G1N (mu)
-// in a WGM x WGN wave grid, one P per work item (items covering several P measured slower: the
-// epilogue's stores then stall the next P's operand waits, as the vector-memory counter retires loads
-// and stores in order).
-// STACK: the n-tiles run over the stacked rows (P, mu) of all np rows of B.
+// gemm1: XT_P[p][mu] = sum_nu Ct[p][nu] B_P[mu][nu], written as a hi/lo pair.  Tile G1M (p) x G1N in a
+// WGM x WGN wave grid, one tile per work item (items covering several tiles measured slower: the
+// epilogue's stores then stall the next tile's operand waits, as the vector-memory counter retires
+// loads and stores in order).
+// VEC: the n-tiles run over the stacked rows (P, mu) of all np rows of B (bstride == nbf * ldb), so only
+// the last tile of the launch is padding, where tiles of one P each pad every P's rows to a multiple of
+// the tile (1200 rows on 256 tiles: 6 % of the products; 200 on 128: 22 %).  The tile's own
+// rows are the base of its loads, so the 32-bit load offsets stay small however large the chunk is.
+// Otherwise (rows that are not 16-byte aligned) one P per tile, staged through registers.
 // EXT / ext: the ring is the caller's (see ring_of); BUDGET: LDS bytes for the ring (0: the whole
 // unit's LDS shared by MINB blocks).
-template <int TERMS, bool BLO, int G1M, int G1N, int WGM, int WGN, int MINB, bool VEC, bool STACK, bool EXT = false,
-          int BUDGET = 0>
+template <int TERMS, bool BLO, int G1M, int G1N, int WGM, int WGN, int MINB, bool VEC, bool EXT = false, int BUDGET = 0>
 __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = nullptr) {
   constexpr bool ALO = TERMS >= 2;
   constexpr int MI = G1M / (16 * WGM), NI = G1N / (16 * WGN);
   const int nbf = g.nbf, nact = g.nact, ldx = g.ldx;
   const int tm_n = (nact + G1M - 1) / G1M;
-  int P = 0, m0, n0;
-  if constexpr (STACK) {
+  int P = 0, m0;
+  long long n0;
+  if constexpr (VEC) {
     m0 = (w % tm_n) * G1M;
-    n0 = (w / tm_n) * G1N;
+    n0 = (long long)(w / tm_n) * G1N;
   } else {
     const int tn_n = (nbf + G1N - 1) / G1N;
     P = w / (tm_n * tn_n);
@@ -604,9 +608,11 @@ __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = n
     n0 = (tile % tn_n) * G1N;
   }
   const long long pstride = (long long)g.ws.nact32 * ldx;
-  u16* XTh = g.xt_hi + (STACK ? 0 : P * pstride);
-  u16* XTl = g.xt_lo ? g.xt_lo + (STACK ? 0 : P * pstride) : nullptr;
+  u16* XTh = g.xt_hi + (VEC ? 0 : P * pstride);
+  u16* XTl = g.xt_lo ? g.xt_lo + (VEC ? 0 : P * pstride) : nullptr;
   const long long nrows = (long long)g.np * nbf;
+  const int P0 = VEC ? (int)((uint32_t)n0 / (uint32_t)nbf) : 0;   // first P of the tile, its first row there
+  const int r0 = VEC ? (int)(n0 - (long long)P0 * nbf) : (int)n0;
   // split mode: X is written as the fp16 pair of X sX
   const float xmul = TERMS >= 2 ? chunk_scales(g.bnd, g.chunk, TERMS == 3).xmul : 1.0f;
   f32x4 acc[MI][NI];
@@ -615,16 +621,15 @@ __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = n
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int jn = 0; jn < NI; ++jn) {
+        const int c = col_of<G1N, WGM, WGN>(jn);
         long long xo;
-        if constexpr (STACK) {
-          const int c = n0 + col_of<G1N, WGM, WGN>(jn);
-          if (c >= nrows) continue;
-          const int Pc = c / nbf;
-          xo = Pc * pstride + (c - Pc * nbf);
+        if constexpr (VEC) {
+          if (n0 + c >= nrows) continue;
+          const int dP = (int)((uint32_t)(r0 + c) / (uint32_t)nbf);
+          xo = (P0 + dP) * pstride + (r0 + c - dP * nbf);
         } else {
-          const int mu = n0 + col_of<G1N, WGM, WGN>(jn);
-          if (mu >= nbf) continue;
-          xo = mu;
+          if (r0 + c >= nbf) continue;
+          xo = r0 + c;
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -642,23 +647,20 @@ __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = n
     // the LDS of one compute unit is shared by MINB blocks
     constexpr int S = ring_depth(G1M, G1N, ALO, BLO, BUDGET > 0 ? BUDGET : (MINB == 2 ? 81920 : 163840));
     auto& sm = ring_of<Ring<G1M, G1N, ALO, BLO, S>, EXT>(ext);
+    const long long o = n0 * g.ldb;
     auto A = [&](int) { return DOpnd{g.ct_hi, g.ct_lo, g.ldk, g.ws.ct_bytes}; };
-    auto B = [&](int) {
-      const long long o = (long long)P * g.bstride;
-      return DOpnd{g.b_hi + o, BLO ? g.b_lo + o : nullptr, g.ldb, g.b_bytes - 2 * o};
-    };
-    mainloop_dl<G1M, G1N, ALO, BLO, S, false, false, true, (TERMS == 3), WGM, WGN, (WGM * WGN == 8)>(sm, 1, 0, nbf, m0, n0,
-                                                                                                     A, B, acc,
-                                                                                      epi);
+    auto B = [&](int) { return DOpnd{g.b_hi + o, BLO ? g.b_lo + o : nullptr, g.ldb, g.b_bytes - 2 * o}; };
+    mainloop_dl<G1M, G1N, ALO, BLO, S, false, false, true, (TERMS == 3), WGM, WGN, (WGM * WGN == 8)>(sm, 1, 0, nbf, m0, 0,
+                                                                                                     A, B, acc, epi);
   } else {
     static_assert(VEC || (WGM == 2 && WGN == 2), "register-staged path: 2 x 2 waves");
     __shared__ Stage<G1M, G1N, ALO, BLO> sm;
     auto A = [&](int) { return Opnd{g.ct_hi, g.ct_lo, g.ldk, nact, nbf, false}; };
     auto B = [&](int) {
       const long long o = (long long)P * g.bstride;
-      return Opnd{g.b_hi + o, BLO ? g.b_lo + o : nullptr, g.ldb, STACK ? (int)nrows : nbf, nbf, false};
+      return Opnd{g.b_hi + o, BLO ? g.b_lo + o : nullptr, g.ldb, nbf, nbf, false};
     };
-    mainloop<G1M, G1N, ALO, BLO, false, false, true, (TERMS == 3)>(sm, 1, 0, nbf, m0, n0, A, B, acc, epi);
+    mainloop<G1M, G1N, ALO, BLO, false, false, true, (TERMS == 3)>(sm, 1, 0, nbf, m0, r0, A, B, acc, epi);
   }
 }
 
@@ -877,9 +879,9 @@ __device__ __forceinline__ void gemm3_body(int w, const G3Args& g, void* ext = n
 
 template <int TERMS, bool BLO, int G1M, int G1N, int WGM, int WGN, int MINB, bool VEC>
 __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm1_kernel(G1Args g) {
-  const int w = xcd_item(g1_items(g, G1M, G1N, false));
+  const int w = xcd_item(g1_items(g, G1M, G1N, VEC));
   if (w < 0) return;
-  gemm1_body<TERMS, BLO, G1M, G1N, WGM, WGN, MINB, VEC, false>(w, g);
+  gemm1_body<TERMS, BLO, G1M, G1N, WGM, WGN, MINB, VEC>(w, g);
 }
 template <int TERMS, bool VEC>
 __global__ __launch_bounds__(128 * g2_wgn(VEC), 1) void gemm2_kernel(G2Args g) {
@@ -906,7 +908,7 @@ __global__ __launch_bounds__(256, 2) void gemm1_grouped(const G1Args* __restrict
   if (w < 0) return;
   const int i = find_instance(off, ninst, w);
   const G1Args g = tab[i];
-  gemm1_body<TERMS, false, TM, 128, 2, 2, 2, true, true>(w - off[i], g);
+  gemm1_body<TERMS, false, TM, 128, 2, 2, 2, true>(w - off[i], g);
 }
 template <int TERMS, int TT>
 __global__ __launch_bounds__(TT == 128 ? 128 * g2_wgn(true) : 256, TT == 128 ? 1 : 2) void gemm2_grouped(
@@ -1008,7 +1010,7 @@ __device__ __forceinline__ void persist_item(const PArgs& a, int i, int ph, int 
         const int t0 = idx * PERSIST_XG, t1 = t0 + PERSIST_XG < nt ? t0 + PERSIST_XG : nt;
         for (int t = t0; t < t1; ++t) {
           if (t > t0) __syncthreads();   // the ring of the tile before is free again
-          gemm1_body<2, false, TX, 128, 2, 2, 2, true, true, true, PBUDGET>(t, g, lds);
+          gemm1_body<2, false, TX, 128, 2, 2, 2, true, true, PBUDGET>(t, g, lds);
         }
       } else {
         f64t::grouped_tile<false, true>(a.f64[i], idx - nx, fs);                           // H C_A
@@ -1177,6 +1179,9 @@ __global__ void persist_reset_k(PSched sc, int nwords_inst, int ninst) {
   if (threadIdx.x == 0) *sc.t_start = wall_clock64();
 }
 
+// Rows (P, mu) of a stacked X launch are counted in 32 bits.
+inline bool rows32(const G1Args& g) { return (long long)g.np * g.nbf < (1LL << 31); }
+
 inline dim3 xcd_grid(long long items) { return dim3((unsigned)(cdiv(items, NXCD) * NXCD)); }
 
 }  // namespace
@@ -1184,12 +1189,14 @@ inline dim3 xcd_grid(long long items) { return dim3((unsigned)(cdiv(items, NXCD)
 inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 template <int TERMS, bool BLO, int G1M, int G1N, int WGM, int WGN, int MINB>
 static void launch_g1(hipStream_t s, const G1Args& g) {
-  const dim3 grid = xcd_grid(g1_items(g, G1M, G1N, false));
-  // direct-to-LDS needs 16-byte aligned rows of the caller's B (nbf % 8 == 0)
-  const bool vec = (g.ldb % 8 == 0) && (g.nbf % 8 == 0) && (g.bstride % 8 == 0) && al16(g.b_hi) &&
+  const dim3 grid = xcd_grid(g1_items(g, G1M, G1N, true));
+  // direct-to-LDS needs 16-byte aligned rows of B, densely stacked (the caller's own when nbf % 8 == 0,
+  // otherwise the chunk's padded copy)
+  const bool vec = rows32(g) && (g.ldb % 8 == 0) && (g.bstride == (long long)g.nbf * g.ldb) && al16(g.b_hi) &&
                    (!g.b_lo || al16(g.b_lo)) && al16(g.ct_hi) && (!g.ct_lo || al16(g.ct_lo)) && (g.ldk % 32 == 0) &&
                    (g.ldx % 32 == 0);
-  // operands without aligned rows take the register-staged 128 x 128 form whatever the variant
+  // operands without aligned rows (a workspace with no room for the copy) take the register-staged
+  // 128 x 128 form whatever the variant
   if (vec)
     hipLaunchKernelGGL((gemm1_kernel<TERMS, BLO, G1M, G1N, WGM, WGN, MINB, true>), grid, dim3(64 * WGM * WGN), 0, s, g);
   else

@@ -93,21 +93,57 @@ __global__ void split_ca_k(int nbf, int nact, int terms, const double* __restric
   }
 }
 
-// float64 B as the fp16 pair of B sB (sB of the chunk), or as one bf16 value when bnd is null.
-__global__ void split_b_k(long long n, const double* __restrict__ B, u16* __restrict__ hi, u16* __restrict__ lo,
-                          const uint32_t* __restrict__ bnd, int chunk) {
-  if (!bnd) {
-    GRID_STRIDE(i, n) hi[i] = f32_to_bf16_bits((float)B[i]);
-    return;
-  }
-  const float sB = chunk_scales(bnd, chunk, true).sB;
-  GRID_STRIDE(i, n) {
-    u16 h, l;
-    const double xs = B[i] * (double)sB;
-    h = f32_to_f16_bits((float)xs);
-    l = f32_to_f16_bits((float)(xs - (double)f16_bits_to_f32(h)));
-    hi[i] = h;
-    lo[i] = l;
+// Rows of float64 B (n elements each) as the fp16 pair of B sB (sB of the chunk), or as one bf16 value
+// when bnd is null, in rows of ldo (a multiple of 8) with zeros from n on; ldo == n: one run of
+// nrows n elements, whatever n is.  One thread per 8 elements: four 16-byte loads, one 16-byte store
+// of each part.
+__global__ __launch_bounds__(NT) void split_b_k(long long tot, uint32_t pieces, int n, const double* __restrict__ B,
+                                                u16* __restrict__ hi, u16* __restrict__ lo, int ldo,
+                                                const uint32_t* __restrict__ bnd, int chunk) {
+  const double sB = bnd ? (double)chunk_scales(bnd, chunk, true).sB : 1.0;
+  const uint32_t per = (uint32_t)(ldo / 8);
+  for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < pieces; i += gridDim.x * NT) {
+    long long so = 8LL * i, o = so;   // first element read and written
+    int valid = (int)min(8LL, tot - so);
+    if (ldo != n) {
+      const uint32_t r = i / per;
+      const int c = 8 * (int)(i - r * per);
+      so = (long long)r * n + c;
+      valid = min(8, n - c);
+    }
+    double x[8];
+    if (valid == 8) {
+      __builtin_memcpy(x, B + so, 64);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = k < valid ? B[so + k] : 0.0;
+    }
+    u16 h[8], l[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (bnd) {
+        const double xs = x[k] * sB;
+        h[k] = f32_to_f16_bits((float)xs);
+        l[k] = f32_to_f16_bits((float)(xs - (double)f16_bits_to_f32(h[k])));
+      } else {
+        h[k] = f32_to_bf16_bits((float)x[k]);
+        l[k] = 0;
+      }
+    }
+    if (valid == 8 || ldo != n) {
+      uint4 v;
+      __builtin_memcpy(&v, h, 16);
+      *reinterpret_cast<uint4*>(hi + o) = v;
+      if (bnd) {
+        __builtin_memcpy(&v, l, 16);
+        *reinterpret_cast<uint4*>(lo + o) = v;
+      }
+    } else {
+      for (int k = 0; k < valid; ++k) {
+        hi[o + k] = h[k];
+        if (bnd) lo[o + k] = l[k];
+      }
+    }
   }
 }
 
@@ -169,70 +205,121 @@ __global__ void bounds_reduce_k(int nact, const float* __restrict__ col, uint32_
   for (int i = threadIdx.x; i < nclear; i += blockDim.x) bnd[SCL_CALL + i] = 0u;
 }
 
-// Row bounds of B (nrows rows of ncols elements, leading dimension ld): for every chunk of
-// rows_per_chunk consecutive rows, the largest row 1-norm and the largest |B|, raised into
-// slot[2c], slot[2c + 1] with integer atomic maxima on the bits of the non-negative floats.  One
-// wavefront per row; each wavefront walks a contiguous range of rows and raises a chunk's words when
-// it leaves that chunk.
-template <bool F64, bool VEC>
-__global__ void b_bounds_k(const void* __restrict__ B, long long nrows, int ncols, long long ld,
-                           long long rows_per_chunk, uint32_t* __restrict__ slot) {
-  const int lane = threadIdx.x & 63;
-  const long long nw = (long long)gridDim.x * (blockDim.x >> 6);
-  const long long w = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const long long per = (nrows + nw - 1) / nw;
-  const long long r0 = w * per, r1 = r0 + per < nrows ? r0 + per : nrows;
-  float rmax = 0.f, amax = 0.f;
-  long long cur = r0 < r1 ? r0 / rows_per_chunk : -1;
-  auto flush = [&]() {
-    if (lane == 0 && cur >= 0) {
-      if (rmax > 0.f) atomicMax(slot + 2 * cur, __float_as_uint(rmax));
-      if (amax > 0.f) atomicMax(slot + 2 * cur + 1, __float_as_uint(amax));
-    }
-    rmax = 0.f;
-    amax = 0.f;
-  };
-  for (long long r = r0; r < r1; ++r) {
-    if (r / rows_per_chunk != cur) {
-      flush();
-      cur = r / rows_per_chunk;
-    }
-    float s = 0.f, a = 0.f;
-    if constexpr (F64) {
-      const double* row = static_cast<const double*>(B) + r * ld;
-      for (int c = lane; c < ncols; c += 64) {
-        const float v = (float)fabs(row[c]);
-        s += v;
-        a = fmaxf(a, v);
-      }
-    } else if constexpr (VEC) {
-      const u16* row = static_cast<const u16*>(B) + r * ld;
-      for (int c = 8 * lane; c < ncols; c += 512) {
-        const uint4 v = *reinterpret_cast<const uint4*>(row + c);
-        const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+// One pass over rows of B (rows of n elements, densely stored): the bounds that fix a chunk's scales
+// and / or a copy with 16-byte aligned rows.  blockIdx.y is the chunk of rows_per_chunk consecutive
+// rows; LPR lanes share a row, each taking 16-byte pieces of it (whatever the row's alignment: the
+// row's last piece is loaded so that it ends with the row and shifted down, so nothing past the row
+// is read), RU rows of a group in flight.
+//   BND   the largest row 1-norm and the largest |B| of the chunk, raised into slot[2c], slot[2c + 1]
+//         with integer atomic maxima on the bits of the non-negative floats, once per block;
+//   PACK  (bf16) row r copied to out + r ldo, zero from n to ldo (a multiple of 8).
+// Memory-bound.  2000 x 500 rows of 500 bf16 (1 GB): the bounds alone 752 us with one wavefront walking
+// 2-byte elements of one row at a time, 217 us here (4.6 TB/s); the copy of bf16 rows in six chunks 391 us (5.1 TB/s read and written).
+// 800 x 200 rows of 200 float64 (256 MB): 405 us before, 99 us here.
+constexpr int RU = 4;
+// The 16 bytes at element c of a row of n (zeros from n on), as loaded from element min(c, n - E) and
+// moved down by c minus that; rows shorter than one piece element by element.
+template <typename T>
+__device__ __forceinline__ unsigned __int128 row_load(const T* __restrict__ row, int c, int n) {
+  constexpr int E = 16 / sizeof(T);
+  unsigned __int128 x = 0;
+  if (n >= E) {
+    __builtin_memcpy(&x, row + (c < n - E ? c : n - E), 16);
+  } else {
+    T v[E] = {};
+    for (int k = 0; k < E; ++k)
+      if (c + k < n) v[k] = row[c + k];
+    __builtin_memcpy(&x, v, 16);
+  }
+  return x;
+}
+template <typename T>
+__device__ __forceinline__ unsigned __int128 row_shift(unsigned __int128 x, int c, int n) {
+  constexpr int E = 16 / sizeof(T);
+  const int d = n >= E && c > n - E ? c - (n - E) : 0;
+  return d >= E ? 0 : x >> (8 * (int)sizeof(T) * d);
+}
+__device__ __forceinline__ void piece_abs(unsigned __int128 x, float (&v)[8]) {
+  uint32_t w[4];
+  __builtin_memcpy(w, &x, 16);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float x = fabsf(__uint_as_float(wd[k] << 16)), y = fabsf(__uint_as_float(wd[k] & 0xFFFF0000u));
-          s += x + y;
-          a = fmaxf(a, fmaxf(x, y));
+  for (int k = 0; k < 4; ++k) {
+    v[2 * k] = fabsf(__uint_as_float(w[k] << 16));
+    v[2 * k + 1] = fabsf(__uint_as_float(w[k] & 0xFFFF0000u));
+  }
+}
+__device__ __forceinline__ void piece_abs(unsigned __int128 x, float (&v)[2]) {
+  double d[2];
+  __builtin_memcpy(d, &x, 16);
+  v[0] = (float)fabs(d[0]);
+  v[1] = (float)fabs(d[1]);
+}
+template <typename T, int LPR, bool BND, bool PACK>
+__global__ __launch_bounds__(NT) void b_rows_k(const T* __restrict__ B, long long nrows, int n, long long rows_per_chunk,
+                                               uint32_t* __restrict__ slot, u16* __restrict__ out, int ldo) {
+  constexpr int E = 16 / sizeof(T), RB = NT / LPR;   // elements per piece, rows of a block at a time
+  const long long c0 = blockIdx.y * rows_per_chunk, c1 = c0 + rows_per_chunk < nrows ? c0 + rows_per_chunk : nrows;
+  const int g = threadIdx.x / LPR, l = threadIdx.x % LPR;
+  const int width = PACK ? ldo : n;
+  float rmax = 0.f, amax = 0.f;
+  for (long long r0 = c0 + (long long)blockIdx.x * (RB * RU); r0 < c1; r0 += (long long)gridDim.x * (RB * RU)) {
+    float s[RU];
+#pragma unroll
+    for (int u = 0; u < RU; ++u) s[u] = 0.f;
+    for (int c = E * l; c < width; c += E * LPR) {
+      unsigned __int128 x[RU];
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const long long r = r0 + u * RB + g;
+        x[u] = row_load(B + (r < c1 ? r : c1 - 1) * n, c, n);
+      }
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const long long r = r0 + u * RB + g;
+        x[u] = r < c1 ? row_shift<T>(x[u], c, n) : 0;
+        if constexpr (PACK) {
+          uint4 w;
+          __builtin_memcpy(&w, &x[u], 16);
+          if (r < c1) *reinterpret_cast<uint4*>(out + r * ldo + c) = w;
+        }
+        if constexpr (BND) {
+          float v[E];
+          piece_abs(x[u], v);
+#pragma unroll
+          for (int k = 0; k < E; ++k) {
+            s[u] += v[k];
+            amax = fmaxf(amax, v[k]);
+          }
         }
       }
-    } else {
-      const u16* row = static_cast<const u16*>(B) + r * ld;
-      for (int c = lane; c < ncols; c += 64) {
-        const float v = fabsf(bf16_bits_to_f32(row[c]));
-        s += v;
-        a = fmaxf(a, v);
+    }
+    if constexpr (BND) {
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+#pragma unroll
+        for (int m = LPR / 2; m >= 1; m >>= 1) s[u] += __shfl_xor(s[u], m, 64);
+        rmax = fmaxf(rmax, s[u]);
       }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      s += __shfl_down(s, off, 64);
-      a = fmaxf(a, __shfl_down(a, off, 64));
-    }
-    rmax = fmaxf(rmax, __shfl(s, 0, 64));
-    amax = fmaxf(amax, __shfl(a, 0, 64));
   }
-  flush();
+  if constexpr (BND) {
+    __shared__ float red[2][NT / 64];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+      rmax = fmaxf(rmax, __shfl_xor(rmax, m, 64));
+      amax = fmaxf(amax, __shfl_xor(amax, m, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[0][threadIdx.x >> 6] = rmax;
+      red[1][threadIdx.x >> 6] = amax;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+      float m = 0.f;
+      for (int w = 0; w < NT / 64; ++w) m = fmaxf(m, red[threadIdx.x][w]);
+      if (m > 0.f) atomicMax(slot + 2 * blockIdx.y + threadIdx.x, __float_as_uint(m));
+    }
+  }
 }
 
 // Hpp[p] = sum_mu C[mu][p] HC[mu][p]: one wavefront per orbital, fixed reduction order.
@@ -872,9 +959,19 @@ hipError_t split_ca(hipStream_t s, int nbf, int nact, int terms, const double* C
                     u16* l16, int ldk, const uint32_t* bnd) {
   LAUNCH(split_ca_k, grid1((long long)nbf * nact), dim3(NT), nbf, nact, terms, C, hi, lo, h16, l16, ldk, bnd);
 }
-hipError_t split_b(hipStream_t s, long long n, const double* B, u16* hi, u16* lo, const uint32_t* bnd, int chunk) {
-  if (n <= 0) return hipSuccess;
-  LAUNCH(split_b_k, grid1(n), dim3(NT), n, B, hi, lo, bnd, chunk);
+hipError_t split_b(hipStream_t s, long long nrows, int n, const double* B, u16* hi, u16* lo, int ldo, const uint32_t* bnd,
+                   int chunk) {
+  if (nrows <= 0) return hipSuccess;
+  if (ldo != n && ldo % 8 != 0) return hipErrorInvalidValue;
+  // 32-bit piece counts: rows in parts of at most 2^29 pieces, each starting on a whole piece
+  const long long part = std::max(1LL, (1LL << 29) / (ldo / 8 + 1)) & ~7LL;
+  if (part == 0) return hipErrorInvalidValue;
+  for (long long r0 = 0; r0 < nrows; r0 += part) {
+    const long long nr = std::min(part, nrows - r0), pieces = (nr * ldo + 7) / 8;
+    hipLaunchKernelGGL(split_b_k, dim3((unsigned)std::min<long long>(cdiv(pieces, NT), 16384)), dim3(NT), 0, s, nr * n,
+                       (uint32_t)pieces, n, B + r0 * n, hi + r0 * ldo, lo ? lo + r0 * ldo : nullptr, ldo, bnd, chunk);
+  }
+  return hipGetLastError();
 }
 hipError_t scale_bounds(hipStream_t s, int nbf, int nact, const double* C, const double* n, int npairs, int ncwo,
                         int nsingle, int functional, float* col, uint32_t* bnd, int nclear) {
@@ -884,14 +981,44 @@ hipError_t scale_bounds(hipStream_t s, int nbf, int nact, const double* C, const
   if (e != hipSuccess) return e;
   LAUNCH(bounds_reduce_k, dim3(1), dim3(NT), nact, col, bnd, nclear);
 }
-hipError_t b_bounds(hipStream_t s, const void* B, int is_f64, long long nrows, int ncols, long long ld,
-                    long long rows_per_chunk, uint32_t* slot) {
+// Lanes per row: the fewest (8 to 64) whose 16-byte pieces cover the row in one go.
+template <typename T, bool BND, bool PACK>
+static hipError_t b_rows(hipStream_t s, const T* B, long long nrows, int n, long long rows_per_chunk, uint32_t* slot,
+                         u16* out, int ldo) {
+  const int pieces = cdiv(PACK ? ldo : n, 16 / (int)sizeof(T));
+  const int lpr = pieces <= 8 ? 8 : pieces <= 16 ? 16 : pieces <= 32 ? 32 : 64;
+  const long long nch = cdiv(nrows, rows_per_chunk);
+  if (nch > 65535) return hipErrorInvalidValue;
+  // about 4096 blocks over the chunks, each with whole passes of its rows
+  const long long per = std::min(nrows, rows_per_chunk);
+  const long long bx = std::min<long long>(cdiv(per, (NT / lpr) * RU), std::max(1LL, 4096 / nch));
+  const dim3 g((unsigned)bx, (unsigned)nch);
+  if (lpr == 8) hipLaunchKernelGGL((b_rows_k<T, 8, BND, PACK>), g, dim3(NT), 0, s, B, nrows, n, rows_per_chunk, slot, out, ldo);
+  else if (lpr == 16) hipLaunchKernelGGL((b_rows_k<T, 16, BND, PACK>), g, dim3(NT), 0, s, B, nrows, n, rows_per_chunk, slot, out, ldo);
+  else if (lpr == 32) hipLaunchKernelGGL((b_rows_k<T, 32, BND, PACK>), g, dim3(NT), 0, s, B, nrows, n, rows_per_chunk, slot, out, ldo);
+  else hipLaunchKernelGGL((b_rows_k<T, 64, BND, PACK>), g, dim3(NT), 0, s, B, nrows, n, rows_per_chunk, slot, out, ldo);
+  return hipGetLastError();
+}
+hipError_t b_bounds(hipStream_t s, const void* B, int is_f64, long long nrows, int n, long long rows_per_chunk,
+                    uint32_t* slot) {
   if (nrows <= 0) return hipSuccess;
-  const dim3 g((unsigned)std::min<long long>(cdiv(nrows, NT / 64), 4096));
-  const bool vec = !is_f64 && (ld % 8 == 0) && ((reinterpret_cast<uintptr_t>(B) & 15) == 0);
-  if (is_f64) LAUNCH((b_bounds_k<true, false>), g, dim3(NT), B, nrows, ncols, ld, rows_per_chunk, slot);
-  if (vec) LAUNCH((b_bounds_k<false, true>), g, dim3(NT), B, nrows, ncols, ld, rows_per_chunk, slot);
-  LAUNCH((b_bounds_k<false, false>), g, dim3(NT), B, nrows, ncols, ld, rows_per_chunk, slot);
+  // the grid's second dimension holds at most 65535 chunks
+  const long long part = 65535 * rows_per_chunk;
+  for (long long r0 = 0; r0 < nrows; r0 += part) {
+    const long long nr = std::min(part, nrows - r0);
+    const hipError_t e = is_f64 ? b_rows<double, true, false>(s, static_cast<const double*>(B) + r0 * n, nr, n,
+                                                              rows_per_chunk, slot, nullptr, 0)
+                                : b_rows<u16, true, false>(s, static_cast<const u16*>(B) + r0 * n, nr, n, rows_per_chunk,
+                                                           slot, nullptr, 0);
+    if (e != hipSuccess) return e;
+    slot += 2 * 65535;
+  }
+  return hipSuccess;
+}
+hipError_t pack_b(hipStream_t s, long long nrows, int n, const u16* B, u16* out, int ldo, uint32_t* slot) {
+  if (nrows <= 0) return hipSuccess;
+  return slot ? b_rows<u16, true, true>(s, B, nrows, n, nrows, slot, out, ldo)
+              : b_rows<u16, false, true>(s, B, nrows, n, nrows, slot, out, ldo);
 }
 hipError_t hpp_from_hc(hipStream_t s, int nbf, int nact, const double* C, const double* HC, double* Hpp) {
   LAUNCH(hpp_k, dim3(nact), dim3(64), nbf, nact, C, HC, Hpp);
