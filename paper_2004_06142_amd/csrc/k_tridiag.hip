@@ -11,7 +11,7 @@
 // coupling b = e[cut - 1] is taken out as a rank-one term: both adjacent diagonal entries lose |b|,
 // and the parent is blockdiag(T1, T2) + |b| v v^T with v = e_last(T1) + sign(b) e_first(T2).
 //
-// Leaves: one wavefront each, cyclic Jacobi (round-robin pairs, the matrix in LDS).
+// Leaves: one wavefront each, implicitly shifted QL.
 // Merge of two children with eigen-decompositions T1 = Q1 D1 Q1^T, T2 = Q2 D2 Q2^T, per level, for
 // all parents of the level at once (kernels in launch order):
 //   deflate  z = [last row of Q1, sign(b) first row of Q2] / sqrt 2, rho = 2 |b|; the children's
@@ -50,7 +50,7 @@
 namespace pnof {
 namespace {
 
-constexpr int DC_LEAF = 16;                 // rows of a leaf at most (Jacobi in one wavefront)
+constexpr int DC_LEAF = 16;                 // rows of a leaf at most (one wavefront)
 constexpr int DC_LP = DC_LEAF + 1;          // leaf LDS row pitch
 constexpr int DMAX = TRIDIAG_MAX_N;
 constexpr int SQ = DMAX / 64;               // entries per lane of a wavefront over one parent
@@ -138,112 +138,111 @@ __global__ __launch_bounds__(1024) void dc_prep_k(DcWs w, const double* __restri
   }
 }
 
-// One leaf per wavefront: cyclic Jacobi with round-robin pairs (every round rotates m/2 disjoint
-// pairs at once), until a sweep rotates nothing.  A pair is left alone when its off-diagonal entry
-// is below eps sqrt(|a_pp a_qq|) or 1e-3 eps of the leaf's largest entry.  Odd sizes add a zero
-// row and column whose pair never rotates.
+// 1 / sqrt(x) from the hardware estimate and one third-order step; x well inside the range of doubles.
+__device__ __forceinline__ double dc_rsqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double r = fma(-x * y, y, 1.0);
+  return fma(y * r, fma(0.375, r, 0.5), y);
+}
+
+// One leaf per wavefront: implicitly shifted QL (each sweep chases the bulge of a shifted step from the
+// bottom of the unreduced part to its top, by plane rotations that are applied to the rows of V, one row
+// per lane).  An off-diagonal entry is taken as zero below eps (|d_i| + |d_i+1|) or 1e-3 eps of the
+// leaf's largest entry.  The rotations are one serial chain of about 1.7 m^2 / 2 links, every lane
+// computing the same scalars; the next link's entries are read ahead of it.  Jacobi on the dense leaf
+// took 95 us (leaves of 9 and 10 rows) to 200 us (16 rows), this 38 to 86 us.
+__device__ __forceinline__ double lane_val(double v, int i) {   // v of lane i (uniform)
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i), __builtin_amdgcn_readlane(__double2loint(v), i));
+}
+
 __global__ __launch_bounds__(64) void dc_leaf_k(DcWs w) {
-  const int n = w.n, T = w.T, tid = threadIdx.x;
-  const int o = seg_lo(n, T, blockIdx.x), m = seg_lo(n, T, blockIdx.x + 1) - o;
-  const int mp = m + (m & 1), np = mp / 2;
-  __shared__ double A[DC_LEAF][DC_LP], V[DC_LEAF][DC_LP];
-  __shared__ double pc[DC_LEAF / 2], ps[DC_LEAF / 2], pt[DC_LEAF / 2];
-  __shared__ int pp[DC_LEAF / 2], pq[DC_LEAF / 2], prot[DC_LEAF / 2];
-  __shared__ int any;
-  double mx = 0.0;
-  for (int x = tid; x < mp * mp; x += 64) {
-    const int r = x / mp, c = x % mp;
-    double a = 0.0;
-    if (r < m && c < m) {
-      if (r == c) a = w.dS[o + r];
-      else if (c == r + 1) a = w.es[o + r];
-      else if (r == c + 1) a = w.es[o + c];
-    }
-    A[r][c] = a;
-    V[r][c] = r == c ? 1.0 : 0.0;
-    mx = fmax(mx, fabs(a));
-  }
-  const double athr = 1e-3 * UEPS * wmax(mx);
+  const int n = w.n, T = w.T, lane = threadIdx.x;
+  const int o = seg_lo(n, T, blockIdx.x), m = __builtin_amdgcn_readfirstlane(seg_lo(n, T, blockIdx.x + 1) - o);
+  __shared__ double V[DC_LEAF][DC_LP];
+  __shared__ double d[DC_LEAF];
+  // lane i holds d_i and e_i, which couples i and i + 1
+  double dv = lane < m ? w.dS[o + lane] : 0.0, ev = lane + 1 < m ? w.es[o + lane] : 0.0;
+  for (int x = lane; x < DC_LEAF * DC_LEAF; x += 64) V[x / DC_LEAF][x % DC_LEAF] = x / DC_LEAF == x % DC_LEAF ? 1.0 : 0.0;
+  const double ethr = 1e-3 * UEPS * wmax(fmax(fabs(dv), fabs(ev)));
   __syncthreads();
-  for (int sweep = 0; sweep < 40; ++sweep) {
-    if (tid == 0) any = 0;
-    __syncthreads();
-    for (int r = 0; r < mp - 1; ++r) {
-      if (tid < np) {
-        int p, q;
-        if (tid == 0) { p = r; q = mp - 1; }
-        else { p = (r + tid) % (mp - 1); q = (r - tid + mp - 1) % (mp - 1); }
-        if (p > q) { const int x = p; p = q; q = x; }
-        double c = 1.0, sn = 0.0, tt = 0.0;
-        int rot = 0;
-        if (q < m) {
-          const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
-          if (fabs(apq) > athr && fabs(apq) > UEPS * sqrt(fabs(app * aqq))) {
-            const double th = (aqq - app) / (2.0 * apq);
-            tt = fabs(th) > 1e150 ? 0.5 / th : copysign(1.0, th) / (fabs(th) + sqrt(1.0 + th * th));
-            c = 1.0 / sqrt(1.0 + tt * tt);
-            sn = tt * c;
-            rot = 1;
-          }
+  double* const row = V[lane & (DC_LEAF - 1)];   // lanes past 15 repeat the rows of the first 16
+  bool ok = true;
+  for (int l = 0; l < m; ++l) {
+    for (int it = 0;; ++it) {
+      // first negligible coupling at or after l
+      const double ae = fabs(ev), dn1 = __shfl_down(dv, 1, 64);
+      const bool small = lane + 1 >= m || ae <= ethr || ae <= UEPS * (fabs(dv) + fabs(dn1));
+      const unsigned long long b = __ballot(small) & (~0ull << l);
+      const int mm = __builtin_amdgcn_readfirstlane(__ffsll((long long)b) - 1);
+      if (mm == l) break;
+      if (it == 60) {
+        ok = false;
+        break;
+      }
+      const double el = lane_val(ev, l), dl = lane_val(dv, l);
+      double dhi = lane_val(dv, mm);   // d[i + 1] before the sweep
+      double g = (lane_val(dv, l + 1) - dl) / (2.0 * el);
+      g = dhi - dl + el / (g + copysign(sqrt(fma(g, g, 1.0)), g));
+      double s = 1.0, c = 1.0, p = 0.0, zc = row[mm], zi = row[mm - 1];
+      double ei = lane_val(ev, mm - 1), di = lane_val(dv, mm - 1);
+      int i = mm - 1;
+      for (; i >= l; --i) {
+        const int ip = i > l ? i - 1 : l;
+        const double en = lane_val(ev, ip), dn = lane_val(dv, ip), zn = row[ip];
+        const double f = s * ei, bb = c * ei;
+        const double q = fma(f, f, g * g);
+        double r;
+        if (__builtin_expect(q > 1e-280, 1)) {
+          const double y = dc_rsqrt(q);
+          r = q * y;
+          s = f * y;
+          c = g * y;
+        } else {
+          r = hypot(f, g);
+          if (r == 0.0) break;
+          s = f / r;
+          c = g / r;
         }
-        pp[tid] = p; pq[tid] = q; pc[tid] = c; ps[tid] = sn; pt[tid] = tt; prot[tid] = rot;
-        if (rot) any = 1;
+        g = dhi - p;
+        const double rr = fma(di - g, s, 2.0 * c * bb);
+        p = s * rr;
+        const bool me = lane == i + 1;
+        ev = me ? r : ev;
+        dv = me ? g + p : dv;
+        g = fma(c, rr, -bb);
+        row[i + 1] = fma(s, zi, c * zc);
+        zc = fma(c, zi, -s * zc);
+        dhi = di;
+        di = dn;
+        ei = en;
+        zi = zn;
       }
-      __syncthreads();
-      // A <- J^T A J on 2 x 2 blocks (pair P1 <= P2, mirrored), V <- V J
-      const int nblk = np * (np + 1) / 2;
-      for (int bk = tid; bk < nblk; bk += 64) {
-        int P1 = 0, rem = bk;
-        while (rem >= np - P1) { rem -= np - P1; ++P1; }
-        const int P2 = P1 + rem;
-        if (!prot[P1] && !prot[P2]) continue;
-        const int p1 = pp[P1], q1 = pq[P1], p2 = pp[P2], q2 = pq[P2];
-        if (P1 == P2) {
-          const double apq = A[p1][q1];
-          A[p1][p1] -= pt[P1] * apq;
-          A[q1][q1] += pt[P1] * apq;
-          A[p1][q1] = 0.0;
-          A[q1][p1] = 0.0;
-          continue;
-        }
-        const double c1 = pc[P1], s1 = ps[P1], c2 = pc[P2], s2 = ps[P2];
-        const double a = A[p1][p2], bb = A[p1][q2], cc = A[q1][p2], dd = A[q1][q2];
-        const double rp0 = c1 * a - s1 * cc, rp1 = c1 * bb - s1 * dd;
-        const double rq0 = s1 * a + c1 * cc, rq1 = s1 * bb + c1 * dd;
-        const double n00 = c2 * rp0 - s2 * rp1, n01 = s2 * rp0 + c2 * rp1;
-        const double n10 = c2 * rq0 - s2 * rq1, n11 = s2 * rq0 + c2 * rq1;
-        A[p1][p2] = n00; A[p2][p1] = n00;
-        A[p1][q2] = n01; A[q2][p1] = n01;
-        A[q1][p2] = n10; A[p2][q1] = n10;
-        A[q1][q2] = n11; A[q2][q1] = n11;
+      // i >= l: the chain met an exact zero, and the part below it has split off
+      const int top = i >= l ? i + 1 : l;
+      row[top] = zc;
+      if (lane == top) {
+        dv = dhi - p;
+        ev = i >= l ? 0.0 : g;
       }
-      for (int x = tid; x < mp * np; x += 64) {
-        const int row = x / np, P = x % np;
-        if (!prot[P]) continue;
-        const int p = pp[P], q = pq[P];
-        const double c = pc[P], sn = ps[P], vp = V[row][p], vq = V[row][q];
-        V[row][p] = c * vp - sn * vq;
-        V[row][q] = sn * vp + c * vq;
-      }
-      __syncthreads();
+      if (lane == mm) ev = 0.0;
     }
-    const int again = any;
-    __syncthreads();
-    if (!again) break;
   }
+  if (lane < m) d[lane] = dv;
+  if (!ok && lane == 0) atomicOr(w.info, 1);
+  __syncthreads();
   // ascending order (ties by index), written at the leaf's block of the level-T buffers
   const int ob = T & 1;
   const double sc = T == 0 ? w.scale[0] : 1.0;
-  for (int i = tid; i < m; i += 64) {
-    const double v = A[i][i];
+  if (lane < m) {
+    const double v = d[lane];
     int rk = 0;
     for (int y = 0; y < m; ++y) {
-      const double u = A[y][y];
-      rk += (u < v) || (u == v && y < i);
+      const double u = d[y];
+      rk += (u < v) || (u == v && y < lane);
     }
     w.dbuf[ob][o + rk] = v * sc;
     double* col = w.zbuf[ob] + (long long)(o + rk) * n + o;
-    for (int r = 0; r < m; ++r) col[r] = V[r][i];
+    for (int r = 0; r < m; ++r) col[r] = V[r][lane];
   }
 }
 
