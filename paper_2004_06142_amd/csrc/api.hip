@@ -1469,7 +1469,7 @@ struct EighWs {
 EighWs take_eigh_ws(Arena& a, int n) {
   EighWs w;
   w.Vh = a.take<double>((long long)n * n);
-  w.p2 = a.take<double>(2LL * n);
+  w.p2 = a.take<double>(tridiag_ws_doubles(n));
   w.e = a.take<double>(n);
   w.tau = a.take<double>(n);
   w.T = a.take<double>(form_q_ws_doubles(std::max(n, 3)));
@@ -1477,18 +1477,22 @@ EighWs take_eigh_ws(Arena& a, int n) {
   w.dc = a.take<double>(tridiag_dc_ws_doubles(std::max(n, 1)));
   return w;
 }
-pnof_status eigh(pnof_ctx ctx, int n, double* A, double* w, double* U, const EighWs& ws, int* info) {
+// Eigenvalues w and column-major eigenvectors U of A (overwritten).  info (device, 2 words): [0] a
+// secular equation did not converge, [1] the one-launch reduction declined (call again with the matrix
+// restored and `launches`).
+pnof_status eigh(pnof_ctx ctx, int n, double* A, double* w, double* U, const EighWs& ws, int* info, bool launches) {
   hipStream_t s = ctx->stream;
   if (n < 3 || n > TRIDIAG_MAX_N) {
     rocblas_status rs = rocsolver_dsyevd(ctx->blas, rocblas_evect_original, rocblas_fill_upper, n, A, n, w, ws.e, info);
     if (rs != rocblas_status_success) return fail(ctx, PNOF_E_DEVICE, "rocsolver_dsyevd failed to launch");
     DEV_CHECK(ctx, hipMemcpyAsync(U, A, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
+    DEV_CHECK(ctx, hipMemsetAsync(info + 1, 0, sizeof(int), s));
     return PNOF_OK;
   }
   if (!ws.Vh || !ws.p2 || !ws.e || !ws.tau || !ws.T || !ws.Q || !ws.dc)
     return fail(ctx, PNOF_E_ARG, "eigensolver workspace missing");
   RB_CHECK(ensure_aux(ctx));
-  DEV_CHECK(ctx, tridiag_f64(s, n, A, ws.Vh, ws.p2, w, ws.e, ws.tau));
+  DEV_CHECK(ctx, tridiag_f64(s, n, A, ws.Vh, ws.p2, w, ws.e, ws.tau, info, launches));
   DEV_CHECK(ctx, hipEventRecord(ctx->fork_ev, s));
   DEV_CHECK(ctx, hipStreamWaitEvent(ctx->aux, ctx->fork_ev, 0));
   DEV_CHECK(ctx, form_q_f64(ctx->aux, n, ws.Vh, ws.tau, ws.T, ws.Q));
@@ -1526,18 +1530,21 @@ pnof_status pnof_orbital_step(pnof_ctx ctx, int32_t nbf, const double* lambda, c
   const EighWs ew = take_eigh_ws(a, nbf);
   int* info = a.take<int>(4);
   hipStream_t s = ctx->stream;
-  DEV_CHECK(ctx, build_s(s, nbf, lambda, diag_prev, zeta, A));
-  if (S_out) DEV_CHECK(ctx, hipMemcpyAsync(S_out, A, n2 * sizeof(double), hipMemcpyDeviceToDevice, s));
-  {
-    StageTimer t_(ctx, PNOF_STAGE_EIG);
-    if ((st = eigh(ctx, nbf, A, eps, U, ew, info)) != PNOF_OK) return st;
+  for (int launches = 0; launches < 2; ++launches) {   // again with a launch per column if the reduction declines
+    DEV_CHECK(ctx, build_s(s, nbf, lambda, diag_prev, zeta, A));
+    if (S_out) DEV_CHECK(ctx, hipMemcpyAsync(S_out, A, n2 * sizeof(double), hipMemcpyDeviceToDevice, s));
+    {
+      StageTimer t_(ctx, PNOF_STAGE_EIG);
+      if ((st = eigh(ctx, nbf, A, eps, U, ew, info, launches != 0)) != PNOF_OK) return st;
+    }
+    DEV_CHECK(ctx, sign_fix_cols(s, nbf, U));
+    // C_new[mu][j] = sum_i C[mu][i] U[i][j], U column-major: U[i][j] = U[j*nbf + i]
+    RB_CHECK(dprod(ctx, nbf, nbf, nbf, C, nbf, 1, U, 1, nbf, C_new, nbf, 1));
+    DEV_CHECK(ctx, hipMemcpyAsync(ctx->host_info, info, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    DEV_CHECK(ctx, hipStreamSynchronize(s));
+    if (ctx->host_info[1] == 0) break;
   }
-  DEV_CHECK(ctx, sign_fix_cols(s, nbf, U));
-  // C_new[mu][j] = sum_i C[mu][i] U[i][j], U column-major: U[i][j] = U[j*nbf + i]
-  RB_CHECK(dprod(ctx, nbf, nbf, nbf, C, nbf, 1, U, 1, nbf, C_new, nbf, 1));
-  DEV_CHECK(ctx, hipMemcpyAsync(ctx->host_info, info, sizeof(int), hipMemcpyDeviceToHost, s));
-  DEV_CHECK(ctx, hipStreamSynchronize(s));
-  if (*ctx->host_info != 0)
+  if (ctx->host_info[0] != 0)
     return fail(ctx, PNOF_E_EIG, "eigensolver did not converge (info = " + std::to_string(*ctx->host_info) + ")");
   return PNOF_OK;
 }
@@ -1620,7 +1627,7 @@ pnof_status pnof_optimize(pnof_ctx ctx, const pnof_problem* prob, const double* 
   double* Ueig = db.get<double>(nn);
   EighWs ew;
   ew.Vh = db.get<double>(nn);
-  ew.p2 = db.get<double>(2LL * nbf);
+  ew.p2 = db.get<double>(tridiag_ws_doubles(nbf));
   ew.e = db.get<double>(nbf);
   ew.tau = db.get<double>(nbf);
   ew.T = db.get<double>(form_q_ws_doubles(std::max(nbf, 3)));
@@ -1689,15 +1696,20 @@ pnof_status pnof_optimize(pnof_ctx ctx, const pnof_problem* prob, const double* 
   };
   // diagonalise S (overwritten by the eigenvectors), new diagonal, C <- C U
   auto diagonalise = [&]() -> pnof_status {
-    pnof_status se = eigh(ctx, nbf, S, diag, Ueig, ew, info);
-    if (se != PNOF_OK) return se;
-    DEV_CHECK(ctx, sign_fix_cols(s, nbf, Ueig));
-    DEV_CHECK(ctx, gemm_f64(s, nbf, nbf, nbf, 1, 1.0, C, nbf, 1, 0, Ueig, 1, nbf, 0, 0.0, Cn, nbf, 1, 0));
+    // T1 keeps the matrix in case the reduction declines and it is taken again with a launch per column
+    DEV_CHECK(ctx, hipMemcpyAsync(T1, S, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
+    for (int launches = 0; launches < 2; ++launches) {
+      if (launches) DEV_CHECK(ctx, hipMemcpyAsync(S, T1, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
+      pnof_status se = eigh(ctx, nbf, S, diag, Ueig, ew, info, launches != 0);
+      if (se != PNOF_OK) return se;
+      DEV_CHECK(ctx, sign_fix_cols(s, nbf, Ueig));
+      DEV_CHECK(ctx, gemm_f64(s, nbf, nbf, nbf, 1, 1.0, C, nbf, 1, 0, Ueig, 1, nbf, 0, 0.0, Cn, nbf, 1, 0));
+      DEV_CHECK(ctx, hipMemcpyAsync(ctx->host_info, info, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+      DEV_CHECK(ctx, hipStreamSynchronize(s));
+      if (ctx->host_info[1] == 0) break;
+    }
+    if (ctx->host_info[0] != 0) return fail(ctx, PNOF_E_EIG, "eigensolver did not converge");
     DEV_CHECK(ctx, hipMemcpyAsync(C, Cn, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
-    int hinfo = 0;
-    DEV_CHECK(ctx, hipMemcpyAsync(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost, s));
-    DEV_CHECK(ctx, hipStreamSynchronize(s));
-    if (hinfo != 0) return fail(ctx, PNOF_E_EIG, "eigensolver did not converge");
     return PNOF_OK;
   };
   // initial step

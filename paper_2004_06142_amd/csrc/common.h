@@ -611,11 +611,15 @@ hipError_t on_map_vjp(hipStream_t s, int kind, int npairs, int ncwo, int nsingle
 hipError_t build_s(hipStream_t s, int nbf, const double* lam, const double* diag_prev, double zeta,
                    double* S);
 hipError_t sign_fix_cols(hipStream_t s, int nbf, double* Ucm);
-// Householder reduction to tridiagonal form (k_eig.hip), one launch per column: A (n x n symmetric,
-// row-major) is overwritten; d (n), e (n - 1), tau (n - 1) and the reflectors as rows of Vh (n x n,
-// read column-major: the lower-storage layout of ormtr); p2: 2n doubles of scratch.
+// Householder reduction to tridiagonal form (k_eig.hip): A (n x n symmetric, row-major) may be
+// overwritten; d (n), e (n - 1), tau (n - 1) and the reflectors as rows of Vh (n x n, read column-major:
+// the lower-storage layout of ormtr); ws: tridiag_ws_doubles(n) doubles.  info[1] (device) is set when
+// the one-launch form declined (too few of its workgroups running at once; d, e, tau are then finite but
+// no result): call again with `launches`, one launch per column.
 constexpr int TRIDIAG_MAX_N = 2048;   // three float64 vectors of n in LDS
-hipError_t tridiag_f64(hipStream_t s, int n, double* A, double* Vh, double* p2, double* d, double* e, double* tau);
+long long tridiag_ws_doubles(int n);
+hipError_t tridiag_f64(hipStream_t s, int n, double* A, double* Vh, double* ws, double* d, double* e, double* tau,
+                       int* info, bool launches);
 // Q = H_0 ... H_{n-2} (column-major n x n) from the reflectors of tridiag_f64 (Vh, tau), applied in
 // blocks of QNB as float64 GEMMs.  ws: form_q_ws_doubles(n) doubles.  3 <= n <= TRIDIAG_MAX_N.
 constexpr int QNB = 128;
