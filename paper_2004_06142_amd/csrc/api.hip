@@ -1,4 +1,5 @@
 // C ABI of libpnof: context, validation, workspace planning and the per-call drivers.
+#include <climits>
 #include <rocblas/rocblas.h>
 #include <rocsolver/rocsolver.h>
 
@@ -190,6 +191,26 @@ struct Plan {
   int terms;    // 1 or 3
 };
 
+// P-splits of a contraction whose blocks take one tile and the P rows of one split, `slots` blocks resident
+// at once: the count whose launch ends soonest, as whole rounds of blocks of floor(np / ns) rows (no less
+// than the even share), one row more where np / ns is not whole, and `fill` rows' worth of time per block
+// for its start and its partial sums.
+int best_splits(int np, long long tiles, int slots, double fill) {
+  int best = 1;
+  double tbest = 1e300;
+  for (int per = np; per >= 1; per = per > 64 ? per / 2 : per - 1)
+    for (int ns : {np / per, (np + per - 1) / per}) {
+      if (ns < 1 || ns > np) continue;
+      const double rounds = (double)cdiv(tiles * ns, slots);
+      const double t = std::max((double)tiles * np / slots, rounds * (np / ns)) + (np % ns ? 1.0 : 0.0) + fill * rounds;
+      if (t < tbest) {
+        tbest = t;
+        best = ns;
+      }
+    }
+  return best;
+}
+
 Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   Plan pl{};
   pl.nbf = p->nbf;
@@ -233,21 +254,30 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   long long pc = tu.pchunk > 0 ? tu.pchunk : std::max(64LL, (4096 + t1 - 1) / t1);
   const long long per_p = pl.split ? (long long)(2LL * pl.nact32 * pl.ldx + 2LL * pl.nact32 * pl.ldw) * 2 +
                                          (p->ints == PNOF_INTS_DF_F64 ? 4LL * pl.nbf * pl.nbf : 0)
-                                   : pl.f32 ? (long long)(pl.nact * pl.ldx + pl.nact * pl.ldw) * 4
-                                            : (long long)(pl.nact * pl.ldx + pl.nact * pl.ldw) * 8 +
-                                                  (p->ints == PNOF_INTS_DF_BF16 ? 8LL * pl.nbf * pl.nbf : 0);
+                                   : (long long)(pl.nact * pl.ldx + pl.nact * pl.ldw) * (pl.f32 ? 4 : 8);
   const long long cap = std::max(1LL, (2LL << 30) / std::max(1LL, per_p));
-  if (tu.pchunk <= 0) pc = std::min(pc, cap);
+  if (tu.pchunk <= 0) {
+    // float64: chunks of equal length of at most 512 rows (a chunk's last blocks leave the chip partly idle:
+    // at 500 functions, 300 active, 2000 rows the Lagrangian takes 15.1 ms in chunks of 103 rows, 13.1 of
+    // 250, 12.7 of 500)
+    if (!pl.split && !pl.f32) pc = cdiv(pl.naux, cdiv(pl.naux, std::max(1LL, std::min(cap, 512LL))));
+    pc = std::min(pc, cap);
+  }
   pc = std::min<long long>(pc, pl.naux);
+  if (!pl.split) pc = std::min(pc, INT_MAX / (long long)pl.nbf);   // X counts a chunk's stacked rows in 32 bits
   pl.pc = (int)std::max(1LL, pc);
   const int tt = cdiv(pl.nact, tile);
   const long long ntri = (long long)tt * (tt + 1) / 2;
-  pl.ns2 = tu.nsplit_b > 0 ? tu.nsplit_b : (int)std::max(1LL, (1024 + ntri - 1) / ntri);
+  const long long auto2 = std::max(1LL, (1024 + ntri - 1) / ntri);
+  pl.ns2 = tu.nsplit_b > 0 ? tu.nsplit_b : pl.split ? (int)auto2 : best_splits(pl.pc, ntri, 768, 0.25);
   pl.ns2 = std::min(pl.ns2, pl.pc);
   // Y: as many P-splits as fit the chip's resident blocks in one round (MI355X: 256 compute units;
-  // the 128 x 128 bf16 tile runs two blocks per unit); the float64 form takes about 1024 blocks
+  // the 128 x 128 bf16 tile runs two blocks per unit, the float64 tile of 128 x 64 three); the float32
+  // form takes about 1024 blocks of 64 x 64 (its splits set the rounding of Y)
   const long long t3 = (long long)cdiv(pl.nbf, ym) * cdiv(pl.nact, yn);
-  const long long auto3 = pl.split ? std::max(1LL, (pl.yv == 1 ? 512 : 256) / t3) : std::max(1LL, (1024 + t3 - 1) / t3);
+  const long long auto3 = pl.split ? std::max(1LL, (pl.yv == 1 ? 512 : 256) / t3)
+                          : pl.f32 ? std::max(1LL, (1024 + t3 - 1) / t3)
+                                   : best_splits(pl.pc, (long long)cdiv(pl.nbf, 128) * cdiv(pl.nact, 64), 768, 0.25);
   pl.ns3 = tu.nsplit_y > 0 ? tu.nsplit_y : (int)auto3;
   pl.ns3 = std::min(pl.ns3, pl.pc);
   return pl;
@@ -261,7 +291,7 @@ struct Bufs {
   u16 *ch16, *cl16;     // split mode: fp16 pair of C~ sC
   uint32_t* bnd;        // split mode: scale bounds (call-level words, then two per chunk)
   float* colb;          // split mode: per-orbital bounds (4 nact)
-  double *XT, *W, *Ypart64, *Bw;   // fp64 chunk
+  double *XT, *W, *Ypart64;   // fp64 chunk
   float *Ct32, *XT32, *W32;        // fp32 path
   u16 *xth, *xtl, *wh, *wl, *bh, *bl;  // split chunk
   u16 *xth2, *xtl2;                    // split: XT of the next chunk (X runs one chunk ahead)
@@ -302,7 +332,6 @@ Bufs carve(const Plan& pl, char* base) {
       b.XT = a.take<double>((long long)pl.pc * pl.nact * pl.ldx);
       b.W = a.take<double>((long long)pl.pc * pl.nact * pl.ldw);
       b.Ypart64 = a.take<double>((long long)pl.ns3 * ny);
-      if (pl.ints == PNOF_INTS_DF_BF16) b.Bw = a.take<double>((long long)pl.pc * pl.nbf * pl.nbf);
     } else {
       b.cth = a.take<u16>((long long)pl.nact32 * pl.ldk);
       b.ctl = a.take<u16>((long long)pl.nact32 * pl.ldk);
@@ -480,7 +509,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
     if (want_y) DEV_CHECK(ctx, fill_f64(s, b.Y2e, ny, 0.0));
     WsDims wd{pl.nact32, 0, 0, 0};
     if (pl.f32) {
-      DEV_CHECK(ctx, transpose_ca_f32(s, nbf, nact, C, b.Ct32, pl.ldk));
+      DEV_CHECK(ctx, transpose_ca(s, nbf, nact, C, b.Ct32, pl.ldk));
       corr_terms = 1;
     } else if (!pl.split) DEV_CHECK(ctx, transpose_ca(s, nbf, nact, C, b.Ct, pl.ldk));
     else {
@@ -515,13 +544,13 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         const bool bb = pl.ints == PNOF_INTS_DF_BF16;
         const void* Bc = bb ? static_cast<const void*>(static_cast<const u16*>(ints) + p0 * bsz)
                             : static_cast<const void*>(static_cast<const double*>(ints) + p0 * bsz);
-        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_f32_gemm1(s, nbf, nact, np, b.Ct32, pl.ldk, Bc, bb, b.XT32, pl.ldx)));
-        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_f32_gemm2(s, nbf, nact, np, ns2, b.Ct32, pl.ldk, b.XT32, pl.ldx,
-                                                              b.beta32, b.Kpart, Dc, b.W32, pl.ldw)));
+        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_fp_gemm1(s, nbf, nact, np, b.Ct32, pl.ldk, Bc, bb, b.XT32, pl.ldx)));
+        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_fp_gemm2<float>(s, nbf, nact, np, ns2, b.Ct32, pl.ldk, b.XT32, pl.ldx,
+                                                                    b.beta32, b.Kpart, p0 == 0, Dc, b.W32, pl.ldw)));
         if (want_y) {
           DEV_CHECK(ctx, add_diag_f32(s, nact, np, Dc, occ, b.dbuf, b.W32, pl.ldw));
-          DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_f32_gemm3(s, nbf, nact, np, ns3, b.XT32, pl.ldx, b.W32, pl.ldw,
-                                                                b.Ypart32)));
+          DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_fp_gemm3(s, nbf, nact, np, ns3, b.XT32, pl.ldx, b.W32, pl.ldw,
+                                                               b.Ypart32)));
           DEV_CHECK(ctx, reduce_y_f32(s, ny, ns3, b.Ypart32, b.Y2e));
         }
         if (r.Jq || r.Kq || r.Fq)
@@ -533,21 +562,19 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         const int np = std::min(pl.pc, pl.naux - p0);
         const int ns2 = std::min(pl.ns2, np), ns3 = std::min(pl.ns3, np);
         double* Dc = b.D + (long long)p0 * nact;
-        const double* Bc;
-        if (pl.ints == PNOF_INTS_DF_F64) Bc = static_cast<const double*>(ints) + p0 * bsz;
-        else {
-          DEV_CHECK(ctx, widen_bf16(s, np * bsz, static_cast<const u16*>(ints) + p0 * bsz, b.Bw));
-          Bc = b.Bw;
-        }
-        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_f64_gemm1(s, nbf, nact, np, b.Ct, pl.ldk, Bc, b.XT, pl.ldx)));
-        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_f64_gemm2(s, nbf, nact, np, ns2, b.Ct, pl.ldk, b.XT, pl.ldx, b.beta, b.Kpart, Dc, b.W, pl.ldw)));
+        const bool bb = pl.ints == PNOF_INTS_DF_BF16;
+        const void* Bc = bb ? static_cast<const void*>(static_cast<const u16*>(ints) + p0 * bsz)
+                            : static_cast<const void*>(static_cast<const double*>(ints) + p0 * bsz);
+        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_fp_gemm1(s, nbf, nact, np, b.Ct, pl.ldk, Bc, bb, b.XT, pl.ldx)));
+        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_fp_gemm2<double>(s, nbf, nact, np, ns2, b.Ct, pl.ldk, b.XT, pl.ldx, b.beta,
+                                                                     b.Kpart, p0 == 0, Dc, b.W, pl.ldw)));
         if (want_y) {
           DEV_CHECK(ctx, add_diag_f64(s, nact, np, Dc, occ, b.dbuf, b.W, pl.ldw));
-          DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_f64_gemm3(s, nbf, nact, np, ns3, b.XT, pl.ldx, b.W, pl.ldw, b.Ypart64)));
+          DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_fp_gemm3(s, nbf, nact, np, ns3, b.XT, pl.ldx, b.W, pl.ldw, b.Ypart64)));
           DEV_CHECK(ctx, reduce_y_f64(s, ny, ns3, b.Ypart64, b.Y2e));
         }
         if (r.Jq || r.Kq || r.Fq)
-          DEV_CHECK(ctx, df_ao_accum(s, nbf, nact, np, r.nq, r.q_idx, Bc, 0, Dc, b.alpha, b.beta, b.XT, nullptr, nullptr,
+          DEV_CHECK(ctx, df_ao_accum(s, nbf, nact, np, r.nq, r.q_idx, Bc, bb, Dc, b.alpha, b.beta, b.XT, nullptr, nullptr,
                                      nullptr, pl.ldx, (long long)nact * pl.ldx, r.Jq, r.Kq, r.Fq, nullptr, 0));
       }
     } else {

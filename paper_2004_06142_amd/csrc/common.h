@@ -305,26 +305,22 @@ struct F64Gemm {
 hipError_t gemm_f64_grouped(hipStream_t s, int ngemm, int maxM, int maxN, bool a_unit_m, bool b_unit_n,
                             const F64Gemm* tab);
 
-// FP64 three-index contractions of one P-chunk (np rows of B).
-//  gemm1: XT[P][p][mu] = sum_nu Ct[p][nu] B_P[mu][nu]      (Ct: nact x ldk, XT: ld ldx)
-//  gemm2: b_P = Ct XT_P^T on lower tiles; Kpart[s] += b^2; D[P][p] = b_pp; W[P] = b o beta
-//  gemm3: Ypart[s][mu][q] = sum_{P in split s} sum_r XT[P][r][mu] W[P][r][q]
-hipError_t df_f64_gemm1(hipStream_t s, int nbf, int nact, int np, const double* Ct, int ldk,
-                        const double* Bchunk, double* XT, int ldx);
-hipError_t df_f64_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, const double* Ct,
-                        int ldk, const double* XT, int ldx, const double* beta, double* Kpart,
-                        double* Dchunk, double* W, int ldw);
-hipError_t df_f64_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, const double* XT,
-                        int ldx, const double* W, int ldw, double* Ypart);
-// Float32 forms (PNOF_FP32): float operands and accumulation, float64 K sums and D; gemm1 reads B as
-// stored (bf16 when b_is_bf16, else float64) and rounds it to float.
-hipError_t df_f32_gemm1(hipStream_t s, int nbf, int nact, int np, const float* Ct, int ldk, const void* Bchunk,
-                        int b_is_bf16, float* XT, int ldx);
-hipError_t df_f32_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, const float* Ct, int ldk,
-                        const float* XT, int ldx, const float* beta32, double* Kpart, double* Dchunk, float* W,
-                        int ldw);
-hipError_t df_f32_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, const float* XT, int ldx,
-                        const float* W, int ldw, float* Ypart);
+// Three-index contractions of one P-chunk (np rows of B), T = double or float (PNOF_FP32: float operands and
+// accumulation within a P row, float64 K sums and D).
+//  gemm1: XT[P][p][mu] = sum_nu Ct[p][nu] B_P[mu][nu]      (Ct: nact x ldk, XT: ld ldx; B read as stored)
+//  gemm2: b_P = Ct XT_P^T on lower tiles; Kpart[s] += b^2 (= with kset); D[P][p] = b_pp; W[P] = b o beta, in
+//         64 x 64 blocks on and below the diagonal
+//  gemm3: Ypart[s][mu][q] = sum_{P in split s} sum_r XT[P][r][mu] W[P][r][q], W as gemm2 stores it
+template <typename T>
+hipError_t df_fp_gemm1(hipStream_t s, int nbf, int nact, int np, const T* Ct, int ldk, const void* Bchunk, int b_is_bf16,
+                       T* XT, int ldx);
+template <typename T>
+hipError_t df_fp_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, const T* Ct, int ldk, const T* XT, int ldx,
+                       const T* beta, double* Kpart, bool kset, double* Dchunk, T* W, int ldw);
+int df_fp_y_tile(int nbf, int nact, int nsplit);   // 128 or 64: rows of gemm3's tile (by 64 active orbitals)
+template <typename T>
+hipError_t df_fp_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, const T* XT, int ldx, const T* W, int ldw,
+                       T* Ypart);
 
 // ---------------------------------------------------------------- bf16 split GEMMs (k_gemm_bf16.hip)
 // terms: 1 = hi*hi; 3 = hi*hi + hi*lo + lo*hi.  variant: 0 = 128 x 128 block tiles (two blocks per
@@ -544,8 +540,8 @@ hipError_t zero_pads_u16(hipStream_t s, u16* base, int nslice, long long sstride
                          int cols);
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                   double* alpha, double* beta, float* beta32);
-hipError_t transpose_ca(hipStream_t s, int nbf, int nact, const double* C, double* Ct, int ldk);
-hipError_t transpose_ca_f32(hipStream_t s, int nbf, int nact, const double* C, float* Ct, int ldk);
+template <typename T>
+hipError_t transpose_ca(hipStream_t s, int nbf, int nact, const double* C, T* Ct, int ldk);
 // The occupations and the subspace layout (the structure of the Coulomb coefficients alpha).
 struct OccLayout {
   const double* n;
@@ -573,7 +569,6 @@ hipError_t scale_bounds(hipStream_t s, int nbf, int nact, const double* C, const
 // raised into slot[2c], slot[2c + 1] (the words must start at zero).
 hipError_t b_bounds(hipStream_t s, const void* B, int is_f64, long long nrows, int n, long long rows_per_chunk,
                     uint32_t* slot);
-hipError_t widen_bf16(hipStream_t s, long long n, const u16* src, double* dst);
 hipError_t hpp_from_hc(hipStream_t s, int nbf, int nact, const double* C, const double* HC, double* Hpp);
 // Split-K float64 product for few output tiles: ks (<= F64_KSPLIT_MAX) dense M x N partial slabs in
 // Cpart, summed by the caller in slab order.  gemm_f64_ksplit gives the split used for a shape.

@@ -53,16 +53,11 @@ __global__ void coeffs_k(int nact, int npairs, int ncwo, int nsingle, int functi
   }
 }
 
-__global__ void transpose_ca_k(int nbf, int nact, const double* __restrict__ C, double* __restrict__ Ct, int ldk) {
+template <typename T>
+__global__ void transpose_ca_k(int nbf, int nact, const double* __restrict__ C, T* __restrict__ Ct, int ldk) {
   GRID_STRIDE(i, (long long)nact * nbf) {
     const int p = (int)(i / nbf), mu = (int)(i % nbf);
-    Ct[(long long)p * ldk + mu] = C[(long long)mu * nbf + p];
-  }
-}
-__global__ void transpose_ca_f32_k(int nbf, int nact, const double* __restrict__ C, float* __restrict__ Ct, int ldk) {
-  GRID_STRIDE(i, (long long)nact * nbf) {
-    const int p = (int)(i / nbf), mu = (int)(i % nbf);
-    Ct[(long long)p * ldk + mu] = (float)C[(long long)mu * nbf + p];
+    Ct[(long long)p * ldk + mu] = (T)C[(long long)mu * nbf + p];
   }
 }
 
@@ -943,12 +938,12 @@ hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, in
   LAUNCH(coeffs_k, grid1((long long)nact * nact), dim3(NT), nact, npairs, ncwo, nsingle, functional, n, alpha, beta,
          beta32);
 }
-hipError_t transpose_ca(hipStream_t s, int nbf, int nact, const double* C, double* Ct, int ldk) {
-  LAUNCH(transpose_ca_k, grid1((long long)nbf * nact), dim3(NT), nbf, nact, C, Ct, ldk);
+template <typename T>
+hipError_t transpose_ca(hipStream_t s, int nbf, int nact, const double* C, T* Ct, int ldk) {
+  LAUNCH(transpose_ca_k<T>, grid1((long long)nbf * nact), dim3(NT), nbf, nact, C, Ct, ldk);
 }
-hipError_t transpose_ca_f32(hipStream_t s, int nbf, int nact, const double* C, float* Ct, int ldk) {
-  LAUNCH(transpose_ca_f32_k, grid1((long long)nbf * nact), dim3(NT), nbf, nact, C, Ct, ldk);
-}
+template hipError_t transpose_ca<double>(hipStream_t, int, int, const double*, double*, int);
+template hipError_t transpose_ca<float>(hipStream_t, int, int, const double*, float*, int);
 hipError_t add_diag_f32(hipStream_t s, int nact, int np, const double* Dc, const OccLayout& oc, double* dbuf, float* W,
                         int ldw) {
   if (np <= 0) return hipSuccess;
@@ -1143,20 +1138,4 @@ hipError_t fock_ao_h(hipStream_t s, int nbf, int nq, const int32_t* q_idx, const
   LAUNCH(fock_ao_h_k, grid1((long long)nq * nbf * nbf), dim3(NT), nbf, nq, q_idx, n, H, Fq);
 }
 
-}  // namespace pnof
-
-namespace pnof {
-namespace {
-__global__ void widen_bf16_k(long long n, const u16* __restrict__ src, double* __restrict__ dst) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    dst[i] = (double)bf16_bits_to_f32(src[i]);
-}
-}  // namespace
-hipError_t widen_bf16(hipStream_t s, long long n, const u16* src, double* dst) {
-  if (n <= 0) return hipSuccess;
-  long long b = (n + 255) / 256;
-  if (b > 65535LL * 16) b = 65535LL * 16;
-  hipLaunchKernelGGL(widen_bf16_k, dim3((unsigned)b), dim3(256), 0, s, n, src, dst);
-  return hipGetLastError();
-}
 }  // namespace pnof
