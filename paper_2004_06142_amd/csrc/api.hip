@@ -504,9 +504,6 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
     if (r.Kq) DEV_CHECK(ctx, gather_ao(s, nbf, r.nq, r.q_idx, b.Kr, r.Kq));
     if (r.Fq) DEV_CHECK(ctx, eri_fock_ao(s, nbf, nact, r.nq, r.q_idx, n, H, b.alpha, b.beta, b.Jr, b.Kr, r.Fq));
   } else {
-    DEV_CHECK(ctx, fill_f64(s, K, n2, 0.0));
-    DEV_CHECK(ctx, fill_f64(s, b.Kpart, (long long)pl.ns2 * n2, 0.0));
-    if (want_y) DEV_CHECK(ctx, fill_f64(s, b.Y2e, ny, 0.0));
     WsDims wd{pl.nact32, 0, 0, 0};
     if (pl.f32) {
       DEV_CHECK(ctx, transpose_ca(s, nbf, nact, C, b.Ct32, pl.ldk));
@@ -516,23 +513,14 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
       const long long nct = (long long)pl.nact32 * pl.ldk, nxt = (long long)pl.pc * pl.nact32 * pl.ldx,
                       nw = (long long)pl.pc * pl.nact32 * pl.ldw;
       wd = WsDims{pl.nact32, 2 * nct, 2 * nxt, 2 * nw};
-      // the zero pads of the tiles are part of the contract of the contraction kernels; the valid
-      // blocks (Ct: nact x nbf, XT_P: nact x nbf, W_P: the part of nact x nact that Y reads) are
-      // overwritten before they are read, so only the pads are cleared
-      const long long sx = (long long)pl.nact32 * pl.ldx, sw = (long long)pl.nact32 * pl.ldw;
-      for (int lo = 0; lo < (pl.terms > 1 ? 2 : 1); ++lo) {
-        DEV_CHECK(ctx, zero_pads_u16(s, lo ? b.ctl : b.cth, 1, nct, nact, pl.nact32, pl.ldk, nbf));
-        if (pl.terms > 1) DEV_CHECK(ctx, zero_pads_u16(s, lo ? b.cl16 : b.ch16, 1, nct, nact, pl.nact32, pl.ldk, nbf));
-        DEV_CHECK(ctx, zero_pads_u16(s, lo ? b.xtl : b.xth, pl.pc, sx, nact, pl.nact32, pl.ldx, nbf));
-        DEV_CHECK(ctx, zero_pads_u16(s, lo ? b.xtl2 : b.xth2, pl.pc, sx, nact, pl.nact32, pl.ldx, nbf));
-        DEV_CHECK(ctx, zero_pads_u16(s, lo ? b.wl : b.wh, pl.pc, sw, nact, pl.nact32, pl.ldw, nact));
-      }
+      // the padding of the tiles is zero as part of the contract of the contraction kernels: whoever
+      // writes an operand writes its padding (split_ca, X, b)
       // split mode: bounds that fix the power-of-two scales of the fp16 pairs (call-level words; the
       // per-chunk words are cleared here and raised by the row bounds of each chunk of B)
       if (pl.terms > 1)
         DEV_CHECK(ctx, scale_bounds(s, nbf, nact, C, n, pl.npairs, pl.ncwo, pl.nsingle, pl.functional, b.colb, b.bnd,
                                     2 * (int)cdiv(pl.naux, pl.pc)));
-      DEV_CHECK(ctx, split_ca(s, nbf, nact, pl.terms, C, b.cth, b.ctl, b.ch16, b.cl16, pl.ldk, b.bnd));
+      DEV_CHECK(ctx, split_ca(s, nbf, nact, pl.nact32, pl.terms, C, b.cth, b.ctl, b.ch16, b.cl16, pl.ldk, b.bnd));
       corr_terms = pl.terms > 1 ? 2 : 1;
     }
     const long long bsz = (long long)nbf * nbf;
@@ -551,7 +539,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
           DEV_CHECK(ctx, add_diag_f32(s, nact, np, Dc, occ, b.dbuf, b.W32, pl.ldw));
           DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_fp_gemm3(s, nbf, nact, np, ns3, b.XT32, pl.ldx, b.W32, pl.ldw,
                                                                b.Ypart32)));
-          DEV_CHECK(ctx, reduce_y_f32(s, ny, ns3, b.Ypart32, b.Y2e));
+          DEV_CHECK(ctx, reduce_y_f32(s, ny, ns3, p0 == 0, b.Ypart32, b.Y2e));
         }
         if (r.Jq || r.Kq || r.Fq)
           DEV_CHECK(ctx, df_ao_accum(s, nbf, nact, np, r.nq, r.q_idx, Bc, bb, Dc, b.alpha, b.beta, nullptr, b.XT32,
@@ -571,7 +559,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         if (want_y) {
           DEV_CHECK(ctx, add_diag_f64(s, nact, np, Dc, occ, b.dbuf, b.W, pl.ldw));
           DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_fp_gemm3(s, nbf, nact, np, ns3, b.XT, pl.ldx, b.W, pl.ldw, b.Ypart64)));
-          DEV_CHECK(ctx, reduce_y_f64(s, ny, ns3, b.Ypart64, b.Y2e));
+          DEV_CHECK(ctx, reduce_y_f64(s, ny, ns3, p0 == 0, b.Ypart64, b.Y2e));
         }
         if (r.Jq || r.Kq || r.Fq)
           DEV_CHECK(ctx, df_ao_accum(s, nbf, nact, np, r.nq, r.q_idx, Bc, bb, Dc, b.alpha, b.beta, b.XT, nullptr, nullptr,
@@ -591,12 +579,6 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
       SplitPtr C16{split ? b.ch16 : b.cth, split ? b.cl16 : nullptr};   // b (and X from float64 B)
       u16* const xth_[2] = {b.xth, b.xth2};
       u16* const xtl_[2] = {b.xtl, b.xtl2};
-      // W stored once per 128 x 128 block pair (b writes only the transposed image of its tiles, the
-      // blocks on and above the diagonal; Y reads each block in the orientation that holds it): needs
-      // Y's direct-load path
-      auto a16 = [](const void* p) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-      const bool wsym = pl.ldx % 32 == 0 && pl.ldw % 32 == 0 && a16(b.xth) && a16(b.xth2) && a16(b.xtl) &&
-                        a16(b.xtl2) && a16(b.wh) && a16(b.wl);
       // one_stream: the second stream's work runs in order on the context's stream
       const bool two = !r.one_stream;
       if (two) RB_CHECK(ensure_aux(ctx));
@@ -659,8 +641,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         double* Dc = b.D + (long long)p0 * nact;
         SplitPtr XT{xth_[c & 1], split ? xtl_[c & 1] : nullptr};
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_bf16_gemm2(s, nbf, nact, np, ns2, pl.terms, C16, pl.ldk, XT, pl.ldx,
-                                                               b.beta32, b.Kpart, Dc, b.wh, b.wl, pl.ldw, wd, b.bnd, c,
-                                                               wsym)));
+                                                               b.beta32, b.Kpart, c == 0, Dc, b.wh, b.wl, pl.ldw, wd, b.bnd, c)));
         if (want_y) {
           if (two) {
             DEV_CHECK(ctx, hipEventRecord(ev_b, s));
@@ -679,12 +660,12 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
           }
           SplitPtr W{b.wh, b.wl};
           DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_bf16_gemm3(s, nbf, nact, np, ns3, pl.terms, XT, pl.ldx, W, pl.ldw,
-                                                                 b.Ypart32, pl.yv, wd, b.bnd, c, wsym)));
+                                                                 b.Ypart32, pl.yv, wd, b.bnd, c)));
           if (two) {
             DEV_CHECK(ctx, hipEventRecord(ev_y, s));
             DEV_CHECK(ctx, hipStreamWaitEvent(sa, ev_y, 0));
           }
-          DEV_CHECK(ctx, reduce_y_f32(sa, ny, ns3, b.Ypart32, b.Y2e));
+          DEV_CHECK(ctx, reduce_y_f32(sa, ny, ns3, c == 0, b.Ypart32, b.Y2e));
           if (two) DEV_CHECK(ctx, hipEventRecord(ev_r, sa));
         }
         if (r.Jq || r.Kq || r.Fq) {
@@ -1124,7 +1105,7 @@ hipError_t batch_enqueue(pnof_batch b, hipStream_t s) {
   BSTEP(hipEventRecord(b->ev[2], s2));
   BSTEP(gemm_f64_grouped(s, n, b->maxM[1], b->maxN[1], false, true, b->d_f64 + n));
   BSTEP(batch_add_diag(s, n, b->d_inst, b->mx));
-  BSTEP(df_bf16_gemm3_grouped(s, n, b->tot3, b->terms, b->tile[2], b->d_g3, b->d_off + 2 * (n + 1)));
+  BSTEP(df_bf16_gemm3_grouped(s, n, b->tot3, b->terms, b->tile[2], b->tile[1], b->d_g3, b->d_off + 2 * (n + 1)));
   BSTEP(batch_reduce(s, n, b->d_inst, b->mx));
   BSTEP(hipStreamWaitEvent(s, b->ev[2], 0));
   BSTEP(batch_energy_y(s, n, b->d_inst, b->mx));

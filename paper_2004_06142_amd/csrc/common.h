@@ -370,10 +370,7 @@ struct G2Args {   // b_P = Ct XT_P^T; K partials, D, W
   WsDims ws;
   const uint32_t* bnd;
   int chunk;
-  // W stored once per 128 x 128 block pair, W_P being symmetric: each tile (on or below the
-  // diagonal) writes only its transposed image W[q][p], so W holds the blocks on and above the
-  // diagonal; gemm3 with wsym reads it that way
-  int wsym = 0;
+  int kset = 1;   // store the K sums (a problem's first chunk) instead of adding them
 };
 struct G3Args {   // Ypart[s] = sum_{P in s} X_P W_P
   int nbf, nact, np, nsplit;
@@ -387,13 +384,12 @@ struct G3Args {   // Ypart[s] = sum_{P in s} X_P W_P
   WsDims ws;
   const uint32_t* bnd;
   int chunk;
-  int wsym = 0;   // W as gemm2 writes it with wsym (see G2Args)
 };
-// Work items of one launch.  The stacked form of X treats the rows (P, mu) of np consecutive B_P
-// as one matrix (B_P rows padded to ldb, bstride == nbf * ldb), so short rows do not waste tiles.
+// Work items of one launch.  The stacked form of X treats the rows (P, mu) of np consecutive B_P, each
+// counted as nbf rounded up to 8, as one matrix, so short rows do not waste tiles.
 // g1m x g1n: the block tile along (p, mu); grid and kernel must use the same values.
 __host__ __device__ inline int g1_items(const G1Args& a, int g1m, int g1n, bool stacked) {
-  return cdiv(a.nact, g1m) * (stacked ? cdiv((long long)a.np * a.nbf, g1n) : a.np * cdiv(a.nbf, g1n));
+  return cdiv(a.nact, g1m) * (stacked ? cdiv((long long)a.np * ((a.nbf + 7) & ~7), g1n) : a.np * cdiv(a.nbf, g1n));
 }
 // tt: the square tile of the b contraction (128; 64 for the grouped form of short active spaces)
 __host__ __device__ inline int g2_items(const G2Args& a, int tt) {
@@ -417,7 +413,7 @@ hipError_t df_bf16_gemm1_grouped(hipStream_t s, int ninst, int total, int terms,
                                  const int* off);
 hipError_t df_bf16_gemm2_grouped(hipStream_t s, int ninst, int total, int terms, int tile, const G2Args* tab,
                                  const int* off);
-hipError_t df_bf16_gemm3_grouped(hipStream_t s, int ninst, int total, int terms, int tile, const G3Args* tab,
+hipError_t df_bf16_gemm3_grouped(hipStream_t s, int ninst, int total, int terms, int tile, int btile, const G3Args* tab,
                                  const int* off);
 
 // Split mode (terms > 1): bnd / chunk give the scales of the chunk (chunk_scales); the X output, the
@@ -426,16 +422,16 @@ hipError_t df_bf16_gemm3_grouped(hipStream_t s, int ninst, int total, int terms,
 hipError_t df_bf16_gemm1(hipStream_t s, int nbf, int nact, int np, int terms, SplitPtr Ct, int ldk, SplitPtr Bp,
                          long long bstride, int ldb, long long b_bytes, u16* XT_hi, u16* XT_lo, int ldx, int variant,
                          const WsDims& d, const uint32_t* bnd, int chunk);
-// wsym: W is written only as the transposed image of b's tiles, i.e. its 128 x 128 blocks on and
-// above the diagonal (gemm2), and Y reads each block of W in the orientation that holds it (gemm3);
-// split mode, 128 x 128 b tiles, Y on the direct-load path only.
+// W is written only as the transposed image of b's tiles, i.e. its 128 x 128 blocks on and above the
+// diagonal (gemm2), and Y reads each block of W in the orientation that holds it (gemm3).  kset: store the K
+// partials (the first chunk) instead of adding to them.  Leading dimensions of 32, operands 16-byte aligned.
 hipError_t df_bf16_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms,
                          SplitPtr Ct, int ldk, SplitPtr XT, int ldx, const float* beta32,
-                         double* Kpart, double* Dchunk, u16* W_hi, u16* W_lo, int ldw, const WsDims& d,
-                         const uint32_t* bnd, int chunk, bool wsym = false);
+                         double* Kpart, int kset, double* Dchunk, u16* W_hi, u16* W_lo, int ldw, const WsDims& d,
+                         const uint32_t* bnd, int chunk);
 hipError_t df_bf16_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms, SplitPtr XT,
                          int ldx, SplitPtr W, int ldw, float* Ypart, int variant, const WsDims& d,
-                         const uint32_t* bnd, int chunk, bool wsym = false);
+                         const uint32_t* bnd, int chunk);
 
 // ---------------------------------------------------------------- batches (k_batch.hip)
 // One instance of a batch: sizes, the caller's inputs and outputs, and its slices of the batch
@@ -535,9 +531,6 @@ hipError_t batch_persist(hipStream_t s, const PArgs& a, int ninst_state_words, i
 // ---------------------------------------------------------------- small kernels (k_small.hip)
 hipError_t fill_f64(hipStream_t s, double* p, long long n, double v);
 hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v);
-// zero columns [cols, ld) of rows [0, rows) and rows [rows, rows_pad) of nslice slices
-hipError_t zero_pads_u16(hipStream_t s, u16* base, int nslice, long long sstride, int rows, int rows_pad, int ld,
-                         int cols);
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                   double* alpha, double* beta, float* beta32);
 template <typename T>
@@ -551,8 +544,9 @@ struct OccLayout {
 hipError_t add_diag_f32(hipStream_t s, int nact, int np, const double* Dchunk, const OccLayout& oc, double* dbuf,
                         float* W, int ldw);
 // C_A^T as bf16 (terms 1) or, in the split mode, the compact bf16 pair (hi, lo) plus the fp16 pair
-// (h16, l16) of the same value times sC (bnd: call-level words already formed).
-hipError_t split_ca(hipStream_t s, int nbf, int nact, int terms, const double* C, u16* Ct_hi,
+// (h16, l16) of the same value times sC (bnd: call-level words already formed); `rows` x ldk in all, the
+// padding zero.
+hipError_t split_ca(hipStream_t s, int nbf, int nact, int rows, int terms, const double* C, u16* Ct_hi,
                     u16* Ct_lo, u16* Ct_h16, u16* Ct_l16, int ldk, const uint32_t* bnd);
 // float64 B rows of one chunk (nrows rows of n) as the fp16 pair of B sB, in rows of ldo (a multiple of
 // 8, zeros from n on; or ldo == n).
@@ -585,9 +579,10 @@ hipError_t add_diag_f64(hipStream_t s, int nact, int np, const double* Dchunk, c
 hipError_t add_diag_bf16(hipStream_t s, int nact, int np, const double* Dchunk, const OccLayout& oc,
                          const float* beta32, double* dbuf, u16* W_hi, u16* W_lo, int ldw, long long pstride,
                          const uint32_t* bnd, int chunk);
+// K = sum of the partials; Y2e += theirs (first: = theirs).
 hipError_t reduce_k(hipStream_t s, int nact, int nsplit, const double* Kpart, double* K);
-hipError_t reduce_y_f64(hipStream_t s, long long n, int nsplit, const double* Ypart, double* Y);
-hipError_t reduce_y_f32(hipStream_t s, long long n, int nsplit, const float* Ypart, double* Y);
+hipError_t reduce_y_f64(hipStream_t s, long long n, int nsplit, int first, const double* Ypart, double* Y);
+hipError_t reduce_y_f32(hipStream_t s, long long n, int nsplit, int first, const float* Ypart, double* Y);
 hipError_t energy(hipStream_t s, int nbf, int nact, const double* n, const double* Hpp,
                   const double* alpha, const double* beta, const double* J, const double* K,
                   const double* Y2e, const double* C, const u16* Ct_hi, const u16* Ct_lo, const float* Ct32, int ldk,

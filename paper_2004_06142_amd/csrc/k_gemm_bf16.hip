@@ -53,19 +53,12 @@ __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
 struct Opnd {
   const u16* hi;
   const u16* lo;
-  long long ld;   // elements between consecutive storage rows
-  int R;          // valid output-index extent (rows of a row operand, columns of a col operand)
-  int K;          // valid k extent
-  bool col;       // storage rows run along k (read through the transposing LDS load)
+  long long ld;   // elements between consecutive rows
+  int R, K;       // valid rows, valid k
 };
 
-__device__ __forceinline__ bool aligned16(const void* p, long long ld) {
-  return ((ld & 7) == 0) && ((reinterpret_cast<uintptr_t>(p) & 15) == 0);
-}
-
 // 8 consecutive elements src[0..7] of a storage row, zero beyond `valid` elements.
-__device__ __forceinline__ u32x4 ld8(const u16* __restrict__ src, int valid, bool vec) {
-  if (valid >= 8 && vec) return *reinterpret_cast<const u32x4*>(src);
+__device__ __forceinline__ u32x4 ld8(const u16* __restrict__ src, int valid) {
   uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (int i = 0; i < 8; ++i)
@@ -82,96 +75,47 @@ __device__ __forceinline__ u32x4 ld8(const u16* __restrict__ src, int valid, boo
 // bit 1 of the chunk on rows with bit 3 set spreads them over four distinct slots.
 __device__ __forceinline__ int swz(int r) { return 2 * ((r >> 3) & 1); }
 
-// LDS geometry of one operand slice with D output-index rows.
-template <int D>
-struct Geo {
-  static constexpr int CP = D + 16;                          // col-layout pitch (bf16)
-  static constexpr int SLOT = (D * RP > BK * CP) ? D * RP : BK * CP;
-  static constexpr int NCH = D * BK / 8 / 256;               // 16-byte chunks per thread
-};
+// Row of the operand that row r of an interleaved slice holds (a permutation within each 32 rows): the
+// two 16 x 16 products of a row pair then leave each lane eight consecutive output elements (rows
+// 4 g .. 4 g + 3 of the first are 8 g .. 8 g + 3, those of the second 8 g + 4 .. 8 g + 7).
+__device__ __forceinline__ int ileave(int r) { return (r & ~31) | (((r >> 2) & 3) << 3) | (((r >> 4) & 1) << 2) | (r & 3); }
 
-// Global -> registers: one BK-deep k-tile of one operand slice (D x BK elements), as raw 16-byte
-// chunks plus the number of valid elements of each.  VEC: every storage row starts 16-byte aligned
-// and may be read in whole chunks up to the next multiple of 8 past K (or R); the load is issued
-// unconditionally from a clamped address, and the invalid elements are cleared only when the chunk
-// is written to LDS, so nothing waits on the load before the matrix-core work of the k-tile.
+// Global -> registers -> LDS: one BK-deep k-tile of one operand slice (D x BK elements, 4 chunks of 8 along
+// k per row), element by element.  IL: interleaved rows.
 template <int D>
 struct Chunks {
-  u32x4 v[Geo<D>::NCH];
-  int valid[Geo<D>::NCH];
+  u32x4 v[D * BK / 8 / 256];
 };
-
-template <int D, bool VEC>
+template <int D, bool IL>
 __device__ __forceinline__ void fetch(const u16* __restrict__ base, const Opnd& o, int r0, int k0, Chunks<D>& ch) {
-  const int t = threadIdx.x;
 #pragma unroll
-  for (int c = 0; c < Geo<D>::NCH; ++c) {
-    const int idx = t + 256 * c;
-    int gr, gk, valid;
-    long long off;
-    if (!o.col) {  // D rows x 4 chunks along k
-      gr = r0 + (idx >> 2);
-      gk = k0 + (idx & 3) * 8;
-      off = (long long)gr * o.ld + gk;
-      valid = o.K - gk;
-    } else {       // BK k-rows x D/8 chunks along the output index
-      gk = k0 + idx / (D / 8);
-      gr = r0 + (idx % (D / 8)) * 8;
-      off = (long long)gk * o.ld + gr;
-      valid = o.R - gr;
-    }
-    const bool ok = gr < o.R && gk < o.K;
-    ch.valid[c] = ok ? (valid < 8 ? valid : 8) : 0;
-    if (VEC) ch.v[c] = *reinterpret_cast<const u32x4*>(base + (ok ? off : 0));
-    else ch.v[c] = ok ? ld8(base + off, valid, false) : u32x4{0u, 0u, 0u, 0u};
+  for (int c = 0; c < D * BK / 8 / 256; ++c) {
+    const int idx = threadIdx.x + 256 * c;
+    const int gr = r0 + (IL ? ileave(idx >> 2) : idx >> 2), gk = k0 + (idx & 3) * 8;
+    ch.v[c] = gr < o.R && gk < o.K ? ld8(base + (long long)gr * o.ld + gk, o.K - gk) : u32x4{0u, 0u, 0u, 0u};
   }
 }
-
-__device__ __forceinline__ u32x4 mask8(u32x4 v, int valid) {
-  uint32_t w[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    w[i] = (2 * i < valid ? (v[i] & 0xFFFFu) : 0u) | (2 * i + 1 < valid ? (v[i] & 0xFFFF0000u) : 0u);
-  return u32x4{w[0], w[1], w[2], w[3]};
-}
-
-// Row layout: the four 16-byte chunks of row r are stored permuted, chunk c at c ^ swz(r), so that
-// fragment reads (one chunk of 16 consecutive rows per lane group) are free of bank conflicts.
+// The four 16-byte chunks of row r are stored permuted, chunk c at c ^ swz(r), so that fragment reads (one
+// chunk of 16 consecutive rows per lane group) are free of bank conflicts.
 template <int D>
-__device__ __forceinline__ void stash(u16* __restrict__ s, bool col, const Chunks<D>& ch) {
-  const int t = threadIdx.x;
+__device__ __forceinline__ void stash(u16* __restrict__ s, const Chunks<D>& ch) {
 #pragma unroll
-  for (int c = 0; c < Geo<D>::NCH; ++c) {
-    const int idx = t + 256 * c;
-    u16* dst = !col ? s + (idx >> 2) * RP + (((idx & 3) ^ swz(idx >> 2)) * 8)
-                    : s + (idx / (D / 8)) * Geo<D>::CP + (idx % (D / 8)) * 8;
-    *reinterpret_cast<u32x4*>(dst) = mask8(ch.v[c], ch.valid[c]);
+  for (int c = 0; c < D * BK / 8 / 256; ++c) {
+    const int idx = threadIdx.x + 256 * c;
+    *reinterpret_cast<u32x4*>(s + (idx >> 2) * RP + (((idx & 3) ^ swz(idx >> 2)) * 8)) = ch.v[c];
   }
 }
-
-// MFMA operand fragment for the 16 output rows starting at r: lane l gets row r + l%16 and the
-// eight k values 8*(l/16)..+7 of the current k-tile.
-template <int D>
-__device__ __forceinline__ bf16x8 frag(const u16* __restrict__ s, bool col, int r) {
-  const int lane = threadIdx.x & 63;
-  if (!col) {
-    const int rr = r + (lane & 15);
-    return *reinterpret_cast<const bf16x8*>(s + rr * RP + (((lane >> 4) ^ swz(rr)) * 8));
-  }
-  const int g = lane >> 4, L = lane & 15, j = L >> 2, q = L & 3;
-  typedef __attribute__((address_space(3))) v4s* lds_v4s;
-  const u16* p0 = s + (8 * g + j) * Geo<D>::CP + r + 4 * q;
-  const u16* p1 = s + (8 * g + 4 + j) * Geo<D>::CP + r + 4 * q;
-  union { v4s h[2]; bf16x8 v; } u;
-  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p0));
-  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p1));
-  return u.v;
+// MFMA operand fragment for the 16 rows starting at r: lane l gets row r + l%16 and the eight k values
+// 8*(l/16)..+7 of the current k-tile.
+__device__ __forceinline__ bf16x8 frag(const u16* __restrict__ s, int r) {
+  const int lane = threadIdx.x & 63, rr = r + (lane & 15);
+  return *reinterpret_cast<const bf16x8*>(s + rr * RP + (((lane >> 4) ^ swz(rr)) * 8));
 }
 
 template <int BM, int BN, bool ALO, bool BLO>
 struct Stage {
-  u16 a[2][ALO ? 2 : 1][Geo<BM>::SLOT];
-  u16 b[2][BLO ? 2 : 1][Geo<BN>::SLOT];
+  u16 a[2][ALO ? 2 : 1][BM * RP];
+  u16 b[2][BLO ? 2 : 1][BN * RP];
 };
 
 template <int MI, int NI>
@@ -182,84 +126,63 @@ __device__ __forceinline__ void zero(f32x4 (&acc)[MI][NI]) {
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// Main loop over a sequence of segments (one per P), each a contraction over k in [0, K), for a
-// BM x BN block tile; 4 waves in 2 x 2, each owning (BM/2) x (BN/2).  acc is reset at the start of
-// each segment when RESET; epi(seg, acc) runs at the end of each.  A(seg, k0) / B(seg, k0) give
-// the operand descriptors of a k-tile (the storage order may change from one k-tile to the next).
-template <int BM, int BN, bool ALO, bool BLO, bool ACOL, bool BCOL, bool RESET, bool F16, typename FA, typename FB,
-          typename EPI>
-__device__ __forceinline__ void mainloop(Stage<BM, BN, ALO, BLO>& sm, int nseg, int kb, int ke, int m0, int n0, FA A,
-                                         FB B, f32x4 (&acc)[BM / 32][BN / 32], EPI epi) {
+// Main loop over k in [0, K) for a BM x BN block tile whose operands' rows need not be aligned; 4 waves in
+// 2 x 2, each owning (BM/2) x (BN/2).  Transposed products of interleaved rows of B, as mainloop_dl with
+// lay 2.
+template <int BM, int BN, bool ALO, bool BLO, bool F16>
+__device__ __forceinline__ void mainloop(Stage<BM, BN, ALO, BLO>& sm, int K, int m0, int n0, const Opnd& A, const Opnd& B,
+                                         f32x4 (&acc)[BM / 32][BN / 32]) {
   constexpr int MI = BM / 32, NI = BN / 32;
   const int wave = threadIdx.x >> 6;
   const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
-  const int KT = (ke - kb + BK - 1) / BK;
-  const int total = nseg * KT;
-  if (total <= 0) return;
   Chunks<BM> ra[ALO ? 2 : 1];
   Chunks<BN> rb[BLO ? 2 : 1];
-  int lseg = 0, lk = kb;
-  auto load = [&]() {
-    Opnd a = A(lseg), b = B(lseg);
-    a.col = ACOL;
-    b.col = BCOL;
-    fetch<BM, false>(a.hi, a, m0, lk, ra[0]);
-    if (ALO) fetch<BM, false>(a.lo, a, m0, lk, ra[ALO ? 1 : 0]);
-    fetch<BN, false>(b.hi, b, n0, lk, rb[0]);
-    if (BLO) fetch<BN, false>(b.lo, b, n0, lk, rb[BLO ? 1 : 0]);
-    lk += BK;
-    if (lk >= ke) { lk = kb; ++lseg; }
+  auto load = [&](int k) {
+    fetch<BM, false>(A.hi, A, m0, k, ra[0]);
+    if (ALO) fetch<BM, false>(A.lo, A, m0, k, ra[ALO ? 1 : 0]);
+    fetch<BN, true>(B.hi, B, n0, k, rb[0]);
+    if (BLO) fetch<BN, true>(B.lo, B, n0, k, rb[BLO ? 1 : 0]);
   };
   auto store = [&](int buf) {
-    stash<BM>(sm.a[buf][0], ACOL, ra[0]);
-    if (ALO) stash<BM>(sm.a[buf][ALO ? 1 : 0], ACOL, ra[ALO ? 1 : 0]);
-    stash<BN>(sm.b[buf][0], BCOL, rb[0]);
-    if (BLO) stash<BN>(sm.b[buf][BLO ? 1 : 0], BCOL, rb[BLO ? 1 : 0]);
+    stash<BM>(sm.a[buf][0], ra[0]);
+    if (ALO) stash<BM>(sm.a[buf][ALO ? 1 : 0], ra[ALO ? 1 : 0]);
+    stash<BN>(sm.b[buf][0], rb[0]);
+    if (BLO) stash<BN>(sm.b[buf][BLO ? 1 : 0], rb[BLO ? 1 : 0]);
   };
-  load();
+  load(0);
   store(0);
   __syncthreads();
-  if (RESET) zero(acc);
-  int it = 0;
-  for (int seg = 0; seg < nseg; ++seg) {
-    for (int kt = 0; kt < KT; ++kt, ++it) {
-      const int buf = it & 1;
-      const bool more = it + 1 < total;
-      if (more) load();
-      bf16x8 ah[MI], bh[NI];
+  zero(acc);
+  for (int k = 0, buf = 0; k < K; k += BK, buf ^= 1) {
+    const bool more = k + BK < K;
+    if (more) load(k + BK);
+    bf16x8 ah[MI], bh[NI];
 #pragma unroll
-      for (int i = 0; i < MI; ++i) ah[i] = frag<BM>(sm.a[buf][0], ACOL, wm + 16 * i);
+    for (int i = 0; i < MI; ++i) ah[i] = frag(sm.a[buf][0], wm + 16 * i);
 #pragma unroll
-      for (int j = 0; j < NI; ++j) bh[j] = frag<BN>(sm.b[buf][0], BCOL, wn + 16 * j);
+    for (int j = 0; j < NI; ++j) bh[j] = frag(sm.b[buf][0], wn + 16 * j);
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-          acc[i][j] = mma<F16>(ah[i], bh[j], acc[i][j]);
-      if (BLO) {
-        bf16x8 bl[NI];
+      for (int j = 0; j < NI; ++j) acc[i][j] = mma<F16>(bh[j], ah[i], acc[i][j]);
+    if (BLO) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j) bl[j] = frag<BN>(sm.b[buf][BLO ? 1 : 0], BCOL, wn + 16 * j);
+      for (int j = 0; j < NI; ++j) {
+        const bf16x8 bl = frag(sm.b[buf][BLO ? 1 : 0], wn + 16 * j);
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j)
-            acc[i][j] = mma<F16>(ah[i], bl[j], acc[i][j]);
+        for (int i = 0; i < MI; ++i) acc[i][j] = mma<F16>(bl, ah[i], acc[i][j]);
       }
-      if (ALO) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          const bf16x8 al = frag<BM>(sm.a[buf][ALO ? 1 : 0], ACOL, wm + 16 * i);
-#pragma unroll
-          for (int j = 0; j < NI; ++j)
-            acc[i][j] = mma<F16>(al, bh[j], acc[i][j]);
-        }
-      }
-      if (more) store(buf ^ 1);
-      __syncthreads();
     }
-    epi(seg, acc);
-    if (RESET) zero(acc);
+    if (ALO) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const bf16x8 al = frag(sm.a[buf][ALO ? 1 : 0], wm + 16 * i);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = mma<F16>(bh[j], al, acc[i][j]);
+      }
+    }
+    if (more) store(buf ^ 1);
+    __syncthreads();
   }
 }
 
@@ -284,14 +207,14 @@ constexpr int waitcnt_vm(int n) {
   return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8);
 }
 
-struct Rsrc {
-  __amdgpu_buffer_rsrc_t r;
+struct RowItself {
+  __device__ int operator()(int r) const { return r; }
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, long long bytes) {
-  const int nrec = bytes > 0x7FFFFFFFLL ? 0x7FFFFFFF : (int)bytes;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, nrec, 0x00020000);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int limit) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, limit, 0x00020000);
 }
+__device__ __forceinline__ int record_limit(long long bytes) { return bytes > 0x7FFFFFFFLL ? 0x7FFFFFFF : (int)bytes; }
 
 // Operand of one k-tile for the direct path: slice base, its record limit, storage layout.
 struct DOpnd {
@@ -301,28 +224,28 @@ struct DOpnd {
   long long bytes;   // readable bytes from hi (and from lo) onwards
 };
 
-template <int D, int NW = 4>
-__device__ __forceinline__ void dl_issue(u16* lds_slice, const u16* base, long long bytes, long long ld, const bool col,
-                                         int r0, int k0) {
-  constexpr int PER_WAVE = D / (16 * NW);   // (D * BK / 8 chunks) / 64 lanes / NW waves
+// Byte offsets of this lane's 16-byte chunks of one slice from the slice's k-tile (see dl_issue): row operand,
+// chunk q % 4 of row row(q / 4); col operand, chunk q % (D / 8) of k-row q / (D / 8).
+template <int D, int NW, bool COL, typename F>
+__device__ __forceinline__ void dl_offsets(unsigned* ofs, int ld, int r0, F row) {
   static_assert(D % (16 * NW) == 0, "slice rows per wave");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
 #pragma unroll
-  for (int i = 0; i < PER_WAVE; ++i) {
-    const int blk = wave * PER_WAVE + i;
-    const int q = blk * 64 + lane;
-    long long off;
-    if (!col) {
-      const int row = q >> 2, c = (q & 3) ^ swz(q >> 2);
-      off = (long long)(r0 + row) * ld + k0 + c * 8;
-    } else {
-      const int kr = q / (D / 8), c = (q % (D / 8)) ^ cswz<D>(q / (D / 8));
-      off = (long long)(k0 + kr) * ld + r0 + c * 8;
-    }
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(lds_slice + blk * 512),
-                                             16, (unsigned)(off * 2), 0, 0, 0);
+  for (int i = 0; i < D / (16 * NW); ++i) {
+    const int q = ((threadIdx.x >> 6) * (D / (16 * NW)) + i) * 64 + (threadIdx.x & 63);
+    if constexpr (!COL) ofs[i] = 2u * (unsigned)(row(q >> 2) * ld + ((q & 3) ^ swz(q >> 2)) * 8);
+    else ofs[i] = 2u * (unsigned)((q / (D / 8)) * ld + r0 + ((q % (D / 8)) ^ cswz<D>(q / (D / 8))) * 8);
   }
+}
+// One k-tile of a slice: every wave's share of its 1 KB blocks.  The k-tile's place is a scalar offset, so a load
+// costs no address arithmetic.
+template <int D, int NW>
+__device__ __forceinline__ void dl_issue(u16* lds_slice, const u16* base, int limit, const unsigned* ofs,
+                                         unsigned k_ofs, int wave) {
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, limit);
+#pragma unroll
+  for (int i = 0; i < D / (16 * NW); ++i)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        rs, (__attribute__((address_space(3))) void*)(lds_slice + (wave * (D / (16 * NW)) + i) * 512), 16, ofs[i], k_ofs, 0, 0);
 }
 
 template <int D, bool COL>
@@ -370,49 +293,80 @@ __device__ __forceinline__ RT& ring_of(void* ext) {
   }
 }
 
-// Contraction over segments seg = 0..nseg-1 and k in [kb, ke) of each; ACOL / BCOL fix the storage
+// Contraction over segments seg = 0..nseg-1 and k in [0, ke) of each; ACOL / BCOL fix the storage
 // order of the operands at compile time.
 // ILV: the k-tile's products run row block by row block (i-major), with the A fragments of block
 // i + 1 read while the products of block i issue, in an order pinned by scheduling groups: a wave
 // then waits only for its B fragments and first A block after the barrier, instead of for most of
 // the k-tile's fragment reads, and the LDS stays busy through the tile.
-// BSYM: the B operand is W as gemm2 writes it with wsym (the 128 x 128 blocks on and above the
-// diagonal), read per 128-wide part of the tile: block (q-block, k-block) is read row-wise (W[q][k])
+// WB > 0: the B operand is W as gemm2 writes it (the WB x WB blocks on and above the diagonal), read per
+// part of the tile that lies in one block column: block (q-block, k-block) is read row-wise (W[q][k])
 // when k-block >= q-block and column-wise (W[k][q], its transpose) otherwise; each part of the stage
 // is laid out for its view.
+// LAY: which output elements a lane holds, for the stores of the epilogue.  0: acc[i][j][e] is row
+// 4 (lane / 16) + e, column lane % 16 of the 16 x 16 block; 1: A's slices are interleaved (ileave), so that
+// acc[2 h][j] and acc[2 h + 1][j] are eight consecutive rows (row8_of); 2: the products are transposed and B's
+// slices interleaved: acc[i][2 h] and acc[i][2 h + 1] are eight consecutive columns (col8_of) of row
+// lane % 16.  Every element's sum runs in the same order in all of them.  brow (LAY 2): storage row of B for
+// row r of the tile.
 template <int BM, int BN, bool ALO, bool BLO, int S, bool ACOL, bool BCOL, bool RESET, bool F16, int WGM = 2,
-          int WGN = 2, bool ILV = false, bool BSYM = false, typename FA, typename FB, typename EPI>
-__device__ __forceinline__ void mainloop_dl(Ring<BM, BN, ALO, BLO, S>& sm, int nseg, int kb, int ke, int m0, int n0,
-                                            FA A, FB B, f32x4 (&acc)[BM / (16 * WGM)][BN / (16 * WGN)], EPI epi) {
-  constexpr int SH = 128;         // BSYM: width of one part of the B tile (the b tile of W)
-  static_assert(!BSYM || (BN % SH == 0 && !BCOL && (BN / WGN) <= SH), "BSYM: parts of 128, one per wave");
+          int WGN = 2, bool ILV = false, int WB = 0, int LAY = 0, typename FA, typename FB, typename EPI, typename BR = RowItself>
+__device__ __forceinline__ void mainloop_dl(Ring<BM, BN, ALO, BLO, S>& sm, int nseg, int ke, int m0, int n0,
+                                            FA A, FB B, f32x4 (&acc)[BM / (16 * WGM)][BN / (16 * WGN)], EPI epi,
+                                            BR brow = BR{}) {
+  constexpr bool BSYM = WB > 0;
+  constexpr int SH = BSYM && WB < BN ? WB : BN;   // width of one part of the B tile (BSYM: within one block of W)
+  static_assert(!BSYM || (BN % SH == 0 && WB % SH == 0 && !BCOL && (BN / WGN) <= SH), "BSYM: whole parts, one per wave");
+  static_assert((LAY != 1 || !ACOL) && (LAY != 2 || (!BCOL && !BSYM)), "row operands are interleaved");
   constexpr int NW = WGM * WGN;   // waves in a WGM x WGN grid, each owning (BM / WGM) x (BN / WGN)
+  auto mm = [](bf16x8 a, bf16x8 b, f32x4 c) { return LAY == 2 ? mma<F16>(b, a, c) : mma<F16>(a, b, c); };
   constexpr int MI = BM / (16 * WGM), NI = BN / (16 * WGN);
   constexpr int L = (ALO ? 2 : 1) * (BM / (16 * NW)) + (BLO ? 2 : 1) * (BN / (16 * NW));   // loads per wave per tile
   static_assert(L * (S - 2) < 64, "vmcnt range");
-  const int wave = threadIdx.x >> 6;
+  const int wave = threadIdx.x >> 6, swave = __builtin_amdgcn_readfirstlane(wave);
   const int wm = (wave / WGN) * (BM / WGM), wn = (wave % WGN) * (BN / WGN);
-  const int KT = (ke - kb + BK - 1) / BK;
+  const int KT = (ke + BK - 1) / BK;
   const int total = nseg * KT;
   if (total <= 0) return;
-  int lseg = 0, lk = kb;
-  auto issue = [&](int stage) {
-    const DOpnd a = A(lseg), b = B(lseg);
-    dl_issue<BM, NW>(sm.a[stage][0], a.hi, a.bytes, a.ld, ACOL, m0, lk);
-    if (ALO) dl_issue<BM, NW>(sm.a[stage][ALO ? 1 : 0], a.lo, a.bytes, a.ld, ACOL, m0, lk);
-    if constexpr (BSYM) {
+  // the loads' addresses: a descriptor per operand and segment, lane offsets that stay, and the k-tile's offset
+  constexpr int NP = BN / SH;   // BSYM: parts of the B tile
+  unsigned ao[BM / (16 * NW)], bo[NP][SH / (16 * NW)], bc[NP][SH / (16 * NW)];
+  const int lda = (int)A(0).ld, ldb = (int)B(0).ld;
+  dl_offsets<BM, NW, ACOL>(ao, lda, m0, [&](int r) { return m0 + (LAY == 1 ? ileave(r) : r); });
 #pragma unroll
-      for (int h = 0; h < BN / SH; ++h) {
-        const bool col = lk / SH < (n0 + SH * h) / SH;
-        dl_issue<SH, NW>(sm.b[stage][0] + h * SH * BK, b.hi, b.bytes, b.ld, col, n0 + SH * h, lk);
-        if (BLO) dl_issue<SH, NW>(sm.b[stage][BLO ? 1 : 0] + h * SH * BK, b.lo, b.bytes, b.ld, col, n0 + SH * h, lk);
+  for (int h = 0; h < NP; ++h) {
+    dl_offsets<SH, NW, BCOL>(bo[h], ldb, n0 + SH * h,
+                             [&](int r) { return LAY == 2 ? brow(ileave(r)) : n0 + SH * h + r; });
+    if constexpr (BSYM) dl_offsets<SH, NW, true>(bc[h], ldb, n0 + SH * h, [](int r) { return r; });
+  }
+  int lseg = 0, lk = 0;
+  DOpnd a = A(0), b = B(0);
+  int alim = record_limit(a.bytes), blim = record_limit(b.bytes);
+  auto issue = [&](int stage) {
+    const unsigned ka = 2u * (unsigned)(ACOL ? lk * lda : lk);
+    dl_issue<BM, NW>(sm.a[stage][0], a.hi, alim, ao, ka, swave);
+    if (ALO) dl_issue<BM, NW>(sm.a[stage][ALO ? 1 : 0], a.lo, alim, ao, ka, swave);
+#pragma unroll
+    for (int h = 0; h < NP; ++h) {
+      if (BSYM && lk / WB < (n0 + SH * h) / WB) {
+        const unsigned kb = 2u * (unsigned)(lk * ldb);
+        dl_issue<SH, NW>(sm.b[stage][0] + h * SH * BK, b.hi, blim, bc[h], kb, swave);
+        if (BLO) dl_issue<SH, NW>(sm.b[stage][BLO ? 1 : 0] + h * SH * BK, b.lo, blim, bc[h], kb, swave);
+      } else {
+        const unsigned kb = 2u * (unsigned)(BCOL ? lk * ldb : lk);
+        dl_issue<SH, NW>(sm.b[stage][0] + h * SH * BK, b.hi, blim, bo[h], kb, swave);
+        if (BLO) dl_issue<SH, NW>(sm.b[stage][BLO ? 1 : 0] + h * SH * BK, b.lo, blim, bo[h], kb, swave);
       }
-    } else {
-      dl_issue<BN, NW>(sm.b[stage][0], b.hi, b.bytes, b.ld, BCOL, n0, lk);
-      if (BLO) dl_issue<BN, NW>(sm.b[stage][BLO ? 1 : 0], b.lo, b.bytes, b.ld, BCOL, n0, lk);
     }
     lk += BK;
-    if (lk >= ke) { lk = kb; ++lseg; }
+    if (lk >= ke) {
+      lk = 0;
+      ++lseg;
+      a = A(lseg);
+      b = B(lseg);
+      alim = record_limit(a.bytes);
+      blim = record_limit(b.bytes);
+    }
   };
 #pragma unroll
   for (int t = 0; t < S - 1; ++t)
@@ -459,14 +413,14 @@ __device__ __forceinline__ void mainloop_dl(Ring<BM, BN, ALO, BLO, S>& sm, int n
         }
         // products in passes over j, so no two consecutive products share an accumulator
 #pragma unroll
-        for (int j = 0; j < NI; ++j) acc[i][j] = mma<F16>(ah[c], bh[j], acc[i][j]);
+        for (int j = 0; j < NI; ++j) acc[i][j] = mm(ah[c], bh[j], acc[i][j]);
         if (BLO) {
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = mma<F16>(ah[c], bl[j], acc[i][j]);
+          for (int j = 0; j < NI; ++j) acc[i][j] = mm(ah[c], bl[j], acc[i][j]);
         }
         if (ALO) {
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = mma<F16>(al[c], bh[j], acc[i][j]);
+          for (int j = 0; j < NI; ++j) acc[i][j] = mm(al[c], bh[j], acc[i][j]);
         }
         __builtin_amdgcn_sched_group_barrier(0x008, PR, 0);
       }
@@ -480,7 +434,7 @@ __device__ __forceinline__ void mainloop_dl(Ring<BM, BN, ALO, BLO, S>& sm, int n
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NI; ++j)
-          acc[i][j] = mma<F16>(ah[i], bh[j], acc[i][j]);
+          acc[i][j] = mm(ah[i], bh[j], acc[i][j]);
       if (BLO) {
         bf16x8 bl[NI];
 #pragma unroll
@@ -489,7 +443,7 @@ __device__ __forceinline__ void mainloop_dl(Ring<BM, BN, ALO, BLO, S>& sm, int n
         for (int i = 0; i < MI; ++i)
 #pragma unroll
           for (int j = 0; j < NI; ++j)
-            acc[i][j] = mma<F16>(ah[i], bl[j], acc[i][j]);
+            acc[i][j] = mm(ah[i], bl[j], acc[i][j]);
       }
       if (ALO) {
 #pragma unroll
@@ -497,7 +451,7 @@ __device__ __forceinline__ void mainloop_dl(Ring<BM, BN, ALO, BLO, S>& sm, int n
           const bf16x8 al = dl_frag<BM, ACOL>(sm.a[stage][ALO ? 1 : 0], wm + 16 * i);
 #pragma unroll
           for (int j = 0; j < NI; ++j)
-            acc[i][j] = mma<F16>(al, bh[j], acc[i][j]);
+            acc[i][j] = mm(al, bh[j], acc[i][j]);
         }
       }
     }
@@ -509,8 +463,8 @@ __device__ __forceinline__ void mainloop_dl(Ring<BM, BN, ALO, BLO, S>& sm, int n
       __builtin_amdgcn_s_barrier();
       if (it + S - 1 < total) issue((stage + S - 1) % S);
       if constexpr (BSYM) {
-        // this wave's part is read column-wise when the k-tile's 128-block lies before the part's
-        if ((kb + kt * BK) / SH < (n0 + wn) / SH) ktile(std::true_type{});
+        // this wave's part is read column-wise when the k-tile's block lies before the part's
+        if (kt * BK / WB < (n0 + wn) / WB) ktile(std::true_type{});
         else ktile(std::false_type{});
       } else {
         ktile(std::false_type{});
@@ -534,6 +488,54 @@ template <int BN, int WGM = 2, int WGN = 2>
 __device__ __forceinline__ int col_of(int jn) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   return (wave % WGN) * (BN / WGN) + jn * 16 + (lane & 15);
+}
+
+// LAY 1: first of the eight rows of acc[2 h], acc[2 h + 1]; LAY 2: first of the eight columns, and the row.
+template <int BM, int WGM, int WGN>
+__device__ __forceinline__ int row8_of(int h) {
+  return ((threadIdx.x >> 6) / WGN) * (BM / WGM) + 32 * h + 8 * ((threadIdx.x & 63) >> 4);
+}
+template <int BN, int WGM, int WGN>
+__device__ __forceinline__ int col8_of(int h) {
+  return ((threadIdx.x >> 6) % WGN) * (BN / WGN) + 32 * h + 8 * ((threadIdx.x & 63) >> 4);
+}
+template <int BM, int WGM, int WGN>
+__device__ __forceinline__ int row1_of(int i) {
+  return ((threadIdx.x >> 6) / WGN) * (BM / WGM) + 16 * i + (threadIdx.x & 15);
+}
+
+// The 8 x 8 blocks of 16-bit pairs (hi, lo) over eight consecutive lanes' eight elements, transposed: element e
+// of lane l goes to element l % 8 of lane l - l % 8 + e.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (M == 4)   // l ^ 7, then l ^ 3
+    return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+  else
+    return __builtin_amdgcn_update_dpp(0, (int)v, M == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
+}
+template <int M>
+__device__ __forceinline__ void transpose_step(uint32_t (&v)[8]) {
+  const bool up = threadIdx.x & M;
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+    if ((r & M) == 0) {
+      const uint32_t other = lane_xor<M>(up ? v[r] : v[r | M]);
+      if (up) v[r] = other;
+      else v[r | M] = other;
+    }
+}
+__device__ __forceinline__ void transpose8(u32x4& hi, u32x4& lo) {
+  uint32_t v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = __builtin_amdgcn_perm(hi[e >> 1], lo[e >> 1], e & 1 ? 0x07060302 : 0x05040100);
+  transpose_step<1>(v);
+  transpose_step<2>(v);
+  transpose_step<4>(v);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    lo[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x05040100);
+    hi[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x07060302);
+  }
 }
 
 // Lower-triangle tile t of a tt x tt tiling, ordered by column (tiles sharing tn are consecutive,
@@ -582,105 +584,132 @@ __device__ __forceinline__ int find_instance(const int* __restrict__ off, int ni
 // WGM x WGN wave grid, one tile per work item (items covering several tiles measured slower: the
 // epilogue's stores then stall the next tile's operand waits, as the vector-memory counter retires
 // loads and stores in order).
-// VEC: the n-tiles run over the stacked rows (P, mu) of all np rows of B (bstride == nbf * ldb), so only
-// the last tile of the launch is padding, where tiles of one P each pad every P's rows to a multiple of
-// the tile (1200 rows on 256 tiles: 6 % of the products; 200 on 128: 22 %).  The tile's own
-// rows are the base of its loads, so the 32-bit load offsets stay small however large the chunk is.
+// VEC: the n-tiles run over the stacked rows (P, mu) of all np B_P (bstride == nbf * ldb), each P counted as
+// nbf rounded up to 8, so only the last tile of the launch is padding, where tiles of one P each pad
+// every P's rows to a multiple of the tile (1200 rows on 256 tiles: 6 % of the products; 200 on 128: 22 %), and
+// a lane's eight columns of XT are one aligned 16-byte store (2-byte stores of 32-byte runs: X of 1200 functions,
+// 4800 rows 33.5 -> 31.7 ms; 16-byte stores at the rows' own alignment slowed 64 problems of 40 to 300
+// functions from 2.55 to 3.65 ms).  The tile's first P is the base of its loads, so the 32-bit load offsets stay
+// small however large the chunk is.
 // Otherwise (rows that are not 16-byte aligned) one P per tile, staged through registers.
 // EXT / ext: the ring is the caller's (see ring_of); BUDGET: LDS bytes for the ring (0: the whole
 // unit's LDS shared by MINB blocks).
-template <int TERMS, bool BLO, int G1M, int G1N, int WGM, int WGN, int MINB, bool VEC, bool EXT = false, int BUDGET = 0>
+template <int TERMS, bool BLO, int G1M, int G1N, int WGM, int WGN, int MINB, bool VEC, bool BATCH = false, bool EXT = false,
+          int BUDGET = 0>
 __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = nullptr) {
   constexpr bool ALO = TERMS >= 2;
   constexpr int MI = G1M / (16 * WGM), NI = G1N / (16 * WGN);
-  const int nbf = g.nbf, nact = g.nact, ldx = g.ldx;
+  const int nbf = g.nbf, nact = g.nact, ldx = g.ldx, nbf8 = (nbf + 7) & ~7;
   const int tm_n = (nact + G1M - 1) / G1M;
-  int P = 0, m0;
-  long long n0;
+  int P0, m0, r0;   // first P of the tile, and the tile's first row there
   if constexpr (VEC) {
     m0 = (w % tm_n) * G1M;
-    n0 = (long long)(w / tm_n) * G1N;
+    const uint32_t n0 = (uint32_t)(w / tm_n) * G1N;
+    P0 = (int)(n0 / (uint32_t)nbf8);
+    r0 = (int)(n0 - (uint32_t)P0 * nbf8);
   } else {
     const int tn_n = (nbf + G1N - 1) / G1N;
-    P = w / (tm_n * tn_n);
+    P0 = w / (tm_n * tn_n);
     const int tile = w % (tm_n * tn_n);
     m0 = (tile / tn_n) * G1M;
-    n0 = (tile % tn_n) * G1N;
+    r0 = (tile % tn_n) * G1N;
   }
   const long long pstride = (long long)g.ws.nact32 * ldx;
-  u16* XTh = g.xt_hi + (VEC ? 0 : P * pstride);
-  u16* XTl = g.xt_lo ? g.xt_lo + (VEC ? 0 : P * pstride) : nullptr;
-  const long long nrows = (long long)g.np * nbf;
-  const int P0 = VEC ? (int)((uint32_t)n0 / (uint32_t)nbf) : 0;   // first P of the tile, its first row there
-  const int r0 = VEC ? (int)(n0 - (long long)P0 * nbf) : (int)n0;
+  u16* XTh = g.xt_hi + P0 * pstride;
+  u16* XTl = g.xt_lo ? g.xt_lo + P0 * pstride : nullptr;
   // split mode: X is written as the fp16 pair of X sX
   const float xmul = TERMS >= 2 ? chunk_scales(g.bnd, g.chunk, TERMS == 3).xmul : 1.0f;
   f32x4 acc[MI][NI];
+  // XT rows to nact32 and columns to ldx are written, those past nact (Ct's are zero) and nbf with zeros; a
+  // batch clears this padding once, when its plan is made
+  const int prows = BATCH ? nact : g.ws.nact32;
   auto epi = [&](int, f32x4(&a)[MI][NI]) {
+    int mu[NI / 2];
+    long long xo[NI / 2];
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int h = 0; h < NI / 2; ++h) {
+      const int c = r0 + col8_of<G1N, WGM, WGN>(h), dP = VEC ? (int)((uint32_t)c / (uint32_t)nbf8) : 0;
+      mu[h] = P0 + dP < g.np ? c - dP * nbf8 : nbf8;
+      xo[h] = dP * pstride + mu[h];
+    }
 #pragma unroll
-      for (int jn = 0; jn < NI; ++jn) {
-        const int c = col_of<G1N, WGM, WGN>(jn);
-        long long xo;
-        if constexpr (VEC) {
-          if (n0 + c >= nrows) continue;
-          const int dP = (int)((uint32_t)(r0 + c) / (uint32_t)nbf);
-          xo = (P0 + dP) * pstride + (r0 + c - dP * nbf);
-        } else {
-          if (r0 + c >= nbf) continue;
-          xo = r0 + c;
+    for (int i = 0; i < MI; ++i) {
+      const int p = m0 + row1_of<G1M, WGM, WGN>(i);
+      if (p >= prows) continue;
+#pragma unroll
+      for (int h = 0; h < NI / 2; ++h) {
+        if (mu[h] >= nbf8) continue;
+        u32x4 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const f32x4 v = a[i][2 * h + (e >> 1)];
+          const float v0 = mu[h] + 2 * e < nbf ? v[2 * (e & 1)] : 0.f, v1 = mu[h] + 2 * e + 1 < nbf ? v[2 * (e & 1) + 1] : 0.f;
+          uint32_t x, y = 0;
+          if (TERMS == 1) x = cvt2_bf16(v0, v1);
+          else split2_f16(v0 * xmul, v1 * xmul, x, y);
+          hi[e] = x;
+          lo[e] = y;
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int p = m0 + row_of<G1M, WGM, WGN>(i, j);
-          if (p >= nact) continue;
-          u16 h, l;
-          if (TERMS == 1) { h = f32_to_bf16_bits(a[i][jn][j]); l = 0; }
-          else split_f16(a[i][jn][j] * xmul, h, l);
-          XTh[(long long)p * ldx + xo] = h;
-          if (XTl) XTl[(long long)p * ldx + xo] = l;
-        }
+        const long long o = xo[h] + (long long)p * ldx;
+        *reinterpret_cast<u32x4*>(XTh + o) = hi;
+        if (XTl) *reinterpret_cast<u32x4*>(XTl + o) = lo;
       }
+    }
+    if (!BATCH && ldx > nbf8) {
+#pragma unroll
+      for (int h = 0; h < NI / 2; ++h)
+        if (mu[h] + 8 == nbf8)
+#pragma unroll
+          for (int i = 0; i < MI; ++i) {
+            const int p = m0 + row1_of<G1M, WGM, WGN>(i);
+            if (p >= prows) continue;
+            for (int k = 8; mu[h] + k < ldx; k += 8) {
+              const long long o = xo[h] + (long long)p * ldx + k;
+              *reinterpret_cast<u32x4*>(XTh + o) = u32x4{0u, 0u, 0u, 0u};
+              if (XTl) *reinterpret_cast<u32x4*>(XTl + o) = u32x4{0u, 0u, 0u, 0u};
+            }
+          }
+    }
   };
+  const long long o = P0 * g.bstride;
   if constexpr (VEC) {
     // the LDS of one compute unit is shared by MINB blocks
     constexpr int S = ring_depth(G1M, G1N, ALO, BLO, BUDGET > 0 ? BUDGET : (MINB == 2 ? 81920 : 163840));
     auto& sm = ring_of<Ring<G1M, G1N, ALO, BLO, S>, EXT>(ext);
-    const long long o = n0 * g.ldb;
     auto A = [&](int) { return DOpnd{g.ct_hi, g.ct_lo, g.ldk, g.ws.ct_bytes}; };
     auto B = [&](int) { return DOpnd{g.b_hi + o, BLO ? g.b_lo + o : nullptr, g.ldb, g.b_bytes - 2 * o}; };
-    mainloop_dl<G1M, G1N, ALO, BLO, S, false, false, true, (TERMS == 3), WGM, WGN, (WGM * WGN == 8)>(sm, 1, 0, nbf, m0, 0,
-                                                                                                     A, B, acc, epi);
+    auto brow = [&](int r) {   // row of the stored B of the tile's row r
+      const int c = r0 + r, dP = min((int)((uint32_t)c / (uint32_t)nbf8), g.np - 1 - P0);
+      return dP * nbf + min(c - dP * nbf8, nbf - 1);
+    };
+    mainloop_dl<G1M, G1N, ALO, BLO, S, false, false, true, (TERMS == 3), WGM, WGN, (WGM * WGN == 8), false, 2>(
+        sm, 1, nbf, m0, 0, A, B, acc, epi, brow);
   } else {
     static_assert(VEC || (WGM == 2 && WGN == 2), "register-staged path: 2 x 2 waves");
     __shared__ Stage<G1M, G1N, ALO, BLO> sm;
-    auto A = [&](int) { return Opnd{g.ct_hi, g.ct_lo, g.ldk, nact, nbf, false}; };
-    auto B = [&](int) {
-      const long long o = (long long)P * g.bstride;
-      return Opnd{g.b_hi + o, BLO ? g.b_lo + o : nullptr, g.ldb, nbf, nbf, false};
-    };
-    mainloop<G1M, G1N, ALO, BLO, false, false, true, (TERMS == 3)>(sm, 1, 0, nbf, m0, r0, A, B, acc, epi);
+    mainloop<G1M, G1N, ALO, BLO, (TERMS == 3)>(sm, nbf, m0, r0, Opnd{g.ct_hi, g.ct_lo, g.ldk, nact, nbf},
+                                               Opnd{g.b_hi + o, BLO ? g.b_lo + o : nullptr, g.ldb, nbf, nbf}, acc);
+    epi(0, acc);
   }
 }
 
 // gemm2: b_P = Ct XT_P^T on lower-triangle tiles; Kpart[s] += sum_{P in s} b^2 (lower triangle, summed
-// over the successive P-chunks of one call), D[P][p] = b_pp, W_P = b o beta as a hi/lo pair.  W is
-// written in full (off-diagonal tiles store their mirror image as well), or with wsym only as the
-// transposed image of each tile: the 128 x 128 blocks on and above the diagonal, which gemm3 with
-// wsym reads.
-// waves along q of a gemm2 block (2 x g2_wgn grid)
-constexpr int g2_wgn(bool vec) { return vec ? 4 : 2; }
+// over the successive P-chunks of one call, the first of which stores: kset), D[P][p] = b_pp, W_P = b o beta
+// as a hi/lo pair, written only as the transposed image of each tile: the TT x TT blocks on and above the
+// diagonal, which gemm3 reads.
+// waves along q of a gemm2 block (2 x g2_wgn grid): the 128 tile runs 8 waves (2 x 4, each 64 x 32), half the
+// accumulators, beta and K sums per wave, so they stay in registers, and two waves per SIMD hide each
+// other's epilogue latency; the 64 tile runs 4 waves of 32 x 32
+constexpr int g2_wgn(int tt) { return tt == 128 ? 4 : 2; }
 
 // TT: the square tile (128, or 64 for the short active spaces of batch instances, with 4 waves).
-// KSET: store the K sums instead of adding them (a launch that covers every P of the problem).
-template <int TERMS, bool VEC, int TT = T2, bool KSET = false, bool EXT = false, int BUDGET = 0>
+// BATCH: one launch covers every P of the problem (K is stored); the blocks on the diagonal hold W[p][q]
+// itself, in place of its image (b_pq and b_qp differ in the last bits), by a transpose between lanes (as 2-byte
+// stores of W[p][q] and its image in every tile, b of 64 problems of 40 to 300 functions took 1.98 ms).
+template <int TERMS, int TT = T2, bool BATCH = false, bool EXT = false, int BUDGET = 0>
 __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = nullptr) {
   constexpr bool LO = TERMS >= 3;
-  // the direct-load form of the 128 tile runs 8 waves (2 x 4, each 64 x 32): half the accumulators,
-  // beta and K sums per wave, so they stay in registers, and two waves per SIMD hide each other's
-  // epilogue latency; the 64 tile runs 4 waves of 32 x 32
-  constexpr int WGN = g2_wgn(VEC && TT == 128), NI = TT / (16 * WGN), MI = TT / 32;
+  constexpr int WGN = g2_wgn(TT), NI = TT / (16 * WGN), MI = TT / 32;
   const int nbf = g.nbf, nact = g.nact, np = g.np, nsplit = g.nsplit, ldw = g.ldw, ldx = g.ldx;
   const int tt = (nact + TT - 1) / TT;
   const int ntri = tt * (tt + 1) / 2;
@@ -705,96 +734,65 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
     for (int jn = 0; jn < NI; ++jn)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int p = m0 + row_of<TT, 2, WGN>(i, j), q = n0 + col_of<TT, 2, WGN>(jn);
+        const int p = m0 + row8_of<TT, 2, WGN>(i >> 1) + 4 * (i & 1) + j, q = n0 + col_of<TT, 2, WGN>(jn);
         bet[i][jn][j] = (p < nact && q < nact) ? g.beta32[(long long)p * nact + q] * wmul : 0.f;
       }
   f32x4 kacc[MI][NI], acc[MI][NI];
   zero(kacc);
   const bool diag = (tm == tn);
+  const int wrows = BATCH ? nact : g.ws.nact32;
   auto epi = [&](int seg, f32x4(&a)[MI][NI]) {
     const int P = pb + seg;
     u16* Wh = g.w_hi + (long long)P * g.ws.nact32 * ldw;
     u16* Wl = LO ? g.w_lo + (long long)P * g.ws.nact32 * ldw : nullptr;
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int h = 0; h < MI / 2; ++h)
 #pragma unroll
       for (int jn = 0; jn < NI; ++jn) {
-        const int p0 = m0 + row_of<TT, 2, WGN>(i, 0), q = n0 + col_of<TT, 2, WGN>(jn);
-        float wv[4];
+        const int p0 = m0 + row8_of<TT, 2, WGN>(h), q = n0 + col_of<TT, 2, WGN>(jn);
+        float wv[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int e = 0; e < 8; ++e) {
+          const int i = 2 * h + (e >> 2), j = e & 3;
           const float b = a[i][jn][j] * invB;
           kacc[i][jn][j] += b * b;
-          wv[j] = a[i][jn][j] * bet[i][jn][j];
+          wv[e] = a[i][jn][j] * bet[i][jn][j];
+          if (diag && p0 + e == q && q < nact) g.Dc[(long long)P * nact + q] = (double)b;
         }
-        uint32_t h01, h23, l01 = 0, l23 = 0;
-        if constexpr (LO) {
-          split2_f16(wv[0], wv[1], h01, l01);
-          split2_f16(wv[2], wv[3], h23, l23);
-        } else {
-          h01 = cvt2_bf16(wv[0], wv[1]);
-          h23 = cvt2_bf16(wv[2], wv[3]);
+        u32x4 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          uint32_t x, y = 0;
+          if constexpr (LO) split2_f16(wv[2 * e], wv[2 * e + 1], x, y);
+          else x = cvt2_bf16(wv[2 * e], wv[2 * e + 1]);
+          hi[e] = x;
+          lo[e] = y;
         }
-        if (q < nact && g.wsym) {
-          // the transposed image only: W[q][p0 .. p0 + 3] in one 8-byte store (the padding columns
-          // past nact receive zeros), covering the blocks on and above the diagonal
-          if (p0 < nact) {
-            const long long o = (long long)q * ldw + p0;
-            *reinterpret_cast<uint2*>(Wh + o) = uint2{h01, h23};
-            if (LO) *reinterpret_cast<uint2*>(Wl + o) = uint2{l01, l23};
-          }
-          if (diag) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (p0 + j == q) g.Dc[(long long)P * nact + q] = (double)(a[i][jn][j] * invB);
-          }
-        } else if (q < nact) {
-          const u16 hv[4] = {(u16)h01, (u16)(h01 >> 16), (u16)h23, (u16)(h23 >> 16)};
-          const u16 lv[4] = {(u16)l01, (u16)(l01 >> 16), (u16)l23, (u16)(l23 >> 16)};
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int p = p0 + j;
-            if (p < nact) {
-              Wh[(long long)p * ldw + q] = hv[j];
-              if (LO) Wl[(long long)p * ldw + q] = lv[j];
-              if (diag && p == q) g.Dc[(long long)P * nact + p] = (double)(a[i][jn][j] * invB);
-            }
-          }
-          if (!diag && p0 < nact) {
-            const long long o = (long long)q * ldw + p0;
-            if ((ldw & 3) == 0) {
-              *reinterpret_cast<uint2*>(Wh + o) = uint2{h01, h23};
-              if (LO) *reinterpret_cast<uint2*>(Wl + o) = uint2{l01, l23};
-            } else {
-#pragma unroll
-              for (int j = 0; j < 4; ++j)
-                if (p0 + j < nact) {
-                  Wh[o + j] = hv[j];
-                  if (LO) Wl[o + j] = lv[j];
-                }
-            }
-          }
+        // the transposed image W[q][p0 .. p0 + 7] (rows and columns from nact to nact32 receive zeros; a batch
+        // clears them once, when its plan is made)
+        int wr = q, wc = p0;
+        if (BATCH && diag) {
+          transpose8(hi, lo);
+          const int lane = threadIdx.x & 63;
+          wr = p0 + (lane & 7);
+          wc = q - (lane & 7);
+        }
+        if (wr < wrows && wc < wrows) {
+          const long long o = (long long)wr * ldw + wc;
+          *reinterpret_cast<u32x4*>(Wh + o) = hi;
+          if (LO) *reinterpret_cast<u32x4*>(Wl + o) = lo;
         }
       }
   };
-  if constexpr (VEC) {
-    constexpr int S = ring_depth(TT, TT, LO, LO, BUDGET > 0 ? BUDGET : (TT == 128 ? 163840 : 81920));
-    auto& sm = ring_of<Ring<TT, TT, LO, LO, S>, EXT>(ext);
-    auto A = [&](int) { return DOpnd{g.ct_hi, g.ct_lo, g.ldk, g.ws.ct_bytes}; };
-    auto B = [&](int seg) {
-      const long long off = (long long)(pb + seg) * g.ws.nact32 * ldx;
-      return DOpnd{g.xt_hi + off, LO ? g.xt_lo + off : nullptr, ldx, g.ws.xt_bytes - 2 * off};
-    };
-    mainloop_dl<TT, TT, LO, LO, S, false, false, true, LO, 2, WGN>(sm, pe - pb, 0, nbf, m0, n0, A, B, acc, epi);
-  } else {
-    __shared__ Stage<TT, TT, LO, LO> sm;
-    auto A = [&](int) { return Opnd{g.ct_hi, g.ct_lo, g.ldk, nact, nbf, false}; };
-    auto B = [&](int seg) {
-      const long long off = (long long)(pb + seg) * g.ws.nact32 * ldx;
-      return Opnd{g.xt_hi + off, LO ? g.xt_lo + off : nullptr, ldx, nact, nbf, false};
-    };
-    mainloop<TT, TT, LO, LO, false, false, true, LO>(sm, pe - pb, 0, nbf, m0, n0, A, B, acc, epi);
-  }
+  constexpr int S = ring_depth(TT, TT, LO, LO, BUDGET > 0 ? BUDGET : (TT == 128 ? 163840 : 81920));
+  auto& sm = ring_of<Ring<TT, TT, LO, LO, S>, EXT>(ext);
+  auto A = [&](int) { return DOpnd{g.ct_hi, g.ct_lo, g.ldk, g.ws.ct_bytes}; };
+  auto B = [&](int seg) {
+    const long long off = (long long)(pb + seg) * g.ws.nact32 * ldx;
+    return DOpnd{g.xt_hi + off, LO ? g.xt_lo + off : nullptr, ldx, g.ws.xt_bytes - 2 * off};
+  };
+  mainloop_dl<TT, TT, LO, LO, S, false, false, true, LO, 2, WGN, false, false, 1>(sm, pe - pb, nbf, m0, n0, A, B, acc,
+                                                                                 epi);
   double* Kp = g.Kpart + (long long)s * nact * nact;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -802,17 +800,17 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
     for (int jn = 0; jn < NI; ++jn)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int p = m0 + row_of<TT, 2, WGN>(i, j), q = n0 + col_of<TT, 2, WGN>(jn);
+        const int p = m0 + row8_of<TT, 2, WGN>(i >> 1) + 4 * (i & 1) + j, q = n0 + col_of<TT, 2, WGN>(jn);
         if (p < nact && q <= p) {
-          if constexpr (KSET) Kp[(long long)p * nact + q] = (double)kacc[i][jn][j];
-          else Kp[(long long)p * nact + q] += (double)kacc[i][jn][j];
+          double* k = Kp + (long long)p * nact + q;
+          *k = (BATCH || g.kset) ? (double)kacc[i][jn][j] : *k + (double)kacc[i][jn][j];
         }
       }
 }
 
 // gemm3: Ypart[s][mu][q] = sum_{P in s} sum_r XT_P[r][mu] W_P[q][r].  XT is read as a col operand,
-// W as a row operand (with wsym, each 128-wide block from the orientation gemm2 stored it in: rows
-// on and above the diagonal, columns below); every block walks (P, r) in the same order, so blocks of one
+// W as a row operand (each WB-wide block from the orientation gemm2 stored it in: rows on and above
+// the diagonal, columns below); every block walks (P, r) in the same order, so blocks of one
 // split that share an operand panel read it at about the same time.  Split mode: 3 fp16 products
 // (2 products, dropping X_lo W_hi at about 2^-12 relative, left lambda 2.2e-5 from the exact values on
 // a 77-function edge shape).
@@ -820,8 +818,8 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
 // matrix-core products one byte read from LDS feeds: a 64 x 64 wave reads 16 KB per k-tile for 48
 // products, a 128 x 64 wave 24 KB for 96; LDS bandwidth (about 128 bytes per clock per compute unit)
 // is what limits the 64 x 64 form.
-template <int TERMS, int G3M, int G3N, int WGM, int WGN, int MINB, bool VEC, bool EXT = false, int BUDGET = 0,
-          bool WSYM = false>
+// WB: the tile of the b contraction that wrote W.
+template <int TERMS, int G3M, int G3N, int WGM, int WGN, int MINB, int WB, bool EXT = false, int BUDGET = 0>
 __device__ __forceinline__ void gemm3_body(int w, const G3Args& g, void* ext = nullptr) {
   constexpr bool LO = TERMS >= 3;
   constexpr int MI = G3M / (16 * WGM), NI = G3N / (16 * WGN);
@@ -835,35 +833,20 @@ __device__ __forceinline__ void gemm3_body(int w, const G3Args& g, void* ext = n
   f32x4 acc[MI][NI];
   zero(acc);
   auto none = [&](int, f32x4(&)[MI][NI]) {};
-  if constexpr (VEC) {
-    // the 128 x 128 tile runs two blocks per compute unit (two-stage ring each): while one block
-    // waits on its fragment reads or barrier, the other keeps the matrix cores busy
-    constexpr int S = ring_depth(G3M, G3N, LO, LO, BUDGET > 0 ? BUDGET : (MINB == 2 ? 81920 : 163840));
-    auto& sm = ring_of<Ring<G3M, G3N, LO, LO, S>, EXT>(ext);
-    auto A = [&](int seg) {
-      const long long off = (long long)(pb + seg) * g.ws.nact32 * ldx;
-      return DOpnd{g.xt_hi + off, LO ? g.xt_lo + off : nullptr, ldx, g.ws.xt_bytes - 2 * off};
-    };
-    auto B = [&](int seg) {
-      const long long off = (long long)(pb + seg) * g.ws.nact32 * ldw;
-      return DOpnd{g.w_hi + off, LO ? g.w_lo + off : nullptr, ldw, g.ws.w_bytes - 2 * off};
-    };
-    mainloop_dl<G3M, G3N, LO, LO, S, true, false, false, LO, WGM, WGN, (WGM * WGN == 8), WSYM>(sm, pe - pb, 0, nact,
-                                                                                             m0, n0, A, B, acc, none);
-  } else {
-    static_assert(VEC || (WGM == 2 && WGN == 2), "register-staged path: 2 x 2 waves");
-    static_assert(!WSYM, "the symmetric W layout is read on the direct-load path only");
-    __shared__ Stage<G3M, G3N, LO, LO> sm;
-    auto A = [&](int seg) {
-      const long long off = (long long)(pb + seg) * g.ws.nact32 * ldx;
-      return Opnd{g.xt_hi + off, LO ? g.xt_lo + off : nullptr, ldx, nbf, nact, true};
-    };
-    auto B = [&](int seg) {
-      const long long off = (long long)(pb + seg) * g.ws.nact32 * ldw;
-      return Opnd{g.w_hi + off, LO ? g.w_lo + off : nullptr, ldw, nact, nact, false};
-    };
-    mainloop<G3M, G3N, LO, LO, true, false, false, LO>(sm, pe - pb, 0, nact, m0, n0, A, B, acc, none);
-  }
+  // the 128 x 128 tile runs two blocks per compute unit (two-stage ring each): while one block
+  // waits on its fragment reads or barrier, the other keeps the matrix cores busy
+  constexpr int S = ring_depth(G3M, G3N, LO, LO, BUDGET > 0 ? BUDGET : (MINB == 2 ? 81920 : 163840));
+  auto& sm = ring_of<Ring<G3M, G3N, LO, LO, S>, EXT>(ext);
+  auto A = [&](int seg) {
+    const long long off = (long long)(pb + seg) * g.ws.nact32 * ldx;
+    return DOpnd{g.xt_hi + off, LO ? g.xt_lo + off : nullptr, ldx, g.ws.xt_bytes - 2 * off};
+  };
+  auto B = [&](int seg) {
+    const long long off = (long long)(pb + seg) * g.ws.nact32 * ldw;
+    return DOpnd{g.w_hi + off, LO ? g.w_lo + off : nullptr, ldw, g.ws.w_bytes - 2 * off};
+  };
+  mainloop_dl<G3M, G3N, LO, LO, S, true, false, false, LO, WGM, WGN, (WGM * WGN == 8), WB>(sm, pe - pb, nact, m0, n0,
+                                                                                           A, B, acc, none);
   float* Y = g.Ypart + (long long)s * nbf * nact;
   const float invY = LO ? chunk_scales(g.bnd, g.chunk, false).invY : 1.0f;   // acc = Y sX sW
 #pragma unroll
@@ -883,17 +866,17 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm1_kernel(G1Args g) {
   if (w < 0) return;
   gemm1_body<TERMS, BLO, G1M, G1N, WGM, WGN, MINB, VEC>(w, g);
 }
-template <int TERMS, bool VEC>
-__global__ __launch_bounds__(128 * g2_wgn(VEC), 1) void gemm2_kernel(G2Args g) {
+template <int TERMS>
+__global__ __launch_bounds__(128 * g2_wgn(T2), 1) void gemm2_kernel(G2Args g) {
   const int w = xcd_item(g2_items(g, T2));
   if (w < 0) return;
-  gemm2_body<TERMS, VEC>(w, g);
+  gemm2_body<TERMS>(w, g);
 }
-template <int TERMS, int G3M, int G3N, int WGM, int WGN, int MINB, bool VEC, bool WSYM = false>
+template <int TERMS, int G3M, int G3N, int WGM, int WGN, int MINB>
 __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm3_kernel(G3Args g) {
   const int w = xcd_item(g3_items(g, G3M, G3N));
   if (w < 0) return;
-  gemm3_body<TERMS, G3M, G3N, WGM, WGN, MINB, VEC, false, 0, WSYM>(w, g);
+  gemm3_body<TERMS, G3M, G3N, WGM, WGN, MINB, T2>(w, g);
 }
 
 // Grouped forms: one launch over the work items of every instance of a batch.  The tile width along
@@ -908,25 +891,25 @@ __global__ __launch_bounds__(256, 2) void gemm1_grouped(const G1Args* __restrict
   if (w < 0) return;
   const int i = find_instance(off, ninst, w);
   const G1Args g = tab[i];
-  gemm1_body<TERMS, false, TM, 128, 2, 2, 2, true>(w - off[i], g);
+  gemm1_body<TERMS, false, TM, 128, 2, 2, 2, true, true>(w - off[i], g);
 }
 template <int TERMS, int TT>
-__global__ __launch_bounds__(TT == 128 ? 128 * g2_wgn(true) : 256, TT == 128 ? 1 : 2) void gemm2_grouped(
+__global__ __launch_bounds__(128 * g2_wgn(TT), TT == 128 ? 1 : 2) void gemm2_grouped(
     const G2Args* __restrict__ tab, const int* __restrict__ off, int ninst, int total) {
   const int w = xcd_item(total);
   if (w < 0) return;
   const int i = find_instance(off, ninst, w);
   const G2Args g = tab[i];
-  gemm2_body<TERMS, true, TT, true>(w - off[i], g);
+  gemm2_body<TERMS, TT, true>(w - off[i], g);
 }
-template <int TERMS, int TN>
+template <int TERMS, int TN, int WB>
 __global__ __launch_bounds__(256, 2) void gemm3_grouped(const G3Args* __restrict__ tab, const int* __restrict__ off,
                                                         int ninst, int total) {
   const int w = xcd_item(total);
   if (w < 0) return;
   const int i = find_instance(off, ninst, w);
   const G3Args g = tab[i];
-  gemm3_body<TERMS, 128, TN, 2, 2, 2, true>(w - off[i], g);
+  gemm3_body<TERMS, 128, TN, 2, 2, 2, WB>(w - off[i], g);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1010,7 +993,7 @@ __device__ __forceinline__ void persist_item(const PArgs& a, int i, int ph, int 
         const int t0 = idx * PERSIST_XG, t1 = t0 + PERSIST_XG < nt ? t0 + PERSIST_XG : nt;
         for (int t = t0; t < t1; ++t) {
           if (t > t0) __syncthreads();   // the ring of the tile before is free again
-          gemm1_body<2, false, TX, 128, 2, 2, 2, true, true, PBUDGET>(t, g, lds);
+          gemm1_body<2, false, TX, 128, 2, 2, 2, true, true, true, PBUDGET>(t, g, lds);
         }
       } else {
         f64t::grouped_tile<false, true>(a.f64[i], idx - nx, fs);                           // H C_A
@@ -1020,7 +1003,7 @@ __device__ __forceinline__ void persist_item(const PArgs& a, int i, int ph, int 
     case PH_B: {
       const G2Args g = a.g2[i];
       const int nb = g2_items(g, 64);
-      if (idx < nb) gemm2_body<3, true, 64, true, true, PBUDGET>(idx, g, lds);
+      if (idx < nb) gemm2_body<3, 64, true, true, PBUDGET>(idx, g, lds);
       else bdev::hpp(d, 0, 1);
       break;
     }
@@ -1035,7 +1018,7 @@ __device__ __forceinline__ void persist_item(const PArgs& a, int i, int ph, int 
       break;
     case PH_Y: {
       const G3Args g = a.g3[i];
-      gemm3_body<3, 128, TY, 2, 2, 2, true, true, PBUDGET>(idx, g, lds);
+      gemm3_body<3, 128, TY, 2, 2, 2, 64, true, PBUDGET>(idx, g, lds);
       break;
     }
     case PH_RED:
@@ -1180,7 +1163,7 @@ __global__ void persist_reset_k(PSched sc, int nwords_inst, int ninst) {
 }
 
 // Rows (P, mu) of a stacked X launch are counted in 32 bits.
-inline bool rows32(const G1Args& g) { return (long long)g.np * g.nbf < (1LL << 31); }
+inline bool rows32(const G1Args& g) { return (long long)g.np * round_up(g.nbf, 8) < (1LL << 31); }
 
 inline dim3 xcd_grid(long long items) { return dim3((unsigned)(cdiv(items, NXCD) * NXCD)); }
 
@@ -1227,49 +1210,32 @@ hipError_t df_bf16_gemm1(hipStream_t s, int nbf, int nact, int np, int terms, Sp
 }
 
 hipError_t df_bf16_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms, SplitPtr Ct, int ldk,
-                         SplitPtr XT, int ldx, const float* beta32, double* Kpart, double* Dchunk, u16* W_hi,
-                         u16* W_lo, int ldw, const WsDims& d, const uint32_t* bnd, int chunk, bool wsym) {
+                         SplitPtr XT, int ldx, const float* beta32, double* Kpart, int kset, double* Dchunk,
+                         u16* W_hi, u16* W_lo, int ldw, const WsDims& d, const uint32_t* bnd, int chunk) {
   if (np <= 0) return hipSuccess;
   const G2Args g{nbf,   nact,  np,     nsplit, Ct.hi, Ct.lo, ldk, XT.hi, XT.lo, ldx, beta32,
-                 Kpart, Dchunk, W_hi, W_lo,   ldw,   d,     bnd, chunk, wsym ? 1 : 0};
-  const dim3 grid = xcd_grid(g2_items(g, T2));
-  const bool vec = (ldk % 32 == 0) && (ldx % 32 == 0) && al16(Ct.hi) && (!Ct.lo || al16(Ct.lo)) && al16(XT.hi) &&
-                   (!XT.lo || al16(XT.lo));
-  if (terms == 1) {
-    if (vec) hipLaunchKernelGGL((gemm2_kernel<1, true>), grid, dim3(128 * g2_wgn(true)), 0, s, g);
-    else hipLaunchKernelGGL((gemm2_kernel<1, false>), grid, dim3(128 * g2_wgn(false)), 0, s, g);
-  } else {
-    if (vec) hipLaunchKernelGGL((gemm2_kernel<3, true>), grid, dim3(128 * g2_wgn(true)), 0, s, g);
-    else hipLaunchKernelGGL((gemm2_kernel<3, false>), grid, dim3(128 * g2_wgn(false)), 0, s, g);
-  }
+                 Kpart, Dchunk, W_hi, W_lo,   ldw,   d,     bnd, chunk, kset};
+  if (ldk % 32 || ldx % 32 || ldw % 32 || !al16(Ct.hi) || !al16(Ct.lo) || !al16(XT.hi) || !al16(XT.lo) || !al16(W_hi) ||
+      !al16(W_lo))
+    return hipErrorInvalidValue;
+  const dim3 grid = xcd_grid(g2_items(g, T2)), block(128 * g2_wgn(T2));
+  if (terms == 1) hipLaunchKernelGGL(gemm2_kernel<1>, grid, block, 0, s, g);
+  else hipLaunchKernelGGL(gemm2_kernel<3>, grid, block, 0, s, g);
   return hipGetLastError();
-}
-
-static bool g3_vec(const G3Args& g) {
-  return (g.ldx % 32 == 0) && (g.ldw % 32 == 0) && al16(g.xt_hi) && (!g.xt_lo || al16(g.xt_lo)) && al16(g.w_hi) &&
-         (!g.w_lo || al16(g.w_lo));
 }
 
 template <int TERMS, int G3M, int G3N, int WGM, int WGN, int MINB>
 static void launch_g3(hipStream_t s, const G3Args& g) {
-  const dim3 grid = xcd_grid(g3_items(g, G3M, G3N));
-  const bool vec = g3_vec(g);
-  // operands without aligned rows take the register-staged 128 x 128 form whatever the variant
-  if (vec && g.wsym)
-    hipLaunchKernelGGL((gemm3_kernel<TERMS, G3M, G3N, WGM, WGN, MINB, true, true>), grid, dim3(64 * WGM * WGN), 0, s, g);
-  else if (vec)
-    hipLaunchKernelGGL((gemm3_kernel<TERMS, G3M, G3N, WGM, WGN, MINB, true>), grid, dim3(64 * WGM * WGN), 0, s, g);
-  else
-    hipLaunchKernelGGL((gemm3_kernel<TERMS, 128, 128, 2, 2, 2, false>), xcd_grid(g3_items(g, 128, 128)), dim3(256), 0,
-                       s, g);
+  hipLaunchKernelGGL((gemm3_kernel<TERMS, G3M, G3N, WGM, WGN, MINB>), xcd_grid(g3_items(g, G3M, G3N)), dim3(64 * WGM * WGN),
+                     0, s, g);
 }
 
 hipError_t df_bf16_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms, SplitPtr XT, int ldx,
                          SplitPtr W, int ldw, float* Ypart, int variant, const WsDims& d, const uint32_t* bnd,
-                         int chunk, bool wsym) {
+                         int chunk) {
   if (np <= 0) return hipSuccess;
-  const G3Args g{nbf, nact, np, nsplit, XT.hi, XT.lo, ldx, W.hi, W.lo, ldw, Ypart, d, bnd, chunk, wsym ? 1 : 0};
-  if (wsym && !g3_vec(g)) return hipErrorInvalidValue;   // the symmetric layout needs the direct-load path
+  const G3Args g{nbf, nact, np, nsplit, XT.hi, XT.lo, ldx, W.hi, W.lo, ldw, Ypart, d, bnd, chunk};
+  if (ldx % 32 || ldw % 32 || !al16(XT.hi) || !al16(XT.lo) || !al16(W.hi) || !al16(W.lo)) return hipErrorInvalidValue;
   // variant (resolved by the planner): 1 = 128 x 128 (4 waves of 64 x 64, two blocks per CU),
   // 2 = 256 x 128 (4 waves of 128 x 64), 3 = 256 x 256 (8 waves of 128 x 64)
   if (terms == 1) {
@@ -1309,22 +1275,26 @@ hipError_t df_bf16_gemm2_grouped(hipStream_t s, int ninst, int total, int terms,
     if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
     else hipLaunchKernelGGL((gemm2_grouped<3, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
   } else {
-    const dim3 bl(128 * g2_wgn(true));
+    const dim3 bl(128 * g2_wgn(128));
     if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 128>), gr, bl, 0, s, tab, off, ninst, total);
     else hipLaunchKernelGGL((gemm2_grouped<3, 128>), gr, bl, 0, s, tab, off, ninst, total);
   }
   return hipGetLastError();
 }
-hipError_t df_bf16_gemm3_grouped(hipStream_t s, int ninst, int total, int terms, int tile, const G3Args* tab,
+template <int TERMS, int TN>
+static void launch_g3_grouped(hipStream_t s, int ninst, int total, int btile, const G3Args* tab, const int* off) {
+  if (btile == 64) hipLaunchKernelGGL((gemm3_grouped<TERMS, TN, 64>), xcd_grid(total), dim3(256), 0, s, tab, off, ninst, total);
+  else hipLaunchKernelGGL((gemm3_grouped<TERMS, TN, 128>), xcd_grid(total), dim3(256), 0, s, tab, off, ninst, total);
+}
+hipError_t df_bf16_gemm3_grouped(hipStream_t s, int ninst, int total, int terms, int tile, int btile, const G3Args* tab,
                                  const int* off) {
   if (total <= 0) return hipSuccess;
-  const dim3 gr = xcd_grid(total);
   if (tile == 64) {
-    if (terms == 1) hipLaunchKernelGGL((gemm3_grouped<1, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
-    else hipLaunchKernelGGL((gemm3_grouped<3, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
+    if (terms == 1) launch_g3_grouped<1, 64>(s, ninst, total, btile, tab, off);
+    else launch_g3_grouped<3, 64>(s, ninst, total, btile, tab, off);
   } else {
-    if (terms == 1) hipLaunchKernelGGL((gemm3_grouped<1, 128>), gr, dim3(256), 0, s, tab, off, ninst, total);
-    else hipLaunchKernelGGL((gemm3_grouped<3, 128>), gr, dim3(256), 0, s, tab, off, ninst, total);
+    if (terms == 1) launch_g3_grouped<1, 128>(s, ninst, total, btile, tab, off);
+    else launch_g3_grouped<3, 128>(s, ninst, total, btile, tab, off);
   }
   return hipGetLastError();
 }

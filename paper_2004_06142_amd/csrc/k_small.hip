@@ -21,25 +21,6 @@ inline dim3 grid1(long long n, int per = NT) {
 __global__ void fill_f64_k(double* p, long long n, double v) { GRID_STRIDE(i, n) p[i] = v; }
 __global__ void fill_u16_k(u16* p, long long n, u16 v) { GRID_STRIDE(i, n) p[i] = v; }
 
-// Zero the pads of nslice row-major slices (slice stride sstride): columns [cols, ld) of rows
-// [0, rows), and rows [rows, rows_pad) in full.
-__global__ void zero_pads_u16_k(u16* __restrict__ base, int nslice, long long sstride, int rows, int rows_pad, int ld,
-                                int cols) {
-  const long long side = (long long)rows * (ld - cols), per = side + (long long)(rows_pad - rows) * ld;
-  GRID_STRIDE(i, (long long)nslice * per) {
-    const long long sl = i / per, j = i % per;
-    long long r, c;
-    if (j < side) {
-      r = j / (ld - cols);
-      c = cols + j % (ld - cols);
-    } else {
-      r = rows + (j - side) / ld;
-      c = (j - side) % ld;
-    }
-    base[sl * sstride + r * ld + c] = 0;
-  }
-}
-
 // alpha, beta of E_2 = sum_pq alpha_pq J_pq + beta_pq K_pq (Eqs. Eg, Efg, Efg_s).
 __global__ void coeffs_k(int nact, int npairs, int ncwo, int nsingle, int functional, const double* __restrict__ n,
                          double* __restrict__ alpha, double* __restrict__ beta, float* __restrict__ beta32) {
@@ -62,15 +43,15 @@ __global__ void transpose_ca_k(int nbf, int nact, const double* __restrict__ C, 
 }
 
 // C_A^T as bf16: one value (terms 1), or the compact bf16 pair C~ = hi + lo of X's contraction plus
-// the exact fp16 pair of C~ sC for the b contraction (and X from a float64 B).
-__global__ void split_ca_k(int nbf, int nact, int terms, const double* __restrict__ C, u16* __restrict__ hi,
+// the exact fp16 pair of C~ sC for the b contraction (and X from a float64 B); zeros in the padding
+// (rows nact to `rows`, columns nbf to ldk).
+__global__ void split_ca_k(int nbf, int nact, int rows, int terms, const double* __restrict__ C, u16* __restrict__ hi,
                            u16* __restrict__ lo, u16* __restrict__ h16, u16* __restrict__ l16, int ldk,
                            const uint32_t* __restrict__ bnd) {
   const float sC = terms > 1 ? chunk_scales(bnd, 0, false).sC : 1.0f;
-  GRID_STRIDE(i, (long long)nact * nbf) {
-    const int p = (int)(i / nbf), mu = (int)(i % nbf);
-    const long long o = (long long)p * ldk + mu;
-    const double x = C[(long long)mu * nbf + p];
+  GRID_STRIDE(o, (long long)rows * ldk) {
+    const int p = (int)(o / ldk), mu = (int)(o % ldk);
+    const double x = p < nact && mu < nbf ? C[(long long)mu * nbf + p] : 0.0;
     if (terms == 1) {
       hi[o] = f32_to_bf16_bits((float)x);
       continue;
@@ -420,15 +401,16 @@ __global__ void reduce_k_k(int nact, int nsplit, const double* __restrict__ Kpar
     const int p = (int)(i / nact), q = (int)(i % nact);
     if (q > p) continue;
     const double s = sum_strided(Kpart + i, nsplit, (long long)nact * nact);
-    K[i] += s;
-    if (q != p) K[(long long)q * nact + p] += s;
+    K[i] = s;
+    if (q != p) K[(long long)q * nact + p] = s;
   }
 }
 
 template <typename T>
-__global__ void reduce_y_k(long long n, int nsplit, const T* __restrict__ Yp, double* __restrict__ Y) {
+__global__ void reduce_y_k(long long n, int nsplit, int first, const T* __restrict__ Yp, double* __restrict__ Y) {
   GRID_STRIDE(i, n) {
-    Y[i] += sum_strided(Yp + i, nsplit, n);
+    const double y = sum_strided(Yp + i, nsplit, n);
+    Y[i] = first ? y : Y[i] + y;
   }
 }
 
@@ -925,14 +907,6 @@ hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v) {
   if (n <= 0) return hipSuccess;
   LAUNCH(fill_u16_k, grid1(n), dim3(NT), p, n, v);
 }
-hipError_t zero_pads_u16(hipStream_t s, u16* base, int nslice, long long sstride, int rows, int rows_pad, int ld,
-                         int cols) {
-  if (nslice <= 0 || rows < 0 || rows_pad < rows || cols < 0 || ld < cols || sstride < (long long)rows_pad * ld)
-    return hipErrorInvalidValue;
-  const long long n = (long long)nslice * ((long long)rows * (ld - cols) + (long long)(rows_pad - rows) * ld);
-  if (n == 0) return hipSuccess;
-  LAUNCH(zero_pads_u16_k, grid1(n), dim3(NT), base, nslice, sstride, rows, rows_pad, ld, cols);
-}
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                   double* alpha, double* beta, float* beta32) {
   LAUNCH(coeffs_k, grid1((long long)nact * nact), dim3(NT), nact, npairs, ncwo, nsingle, functional, n, alpha, beta,
@@ -950,9 +924,9 @@ hipError_t add_diag_f32(hipStream_t s, int nact, int np, const double* Dc, const
   hipLaunchKernelGGL(d_alpha_k, dim3(np), dim3(NT), 0, s, nact, oc.npairs, oc.ncwo, oc.nsingle, oc.n, Dc, dbuf);
   LAUNCH(add_diag_f32_k, grid1((long long)np * nact), dim3(NT), nact, np, 1, dbuf, W, ldw);
 }
-hipError_t split_ca(hipStream_t s, int nbf, int nact, int terms, const double* C, u16* hi, u16* lo, u16* h16,
+hipError_t split_ca(hipStream_t s, int nbf, int nact, int rows, int terms, const double* C, u16* hi, u16* lo, u16* h16,
                     u16* l16, int ldk, const uint32_t* bnd) {
-  LAUNCH(split_ca_k, grid1((long long)nbf * nact), dim3(NT), nbf, nact, terms, C, hi, lo, h16, l16, ldk, bnd);
+  LAUNCH(split_ca_k, grid1((long long)rows * ldk), dim3(NT), nbf, nact, rows, terms, C, hi, lo, h16, l16, ldk, bnd);
 }
 hipError_t split_b(hipStream_t s, long long nrows, int n, const double* B, u16* hi, u16* lo, int ldo, const uint32_t* bnd,
                    int chunk) {
@@ -1046,11 +1020,11 @@ hipError_t offdiag_copy(hipStream_t s, int nbf, const double* src, double* dst) 
 hipError_t reduce_k(hipStream_t s, int nact, int nsplit, const double* Kpart, double* K) {
   LAUNCH(reduce_k_k, grid1((long long)nact * nact), dim3(NT), nact, nsplit, Kpart, K);
 }
-hipError_t reduce_y_f64(hipStream_t s, long long n, int nsplit, const double* Yp, double* Y) {
-  LAUNCH(reduce_y_k<double>, grid1(n), dim3(NT), n, nsplit, Yp, Y);
+hipError_t reduce_y_f64(hipStream_t s, long long n, int nsplit, int first, const double* Yp, double* Y) {
+  LAUNCH(reduce_y_k<double>, grid1(n), dim3(NT), n, nsplit, first, Yp, Y);
 }
-hipError_t reduce_y_f32(hipStream_t s, long long n, int nsplit, const float* Yp, double* Y) {
-  LAUNCH(reduce_y_k<float>, grid1(n), dim3(NT), n, nsplit, Yp, Y);
+hipError_t reduce_y_f32(hipStream_t s, long long n, int nsplit, int first, const float* Yp, double* Y) {
+  LAUNCH(reduce_y_k<float>, grid1(n), dim3(NT), n, nsplit, first, Yp, Y);
 }
 hipError_t energy(hipStream_t s, int nbf, int nact, const double* n, const double* Hpp,
                   const double* alpha, const double* beta, const double* J, const double* K,
