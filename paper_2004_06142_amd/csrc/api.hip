@@ -189,20 +189,22 @@ struct Plan {
   bool split;   // bf16 family
   bool f32;     // PNOF_FP32: the float64 path's kernels in float32
   int terms;    // 1 or 3
+  int kr;       // split: rows of P that one float32 sum of b^2 covers
 };
 
 // P-splits of a contraction whose blocks take one tile and the P rows of one split, `slots` blocks resident
 // at once: the count whose launch ends soonest, as whole rounds of blocks of floor(np / ns) rows (no less
-// than the even share), one row more where np / ns is not whole, and `fill` rows' worth of time per block
-// for its start and its partial sums.
-int best_splits(int np, long long tiles, int slots, double fill) {
+// than the even share), one row more where np / ns is not whole, `fill` rows' worth of time per block
+// for its start and its partial sums, and the share `tail` of a block at the launch's uneven end.
+int best_splits(int np, long long tiles, int slots, double fill, double tail = 0.0) {
   int best = 1;
   double tbest = 1e300;
   for (int per = np; per >= 1; per = per > 64 ? per / 2 : per - 1)
     for (int ns : {np / per, (np + per - 1) / per}) {
       if (ns < 1 || ns > np) continue;
       const double rounds = (double)cdiv(tiles * ns, slots);
-      const double t = std::max((double)tiles * np / slots, rounds * (np / ns)) + (np % ns ? 1.0 : 0.0) + fill * rounds;
+      const double t = std::max((double)tiles * np / slots, rounds * (np / ns)) + (np % ns ? 1.0 : 0.0) + fill * rounds +
+                       tail * np / ns;
       if (t < tbest) {
         tbest = t;
         best = ns;
@@ -269,7 +271,15 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   const int tt = cdiv(pl.nact, tile);
   const long long ntri = (long long)tt * (tt + 1) / 2;
   const long long auto2 = std::max(1LL, (1024 + ntri - 1) / ntri);
-  pl.ns2 = tu.nsplit_b > 0 ? tu.nsplit_b : pl.split ? (int)auto2 : best_splits(pl.pc, ntri, 768, 0.25);
+  // b: two (split) or three blocks per compute unit, whole rounds (1200 functions, 55 tiles of 164 rows: 19
+  // splits are 4.08 rounds of 256, 42.7 ms over the step; 27 of the present form, 35.1).  The sums of b^2 are
+  // float64, in the split mode over float32 sums of at most kr rows: 8, or the even share of 1024 blocks (K's
+  // distance from float64 arithmetic, 6e-7 to 1e-6 at 200 to 500 functions, is the same to four digits with
+  // 2 or 3 rows; adding to float64 sums that often cost a tenth of b)
+  pl.kr = std::max(8, cdiv(pl.pc, std::min<long long>(pl.pc, auto2)));
+  pl.ns2 = tu.nsplit_b > 0 ? tu.nsplit_b
+           : pl.split      ? best_splits(pl.pc, ntri, 512, 0.25, 0.1)
+                           : best_splits(pl.pc, ntri, 768, 0.25);
   pl.ns2 = std::min(pl.ns2, pl.pc);
   // Y: as many P-splits as fit the chip's resident blocks in one round (MI355X: 256 compute units;
   // the 128 x 128 bf16 tile runs two blocks per unit, the float64 tile of 128 x 64 three); the float32
@@ -308,7 +318,7 @@ Bufs carve(const Plan& pl, char* base) {
   const long long ny = (long long)pl.nbf * pl.nact;
   b.alpha = a.take<double>(n2);
   b.beta = a.take<double>(n2);
-  b.beta32 = a.take<float>(n2);
+  b.beta32 = a.take<float>((long long)pl.nact32 * pl.nact32);
   b.HC = a.take<double>(ny);
   b.Hpp = a.take<double>(pl.nact);
   b.J = a.take<double>(n2);
@@ -483,7 +493,8 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
   const bool have_n = (n != nullptr);
   const OccLayout occ{n, pl.npairs, pl.ncwo, pl.nsingle};
 
-  if (have_n) DEV_CHECK(ctx, coeffs(s, nact, pl.npairs, pl.ncwo, pl.nsingle, pl.functional, n, b.alpha, b.beta, b.beta32));
+  if (have_n) DEV_CHECK(ctx, coeffs(s, nact, pl.npairs, pl.ncwo, pl.nsingle, pl.functional, n, b.alpha, b.beta, b.beta32,
+                                pl.nact32));
   if (H) {
     // HC = H C_A ; Hpp = diag(C_A^T H C_A)
     RB_CHECK(dprod(ctx, nbf, nact, nbf, H, nbf, 1, C, nbf, 1, b.HC, nact, 1));
@@ -534,7 +545,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
                             : static_cast<const void*>(static_cast<const double*>(ints) + p0 * bsz);
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_fp_gemm1(s, nbf, nact, np, b.Ct32, pl.ldk, Bc, bb, b.XT32, pl.ldx)));
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_fp_gemm2<float>(s, nbf, nact, np, ns2, b.Ct32, pl.ldk, b.XT32, pl.ldx,
-                                                                    b.beta32, b.Kpart, p0 == 0, Dc, b.W32, pl.ldw)));
+                                                                    b.beta32, pl.nact32, b.Kpart, p0 == 0, Dc, b.W32, pl.ldw)));
         if (want_y) {
           DEV_CHECK(ctx, add_diag_f32(s, nact, np, Dc, occ, b.dbuf, b.W32, pl.ldw));
           DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_fp_gemm3(s, nbf, nact, np, ns3, b.XT32, pl.ldx, b.W32, pl.ldw,
@@ -554,7 +565,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         const void* Bc = bb ? static_cast<const void*>(static_cast<const u16*>(ints) + p0 * bsz)
                             : static_cast<const void*>(static_cast<const double*>(ints) + p0 * bsz);
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_fp_gemm1(s, nbf, nact, np, b.Ct, pl.ldk, Bc, bb, b.XT, pl.ldx)));
-        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_fp_gemm2<double>(s, nbf, nact, np, ns2, b.Ct, pl.ldk, b.XT, pl.ldx, b.beta,
+        DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_fp_gemm2<double>(s, nbf, nact, np, ns2, b.Ct, pl.ldk, b.XT, pl.ldx, b.beta, nact,
                                                                      b.Kpart, p0 == 0, Dc, b.W, pl.ldw)));
         if (want_y) {
           DEV_CHECK(ctx, add_diag_f64(s, nact, np, Dc, occ, b.dbuf, b.W, pl.ldw));
@@ -641,7 +652,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         double* Dc = b.D + (long long)p0 * nact;
         SplitPtr XT{xth_[c & 1], split ? xtl_[c & 1] : nullptr};
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_bf16_gemm2(s, nbf, nact, np, ns2, pl.terms, C16, pl.ldk, XT, pl.ldx,
-                                                               b.beta32, b.Kpart, c == 0, Dc, b.wh, b.wl, pl.ldw, wd, b.bnd, c)));
+                                                               b.beta32, b.Kpart, c == 0, pl.kr, Dc, b.wh, b.wl, pl.ldw, wd, b.bnd, c)));
         if (want_y) {
           if (two) {
             DEV_CHECK(ctx, hipEventRecord(ev_b, s));
@@ -765,7 +776,7 @@ struct OnObjective {
     hipStream_t s = ctx->stream;
     DEV_CHECK(ctx, hipMemcpyAsync(gam, x.data(), sizeof(double) * ngam, hipMemcpyHostToDevice, s));
     DEV_CHECK(ctx, on_map(s, kind, npairs, ncwo, nsingle, gam, n, nullptr));
-    DEV_CHECK(ctx, coeffs(s, nact, npairs, ncwo, nsingle, functional, n, alpha, beta, nullptr));
+    DEV_CHECK(ctx, coeffs(s, nact, npairs, ncwo, nsingle, functional, n, alpha, beta));
     DEV_CHECK(ctx, energy(s, nbf, nact, n, Hpp, alpha, beta, J, K, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0,
                           partials, E));
     DEV_CHECK(ctx, grad_n(s, nact, npairs, ncwo, nsingle, functional, n, Hpp, J, K, dEdn));
@@ -1687,7 +1698,7 @@ pnof_status pnof_optimize(pnof_ctx ctx, const pnof_problem* prob, const double* 
     pnof_status st2 = run_step(ctx, &pr, C, nullptr, H, ints, r);
     if (st2 != PNOF_OK) return st2;
     if (op.fix_n) {
-      DEV_CHECK(ctx, coeffs(s, nact, pr.npairs, pr.ncwo, pr.nsingle, pr.functional, n, o.alpha, o.beta, nullptr));
+      DEV_CHECK(ctx, coeffs(s, nact, pr.npairs, pr.ncwo, pr.nsingle, pr.functional, n, o.alpha, o.beta));
       DEV_CHECK(ctx, energy(s, nbf, nact, n, Hpp, o.alpha, o.beta, J, K, nullptr, nullptr, nullptr, nullptr, nullptr,
                             0, 0, o.partials, o.E));
       DEV_CHECK(ctx, hipMemcpyAsync(host2, o.E, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1857,7 +1868,7 @@ pnof_status pnof_batch_plan(pnof_ctx ctx, int32_t ninst, const pnof_problem* pro
       }
       d.alpha = a.take<double>(n2);
       d.beta = a.take<double>(n2);
-      d.beta32 = a.take<float>(n2);
+      d.beta32 = a.take<float>((long long)g.nact32 * g.nact32);
       d.J = a.take<double>(n2);
       d.K = a.take<double>(n2);
       d.Kpart = a.take<double>((long long)g.ns2 * n2);

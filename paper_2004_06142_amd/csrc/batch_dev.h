@@ -107,6 +107,11 @@ __device__ inline void prep(const BInst& d, int part, int nparts, float sC) {
     pnof_coeff(p, q, d.n[p], d.n[q], d.npairs, d.ncwo, d.nsingle, d.functional, a, b);
     d.alpha[i] = a;
     d.beta[i] = b;
+  }
+  BDEV_STRIDE(i, (long long)d.nact32 * d.nact32) {   // beta in float32, zero past nact
+    const int p = (int)(i / d.nact32), q = (int)(i % d.nact32);
+    double a, b = 0.0;
+    if (p < nact && q < nact) pnof_coeff(p, q, d.n[p], d.n[q], d.npairs, d.ncwo, d.nsingle, d.functional, a, b);
     d.beta32[i] = (float)b;
   }
   BDEV_STRIDE(i, (long long)nact * nbf) {
@@ -148,7 +153,7 @@ __device__ inline void add_diag(const BInst& d, int part, int nparts) {
     const long long P = i / d.nact;
     const int p = (int)(i % d.nact);
     const long long o = P * pstride + (long long)p * d.ldw + p;
-    const float wv = (float)d.D[i] * d.beta32[(long long)p * d.nact + p];
+    const float wv = (float)d.D[i] * d.beta32[(long long)p * d.nact32 + p];
     const double w = (double)wv + d.dbuf[i];
     if (d.wl) {
       u16 h, l;

@@ -316,7 +316,7 @@ hipError_t df_fp_gemm1(hipStream_t s, int nbf, int nact, int np, const T* Ct, in
                        T* XT, int ldx);
 template <typename T>
 hipError_t df_fp_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, const T* Ct, int ldk, const T* XT, int ldx,
-                       const T* beta, double* Kpart, bool kset, double* Dchunk, T* W, int ldw);
+                       const T* beta, int ldbeta, double* Kpart, bool kset, double* Dchunk, T* W, int ldw);
 int df_fp_y_tile(int nbf, int nact, int nsplit);   // 128 or 64: rows of gemm3's tile (by 64 active orbitals)
 template <typename T>
 hipError_t df_fp_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, const T* XT, int ldx, const T* W, int ldw,
@@ -371,6 +371,7 @@ struct G2Args {   // b_P = Ct XT_P^T; K partials, D, W
   const uint32_t* bnd;
   int chunk;
   int kset = 1;   // store the K sums (a problem's first chunk) instead of adding them
+  int krows = 0;  // P rows that one float32 sum of b^2 runs over (single problem; a batch: the split)
 };
 struct G3Args {   // Ypart[s] = sum_{P in s} X_P W_P
   int nbf, nact, np, nsplit;
@@ -424,10 +425,10 @@ hipError_t df_bf16_gemm1(hipStream_t s, int nbf, int nact, int np, int terms, Sp
                          const WsDims& d, const uint32_t* bnd, int chunk);
 // W is written only as the transposed image of b's tiles, i.e. its 128 x 128 blocks on and above the
 // diagonal (gemm2), and Y reads each block of W in the orientation that holds it (gemm3).  kset: store the K
-// partials (the first chunk) instead of adding to them.  Leading dimensions of 32, operands 16-byte aligned.
+// partials (the first chunk) instead of adding to them; krows: P rows of one float32 sum of b^2.  Leading dimensions of 32, operands 16-byte aligned.
 hipError_t df_bf16_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms,
                          SplitPtr Ct, int ldk, SplitPtr XT, int ldx, const float* beta32,
-                         double* Kpart, int kset, double* Dchunk, u16* W_hi, u16* W_lo, int ldw, const WsDims& d,
+                         double* Kpart, int kset, int krows, double* Dchunk, u16* W_hi, u16* W_lo, int ldw, const WsDims& d,
                          const uint32_t* bnd, int chunk);
 hipError_t df_bf16_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms, SplitPtr XT,
                          int ldx, SplitPtr W, int ldw, float* Ypart, int variant, const WsDims& d,
@@ -532,7 +533,7 @@ hipError_t batch_persist(hipStream_t s, const PArgs& a, int ninst_state_words, i
 hipError_t fill_f64(hipStream_t s, double* p, long long n, double v);
 hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v);
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
-                  double* alpha, double* beta, float* beta32);
+                  double* alpha, double* beta, float* beta32 = nullptr, int ld32 = 0);
 template <typename T>
 hipError_t transpose_ca(hipStream_t s, int nbf, int nact, const double* C, T* Ct, int ldk);
 // The occupations and the subspace layout (the structure of the Coulomb coefficients alpha).
@@ -572,7 +573,7 @@ hipError_t gemm_f64_splitk(hipStream_t s, int M, int N, int K, int ks, const dou
                            const double* B, long long sbk, long long sbn, double* Cpart);
 // d = Dchunk alpha (np x nact into dbuf), formed from the structure of alpha (2 n_p n_q between
 // subspaces, 0 within one) in O(np nact), then W_P[p][p] += d[P][p].  The split form rebuilds the
-// diagonal from Dchunk (the b contraction's float accumulators b^P_pp) as float(b^P_pp * beta32_pp) +
+// diagonal from Dchunk (the b contraction's float accumulators b^P_pp) as float(b^P_pp * beta32_pp) (beta32: ldw x ldw) +
 // d[P][p] and only writes it, so W's scattered diagonal is never read back.
 hipError_t add_diag_f64(hipStream_t s, int nact, int np, const double* Dchunk, const OccLayout& oc,
                         double* dbuf, double* W, int ldw);

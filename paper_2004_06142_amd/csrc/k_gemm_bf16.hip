@@ -697,11 +697,14 @@ __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = n
 // over the successive P-chunks of one call, the first of which stores: kset), D[P][p] = b_pp, W_P = b o beta
 // as a hi/lo pair, written only as the transposed image of each tile: the TT x TT blocks on and above the
 // diagonal, which gemm3 reads.
-// waves along q of a gemm2 block (2 x g2_wgn grid): the 128 tile runs 8 waves (2 x 4, each 64 x 32), half the
-// accumulators, beta and K sums per wave, so they stay in registers, and two waves per SIMD hide each
-// other's epilogue latency; the 64 tile runs 4 waves of 32 x 32
-constexpr int g2_wgn(int tt) { return tt == 128 ? 4 : 2; }
-
+// 4 waves of (TT / 2)^2, two blocks per compute unit: a 64 x 64 wave reads 16 KB of LDS per k-tile for 48
+// products, an 8-wave 64 x 32 form 12 KB for 24, which LDS bandwidth bounds, and while one block forms K and W the
+// other keeps the matrix cores busy.  Against 8 waves and one block, b over the step: 1200 functions 42.7 ->
+// 36.1 ms, 500 functions (300 active, 2000 rows) 1.40 -> 0.91, 413 functions 0.85 -> 0.55 (with the splits that the
+// planner takes for it).
+// The sums of b^2 are float32 over at most krows rows, then float64 in Kpart: each block adds to its own partial
+// sums only, with atomics, which need no wait (as loads and stores, 1200 functions in 164 splits 53.0 ms, with
+// atomics 40.0).
 // TT: the square tile (128, or 64 for the short active spaces of batch instances, with 4 waves).
 // BATCH: one launch covers every P of the problem (K is stored); the blocks on the diagonal hold W[p][q]
 // itself, in place of its image (b_pq and b_qp differ in the last bits), by a transpose between lanes (as 2-byte
@@ -709,7 +712,7 @@ constexpr int g2_wgn(int tt) { return tt == 128 ? 4 : 2; }
 template <int TERMS, int TT = T2, bool BATCH = false, bool EXT = false, int BUDGET = 0>
 __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = nullptr) {
   constexpr bool LO = TERMS >= 3;
-  constexpr int WGN = g2_wgn(TT), NI = TT / (16 * WGN), MI = TT / 32;
+  constexpr int WGN = 2, NI = TT / 32, MI = TT / 32;
   const int nbf = g.nbf, nact = g.nact, np = g.np, nsplit = g.nsplit, ldw = g.ldw, ldx = g.ldx;
   const int tt = (nact + TT - 1) / TT;
   const int ntri = tt * (tt + 1) / 2;
@@ -725,22 +728,29 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
     invB = sc.invB;
     wmul = sc.wmul;
   }
-  // beta (times the W scale) of this lane's accumulator positions, kept in registers for the whole
-  // P-range
-  f32x4 bet[MI][NI];
+  // beta (symmetric, nact32 x nact32) of this lane's accumulator positions.  The 64 tile keeps it in registers
+  // for the whole P-range; in the 128 tile, whose sums of b^2 and accumulators fill them, each P reads it anew
+  constexpr bool BREG = TT == 64;
+  auto beta8 = [&](int h, int jn, f32x4(&v)[2]) {
+    const int p0 = m0 + row8_of<TT, 2, WGN>(h), q = n0 + col_of<TT, 2, WGN>(jn);
+    if (p0 < g.ws.nact32 && q < g.ws.nact32) {
+      const f32x4* src = reinterpret_cast<const f32x4*>(g.beta32 + (long long)q * g.ws.nact32 + p0);
+      v[0] = src[0] * wmul;
+      v[1] = src[1] * wmul;
+    } else v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  f32x4 bet[BREG ? MI / 2 : 1][BREG ? NI : 1][2];
+  if constexpr (BREG)
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+    for (int h = 0; h < MI / 2; ++h)
 #pragma unroll
-    for (int jn = 0; jn < NI; ++jn)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = m0 + row8_of<TT, 2, WGN>(i >> 1) + 4 * (i & 1) + j, q = n0 + col_of<TT, 2, WGN>(jn);
-        bet[i][jn][j] = (p < nact && q < nact) ? g.beta32[(long long)p * nact + q] * wmul : 0.f;
-      }
+      for (int jn = 0; jn < NI; ++jn) beta8(h, jn, bet[h][jn]);
   f32x4 kacc[MI][NI], acc[MI][NI];
   zero(kacc);
   const bool diag = (tm == tn);
   const int wrows = BATCH ? nact : g.ws.nact32;
+  int kleft = BATCH ? pe - pb : min(g.krows, pe - pb);   // rows of P left for the float32 sums
+  bool kset = BATCH || g.kset;
   auto epi = [&](int seg, f32x4(&a)[MI][NI]) {
     const int P = pb + seg;
     u16* Wh = g.w_hi + (long long)P * g.ws.nact32 * ldw;
@@ -751,12 +761,17 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
       for (int jn = 0; jn < NI; ++jn) {
         const int p0 = m0 + row8_of<TT, 2, WGN>(h), q = n0 + col_of<TT, 2, WGN>(jn);
         float wv[8];
+        f32x4 bv[2];
+        if constexpr (BREG) {
+          bv[0] = bet[h][jn][0];
+          bv[1] = bet[h][jn][1];
+        } else beta8(h, jn, bv);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int i = 2 * h + (e >> 2), j = e & 3;
           const float b = a[i][jn][j] * invB;
           kacc[i][jn][j] += b * b;
-          wv[e] = a[i][jn][j] * bet[i][jn][j];
+          wv[e] = a[i][jn][j] * bv[e >> 2][j];
           if (diag && p0 + e == q && q < nact) g.Dc[(long long)P * nact + q] = (double)b;
         }
         u32x4 hi, lo;
@@ -783,8 +798,26 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
           if (LO) *reinterpret_cast<u32x4*>(Wl + o) = lo;
         }
       }
+    if (--kleft > 0) return;
+    double* Kp = g.Kpart + (long long)s * nact * nact;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int jn = 0; jn < NI; ++jn)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int p = m0 + row8_of<TT, 2, WGN>(i >> 1) + 4 * (i & 1) + j, q = n0 + col_of<TT, 2, WGN>(jn);
+          if (p < nact && q <= p) {
+            double* k = Kp + (long long)p * nact + q;
+            if (kset) *k = (double)kacc[i][jn][j];
+            else unsafeAtomicAdd(k, (double)kacc[i][jn][j]);   // nobody else's: an add that needs no wait
+          }
+        }
+    zero(kacc);
+    kset = false;
+    kleft = min(g.krows, pe - 1 - P);
   };
-  constexpr int S = ring_depth(TT, TT, LO, LO, BUDGET > 0 ? BUDGET : (TT == 128 ? 163840 : 81920));
+  constexpr int S = ring_depth(TT, TT, LO, LO, BUDGET > 0 ? BUDGET : 81920);
   auto& sm = ring_of<Ring<TT, TT, LO, LO, S>, EXT>(ext);
   auto A = [&](int) { return DOpnd{g.ct_hi, g.ct_lo, g.ldk, g.ws.ct_bytes}; };
   auto B = [&](int seg) {
@@ -793,19 +826,6 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
   };
   mainloop_dl<TT, TT, LO, LO, S, false, false, true, LO, 2, WGN, false, false, 1>(sm, pe - pb, nbf, m0, n0, A, B, acc,
                                                                                  epi);
-  double* Kp = g.Kpart + (long long)s * nact * nact;
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int jn = 0; jn < NI; ++jn)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = m0 + row8_of<TT, 2, WGN>(i >> 1) + 4 * (i & 1) + j, q = n0 + col_of<TT, 2, WGN>(jn);
-        if (p < nact && q <= p) {
-          double* k = Kp + (long long)p * nact + q;
-          *k = (BATCH || g.kset) ? (double)kacc[i][jn][j] : *k + (double)kacc[i][jn][j];
-        }
-      }
 }
 
 // gemm3: Ypart[s][mu][q] = sum_{P in s} sum_r XT_P[r][mu] W_P[q][r].  XT is read as a col operand,
@@ -867,7 +887,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm1_kernel(G1Args g) {
   gemm1_body<TERMS, BLO, G1M, G1N, WGM, WGN, MINB, VEC>(w, g);
 }
 template <int TERMS>
-__global__ __launch_bounds__(128 * g2_wgn(T2), 1) void gemm2_kernel(G2Args g) {
+__global__ __launch_bounds__(256, 2) void gemm2_kernel(G2Args g) {
   const int w = xcd_item(g2_items(g, T2));
   if (w < 0) return;
   gemm2_body<TERMS>(w, g);
@@ -894,7 +914,7 @@ __global__ __launch_bounds__(256, 2) void gemm1_grouped(const G1Args* __restrict
   gemm1_body<TERMS, false, TM, 128, 2, 2, 2, true, true>(w - off[i], g);
 }
 template <int TERMS, int TT>
-__global__ __launch_bounds__(128 * g2_wgn(TT), TT == 128 ? 1 : 2) void gemm2_grouped(
+__global__ __launch_bounds__(256, 2) void gemm2_grouped(
     const G2Args* __restrict__ tab, const int* __restrict__ off, int ninst, int total) {
   const int w = xcd_item(total);
   if (w < 0) return;
@@ -1210,15 +1230,15 @@ hipError_t df_bf16_gemm1(hipStream_t s, int nbf, int nact, int np, int terms, Sp
 }
 
 hipError_t df_bf16_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms, SplitPtr Ct, int ldk,
-                         SplitPtr XT, int ldx, const float* beta32, double* Kpart, int kset, double* Dchunk,
+                         SplitPtr XT, int ldx, const float* beta32, double* Kpart, int kset, int krows, double* Dchunk,
                          u16* W_hi, u16* W_lo, int ldw, const WsDims& d, const uint32_t* bnd, int chunk) {
   if (np <= 0) return hipSuccess;
   const G2Args g{nbf,   nact,  np,     nsplit, Ct.hi, Ct.lo, ldk, XT.hi, XT.lo, ldx, beta32,
-                 Kpart, Dchunk, W_hi, W_lo,   ldw,   d,     bnd, chunk, kset};
+                 Kpart, Dchunk, W_hi, W_lo,   ldw,   d,     bnd, chunk, kset, krows};
   if (ldk % 32 || ldx % 32 || ldw % 32 || !al16(Ct.hi) || !al16(Ct.lo) || !al16(XT.hi) || !al16(XT.lo) || !al16(W_hi) ||
       !al16(W_lo))
     return hipErrorInvalidValue;
-  const dim3 grid = xcd_grid(g2_items(g, T2)), block(128 * g2_wgn(T2));
+  const dim3 grid = xcd_grid(g2_items(g, T2)), block(256);
   if (terms == 1) hipLaunchKernelGGL(gemm2_kernel<1>, grid, block, 0, s, g);
   else hipLaunchKernelGGL(gemm2_kernel<3>, grid, block, 0, s, g);
   return hipGetLastError();
@@ -1275,9 +1295,8 @@ hipError_t df_bf16_gemm2_grouped(hipStream_t s, int ninst, int total, int terms,
     if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
     else hipLaunchKernelGGL((gemm2_grouped<3, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
   } else {
-    const dim3 bl(128 * g2_wgn(128));
-    if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 128>), gr, bl, 0, s, tab, off, ninst, total);
-    else hipLaunchKernelGGL((gemm2_grouped<3, 128>), gr, bl, 0, s, tab, off, ninst, total);
+    if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 128>), gr, dim3(256), 0, s, tab, off, ninst, total);
+    else hipLaunchKernelGGL((gemm2_grouped<3, 128>), gr, dim3(256), 0, s, tab, off, ninst, total);
   }
   return hipGetLastError();
 }

@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256, 3) void df_x_kernel(int nbf, int nact, int np,
 // lower).
 template <typename T>
 __global__ __launch_bounds__(256, 3) void df_b_kernel(int nbf, int nact, int np, int nsplit, const T* __restrict__ Ct, int ldk,
-                                                   const T* __restrict__ XT, int ldx, const T* __restrict__ beta,
+                                                   const T* __restrict__ XT, int ldx, const T* __restrict__ beta, int ldbeta,
                                                    double* __restrict__ Kpart, int kset, double* __restrict__ Dc,
                                                    T* __restrict__ W, int ldw) {
   __shared__ FpSlab<T, BT> sa[2], sb[2];
@@ -437,7 +437,7 @@ __global__ __launch_bounds__(256, 3) void df_b_kernel(int nbf, int nact, int np,
           const T b = a[i][j][e];
           kacc[i][j][e] += (double)b * (double)b;
           if (p < nact && q <= p) {
-            const T wv = b * beta[p * nact + q];
+            const T wv = b * beta[p * ldbeta + q];
             Wp[p * ldw + q] = wv;
             if (tm == tn) {
               Wp[q * ldw + p] = wv;
@@ -594,11 +594,11 @@ hipError_t df_fp_gemm1(hipStream_t s, int nbf, int nact, int np, const T* Ct, in
 }
 template <typename T>
 hipError_t df_fp_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, const T* Ct, int ldk, const T* XT, int ldx,
-                       const T* beta, double* Kpart, bool kset, double* Dchunk, T* W, int ldw) {
+                       const T* beta, int ldbeta, double* Kpart, bool kset, double* Dchunk, T* W, int ldw) {
   if (np <= 0) return hipSuccess;
   const long long t = cdiv(nact, BT);
   hipLaunchKernelGGL(df_b_kernel<T>, xcd_grid(t * (t + 1) / 2 * nsplit), dim3(256), 0, s, nbf, nact, np, nsplit, Ct, ldk, XT,
-                     ldx, beta, Kpart, kset ? 1 : 0, Dchunk, W, ldw);
+                     ldx, beta, ldbeta, Kpart, kset ? 1 : 0, Dchunk, W, ldw);
   return hipGetLastError();
 }
 template <typename T>
@@ -615,8 +615,8 @@ hipError_t df_fp_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, con
 }
 #define DF_FP(T)                                                                                                            \
   template hipError_t df_fp_gemm1<T>(hipStream_t, int, int, int, const T*, int, const void*, int, T*, int);                 \
-  template hipError_t df_fp_gemm2<T>(hipStream_t, int, int, int, int, const T*, int, const T*, int, const T*, double*, bool, \
-                                     double*, T*, int);                                                                     \
+  template hipError_t df_fp_gemm2<T>(hipStream_t, int, int, int, int, const T*, int, const T*, int, const T*, int, double*,  \
+                                     bool, double*, T*, int);                                                               \
   template hipError_t df_fp_gemm3<T>(hipStream_t, int, int, int, int, const T*, int, const T*, int, T*)
 DF_FP(double);
 DF_FP(float);

@@ -21,15 +21,19 @@ inline dim3 grid1(long long n, int per = NT) {
 __global__ void fill_f64_k(double* p, long long n, double v) { GRID_STRIDE(i, n) p[i] = v; }
 __global__ void fill_u16_k(u16* p, long long n, u16 v) { GRID_STRIDE(i, n) p[i] = v; }
 
-// alpha, beta of E_2 = sum_pq alpha_pq J_pq + beta_pq K_pq (Eqs. Eg, Efg, Efg_s).
-__global__ void coeffs_k(int nact, int npairs, int ncwo, int nsingle, int functional, const double* __restrict__ n,
+// alpha, beta of E_2 = sum_pq alpha_pq J_pq + beta_pq K_pq (Eqs. Eg, Efg, Efg_s); beta32: ld32 x ld32, zero past
+// nact.
+__global__ void coeffs_k(int nact, int ld32, int npairs, int ncwo, int nsingle, int functional, const double* __restrict__ n,
                          double* __restrict__ alpha, double* __restrict__ beta, float* __restrict__ beta32) {
-  GRID_STRIDE(i, (long long)nact * nact) {
-    const int p = (int)(i / nact), q = (int)(i % nact);
-    double a, b;
-    pnof_coeff(p, q, n[p], n[q], npairs, ncwo, nsingle, functional, a, b);
-    alpha[i] = a;
-    beta[i] = b;
+  const int w = beta32 ? ld32 : nact;
+  GRID_STRIDE(i, (long long)w * w) {
+    const int p = (int)(i / w), q = (int)(i % w);
+    double a, b = 0.0;
+    if (p < nact && q < nact) {
+      pnof_coeff(p, q, n[p], n[q], npairs, ncwo, nsingle, functional, a, b);
+      alpha[(long long)p * nact + q] = a;
+      beta[(long long)p * nact + q] = b;
+    }
     if (beta32) beta32[i] = (float)b;
   }
 }
@@ -381,7 +385,7 @@ __global__ void add_diag_bf16_k(int nact, int np, int ks, const double* __restri
     const long long P = i / nact;
     const int p = (int)(i % nact);
     const long long o = P * pstride + (long long)p * ldw + p;
-    const float wv = (float)Dc[i] * beta32[(long long)p * nact + p];
+    const float wv = (float)Dc[i] * beta32[(long long)p * ldw + p];
     const double w = (double)wv + sum_slabs(d, ks, slab, i);
     if (Wl) {   // split mode: the fp16 pair of W sW
       u16 h, l;
@@ -908,9 +912,9 @@ hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v) {
   LAUNCH(fill_u16_k, grid1(n), dim3(NT), p, n, v);
 }
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
-                  double* alpha, double* beta, float* beta32) {
-  LAUNCH(coeffs_k, grid1((long long)nact * nact), dim3(NT), nact, npairs, ncwo, nsingle, functional, n, alpha, beta,
-         beta32);
+                  double* alpha, double* beta, float* beta32, int ld32) {
+  const long long w = beta32 ? ld32 : nact;
+  LAUNCH(coeffs_k, grid1(w * w), dim3(NT), nact, ld32, npairs, ncwo, nsingle, functional, n, alpha, beta, beta32);
 }
 template <typename T>
 hipError_t transpose_ca(hipStream_t s, int nbf, int nact, const double* C, T* Ct, int ldk) {
