@@ -501,16 +501,12 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
     DEV_CHECK(ctx, hpp_from_hc(s, nbf, nact, C, b.HC, b.Hpp));
     if (r.Hpp) DEV_CHECK(ctx, hipMemcpyAsync(r.Hpp, b.Hpp, sizeof(double) * nact, hipMemcpyDeviceToDevice, s));
   }
-  if (r.Jq) DEV_CHECK(ctx, fill_f64(s, r.Jq, (long long)r.nq * nbf * nbf, 0.0));
-  if (r.Kq) DEV_CHECK(ctx, fill_f64(s, r.Kq, (long long)r.nq * nbf * nbf, 0.0));
-  if (r.Fq) DEV_CHECK(ctx, fill_f64(s, r.Fq, (long long)r.nq * nbf * nbf, 0.0));
 
   int corr_terms = 0;
   if (!is_df(pl.ints)) {
     const double* ERI = static_cast<const double*>(ints);
     DEV_CHECK(ctx, eri_jk_ao(s, nbf, nact, ERI, C, b.Jr, b.Kr));
-    DEV_CHECK(ctx, eri_jk_no(s, nbf, nact, C, b.Jr, b.Kr, J, K));
-    if (want_y) DEV_CHECK(ctx, eri_y(s, nbf, nact, C, n, b.HC, b.alpha, b.beta, b.Jr, b.Kr, b.Y2e));
+    DEV_CHECK(ctx, eri_no(s, nbf, nact, C, b.alpha, b.beta, b.Jr, b.Kr, J, K, want_y ? b.Y2e : nullptr));
     if (r.Jq) DEV_CHECK(ctx, gather_ao(s, nbf, r.nq, r.q_idx, b.Jr, r.Jq));
     if (r.Kq) DEV_CHECK(ctx, gather_ao(s, nbf, r.nq, r.q_idx, b.Kr, r.Kq));
     if (r.Fq) DEV_CHECK(ctx, eri_fock_ao(s, nbf, nact, r.nq, r.q_idx, n, H, b.alpha, b.beta, b.Jr, b.Kr, r.Fq));
@@ -554,7 +550,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         }
         if (r.Jq || r.Kq || r.Fq)
           DEV_CHECK(ctx, df_ao_accum(s, nbf, nact, np, r.nq, r.q_idx, Bc, bb, Dc, b.alpha, b.beta, nullptr, b.XT32,
-                                     nullptr, nullptr, pl.ldx, (long long)nact * pl.ldx, r.Jq, r.Kq, r.Fq, nullptr, 0));
+                                     nullptr, nullptr, pl.ldx, (long long)nact * pl.ldx, r.Jq, r.Kq, r.Fq, nullptr, 0, p0 == 0));
       }
     } else if (!pl.split) {
       for (int p0 = 0; p0 < pl.naux; p0 += pl.pc) {
@@ -574,7 +570,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         }
         if (r.Jq || r.Kq || r.Fq)
           DEV_CHECK(ctx, df_ao_accum(s, nbf, nact, np, r.nq, r.q_idx, Bc, bb, Dc, b.alpha, b.beta, b.XT, nullptr, nullptr,
-                                     nullptr, pl.ldx, (long long)nact * pl.ldx, r.Jq, r.Kq, r.Fq, nullptr, 0));
+                                     nullptr, pl.ldx, (long long)nact * pl.ldx, r.Jq, r.Kq, r.Fq, nullptr, 0, p0 == 0));
       }
     } else {
       // Chunk pipeline: X of chunk c + 1 runs between b and Y of chunk c (XT is double-buffered,
@@ -685,7 +681,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
                                  : static_cast<const void*>(static_cast<const double*>(ints) + (long long)p0 * bsz);
           DEV_CHECK(ctx, df_ao_accum(s, nbf, nact, np, r.nq, r.q_idx, Bsrc, pl.ints == PNOF_INTS_DF_BF16, Dc, b.alpha,
                                      b.beta, nullptr, nullptr, XT.hi, XT.lo, pl.ldx, (long long)pl.nact32 * pl.ldx, r.Jq,
-                                     r.Kq, r.Fq, b.bnd, c));
+                                     r.Kq, r.Fq, b.bnd, c, c == 0));
         }
       }
       if (want_y && two) DEV_CHECK(ctx, hipStreamWaitEvent(s, ev_r, 0));

@@ -626,22 +626,20 @@ hipError_t count_nonfinite(hipStream_t s, const void* p, long long n, int is_bf1
 // explicit four-index integrals (nbf <= 64)
 hipError_t eri_jk_ao(hipStream_t s, int nbf, int nact, const double* ERI, const double* C,
                      double* Jr, double* Kr);
-hipError_t eri_jk_no(hipStream_t s, int nbf, int nact, const double* C, const double* Jr,
-                     const double* Kr, double* J, double* K);
-hipError_t eri_y(hipStream_t s, int nbf, int nact, const double* C, const double* n,
-                 const double* HC, const double* alpha, const double* beta, const double* Jr,
-                 const double* Kr, double* Y2e);
+// J, K and, unless it is null, Y2e (which alone reads alpha and beta)
+hipError_t eri_no(hipStream_t s, int nbf, int nact, const double* C, const double* alpha, const double* beta,
+                  const double* Jr, const double* Kr, double* J, double* K, double* Y2e);
 hipError_t gather_ao(hipStream_t s, int nbf, int nq, const int32_t* q_idx, const double* src,
                      double* dst);
 hipError_t eri_fock_ao(hipStream_t s, int nbf, int nact, int nq, const int32_t* q_idx,
                        const double* n, const double* H, const double* alpha, const double* beta,
                        const double* Jr, const double* Kr, double* Fq);
-// density-fitted per-orbital AO matrices, accumulated one P-chunk at a time
+// density-fitted per-orbital AO matrices, accumulated one P-chunk at a time (first: stored)
 hipError_t df_ao_accum(hipStream_t s, int nbf, int nact, int np, int nq, const int32_t* q_idx,
                        const void* Bchunk, int b_is_bf16, const double* Dchunk,
                        const double* alpha, const double* beta, const double* XT, const float* XT32, const u16* XT_hi,
                        const u16* XT_lo, int ldx, long long xps, double* Jq, double* Kq, double* Fq,
-                       const uint32_t* bnd, int chunk);
+                       const uint32_t* bnd, int chunk, int first);
 hipError_t fock_ao_h(hipStream_t s, int nbf, int nq, const int32_t* q_idx, const double* n,
                      const double* H, double* Fq);
 

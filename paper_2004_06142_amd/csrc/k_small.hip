@@ -736,78 +736,6 @@ __global__ void nonfinite_k(const void* p, long long n, int is_bf16, int* flag) 
   if (bad) atomicOr(flag, 1);
 }
 
-// ---- explicit four-index integrals (nbf <= 64) ----
-// Jr[r][m][n] = sum_ls (mn|ls) C_lr C_sr ; Kr[r][m][n] = sum_ls (ml|ns) C_lr C_sr (Eq. Gpmn).
-__global__ void eri_jk_ao_k(int nbf, int nact, const double* __restrict__ ERI, const double* __restrict__ C,
-                            double* __restrict__ Jr, double* __restrict__ Kr) {
-  const long long n2 = (long long)nbf * nbf;
-  GRID_STRIDE(i, (long long)nact * n2) {
-    const int r = (int)(i / n2);
-    const int m = (int)((i % n2) / nbf), n = (int)(i % nbf);
-    double sj = 0.0, sk = 0.0;
-    for (int l = 0; l < nbf; ++l) {
-      const double cl = C[(long long)l * nbf + r];
-      double tj = 0.0, tk = 0.0;
-      for (int s = 0; s < nbf; ++s) {
-        const double cs = C[(long long)s * nbf + r];
-        tj += ERI[(((long long)m * nbf + n) * nbf + l) * nbf + s] * cs;
-        tk += ERI[(((long long)m * nbf + l) * nbf + n) * nbf + s] * cs;
-      }
-      sj += cl * tj;
-      sk += cl * tk;
-    }
-    Jr[i] = sj;
-    Kr[i] = sk;
-  }
-}
-
-// J_pq = c_p^T J^q c_p, K_pq = c_p^T K^q c_p (Eq. JKpq).
-__global__ void eri_jk_no_k(int nbf, int nact, const double* __restrict__ C, const double* __restrict__ Jr,
-                            const double* __restrict__ Kr, double* __restrict__ J, double* __restrict__ K) {
-  GRID_STRIDE(i, (long long)nact * nact) {
-    const int p = (int)(i / nact), q = (int)(i % nact);
-    const double* Jq = Jr + (long long)q * nbf * nbf;
-    const double* Kq = Kr + (long long)q * nbf * nbf;
-    double sj = 0.0, sk = 0.0;
-    for (int m = 0; m < nbf; ++m) {
-      double tj = 0.0, tk = 0.0;
-      for (int n = 0; n < nbf; ++n) {
-        const double cn = C[(long long)n * nbf + p];
-        tj += Jq[(long long)m * nbf + n] * cn;
-        tk += Kq[(long long)m * nbf + n] * cn;
-      }
-      const double cm = C[(long long)m * nbf + p];
-      sj += cm * tj;
-      sk += cm * tk;
-    }
-    J[i] = sj;
-    K[i] = sk;
-  }
-}
-
-// Y2e[m][q] = sum_r (alpha_qr J^r + beta_qr K^r) c_q.
-__global__ void eri_y_k(int nbf, int nact, const double* __restrict__ C, const double* __restrict__ alpha,
-                        const double* __restrict__ beta, const double* __restrict__ Jr,
-                        const double* __restrict__ Kr, double* __restrict__ Y2e) {
-  GRID_STRIDE(i, (long long)nbf * nact) {
-    const int m = (int)(i / nact), q = (int)(i % nact);
-    double s = 0.0;
-    for (int r = 0; r < nact; ++r) {
-      const double a = alpha[(long long)q * nact + r], b = beta[(long long)q * nact + r];
-      const double* Jm = Jr + ((long long)r * nbf + m) * nbf;
-      const double* Km = Kr + ((long long)r * nbf + m) * nbf;
-      double tj = 0.0, tk = 0.0;
-      for (int n = 0; n < nbf; ++n) {
-        const double cn = C[(long long)n * nbf + q];
-        tj += Jm[n] * cn;
-        tk += Km[n] * cn;
-      }
-      s += a * tj + b * tk;
-    }
-    Y2e[i] = s;
-  }
-}
-
 __global__ void gather_ao_k(int nbf, int nq, const int32_t* __restrict__ q_idx, const double* __restrict__ src,
                             double* __restrict__ dst) {
   const long long n2 = (long long)nbf * nbf;
@@ -840,58 +768,6 @@ __global__ void fock_ao_h_k(int nbf, int nq, const int32_t* __restrict__ q_idx, 
   GRID_STRIDE(i, (long long)nq * n2) {
     const int k = (int)(i / n2);
     Fq[i] += n[q_idx[k]] * H[i % n2];
-  }
-}
-
-// Per-orbital AO matrices from one P-chunk:  J^q += sum_P D_Pq B_P,  K^q += sum_P x_Pq x_Pq^T,
-// F^q += sum_P [d_Pq B_P + sum_r beta_qr x_Pr x_Pr^T]  with x_Pr[mu] = XT[P][r][mu].
-// XT is float64, one bf16 value (terms 1), or the fp16 pair of X sX (split mode; invX = 1 / sX).
-__device__ inline double xt_val(const double* XT, const float* XT32, const u16* xh, const u16* xl, double invX,
-                                long long o) {
-  if (XT) return XT[o];
-  if (XT32) return (double)XT32[o];
-  if (!xl) return (double)bf16_bits_to_f32(xh[o]);
-  return ((double)f16_bits_to_f32(xh[o]) + (double)f16_bits_to_f32(xl[o])) * invX;
-}
-
-__global__ void df_ao_accum_k(int nbf, int nact, int np, int nq, const int32_t* __restrict__ q_idx,
-                              const void* __restrict__ Bc, int b_bf16, const double* __restrict__ Dc,
-                              const double* __restrict__ alpha, const double* __restrict__ beta,
-                              const double* __restrict__ XT, const float* __restrict__ XT32, const u16* __restrict__ xh,
-                              const u16* __restrict__ xl, int ldx, long long xps, double* __restrict__ Jq,
-                              double* __restrict__ Kq, double* __restrict__ Fq, const uint32_t* __restrict__ bnd,
-                              int chunk) {
-  const long long n2 = (long long)nbf * nbf;
-  const double invX = xl ? (double)chunk_scales(bnd, chunk, false).invX : 1.0;
-  GRID_STRIDE(i, (long long)nq * n2) {
-    const int k = (int)(i / n2);
-    const long long e = i % n2;
-    const int m = (int)(e / nbf), nn = (int)(e % nbf);
-    const int q = q_idx[k];
-    double sj = 0.0, sk = 0.0, sf = 0.0;
-    for (int P = 0; P < np; ++P) {
-      const long long bo = (long long)P * n2 + e;
-      const double b = b_bf16 ? (double)bf16_bits_to_f32(reinterpret_cast<const u16*>(Bc)[bo])
-                              : reinterpret_cast<const double*>(Bc)[bo];
-      const double* Dp = Dc + (long long)P * nact;
-      const long long xo = (long long)P * xps;
-      sj += Dp[q] * b;
-      const double xm = xt_val(XT, XT32, xh, xl, invX, xo + (long long)q * ldx + m);
-      const double xn = xt_val(XT, XT32, xh, xl, invX, xo + (long long)q * ldx + nn);
-      sk += xm * xn;
-      if (Fq) {
-        double d = 0.0, kk = 0.0;
-        for (int r = 0; r < nact; ++r) {
-          d += alpha[(long long)q * nact + r] * Dp[r];
-          kk += beta[(long long)q * nact + r] * xt_val(XT, XT32, xh, xl, invX, xo + (long long)r * ldx + m) *
-                xt_val(XT, XT32, xh, xl, invX, xo + (long long)r * ldx + nn);
-        }
-        sf += d * b + kk;
-      }
-    }
-    if (Jq) Jq[i] += sj;
-    if (Kq) Kq[i] += sk;
-    if (Fq) Fq[i] += sf;
   }
 }
 
@@ -1081,17 +957,6 @@ hipError_t count_nonfinite(hipStream_t s, const void* p, long long n, int is_bf1
   if (n <= 0) return hipSuccess;
   LAUNCH(nonfinite_k, grid1(n), dim3(NT), p, n, is_bf16, flag);
 }
-hipError_t eri_jk_ao(hipStream_t s, int nbf, int nact, const double* ERI, const double* C, double* Jr, double* Kr) {
-  LAUNCH(eri_jk_ao_k, grid1((long long)nact * nbf * nbf), dim3(NT), nbf, nact, ERI, C, Jr, Kr);
-}
-hipError_t eri_jk_no(hipStream_t s, int nbf, int nact, const double* C, const double* Jr, const double* Kr,
-                     double* J, double* K) {
-  LAUNCH(eri_jk_no_k, grid1((long long)nact * nact), dim3(NT), nbf, nact, C, Jr, Kr, J, K);
-}
-hipError_t eri_y(hipStream_t s, int nbf, int nact, const double* C, const double* /*n*/, const double* /*HC*/,
-                 const double* alpha, const double* beta, const double* Jr, const double* Kr, double* Y2e) {
-  LAUNCH(eri_y_k, grid1((long long)nbf * nact), dim3(NT), nbf, nact, C, alpha, beta, Jr, Kr, Y2e);
-}
 hipError_t gather_ao(hipStream_t s, int nbf, int nq, const int32_t* q_idx, const double* src, double* dst) {
   if (nq <= 0) return hipSuccess;
   LAUNCH(gather_ao_k, grid1((long long)nq * nbf * nbf), dim3(NT), nbf, nq, q_idx, src, dst);
@@ -1101,14 +966,6 @@ hipError_t eri_fock_ao(hipStream_t s, int nbf, int nact, int nq, const int32_t* 
                        const double* Kr, double* Fq) {
   if (nq <= 0) return hipSuccess;
   LAUNCH(eri_fock_ao_k, grid1((long long)nq * nbf * nbf), dim3(NT), nbf, nact, nq, q_idx, n, H, alpha, beta, Jr, Kr, Fq);
-}
-hipError_t df_ao_accum(hipStream_t s, int nbf, int nact, int np, int nq, const int32_t* q_idx,
-                       const void* Bchunk, int b_is_bf16, const double* Dchunk, const double* alpha,
-                       const double* beta, const double* XT, const float* XT32, const u16* XT_hi, const u16* XT_lo,
-                       int ldx, long long xps, double* Jq, double* Kq, double* Fq, const uint32_t* bnd, int chunk) {
-  if (nq <= 0 || np <= 0) return hipSuccess;
-  LAUNCH(df_ao_accum_k, grid1((long long)nq * nbf * nbf), dim3(NT), nbf, nact, np, nq, q_idx, Bchunk,
-         b_is_bf16, Dchunk, alpha, beta, XT, XT32, XT_hi, XT_lo, ldx, xps, Jq, Kq, Fq, bnd, chunk);
 }
 hipError_t fock_ao_h(hipStream_t s, int nbf, int nq, const int32_t* q_idx, const double* n, const double* H,
                      double* Fq) {
