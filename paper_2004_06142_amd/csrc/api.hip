@@ -54,6 +54,8 @@ struct pnof_ctx_s {
   struct Slot { void* p; size_t bytes; };
   std::vector<Slot> slots;
   size_t slot_top = 0;
+  double* host_on = nullptr;   // pinned: gamma, E and dE/dgamma of one evaluation of the occupation optimisation
+  size_t host_on_bytes = 0;
   // integrals bound by pnof_bind_integrals: their per-chunk row bounds (split mode) and the key they
   // were computed under
   struct Bound {
@@ -764,25 +766,26 @@ struct OnObjective {
   pnof_ctx ctx;
   int kind, npairs, ncwo, nsingle, nact, nbf, functional, ngam;
   const double *Hpp, *J, *K;
-  double *gam, *n, *alpha, *beta, *partials, *E, *dEdn, *g;
-  std::vector<double> host;
+  double *gam, *n, *alpha, *beta, *partials, *E, *dEdn, *erow;
+  unsigned* counter;
   int evals = 0;
 
+  // gamma is read by the kernel from the context's pinned buffer, or, past the number of variables that pays
+  // (every block reads them over the host link), from a copy; E and the gradient are written there
   pnof_status eval(const std::vector<double>& x, double& f, std::vector<double>& grad) {
     hipStream_t s = ctx->stream;
-    DEV_CHECK(ctx, hipMemcpyAsync(gam, x.data(), sizeof(double) * ngam, hipMemcpyHostToDevice, s));
-    DEV_CHECK(ctx, on_map(s, kind, npairs, ncwo, nsingle, gam, n, nullptr));
-    DEV_CHECK(ctx, coeffs(s, nact, npairs, ncwo, nsingle, functional, n, alpha, beta));
-    DEV_CHECK(ctx, energy(s, nbf, nact, n, Hpp, alpha, beta, J, K, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0,
-                          partials, E));
-    DEV_CHECK(ctx, grad_n(s, nact, npairs, ncwo, nsingle, functional, n, Hpp, J, K, dEdn));
-    DEV_CHECK(ctx, on_map_vjp(s, kind, npairs, ncwo, nsingle, gam, dEdn, g));
-    host.resize(ngam + 1);
-    DEV_CHECK(ctx, hipMemcpyAsync(host.data(), E, sizeof(double), hipMemcpyDeviceToHost, s));
-    DEV_CHECK(ctx, hipMemcpyAsync(host.data() + 1, g, sizeof(double) * ngam, hipMemcpyDeviceToHost, s));
+    double* host = ctx->host_on;
+    std::copy(x.begin(), x.end(), host);
+    const double* src = host;
+    if (ngam > ON_EVAL_HOST) {
+      DEV_CHECK(ctx, hipMemcpyAsync(gam, host, sizeof(double) * ngam, hipMemcpyHostToDevice, s));
+      src = gam;
+    }
+    double* out = host + ngam;
+    DEV_CHECK(ctx, on_eval(s, kind, nact, npairs, ncwo, nsingle, functional, ngam, src, Hpp, J, K, n, erow, dEdn, counter, out));
     DEV_CHECK(ctx, hipStreamSynchronize(s));
-    f = host[0];
-    grad.assign(host.begin() + 1, host.end());
+    f = out[0];
+    grad.assign(out + 1, out + 1 + ngam);
     ++evals;
     if (!std::isfinite(f)) return fail(ctx, PNOF_E_NONFINITE, "occupation optimisation reached a non-finite energy");
     return PNOF_OK;
@@ -811,8 +814,22 @@ pnof_status on_objective_init(pnof_ctx ctx, DevBuf& db, const pnof_problem* prob
   o.partials = db.get<double>(512);
   o.E = db.get<double>(4);
   o.dEdn = db.get<double>(o.nact);
-  o.g = db.get<double>(o.ngam);
+  o.erow = db.get<double>(o.nact);
+  o.counter = db.get<unsigned>(2);
   if (!db.ok) return fail(ctx, PNOF_E_NOMEM, "allocation of the occupation-optimisation buffers failed");
+  const size_t want = sizeof(double) * (2 * (size_t)o.ngam + 1);
+  if (ctx->host_on_bytes < want) {
+    DEV_CHECK(ctx, hipStreamSynchronize(ctx->stream));
+    if (ctx->host_on) hipHostFree(ctx->host_on);
+    ctx->host_on = nullptr;
+    ctx->host_on_bytes = 0;
+    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->host_on), want) != hipSuccess) {
+      hipGetLastError();
+      return fail(ctx, PNOF_E_NOMEM, "allocation of the occupation-optimisation buffers failed");
+    }
+    ctx->host_on_bytes = want;
+  }
+  DEV_CHECK(ctx, fill_f64(ctx->stream, reinterpret_cast<double*>(o.counter), 1, 0.0));
   return PNOF_OK;
 }
 
@@ -1203,6 +1220,7 @@ void pnof_destroy(pnof_ctx ctx) {
     hipEventDestroy(e.b);
   }
   for (auto e : ctx->pool) hipEventDestroy(e);
+  if (ctx->host_on) hipHostFree(ctx->host_on);
   for (auto& sl : ctx->slots)
     if (sl.p) hipFree(sl.p);
   if (ctx->aux) {

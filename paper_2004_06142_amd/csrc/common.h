@@ -62,6 +62,30 @@ __device__ inline double grad_n_term(int p, int q, double np_, double nq, double
 // ---------------------------------------------------------------- ON maps (Section 3.1)
 __device__ inline double sigm(double x) { return 1.0 / (1.0 + exp(-x)); }
 
+// ON map of pair g: n of its strong and weak orbitals.
+__device__ inline void on_map_pair(int kind, int npairs, int ncwo, int nsingle, const double* __restrict__ gamma,
+                                   double* __restrict__ n, int g) {
+  if (kind == 0) {
+    double S = sigm(gamma[g]);
+    for (int k = 0; k < ncwo; ++k) S += sigm(gamma[weak_index(g, k, npairs, ncwo, nsingle)]);
+    for (int a = -1; a < ncwo; ++a) {
+      const int p = a < 0 ? g : weak_index(g, a, npairs, ncwo, nsingle);
+      n[p] = sigm(gamma[p]) / S;
+    }
+  } else {
+    const double cg = cos(gamma[g]), sg = sin(gamma[g]);
+    n[g] = 0.5 * (1.0 + cg * cg);
+    const double h = 0.5 * sg * sg;
+    double prod = 1.0;
+    for (int i = 0; i < ncwo; ++i) {
+      const double gi = i == ncwo - 1 ? 0.0 : gamma[npairs + g * (ncwo - 1) + i];
+      const double si = i == ncwo - 1 ? 1.0 : sin(gi), ci = cos(gi);
+      n[weak_index(g, i, npairs, ncwo, nsingle)] = h * prod * (si * si);
+      prod *= ci * ci;
+    }
+  }
+}
+
 // Adjoint of the ON map for subspace g (pair g < npairs, or a singly occupied orbital): the entries
 // out[r] = sum_p dEdn[p] dn_p/dgamma_r of the gamma variables of that subspace.  kind 0: sigmoid map
 // normalised per pair (one gamma per active orbital); kind 1: trigonometric map (Eqs. soo, woo).
@@ -532,6 +556,13 @@ hipError_t batch_persist(hipStream_t s, const PArgs& a, int ninst_state_words, i
 // ---------------------------------------------------------------- small kernels (k_small.hip)
 hipError_t fill_f64(hipStream_t s, double* p, long long n, double v);
 hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v);
+// E(n(gamma)) and dE/dgamma at fixed H_pp, J, K in one launch: out[0] = E, out[1 ..] = dE/dgamma (ngam of them).
+// out is written by the device and may be pinned host memory; so may gamma, up to ON_EVAL_HOST variables (each
+// block reads them).  nbuf, erow, dEdn: nact doubles each; counter: one word, zero, and zero again afterwards.
+constexpr int ON_EVAL_HOST = 256;
+hipError_t on_eval(hipStream_t s, int kind, int nact, int npairs, int ncwo, int nsingle, int functional, int ngam,
+                   const double* gamma, const double* Hpp, const double* J, const double* K, double* nbuf, double* erow,
+                   double* dEdn, unsigned* counter, double* out);
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                   double* alpha, double* beta, float* beta32 = nullptr, int ld32 = 0);
 template <typename T>

@@ -670,6 +670,65 @@ __global__ void on_map_vjp_k(int kind, int npairs, int ncwo, int nsingle, const 
   if (g < npairs + nsingle) on_map_vjp_subspace(kind, npairs, ncwo, nsingle, gamma, dEdn, out, g);
 }
 
+// E(n(gamma)) and dE/dgamma at fixed H_pp, J, K.  Every block forms all of n itself (in LDS; from nglob where that
+// does not fit); a wave sums one row p of E and dE/dn_p; the block that finishes last adds the rows and takes
+// dE/dn back through the map.  Bound by its own latency and the launch: as a map, coefficients, two stages of the
+// energy, gradient and adjoint launch by launch, with three copies, an evaluation at 24 orbitals took 60 us more.
+__global__ __launch_bounds__(NT) void on_eval_k(int kind, int nact, int npairs, int ncwo, int nsingle, int functional, int ngam,
+                                                const double* __restrict__ gamma, const double* __restrict__ nglob,
+                                                const double* __restrict__ Hpp, const double* __restrict__ J,
+                                                const double* __restrict__ K, double* __restrict__ erow,
+                                                double* __restrict__ dEdn, unsigned* __restrict__ counter,
+                                                double* __restrict__ out) {
+  extern __shared__ double sh[];
+  __shared__ bool s_last;
+  const int t = threadIdx.x, lane = t & 63, p = blockIdx.x * (NT / 64) + (t >> 6);
+  const double *n = nglob, *gam = gamma;
+  if (!nglob) {
+    double* sg = sh + nact;
+    for (int i = t; i < ngam; i += NT) sg[i] = gamma[i];
+    for (int i = t; i < nsingle; i += NT) sh[npairs + i] = 0.5;
+    __syncthreads();
+    for (int g = t; g < npairs; g += NT) on_map_pair(kind, npairs, ncwo, nsingle, sg, sh, g);
+    __syncthreads();
+    n = sh;
+    gam = sg;
+  }
+  if (p < nact) {
+    const double np_ = n[p], php = sqrt(np_ * (1.0 - np_));
+    double e = 0.0, s = 0.0;
+    for (int q = lane; q < nact; q += 64) {
+      const double nq = n[q], j = J[(long long)p * nact + q], k = K[(long long)p * nact + q];
+      double a, b;
+      pnof_coeff(p, q, np_, nq, npairs, ncwo, nsingle, functional, a, b);
+      e += a * j + b * k;
+      if (q != p) s += grad_n_term(p, q, np_, nq, php, j, k, npairs, ncwo, nsingle, functional);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      e += __shfl_down(e, off, 64);
+      s += __shfl_down(s, off, 64);
+    }
+    if (lane == 0) {
+      erow[p] = 2.0 * np_ * Hpp[p] + e;
+      dEdn[p] = 2.0 * Hpp[p] + (is_single(p, npairs, nsingle) ? 0.0 : K[(long long)p * nact + p]) + s;
+      __threadfence();
+    }
+  }
+  __syncthreads();
+  if (t == 0) s_last = atomicAdd(counter, 1u) == gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  double e = 0.0;
+  for (int i = t; i < nact; i += NT) e += erow[i];
+  e = block_sum(e);
+  if (t == 0) {
+    out[0] = e;
+    *counter = 0;
+  }
+  for (int g = t; g < npairs + nsingle; g += NT) on_map_vjp_subspace(kind, npairs, ncwo, nsingle, gam, dEdn, out + 1, g);
+}
+
 // dst = src with a zero diagonal (the error vector of the DIIS extrapolation).
 __global__ void offdiag_k(int nbf, const double* __restrict__ src, double* __restrict__ dst) {
   GRID_STRIDE(i, (long long)nbf * nbf) dst[i] = (i / nbf == i % nbf) ? 0.0 : src[i];
@@ -786,6 +845,19 @@ hipError_t fill_f64(hipStream_t s, double* p, long long n, double v) {
 hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v) {
   if (n <= 0) return hipSuccess;
   LAUNCH(fill_u16_k, grid1(n), dim3(NT), p, n, v);
+}
+hipError_t on_eval(hipStream_t s, int kind, int nact, int npairs, int ncwo, int nsingle, int functional, int ngam,
+                   const double* gamma, const double* Hpp, const double* J, const double* K, double* nbuf, double* erow,
+                   double* dEdn, unsigned* counter, double* out) {
+  const size_t lds = sizeof(double) * (size_t)(nact + ngam);
+  const bool fits = lds <= 60 * 1024;
+  if (!fits) {
+    const hipError_t e = on_map(s, kind, npairs, ncwo, nsingle, gamma, nbuf, nullptr);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(on_eval_k, dim3((unsigned)cdiv(nact, NT / 64)), dim3(NT), fits ? lds : 0, s, kind, nact, npairs, ncwo,
+                     nsingle, functional, ngam, gamma, fits ? nullptr : nbuf, Hpp, J, K, erow, dEdn, counter, out);
+  return hipGetLastError();
 }
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                   double* alpha, double* beta, float* beta32, int ld32) {
