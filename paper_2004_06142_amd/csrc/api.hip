@@ -1152,7 +1152,7 @@ hipError_t batch_enqueue_persistent(pnof_batch b, hipStream_t s) {
   a.f64 = b->d_f64;
   a.sc = b->ps;
   a.sc.stall_ticks = (unsigned long long)(b->stall_us * b->clock_khz * 1e-3) + 1;
-  return batch_persist(s, a, b->ninst * PH_N, b->tile[0], b->tile[2], b->pblocks);
+  return batch_persist(s, a, b->tile[0], b->tile[2], b->pblocks);
 }
 
 pnof_status batch_fail(pnof_batch b, pnof_status st, const std::string& msg) { return fail(b ? b->ctx : nullptr, st, msg); }
@@ -1903,12 +1903,11 @@ pnof_status pnof_batch_plan(pnof_ctx ctx, int32_t ninst, const pnof_problem* pro
     b->d_f64 = a.take<F64Gemm>(4LL * ninst);
     b->d_cnt = a.take<int>((long long)ninst * PH_N);
     b->ps.cnt = b->d_cnt;
-    b->ps.claim = a.take<int>((long long)ninst * PH_N);
-    b->ps.done = a.take<int>((long long)ninst * PH_N);
+    b->ps.claim = a.take<int>((long long)ninst * PH_ROW);
     b->ps.phase = a.take<int>(ninst);
     b->ps.t_end = a.take<unsigned long long>(ninst);
     b->ps.t_start = a.take<unsigned long long>(1);
-    b->ps.prog = a.take<int>(4);
+    b->ps.prog = a.take<int>(PROG_ROW * (1 + PERSIST_MAX_DIES));
     b->d_order = a.take<int>(ninst);
     b->d_xoff = a.take<int>(PERSIST_MAX_DIES + 1);
     b->ps.order = b->d_order;

@@ -508,12 +508,13 @@ hipError_t batch_vjp(hipStream_t s, int ninst, const BInst* tab, const BMax& mx)
 // One launch runs every step of every instance: blocks claim work items of an instance's current
 // phase (all items of the previous phase complete), in instance order.  Phases of one instance:
 enum {
-  PH_PREP = 0,   // scale bounds, alpha/beta, C split (one item)
-  PH_X,          // X tiles, then the float64 tiles of H C_A
-  PH_B,          // b tiles (64-wide), then H_pp (one item)
-  PH_DJ,         // float64 tiles of D alpha, then of J = D^T D
+  PH_BND = 0,    // scale bounds, raised in the instance's row of counters
+  PH_PREP,       // the call-level bound words, alpha/beta, C split
+  PH_X,          // float64 tiles of H C_A, then X tiles
+  PH_B,          // H_pp (one item), then b tiles (64-wide)
+  PH_DA,         // float64 tiles of D alpha
   PH_DIAG,       // W diagonal
-  PH_Y,          // Y tiles
+  PH_Y,          // float64 tiles of J = D^T D, then Y tiles
   PH_RED,        // Y2e and K reductions
   PH_EY,         // BATCH_EPARTS energy partials, then Y = n o (H C_A) + Y2e
   PH_LAM,        // float64 tiles of lambda = C^T Y
@@ -521,18 +522,21 @@ enum {
   PH_VJP,        // dE/dgamma; the instance's completion time
   PH_N
 };
-constexpr int PERSIST_PARTS = 8;   // items of the element-wise phases (W diagonal, reductions, Y, finish)
+constexpr int PERSIST_PARTS = 32;  // items of the element-wise phases (prep, W diagonal, reductions, Y, finish)
 constexpr int PERSIST_XG = 4;      // X tiles per work item (consecutive tiles share their rows of B)
 constexpr int PERSIST_MAX_DIES = 16;   // accelerator complex dies (one L2 each) a device may have
 // Scheduling state (device memory, cleared by batch_persist before each run).
+constexpr int PH_ROW = 32, PH_DONE = 16;   // one 128-byte line per instance: dies do not share them
+constexpr int PH_BND_WORDS = 12;           // in it: maxima of |C| columns' 1-norm, |C|, the rows' sum of |alpha|, |beta|
+constexpr int PROG_ROW = 32;               // and one per group
+static_assert(PH_N <= PH_BND_WORDS && PH_BND_WORDS + 4 <= PH_DONE, "row of an instance's counters");
 struct PSched {
   const int* cnt;                 // [ninst][PH_N] items of each phase
-  int* claim;                     // [ninst][PH_N] items handed out
-  int* done;                      // [ninst][PH_N] items completed
+  int* claim;                     // [ninst][PH_ROW] items handed out of each phase, and from PH_DONE on completed
   int* phase;                     // [ninst] first phase not complete
   unsigned long long* t_end;      // [ninst] device wall clock when the instance completed
   unsigned long long* t_start;    // device wall clock when the run started
-  int* prog;                      // [0] items completed, [1] instances completed, [2] stalled
+  int* prog;                      // [1] instances completed, [2] stalled; [PROG_ROW (1 + x)] changes with group x's items
   const int* order;               // instances grouped by the die that runs them, each group ascending
   const int* xoff;                // [ndie + 1]: group x is order[xoff[x] .. xoff[x + 1])
   int* die_of;                    // [ndie]: the hardware die id that took group x (-1 before)
@@ -551,7 +555,7 @@ struct PArgs {
 // Items of instance i in each phase for X / Y tile widths tx, ty (the b contraction runs 64-wide).
 void persist_counts(const BInst& d, const G1Args& g1, const G2Args& g2, const G3Args& g3, int tx, int ty, int* cnt);
 // Clears the scheduling state, stamps the start and runs the persistent kernel (grid: blocks).
-hipError_t batch_persist(hipStream_t s, const PArgs& a, int ninst_state_words, int tx, int ty, int blocks);
+hipError_t batch_persist(hipStream_t s, const PArgs& a, int tx, int ty, int blocks);
 
 // ---------------------------------------------------------------- small kernels (k_small.hip)
 hipError_t fill_f64(hipStream_t s, double* p, long long n, double v);

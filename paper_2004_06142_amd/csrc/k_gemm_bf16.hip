@@ -951,16 +951,13 @@ union PersistLds {
 };
 
 __device__ __forceinline__ int ld_dev(const int* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ int ld_uni(const int* p) { return __builtin_amdgcn_readfirstlane(ld_dev(p)); }
 
-// The prep item (one block): the call-level scale bounds reduced in LDS (the grouped launches take
-// two launches and a global array for them; the words are the same), then alpha, beta and C's split.
-__device__ inline void persist_prep(const BInst& d) {
-  __shared__ uint32_t m[4];
-  if (threadIdx.x < 4) m[threadIdx.x] = 0u;
-  __syncthreads();
+// The call-level scale bounds (the grouped launches take two launches and a global array for them; the words
+// are the same): a wave per orbital, its maxima raised in the instance's words.
+__host__ __device__ inline int bnd_items(int nact) { return cdiv(nact, 4) < PERSIST_PARTS ? cdiv(nact, 4) : PERSIST_PARTS; }
+__device__ inline void persist_bounds(const BInst& d, int part, int nparts, uint32_t* words) {
   const int lane = threadIdx.x & 63;
-  for (int q = threadIdx.x >> 6; q < d.nact; q += blockDim.x >> 6) {
+  for (int q = 4 * part + (threadIdx.x >> 6); q < d.nact; q += 4 * nparts) {
     double s1 = 0.0, cm = 0.0, sa = 0.0, bm = 0.0;
     for (int mu = lane; mu < d.nbf; mu += 64) {
       const double c = fabs(d.C[(long long)mu * d.nbf + q]);
@@ -980,21 +977,23 @@ __device__ inline void persist_prep(const BInst& d) {
       bm = fmax(bm, __shfl_down(bm, off, 64));
     }
     if (lane == 0) {
-      atomicMax(&m[0], __float_as_uint((float)s1));
-      atomicMax(&m[1], __float_as_uint((float)cm));
-      atomicMax(&m[2], __float_as_uint((float)sa));
-      atomicMax(&m[3], __float_as_uint((float)bm));
+      atomicMax(&words[0], __float_as_uint((float)s1));
+      atomicMax(&words[1], __float_as_uint((float)cm));
+      atomicMax(&words[2], __float_as_uint((float)sa));
+      atomicMax(&words[3], __float_as_uint((float)bm));
     }
   }
-  __syncthreads();
-  const uint32_t w0 = m[1], w1 = m[0], w2 = __float_as_uint(__uint_as_float(m[3]) + __uint_as_float(m[2]));
-  if (threadIdx.x == 0) {
+}
+__device__ inline void persist_prep(const BInst& d, int part, int nparts, const uint32_t* words) {
+  const int* m = reinterpret_cast<const int*>(words);
+  const uint32_t w0 = (uint32_t)ld_dev(m + 1), w1 = (uint32_t)ld_dev(m);
+  if (part == 0 && threadIdx.x == 0) {
     d.bnd[0] = w0;
     d.bnd[1] = w1;
-    d.bnd[2] = w2;
+    d.bnd[2] = __float_as_uint(__int_as_float(ld_dev(m + 3)) + __int_as_float(ld_dev(m + 2)));
   }
   // sC exactly as chunk_scales forms it from bnd[0]
-  bdev::prep(d, 0, 1, ldexpf(1.0f, 13 - bound_exp(__uint_as_float(w0) * 1.01f)));
+  bdev::prep(d, part, nparts, ldexpf(1.0f, 13 - bound_exp(__uint_as_float(w0) * 1.01f)));
 }
 
 template <int TX, int TY>
@@ -1003,42 +1002,43 @@ __device__ __forceinline__ void persist_item(const PArgs& a, int i, int ph, int 
   f64t::F64Smem& fs = *reinterpret_cast<f64t::F64Smem*>(lds);
   const int n = a.ninst;
   switch (ph) {
+    case PH_BND:
+      persist_bounds(d, idx, bnd_items(d.nact), reinterpret_cast<uint32_t*>(a.sc.claim + i * PH_ROW + PH_BND_WORDS));
+      break;
     case PH_PREP:
-      persist_prep(d);
+      persist_prep(d, idx, PERSIST_PARTS, reinterpret_cast<const uint32_t*>(a.sc.claim + i * PH_ROW + PH_BND_WORDS));
       break;
     case PH_X: {
       const G1Args g = a.g1[i];
-      const int nt = g1_items(g, TX, 128, true), nx = cdiv(nt, PERSIST_XG);
-      if (idx < nx) {
-        const int t0 = idx * PERSIST_XG, t1 = t0 + PERSIST_XG < nt ? t0 + PERSIST_XG : nt;
+      const int nh = f64t::grouped_tiles(d.nbf, d.nact), nt = g1_items(g, TX, 128, true);
+      if (idx < nh) {
+        f64t::grouped_tile<false, true>(a.f64[i], idx, fs);                                // H C_A
+      } else {
+        const int t0 = (idx - nh) * PERSIST_XG, t1 = t0 + PERSIST_XG < nt ? t0 + PERSIST_XG : nt;
         for (int t = t0; t < t1; ++t) {
           if (t > t0) __syncthreads();   // the ring of the tile before is free again
           gemm1_body<2, false, TX, 128, 2, 2, 2, true, true, true, PBUDGET>(t, g, lds);
         }
-      } else {
-        f64t::grouped_tile<false, true>(a.f64[i], idx - nx, fs);                           // H C_A
       }
       break;
     }
     case PH_B: {
       const G2Args g = a.g2[i];
-      const int nb = g2_items(g, 64);
-      if (idx < nb) gemm2_body<3, 64, true, true, PBUDGET>(idx, g, lds);
-      else bdev::hpp(d, 0, 1);
+      if (idx == 0) bdev::hpp(d, 0, 1);
+      else gemm2_body<3, 64, true, true, PBUDGET>(idx - 1, g, lds);
       break;
     }
-    case PH_DJ: {
-      const int nd = f64t::grouped_tiles(d.naux, d.nact);
-      if (idx < nd) f64t::grouped_tile<false, true>(a.f64[n + i], idx, fs);                // D alpha
-      else f64t::grouped_tile<true, true>(a.f64[2 * n + i], idx - nd, fs);                // J = D^T D
+    case PH_DA:
+      f64t::grouped_tile<false, true>(a.f64[n + i], idx, fs);                              // D alpha
       break;
-    }
     case PH_DIAG:
       bdev::add_diag(d, idx, PERSIST_PARTS);
       break;
     case PH_Y: {
       const G3Args g = a.g3[i];
-      gemm3_body<3, 128, TY, 2, 2, 2, 64, true, PBUDGET>(idx, g, lds);
+      const int nj = f64t::grouped_tiles(d.nact, d.nact);
+      if (idx < nj) f64t::grouped_tile<true, true>(a.f64[2 * n + i], idx, fs);             // J = D^T D
+      else gemm3_body<3, 128, TY, 2, 2, 2, 64, true, PBUDGET>(idx - nj, g, lds);
       break;
     }
     case PH_RED:
@@ -1068,6 +1068,12 @@ __device__ __forceinline__ void persist_item(const PArgs& a, int i, int ph, int 
 // barrier that ends the item) and sees the other blocks' stores after invalidating its compute
 // unit's L1 (after claiming); no L2 write-back or invalidation is needed.  The scheduling words are
 // touched with device-scope atomics and coherent loads only.
+// A block that ends an item claims the next one of the same phase in the round trip that publishes it, and looks
+// further only when the phase has none left; each instance's counters and each die's progress word lie in a line of
+// their own.  (With one progress word for the device, raised by every item, and the state read in seven round trips
+// an item, halving the items' size cost 24 problems of 40 to 180 functions 1.33 -> 1.81 ms; now it costs nothing.
+// With this, the bounds and prep in parts, J beside Y instead of before it, and 32 parts of the element-wise phases
+// instead of 8: 1.33 -> 0.96 ms.)  What bounds the run is the die that holds the largest problem.
 // The scheduling runs in wavefront 0 as a whole; the other wavefronts wait at the barrier.  Lane l
 // of wavefront 0 looks at the die's instance base + l, a ballot picks the first one with unclaimed
 // items of its open phase, and lane 0 alone performs the atomics (every value the lanes branch on
@@ -1094,24 +1100,47 @@ __global__ __launch_bounds__(256, 2) void batch_persist_k(PArgs a) {
   const int lo = __builtin_amdgcn_readfirstlane(sc.xoff[grp]), hi = __builtin_amdgcn_readfirstlane(sc.xoff[grp + 1]);
   const int lane = threadIdx.x;   // in wavefront 0
   const bool lead = threadIdx.x == 0;
-  int last = -1;   // state word (instance * PH_N + phase) of the item this block completed last
+  int last = -1;   // instance * PH_N + phase of the item this block completed last
   for (;;) {
     if (threadIdx.x < 64) {
-      if (last >= 0 && lead) {   // publish it
-        const int dn = atomicAdd(sc.done + last, 1) + 1;
-        if (dn == sc.cnt[last]) {
-          const int i = last / PH_N, ph = last % PH_N;
-          if (ph + 1 == PH_N) __hip_atomic_store(sc.t_end + i, wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          atomicExch(sc.phase + i, ph + 1);
-          if (ph + 1 == PH_N) atomicAdd(sc.prog + 1, 1);
-        }
-        atomicAdd(sc.prog, 1);
-      }
       int inst = -1, ph = 0, idx = 0;
-      int seen = ld_uni(sc.prog);
+      if (last >= 0) {   // publish it, and claim the next item of its phase in the same round trip
+        const int i = last / PH_N, p = last % PH_N, cc = sc.cnt[last];
+        int* row = sc.claim + i * PH_ROW + p;
+        int dn = 0, c = 0;
+        if (lead) {
+          c = atomicAdd(row, 1);
+          dn = atomicAdd(row + PH_DONE, 1) + 1;
+          __hip_atomic_store(sc.prog + PROG_ROW * (1 + grp), (int)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        c = __builtin_amdgcn_readlane(c, 0);
+        dn = __builtin_amdgcn_readlane(dn, 0);
+        if (dn == cc && lead) {
+          if (p + 1 == PH_N) __hip_atomic_store(sc.t_end + i, wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          atomicExch(sc.phase + i, p + 1);
+          if (p + 1 == PH_N) atomicAdd(sc.prog + 1, 1);
+        }
+        if (c < cc) {
+          inst = i;
+          ph = p;
+          idx = c;
+        }
+      }
+      // lanes: the groups' progress words, then instances completed and the stall flag
+      const int* word = sc.prog + (lane < sc.ndie ? PROG_ROW * (1 + lane) : lane == sc.ndie ? 1 : 2);
+      int seen = 0;
       unsigned long long t_seen = wall_clock64();
-      for (;;) {
-        if (ld_uni(sc.prog + 1) >= a.ninst || ld_uni(sc.prog + 2) != 0) break;
+      for (bool first = true; inst < 0; first = false) {
+        const int now = lane < sc.ndie + 2 ? ld_dev(word) : 0;
+        if (__builtin_amdgcn_readlane(now, sc.ndie) >= a.ninst || __builtin_amdgcn_readlane(now, sc.ndie + 1) != 0) break;
+        const unsigned long long t = wall_clock64();
+        if (first || __ballot(lane < sc.ndie && now != seen) != 0) {
+          seen = now;
+          t_seen = t;
+        } else if (t - t_seen > sc.stall_ticks) {
+          if (lead) atomicExch(sc.prog + 2, 1);
+          break;
+        }
         for (int base = lo; base < hi && inst < 0; base += 64) {
           int i = -1, p = PH_N, k = 0, cnt = 0;
           bool open = false;
@@ -1119,8 +1148,8 @@ __global__ __launch_bounds__(256, 2) void batch_persist_k(PArgs a) {
             i = sc.order[base + lane];
             p = ld_dev(sc.phase + i);
             if (p < PH_N) {
-              k = i * PH_N + p;
-              cnt = sc.cnt[k];
+              k = i * PH_ROW + p;
+              cnt = sc.cnt[i * PH_N + p];
               open = ld_dev(sc.claim + k) < cnt;
             }
           }
@@ -1140,17 +1169,7 @@ __global__ __launch_bounds__(256, 2) void batch_persist_k(PArgs a) {
             m &= m - 1;   // that phase ran out meanwhile: the next instance
           }
         }
-        if (inst >= 0) break;
-        __builtin_amdgcn_s_sleep(8);
-        const int now = ld_uni(sc.prog);
-        const unsigned long long t = wall_clock64();
-        if (now != seen) {
-          seen = now;
-          t_seen = t;
-        } else if (t - t_seen > sc.stall_ticks) {
-          if (lead) atomicExch(sc.prog + 2, 1);
-          break;
-        }
+        if (inst < 0) __builtin_amdgcn_s_sleep(8);
       }
       if (inst >= 0) l1_invalidate();
       if (lead) {
@@ -1171,14 +1190,11 @@ __global__ __launch_bounds__(256, 2) void batch_persist_k(PArgs a) {
 }
 
 // Clears the scheduling state of a run and stamps its start.
-__global__ void persist_reset_k(PSched sc, int nwords_inst, int ninst) {
-  for (int i = threadIdx.x; i < nwords_inst; i += blockDim.x) {
-    sc.claim[i] = 0;
-    sc.done[i] = 0;
-  }
+__global__ void persist_reset_k(PSched sc, int ninst) {
+  for (int i = threadIdx.x; i < ninst * PH_ROW; i += blockDim.x) sc.claim[i] = 0;
   for (int i = threadIdx.x; i < ninst; i += blockDim.x) sc.phase[i] = 0;
   for (int i = threadIdx.x; i < sc.ndie; i += blockDim.x) sc.die_of[i] = -1;
-  if (threadIdx.x < 3) sc.prog[threadIdx.x] = 0;
+  for (int i = threadIdx.x; i < PROG_ROW * (1 + sc.ndie); i += blockDim.x) sc.prog[i] = 0;
   if (threadIdx.x == 0) *sc.t_start = wall_clock64();
 }
 
@@ -1323,12 +1339,13 @@ hipError_t df_bf16_gemm3_grouped(hipStream_t s, int ninst, int total, int terms,
 namespace pnof {
 
 void persist_counts(const BInst& d, const G1Args& g1, const G2Args& g2, const G3Args& g3, int tx, int ty, int* cnt) {
-  cnt[PH_PREP] = 1;
+  cnt[PH_BND] = bnd_items(d.nact);
+  cnt[PH_PREP] = PERSIST_PARTS;
   cnt[PH_X] = cdiv(g1_items(g1, tx, 128, true), PERSIST_XG) + f64t::grouped_tiles(d.nbf, d.nact);
   cnt[PH_B] = g2_items(g2, 64) + 1;
-  cnt[PH_DJ] = f64t::grouped_tiles(d.naux, d.nact) + f64t::grouped_tiles(d.nact, d.nact);
+  cnt[PH_DA] = f64t::grouped_tiles(d.naux, d.nact);
   cnt[PH_DIAG] = PERSIST_PARTS;
-  cnt[PH_Y] = g3_items(g3, 128, ty);
+  cnt[PH_Y] = f64t::grouped_tiles(d.nact, d.nact) + g3_items(g3, 128, ty);
   cnt[PH_RED] = PERSIST_PARTS;
   cnt[PH_EY] = BATCH_EPARTS + PERSIST_PARTS;
   cnt[PH_LAM] = f64t::grouped_tiles(d.nbf, d.nact);
@@ -1336,8 +1353,8 @@ void persist_counts(const BInst& d, const G1Args& g1, const G2Args& g2, const G3
   cnt[PH_VJP] = 1;
 }
 
-hipError_t batch_persist(hipStream_t s, const PArgs& a, int ninst_state_words, int tx, int ty, int blocks) {
-  hipLaunchKernelGGL(persist_reset_k, dim3(1), dim3(256), 0, s, a.sc, ninst_state_words, a.ninst);
+hipError_t batch_persist(hipStream_t s, const PArgs& a, int tx, int ty, int blocks) {
+  hipLaunchKernelGGL(persist_reset_k, dim3(1), dim3(256), 0, s, a.sc, a.ninst);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (tx == 64 && ty == 64) hipLaunchKernelGGL((batch_persist_k<64, 64>), dim3(blocks), dim3(256), 0, s, a);
