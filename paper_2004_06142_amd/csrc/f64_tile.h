@@ -140,7 +140,7 @@ struct Smem {
 template <bool AM>
 __device__ __forceinline__ void load_a(const double* __restrict__ A, long long sam, long long sak, int M, int K, int m0,
                                        int k0, double (&r)[BK / 4]) {
-  const int t = threadIdx.x;
+  const int t = threadIdx.x & 255;
 #pragma unroll
   for (int i = 0; i < BK / 4; ++i) {
     const int m = AM ? (t & 63) : (t >> 2), k = AM ? ((t >> 6) + 4 * i) : ((t & 3) * (BK / 4) + i);
@@ -150,7 +150,7 @@ __device__ __forceinline__ void load_a(const double* __restrict__ A, long long s
 }
 template <bool AM>
 __device__ __forceinline__ void store_a(double (*S)[BM + PAD], const double (&r)[BK / 4]) {
-  const int t = threadIdx.x;
+  const int t = threadIdx.x & 255;
 #pragma unroll
   for (int i = 0; i < BK / 4; ++i) {
     const int m = AM ? (t & 63) : (t >> 2), k = AM ? ((t >> 6) + 4 * i) : ((t & 3) * (BK / 4) + i);
@@ -161,7 +161,7 @@ __device__ __forceinline__ void store_a(double (*S)[BM + PAD], const double (&r)
 template <bool BN>
 __device__ __forceinline__ void load_b(const double* __restrict__ B, long long sbk, long long sbn, int N, int K, int n0,
                                        int k0, double (&r)[BK / 8]) {
-  const int t = threadIdx.x;
+  const int t = threadIdx.x & 255;
 #pragma unroll
   for (int i = 0; i < BK / 8; ++i) {
     const int n = BN ? (t & 31) : (t >> 3), k = BN ? ((t >> 5) + 8 * i) : ((t & 7) * (BK / 8) + i);
@@ -171,7 +171,7 @@ __device__ __forceinline__ void load_b(const double* __restrict__ B, long long s
 }
 template <bool BN>
 __device__ __forceinline__ void store_b(double (*S)[BNT + PAD], const double (&r)[BK / 8]) {
-  const int t = threadIdx.x;
+  const int t = threadIdx.x & 255;
 #pragma unroll
   for (int i = 0; i < BK / 8; ++i) {
     const int n = BN ? (t & 31) : (t >> 3), k = BN ? ((t >> 5) + 8 * i) : ((t & 7) * (BK / 8) + i);
@@ -182,19 +182,19 @@ __device__ __forceinline__ void store_b(double (*S)[BNT + PAD], const double (&r
 
 
 // acc[mi] (rows wide_row(mi, j), column wide_col() of the tile at (m0, n0)) = A(m0.., :) B(:, n0..)
-// over k in [0, K).  Every thread of the block must call it (it synchronises the block).
+// over the ns slabs of BK from kb on, of k below K, by 256 threads.  Every thread of the block must call it, with
+// the same ns (it synchronises the block).
 template <bool AM, bool BN>
 __device__ __forceinline__ void wide_tile(Smem& sm, const double* __restrict__ A, long long sam, long long sak,
                                           const double* __restrict__ B, long long sbk, long long sbn, int M, int N,
-                                          int K, int m0, int n0, f64x4 (&acc)[2]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                          int K, int kb, int ns, int m0, int n0, f64x4 (&acc)[2]) {
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 16;
   acc[0] = f64x4{0.0, 0.0, 0.0, 0.0};
   acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
   // slab j travels in register set j % 2, loaded two slabs ahead of its multiplication; LDS stage
   // j % 2 holds it while it is multiplied
   double ra[2][BK / 4], rb[2][BK / 8];
-  const int ns = (K + BK - 1) / BK;
   auto mul = [&](int st) {
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 4) {
@@ -205,13 +205,13 @@ __device__ __forceinline__ void wide_tile(Smem& sm, const double* __restrict__ A
       acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1], 0, 0, 0);
     }
   };
-  load_a<AM>(A, sam, sak, M, K, m0, 0, ra[0]);
-  load_b<BN>(B, sbk, sbn, N, K, n0, 0, rb[0]);
+  load_a<AM>(A, sam, sak, M, K, m0, kb, ra[0]);
+  load_b<BN>(B, sbk, sbn, N, K, n0, kb, rb[0]);
   store_a<AM>(sm.a[0], ra[0]);
   store_b<BN>(sm.b[0], rb[0]);
   if (1 < ns) {
-    load_a<AM>(A, sam, sak, M, K, m0, BK, ra[1]);
-    load_b<BN>(B, sbk, sbn, N, K, n0, BK, rb[1]);
+    load_a<AM>(A, sam, sak, M, K, m0, kb + BK, ra[1]);
+    load_b<BN>(B, sbk, sbn, N, K, n0, kb + BK, rb[1]);
   }
   __syncthreads();
   for (int s0 = 0; s0 < ns; s0 += 2) {
@@ -220,8 +220,8 @@ __device__ __forceinline__ void wide_tile(Smem& sm, const double* __restrict__ A
       const int ss = s0 + d;
       if (ss < ns) {
         if (ss + 2 < ns) {
-          load_a<AM>(A, sam, sak, M, K, m0, (ss + 2) * BK, ra[d]);
-          load_b<BN>(B, sbk, sbn, N, K, n0, (ss + 2) * BK, rb[d]);
+          load_a<AM>(A, sam, sak, M, K, m0, kb + (ss + 2) * BK, ra[d]);
+          load_b<BN>(B, sbk, sbn, N, K, n0, kb + (ss + 2) * BK, rb[d]);
         }
         mul(d);
         if (ss + 1 < ns) {
@@ -235,11 +235,11 @@ __device__ __forceinline__ void wide_tile(Smem& sm, const double* __restrict__ A
 }
 // Row / column (relative to the tile origin) of component j of acc[mi] of wide_tile.
 __device__ __forceinline__ int wide_row(int mi, int j) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
   return (wave >> 1) * 32 + mi * 16 + (lane >> 4) + 4 * j;
 }
 __device__ __forceinline__ int wide_col() {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
   return (wave & 1) * 16 + (lane & 15);
 }
 }  // namespace wide

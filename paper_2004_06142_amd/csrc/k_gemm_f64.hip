@@ -6,6 +6,8 @@
 // supplies A[m = l%16][k = l/16] and B[k = l/16][n = l%16]; the result element (l/16 + 4*j, l%16)
 // sits in component j of lane l).  Register prefetch of the next k-slab overlaps global loads
 // with the matrix-core work.
+#include <type_traits>
+
 #include "common.h"
 #include "f64_tile.h"
 
@@ -51,18 +53,36 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(int M, int N, int K, doub
 // stages, loaded into registers two slabs ahead of their multiplication; one barrier per slab
 // separates the writes of one stage from the reads of the other (1200^3: 94-101 us, against
 // 103-113 us with slabs of 32 one ahead and 117-130 us with 64 x 64 tiles).
-template <bool AM, bool BN>
-__global__ __launch_bounds__(256, 3) void gemm_f64_wide_kernel(int M, int N, int K, double alpha,
+// KG groups of 4 waves share a tile's slabs between them (their sums are added in LDS, in order): a slab takes a
+// block about 0.8 us, most of it waiting for its loads, so a product whose tiles do not fill the chip is bound by
+// the length of k (gemm_f64_groups; with 4 groups J of 300 orbitals over 2000 rows 109 -> 65 us, lambda of 500
+// functions 33 -> 20; at 24 functions, whose five products have two slabs, one group each).
+template <bool AM, bool BN, int KG>
+__global__ __launch_bounds__(256 * KG, KG == 1 ? 3 : 1) void gemm_f64_wide_kernel(int M, int N, int K, double alpha,
                                                               const double* __restrict__ A, long long sam,
                                                               long long sak, const double* __restrict__ B,
                                                               long long sbk, long long sbn, double beta,
                                                               double* __restrict__ C, long long scm, long long scn) {
   using namespace wide;
-  __shared__ Smem sm;
-  const int tn_n = (N + BNT - 1) / BNT;
+  __shared__ Smem sm[KG];
+  const int tn_n = (N + BNT - 1) / BNT, grp = KG == 1 ? 0 : threadIdx.x >> 8;
   const int m0 = (blockIdx.x / tn_n) * BM, n0 = (blockIdx.x % tn_n) * BNT;
+  const int ns = ((K + BK - 1) / BK + KG - 1) / KG;
   f64x4 acc[2];
-  wide_tile<AM, BN>(sm, A, sam, sak, B, sbk, sbn, M, N, K, m0, n0, acc);
+  wide_tile<AM, BN>(sm[grp], A, sam, sak, B, sbk, sbn, M, N, K, grp * ns * BK, ns, m0, n0, acc);
+  if constexpr (KG > 1) {
+    static_assert(sizeof(Smem) >= 256 * 8 * sizeof(double), "a group's sums in its stages");
+    double* own = reinterpret_cast<double*>(&sm[grp]) + (threadIdx.x & 255);
+    if (grp > 0)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) own[256 * e] = acc[e >> 2][e & 3];
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int g = 1; g < KG; ++g)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e >> 2][e & 3] += reinterpret_cast<const double*>(&sm[g])[threadIdx.x + 256 * e];
+  }
 #pragma unroll
   for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -73,6 +93,13 @@ __global__ __launch_bounds__(256, 3) void gemm_f64_wide_kernel(int M, int N, int
         *c = alpha * acc[mi][j] + (beta != 0.0 ? beta * *c : 0.0);
       }
     }
+}
+// Groups for a product: 4 while its tiles make one block per compute unit, 2 while they make two, if each group
+// has at least two slabs.
+int gemm_f64_groups(int M, int N, int K) {
+  const long long tiles = (long long)cdiv(M, wide::BM) * cdiv(N, wide::BNT);
+  const int ns = cdiv(K, wide::BK);
+  return tiles <= 256 && ns >= 8 ? 4 : tiles <= 512 && ns >= 4 ? 2 : 1;
 }
 
 // One product of a grouped launch per blockIdx.y; blocks beyond that product's tiles exit.
@@ -509,14 +536,21 @@ hipError_t gemm_f64(hipStream_t s, int M, int N, int K, int batch, double alpha,
   const bool am = (sam == 1), bn = (sbn == 1);
   if (batch == 1) {
     const dim3 g1((unsigned)(cdiv(M, wide::BM) * cdiv(N, wide::BNT)));
-    if (am && bn)
-      hipLaunchKernelGGL((gemm_f64_wide_kernel<true, true>), g1, dim3(256), 0, s, M, N, K, alpha, A, sam, sak, B, sbk, sbn, beta, C, scm, scn);
-    else if (am)
-      hipLaunchKernelGGL((gemm_f64_wide_kernel<true, false>), g1, dim3(256), 0, s, M, N, K, alpha, A, sam, sak, B, sbk, sbn, beta, C, scm, scn);
-    else if (bn)
-      hipLaunchKernelGGL((gemm_f64_wide_kernel<false, true>), g1, dim3(256), 0, s, M, N, K, alpha, A, sam, sak, B, sbk, sbn, beta, C, scm, scn);
-    else
-      hipLaunchKernelGGL((gemm_f64_wide_kernel<false, false>), g1, dim3(256), 0, s, M, N, K, alpha, A, sam, sak, B, sbk, sbn, beta, C, scm, scn);
+    auto go = [&](auto kern, int kg) {
+      hipLaunchKernelGGL(kern, g1, dim3(256 * kg), 0, s, M, N, K, alpha, A, sam, sak, B, sbk, sbn, beta, C, scm, scn);
+    };
+    auto pick = [&](auto am_, auto bn_) {
+      constexpr bool AM = decltype(am_)::value, BN = decltype(bn_)::value;
+      switch (gemm_f64_groups(M, N, K)) {
+        case 4: go(gemm_f64_wide_kernel<AM, BN, 4>, 4); break;
+        case 2: go(gemm_f64_wide_kernel<AM, BN, 2>, 2); break;
+        default: go(gemm_f64_wide_kernel<AM, BN, 1>, 1); break;
+      }
+    };
+    if (am && bn) pick(std::true_type{}, std::true_type{});
+    else if (am) pick(std::true_type{}, std::false_type{});
+    else if (bn) pick(std::false_type{}, std::true_type{});
+    else pick(std::false_type{}, std::false_type{});
     return hipGetLastError();
   }
   dim3 grid(cdiv(M, TM) * cdiv(N, TN), batch);

@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256, 3) void dc_gemm_k(DcWs w, int t, int tm_n, int
   const double* A = w.Qc + (long long)(o + c0) * n + o + r0;   // A(r, c) at c * n + r
   const double* B = w.Mm + (long long)o * n + o + c0;          // B(c, i) at i * n + c
   f64x4 acc[2];
-  wide_tile<true, false>(sm, A, 1, n, B, 1, n, rows, P.k, K, m0, n0, acc);
+  wide_tile<true, false>(sm, A, 1, n, B, 1, n, rows, P.k, K, 0, (K + BK - 1) / BK, m0, n0, acc);
   double* Zout = w.zbuf[t & 1];
   const int i = n0 + wide_col();
   if (i >= P.k) return;
