@@ -694,19 +694,12 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
     if (r.Fq) DEV_CHECK(ctx, fock_ao_h(s, nbf, r.nq, r.q_idx, n, H, r.Fq));
   }
 
-  if (want_e) {
-    double* E = r.E ? r.E : b.E;
-    DEV_CHECK(ctx, energy(s, nbf, nact, n, b.Hpp, b.alpha, b.beta, J, K, b.Y2e, C, b.cth, b.ctl, b.Ct32, pl.ldk,
-                          corr_terms, b.partials, E));
-  }
-  if (want_y) DEV_CHECK(ctx, assemble_y(s, nbf, nact, n, b.HC, b.Y2e, Y));
-  if (r.lam) {
-    RB_CHECK(dprod(ctx, nbf, nact, nbf, C, 1, nbf, Y, nact, 1, r.lam, nbf, 1));
-    DEV_CHECK(ctx, zero_cols(s, nbf, nact, r.lam));
-    if (r.asym) DEV_CHECK(ctx, max_asym(s, nbf, r.lam, b.partials + 256, r.asym));
-  }
-  if (r.dEdC) DEV_CHECK(ctx, grad_c(s, nbf, nact, Y, r.dEdC));
-  if (r.dEdn) DEV_CHECK(ctx, grad_n(s, nact, pl.npairs, pl.ncwo, pl.nsingle, pl.functional, n, b.Hpp, J, K, r.dEdn));
+  double* const part = want_e ? b.partials : nullptr;
+  DEV_CHECK(ctx, step_tail(s, nbf, nact, pl.npairs, pl.ncwo, pl.nsingle, pl.functional, n, b.Hpp, b.alpha, b.beta, J, K, b.HC,
+                           b.Y2e, C, b.cth, b.ctl, b.Ct32, pl.ldk, corr_terms, part, want_y ? Y : nullptr, r.dEdC, r.dEdn,
+                           r.lam, r.asym));
+  if (r.lam) RB_CHECK(dprod(ctx, nbf, nact, nbf, C, 1, nbf, Y, nact, 1, r.lam, nbf, 1));
+  DEV_CHECK(ctx, step_end(s, nbf, nact, corr_terms, part, r.E ? r.E : b.E, r.lam, r.lam ? r.asym : nullptr));
   return PNOF_OK;
 }
 

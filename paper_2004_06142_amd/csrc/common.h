@@ -623,13 +623,15 @@ hipError_t energy(hipStream_t s, int nbf, int nact, const double* n, const doubl
                   const double* alpha, const double* beta, const double* J, const double* K,
                   const double* Y2e, const double* C, const u16* Ct_hi, const u16* Ct_lo, const float* Ct32, int ldk,
                   int corr_terms, double* partials, double* E);
-hipError_t assemble_y(hipStream_t s, int nbf, int nact, const double* n, const double* HC,
-                      const double* Y2e, double* Y);
-hipError_t grad_c(hipStream_t s, int nbf, int nact, const double* Y, double* dEdC);
-hipError_t zero_cols(hipStream_t s, int nbf, int col0, double* M);
-hipError_t max_asym(hipStream_t s, int nbf, const double* lam, double* partials, double* out);
-hipError_t grad_n(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
-                  const double* Hpp, const double* J, const double* K, double* dEdn);
+// Everything of the step but lambda's product, before it (step_tail: the partial sums of E unless partials is null,
+// dE/dn, Y, dE/dC, the columns of lambda past nact, each unless null) and after it (step_end: E, max |lambda - lambda^T|).
+hipError_t step_tail(hipStream_t s, int nbf, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
+                     const double* Hpp, const double* alpha, const double* beta, const double* J, const double* K,
+                     const double* HC, const double* Y2e, const double* C, const u16* cth, const u16* ctl, const float* ct32,
+                     int ldk, int corr_terms, double* partials, double* Y, double* dEdC, double* dEdn, double* lam,
+                     double* asym);
+hipError_t step_end(hipStream_t s, int nbf, int nact, int corr_terms, const double* partials, double* E, const double* lam,
+                    double* asym);
 hipError_t on_map(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, const double* gamma, double* n,
                   double* jac);
 hipError_t on_map_vjp(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, const double* gamma,

@@ -433,35 +433,41 @@ __device__ inline double block_sum(double v) {
   return s;
 }
 
-__global__ void energy_stage1_k(int nbf, int nact, const double* __restrict__ n, const double* __restrict__ Hpp,
-                                const double* __restrict__ alpha, const double* __restrict__ beta,
-                                const double* __restrict__ J, const double* __restrict__ K,
-                                const double* __restrict__ Y2e, const double* __restrict__ C,
-                                const u16* __restrict__ cth, const u16* __restrict__ ctl,
-                                const float* __restrict__ ct32, int ldk, int corr_terms,
-                                double* __restrict__ partials) {
+struct EnergyArgs {
+  int nbf, nact;
+  const double *n, *Hpp, *alpha, *beta, *J, *K, *Y2e, *C;
+  const u16 *cth, *ctl;
+  const float* ct32;
+  int ldk, corr_terms;
+};
+// Block `part` of `parts`: its range of the terms of E.
+__device__ inline double energy_part(const EnergyArgs& a, int part, int parts) {
+  const int nact = a.nact;
   const long long n2 = (long long)nact * nact;
-  const long long ncorr = corr_terms > 0 ? (long long)nbf * nact : 0;
+  const long long ncorr = a.corr_terms > 0 ? (long long)a.nbf * nact : 0;
   const long long total = nact + n2 + ncorr;
-  const long long per = (total + gridDim.x - 1) / gridDim.x;
-  const long long b0 = blockIdx.x * per, b1 = min(total, b0 + per);
+  const long long per = (total + parts - 1) / parts;
+  const long long b0 = part * per, b1 = min(total, b0 + per);
   double s = 0.0;
   for (long long i = b0 + threadIdx.x; i < b1; i += blockDim.x) {
-    if (i < nact) s += 2.0 * n[i] * Hpp[i];
-    else if (i < nact + n2) { const long long k = i - nact; s += alpha[k] * J[k] + beta[k] * K[k]; }
+    if (i < nact) s += 2.0 * a.n[i] * a.Hpp[i];
+    else if (i < nact + n2) { const long long k = i - nact; s += a.alpha[k] * a.J[k] + a.beta[k] * a.K[k]; }
     else {
       const long long k = i - nact - n2;
       const int mu = (int)(k / nact), p = (int)(k % nact);
       double ct;
-      if (ct32) ct = (double)ct32[(long long)p * ldk + mu];
+      if (a.ct32) ct = (double)a.ct32[(long long)p * a.ldk + mu];
       else {
-        ct = (double)bf16_bits_to_f32(cth[(long long)p * ldk + mu]);
-        if (corr_terms > 1) ct += (double)bf16_bits_to_f32(ctl[(long long)p * ldk + mu]);
+        ct = (double)bf16_bits_to_f32(a.cth[(long long)p * a.ldk + mu]);
+        if (a.corr_terms > 1) ct += (double)bf16_bits_to_f32(a.ctl[(long long)p * a.ldk + mu]);
       }
-      s += 4.0 * Y2e[k] * (C[(long long)mu * nbf + p] - ct);
+      s += 4.0 * a.Y2e[k] * (a.C[(long long)mu * a.nbf + p] - ct);
     }
   }
-  s = block_sum(s);
+  return block_sum(s);
+}
+__global__ void energy_stage1_k(EnergyArgs a, double* __restrict__ partials) {
+  const double s = energy_part(a, blockIdx.x, gridDim.x);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
@@ -531,30 +537,6 @@ __global__ void sum2_partials_k(int nparts, const double* __restrict__ partials,
   }
 }
 
-__global__ void assemble_y_k(int nbf, int nact, const double* __restrict__ n, const double* __restrict__ HC,
-                             const double* __restrict__ Y2e, double* __restrict__ Y) {
-  GRID_STRIDE(i, (long long)nbf * nact) {
-    const int q = (int)(i % nact);
-    Y[i] = n[q] * HC[i] + Y2e[i];
-  }
-}
-
-__global__ void grad_c_k(int nbf, int nact, const double* __restrict__ Y, double* __restrict__ G) {
-  GRID_STRIDE(i, (long long)nbf * nbf) {
-    const int mu = (int)(i / nbf), q = (int)(i % nbf);
-    G[i] = q < nact ? 4.0 * Y[(long long)mu * nact + q] : 0.0;
-  }
-}
-
-__global__ void zero_cols_k(int nbf, int col0, double* __restrict__ M) {
-  const long long w = nbf - col0;
-  GRID_STRIDE(i, (long long)nbf * w) {
-    const long long r = i / w;
-    const int c = col0 + (int)(i % w);
-    M[r * nbf + c] = 0.0;
-  }
-}
-
 __device__ inline double block_max(double v) {
   __shared__ double red[NT / 64];
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
@@ -568,28 +550,11 @@ __device__ inline double block_max(double v) {
   return s;
 }
 
-__global__ void asym_stage1_k(int nbf, const double* __restrict__ lam, double* __restrict__ partials) {
-  double m = 0.0;
-  GRID_STRIDE(i, (long long)nbf * nbf) {
-    const long long p = i / nbf, q = i % nbf;
-    m = fmax(m, fabs(lam[i] - lam[q * nbf + p]));
-  }
-  m = block_max(m);
-  if (threadIdx.x == 0) partials[blockIdx.x] = m;
-}
-
-__global__ void max_partials_k(int nparts, const double* __restrict__ partials, double* __restrict__ out) {
-  double m = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += blockDim.x) m = fmax(m, partials[i]);
-  m = block_max(m);
-  if (threadIdx.x == 0) *out = m;
-}
-
-// dE/dn_p (derivative of Eqs. Eg, Efg at fixed J, K, H_pp): one wavefront per orbital.
-__global__ void grad_n_k(int nact, int npairs, int ncwo, int nsingle, int functional, const double* __restrict__ n,
-                         const double* __restrict__ Hpp, const double* __restrict__ J,
-                         const double* __restrict__ K, double* __restrict__ g) {
-  const int p = blockIdx.x, lane = threadIdx.x;
+// dE/dn_p (derivative of Eqs. Eg, Efg at fixed J, K, H_pp), by one wavefront.
+__device__ inline void grad_n_row(int p, int nact, int npairs, int ncwo, int nsingle, int functional, const double* __restrict__ n,
+                                  const double* __restrict__ Hpp, const double* __restrict__ J, const double* __restrict__ K,
+                                  double* __restrict__ g) {
+  const int lane = threadIdx.x & 63;
   const double np_ = n[p];
   const double php = sqrt(np_ * (1.0 - np_));
   double s = 0.0;
@@ -603,6 +568,64 @@ __global__ void grad_n_k(int nact, int npairs, int ncwo, int nsingle, int functi
   if (lane == 0) g[p] = 2.0 * Hpp[p] + (is_single(p, npairs, nsingle) ? 0.0 : K[(long long)p * nact + p]) + s;
 }
 
+// What the step forms between the contractions and lambda = C^T Y, in one launch: blocks [0, ne) the partial sums of
+// E; the next ng dE/dn, a wave per orbital; the rest element by element Y = n o (H C_A) + Y2e, dE/dC = 4 Y, the zero
+// columns of dE/dC and lambda past nact, and the zero from which step_end_k raises the asymmetry.
+struct TailArgs {
+  EnergyArgs e;
+  int ne, ng, npairs, ncwo, nsingle, functional;
+  const double* HC;
+  double *partials, *dEdn, *Y, *dEdC, *lam, *asym;
+};
+__global__ void step_tail_k(TailArgs a) {
+  const int nbf = a.e.nbf, nact = a.e.nact;
+  int b = blockIdx.x;
+  if (b < a.ne) {
+    const double s = energy_part(a.e, b, a.ne);
+    if (threadIdx.x == 0) a.partials[b] = s;
+    return;
+  }
+  b -= a.ne;
+  if (b < a.ng) {
+    const int p = b * (NT / 64) + (threadIdx.x >> 6);
+    if (p < nact) grad_n_row(p, nact, a.npairs, a.ncwo, a.nsingle, a.functional, a.e.n, a.e.Hpp, a.e.J, a.e.K, a.dEdn);
+    return;
+  }
+  b -= a.ng;
+  if (b == 0 && threadIdx.x == 0 && a.asym) *a.asym = 0.0;
+  const int w = a.dEdC || a.lam ? nbf : nact;
+  const long long stride = (long long)(gridDim.x - a.ne - a.ng) * NT;
+  for (long long i = (long long)b * NT + threadIdx.x; i < (long long)nbf * w; i += stride) {
+    const long long mu = i / w;
+    const int q = (int)(i - mu * w);
+    double y = 0.0;
+    if (q < nact) {
+      const long long o = mu * nact + q;
+      y = a.e.n[q] * a.HC[o] + a.e.Y2e[o];
+      a.Y[o] = y;
+    } else if (a.lam) a.lam[i] = 0.0;
+    if (a.dEdC) a.dEdC[i] = 4.0 * y;
+  }
+}
+// After lambda: block 0 adds the partial sums of E, the others raise max |lambda - lambda^T| (not negative, so its bits
+// order as its value).
+__global__ void step_end_k(int ne, const double* __restrict__ partials, double* __restrict__ E, int nbf,
+                           const double* __restrict__ lam, double* __restrict__ asym) {
+  if (blockIdx.x == 0) {
+    double s = 0.0;
+    for (int i = threadIdx.x; i < ne; i += blockDim.x) s += partials[i];
+    s = block_sum(s);
+    if (threadIdx.x == 0 && ne > 0) *E = s;
+    return;
+  }
+  double m = 0.0;
+  for (long long i = (long long)(blockIdx.x - 1) * NT + threadIdx.x; i < (long long)nbf * nbf; i += (long long)(gridDim.x - 1) * NT) {
+    const long long p = i / nbf, q = i % nbf;
+    m = fmax(m, fabs(lam[i] - lam[q * nbf + p]));
+  }
+  m = block_max(m);
+  if (threadIdx.x == 0) atomicMax(reinterpret_cast<unsigned long long*>(asym), (unsigned long long)__double_as_longlong(m));
+}
 
 // ON maps, one thread per pair (Section 3.1); singly occupied orbitals get n = 1/2 (their rows of
 // the Jacobian stay zero).
@@ -983,33 +1006,35 @@ hipError_t energy(hipStream_t s, int nbf, int nact, const double* n, const doubl
                   const double* Y2e, const double* C, const u16* cth, const u16* ctl, const float* ct32, int ldk,
                   int corr_terms, double* partials, double* E) {
   const int nb = 256;
-  hipLaunchKernelGGL(energy_stage1_k, dim3(nb), dim3(NT), 0, s, nbf, nact, n, Hpp, alpha, beta, J, K, Y2e,
-                     C, cth, ctl, ct32, ldk, corr_terms, partials);
+  const EnergyArgs a{nbf, nact, n, Hpp, alpha, beta, J, K, Y2e, C, cth, ctl, ct32, ldk, corr_terms};
+  hipLaunchKernelGGL(energy_stage1_k, dim3(nb), dim3(NT), 0, s, a, partials);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   LAUNCH(sum_partials_k, dim3(1), dim3(NT), nb, partials, E);
 }
-hipError_t assemble_y(hipStream_t s, int nbf, int nact, const double* n, const double* HC, const double* Y2e,
-                      double* Y) {
-  LAUNCH(assemble_y_k, grid1((long long)nbf * nact), dim3(NT), nbf, nact, n, HC, Y2e, Y);
+static int tail_parts(int nbf, int nact, int corr_terms) {   // 256 blocks at most, of 1024 terms at least
+  const long long total = nact + (long long)nact * nact + (corr_terms > 0 ? (long long)nbf * nact : 0);
+  return (int)std::min(256LL, (total + 1023) / 1024);
 }
-hipError_t grad_c(hipStream_t s, int nbf, int nact, const double* Y, double* G) {
-  LAUNCH(grad_c_k, grid1((long long)nbf * nbf), dim3(NT), nbf, nact, Y, G);
+hipError_t step_tail(hipStream_t s, int nbf, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
+                     const double* Hpp, const double* alpha, const double* beta, const double* J, const double* K,
+                     const double* HC, const double* Y2e, const double* C, const u16* cth, const u16* ctl, const float* ct32,
+                     int ldk, int corr_terms, double* partials, double* Y, double* dEdC, double* dEdn, double* lam,
+                     double* asym) {
+  TailArgs a{{nbf, nact, n, Hpp, alpha, beta, J, K, Y2e, C, cth, ctl, ct32, ldk, corr_terms}, 0, 0, npairs, ncwo, nsingle,
+             functional, HC, partials, dEdn, Y, dEdC, lam, asym};
+  a.ne = partials ? tail_parts(nbf, nact, corr_terms) : 0;
+  a.ng = dEdn ? cdiv(nact, NT / 64) : 0;
+  const unsigned nel = Y ? grid1((long long)nbf * (dEdC || lam ? nbf : nact)).x : 0;
+  if (a.ne + a.ng + nel == 0) return hipSuccess;
+  LAUNCH(step_tail_k, dim3(a.ne + a.ng + nel), dim3(NT), a);
 }
-hipError_t zero_cols(hipStream_t s, int nbf, int col0, double* M) {
-  if (col0 >= nbf) return hipSuccess;
-  LAUNCH(zero_cols_k, grid1((long long)nbf * (nbf - col0)), dim3(NT), nbf, col0, M);
-}
-hipError_t max_asym(hipStream_t s, int nbf, const double* lam, double* partials, double* out) {
-  const int nb = 256;
-  hipLaunchKernelGGL(asym_stage1_k, dim3(nb), dim3(NT), 0, s, nbf, lam, partials);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  LAUNCH(max_partials_k, dim3(1), dim3(NT), nb, partials, out);
-}
-hipError_t grad_n(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
-                  const double* Hpp, const double* J, const double* K, double* dEdn) {
-  LAUNCH(grad_n_k, dim3(nact), dim3(64), nact, npairs, ncwo, nsingle, functional, n, Hpp, J, K, dEdn);
+hipError_t step_end(hipStream_t s, int nbf, int nact, int corr_terms, const double* partials, double* E, const double* lam,
+                    double* asym) {
+  const int ne = partials ? tail_parts(nbf, nact, corr_terms) : 0;
+  const unsigned na = asym ? (unsigned)std::min(256LL, ((long long)nbf * nbf + NT - 1) / NT) : 0;
+  if (ne == 0 && na == 0) return hipSuccess;
+  LAUNCH(step_end_k, dim3(1 + na), dim3(NT), ne, partials, E, nbf, lam, asym);
 }
 hipError_t on_map(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, const double* gamma, double* n,
                   double* jac) {
