@@ -126,25 +126,21 @@ __device__ inline void on_map_vjp_subspace(int kind, int npairs, int ncwo, int n
       if (!last) { const double ci = cos(gamma[base + i]); prod *= ci * ci; }
     }
     out[g] = acc_g;
+    double before = h;                              // h prod_{k < j} c_k^2
     for (int j = 0; j < ncwo - 1; ++j) {
       const double cj = cos(gamma[base + j]), sj = sin(gamma[base + j]);
-      double sum = 0.0;
-      for (int i = j; i < ncwo; ++i) {
+      double other = before;                        // h prod_{k < i, k != j} c_k^2
+      double sum = other * 2.0 * sj * cj * dEdn[weak_index(g, j, npairs, ncwo, nsingle)];   // d(s_j^2)
+      for (int i = j + 1; i < ncwo; ++i) {          // d(c_j^2) f_i
         const bool last = (i == ncwo - 1);
-        double other = h;                           // prod over k < i, k != j of c_k^2
-        for (int k = 0; k < i; ++k) {
-          if (k == j) continue;
-          const double ck = cos(gamma[base + k]);
-          other *= ck * ck;
+        const double si = last ? 0.0 : sin(gamma[base + i]);
+        sum += other * (-2.0 * cj * sj) * (last ? 1.0 : si * si) * dEdn[weak_index(g, i, npairs, ncwo, nsingle)];
+        if (!last) {
+          const double ci = cos(gamma[base + i]);
+          other *= ci * ci;
         }
-        double d;
-        if (i == j) d = other * 2.0 * sj * cj;      // d(s_j^2)
-        else {
-          const double si = last ? 0.0 : sin(gamma[base + i]);
-          d = other * (-2.0 * cj * sj) * (last ? 1.0 : si * si);  // d(c_j^2) * f_i
-        }
-        sum += d * dEdn[weak_index(g, i, npairs, ncwo, nsingle)];
       }
+      before *= cj * cj;
       out[base + j] = sum;
     }
   }
