@@ -759,7 +759,7 @@ struct OnObjective {
   pnof_ctx ctx;
   int kind, npairs, ncwo, nsingle, nact, nbf, functional, ngam;
   const double *Hpp, *J, *K;
-  double *gam, *n, *alpha, *beta, *partials, *E, *dEdn, *erow;
+  double *gam, *n, *alpha, *beta, *partials, *E, *dEdn;
   unsigned* counter;
   int evals = 0;
 
@@ -775,7 +775,7 @@ struct OnObjective {
       src = gam;
     }
     double* out = host + ngam;
-    DEV_CHECK(ctx, on_eval(s, kind, nact, npairs, ncwo, nsingle, functional, ngam, src, Hpp, J, K, n, erow, dEdn, counter, out));
+    DEV_CHECK(ctx, on_eval(s, kind, nact, npairs, ncwo, nsingle, functional, ngam, src, Hpp, J, K, n, partials, dEdn, counter, out));
     DEV_CHECK(ctx, hipStreamSynchronize(s));
     f = out[0];
     grad.assign(out + 1, out + 1 + ngam);
@@ -807,7 +807,6 @@ pnof_status on_objective_init(pnof_ctx ctx, DevBuf& db, const pnof_problem* prob
   o.partials = db.get<double>(512);
   o.E = db.get<double>(4);
   o.dEdn = db.get<double>(o.nact);
-  o.erow = db.get<double>(o.nact);
   o.counter = db.get<unsigned>(2);
   if (!db.ok) return fail(ctx, PNOF_E_NOMEM, "allocation of the occupation-optimisation buffers failed");
   const size_t want = sizeof(double) * (2 * (size_t)o.ngam + 1);

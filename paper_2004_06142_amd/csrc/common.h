@@ -558,10 +558,10 @@ hipError_t fill_f64(hipStream_t s, double* p, long long n, double v);
 hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v);
 // E(n(gamma)) and dE/dgamma at fixed H_pp, J, K in one launch: out[0] = E, out[1 ..] = dE/dgamma (ngam of them).
 // out is written by the device and may be pinned host memory; so may gamma, up to ON_EVAL_HOST variables (each
-// block reads them).  nbuf, erow, dEdn: nact doubles each; counter: one word, zero, and zero again afterwards.
+// block reads them).  nbuf, dEdn: nact doubles each; epart: 256; counter: one word, zero, and zero again afterwards.
 constexpr int ON_EVAL_HOST = 256;
 hipError_t on_eval(hipStream_t s, int kind, int nact, int npairs, int ncwo, int nsingle, int functional, int ngam,
-                   const double* gamma, const double* Hpp, const double* J, const double* K, double* nbuf, double* erow,
+                   const double* gamma, const double* Hpp, const double* J, const double* K, double* nbuf, double* epart,
                    double* dEdn, unsigned* counter, double* out);
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                   double* alpha, double* beta, float* beta32 = nullptr, int ld32 = 0);

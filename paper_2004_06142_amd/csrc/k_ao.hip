@@ -65,13 +65,14 @@ __global__ __launch_bounds__(NT) void eri_jk_ao_k(int nbf, int nact, const doubl
 
 // Blocks q < nact: J_pq = c_p^T J^q c_p, K_pq = c_p^T K^q c_p (Eq. JKpq).  Blocks nact + m: row m of
 // Y2e[m][q] = sum_r (alpha_qr J^r + beta_qr K^r) c_q.  Matrices in LDS; the threads of one p (or q) share the
-// rows (or r) between them.  As one thread per element 24 functions took 77 + 27 us; here 4.4.
+// rows (or r) between them, and one adds their products in order (an optimisation of the occupations amplifies
+// a change in the last bits of J and K).  As one thread per element 24 functions took 77 + 27 us; here 4.4.
 template <int MX>
 __global__ __launch_bounds__(NT) void eri_no_k(int nbf, int nact, const double* __restrict__ C, const double* __restrict__ alpha,
                                                const double* __restrict__ beta, const double* __restrict__ Jr,
                                                const double* __restrict__ Kr, double* __restrict__ J, double* __restrict__ K,
                                                double* __restrict__ Y2e) {
-  __shared__ double js[MX * MX], ks[MX * MX], cs[MX * MX], red[2][NT];
+  __shared__ double js[MX * MX], ks[MX * MX], cs[MX * MX], tj_[MX * MX], tk_[MX * MX];
   const int t = threadIdx.x;
   const bool no = (int)blockIdx.x < nact;
   const int id = no ? blockIdx.x : blockIdx.x - nact, rows = no ? nbf : nact;   // js: rows of nbf
@@ -83,7 +84,6 @@ __global__ __launch_bounds__(NT) void eri_no_k(int nbf, int nact, const double* 
   for (int i = t; i < nbf * nact; i += NT) cs[i] = C[(long long)(i / nact) * nbf + i % nact];
   __syncthreads();
   const int parts = NT / nact, p = t % nact, part = t / nact;
-  double sj = 0.0, sk = 0.0;
   if (part < parts)
     for (int m = part; m < rows; m += parts) {
       double tj = 0.0, tk = 0.0;
@@ -91,20 +91,20 @@ __global__ __launch_bounds__(NT) void eri_no_k(int nbf, int nact, const double* 
         tj += js[m * nbf + n] * cs[n * nact + p];
         tk += ks[m * nbf + n] * cs[n * nact + p];
       }
-      if (no) {
-        sj += cs[m * nact + p] * tj;
-        sk += cs[m * nact + p] * tk;
-      } else {
-        sj += alpha[(long long)p * nact + m] * tj + beta[(long long)p * nact + m] * tk;
-      }
+      tj_[m * nact + p] = tj;
+      tk_[m * nact + p] = tk;
     }
-  red[0][t] = sj;
-  red[1][t] = sk;
   __syncthreads();
   if (t >= nact) return;
-  for (int u = 1; u < parts; ++u) {
-    sj += red[0][t + u * nact];
-    sk += red[1][t + u * nact];
+  double sj = 0.0, sk = 0.0;
+  for (int m = 0; m < rows; ++m) {
+    const double tj = tj_[m * nact + t], tk = tk_[m * nact + t];
+    if (no) {
+      sj += cs[m * nact + t] * tj;
+      sk += cs[m * nact + t] * tk;
+    } else {
+      sj += alpha[(long long)t * nact + m] * tj + beta[(long long)t * nact + m] * tk;
+    }
   }
   if (no) {
     J[(long long)t * nact + id] = sj;

@@ -718,18 +718,21 @@ __global__ void on_map_vjp_k(int kind, int npairs, int ncwo, int nsingle, const 
 }
 
 // E(n(gamma)) and dE/dgamma at fixed H_pp, J, K.  Every block forms all of n itself (in LDS; from nglob where that
-// does not fit); a wave sums one row p of E and dE/dn_p; the block that finishes last adds the rows and takes
-// dE/dn back through the map.  Bound by its own latency and the launch: as a map, coefficients, two stages of the
+// does not fit); a wave sums dE/dn of a row p, and the terms of E are summed in energy_part's ON_EVAL_PARTS ranges, by a
+// wave each where a range has at most 64 terms, otherwise by a block; the block that finishes last adds the ranges and
+// takes dE/dn back through the map.  (Every sum runs in the order of the separate kernels: the optimisation amplifies a
+// change in the last bits.)  Bound by its own latency and the launch: as a map, coefficients, two stages of the
 // energy, gradient and adjoint launch by launch, with three copies, an evaluation at 24 orbitals took 60 us more.
+constexpr int ON_EVAL_PARTS = 256;
 __global__ __launch_bounds__(NT) void on_eval_k(int kind, int nact, int npairs, int ncwo, int nsingle, int functional, int ngam,
                                                 const double* __restrict__ gamma, const double* __restrict__ nglob,
                                                 const double* __restrict__ Hpp, const double* __restrict__ J,
-                                                const double* __restrict__ K, double* __restrict__ erow,
+                                                const double* __restrict__ K, double* __restrict__ epart,
                                                 double* __restrict__ dEdn, unsigned* __restrict__ counter,
                                                 double* __restrict__ out) {
   extern __shared__ double sh[];
   __shared__ bool s_last;
-  const int t = threadIdx.x, lane = t & 63, p = blockIdx.x * (NT / 64) + (t >> 6);
+  const int t = threadIdx.x, lane = t & 63, wave = blockIdx.x * (NT / 64) + (t >> 6);
   const double *n = nglob, *gam = gamma;
   if (!nglob) {
     double* sg = sh + nact;
@@ -741,33 +744,39 @@ __global__ __launch_bounds__(NT) void on_eval_k(int kind, int nact, int npairs, 
     n = sh;
     gam = sg;
   }
-  if (p < nact) {
-    const double np_ = n[p], php = sqrt(np_ * (1.0 - np_));
-    double e = 0.0, s = 0.0;
-    for (int q = lane; q < nact; q += 64) {
-      const double nq = n[q], j = J[(long long)p * nact + q], k = K[(long long)p * nact + q];
-      double a, b;
-      pnof_coeff(p, q, np_, nq, npairs, ncwo, nsingle, functional, a, b);
-      e += a * j + b * k;
-      if (q != p) s += grad_n_term(p, q, np_, nq, php, j, k, npairs, ncwo, nsingle, functional);
+  if (wave < nact) grad_n_row(wave, nact, npairs, ncwo, nsingle, functional, n, Hpp, J, K, dEdn);
+  const long long total = nact + (long long)nact * nact, per = (total + ON_EVAL_PARTS - 1) / ON_EVAL_PARTS;
+  auto term = [&](long long i) {
+    if (i < nact) return 2.0 * n[i] * Hpp[i];
+    const long long k = i - nact;
+    const int p = (int)(k / nact), q = (int)(k % nact);
+    double a, b;
+    pnof_coeff(p, q, n[p], n[q], npairs, ncwo, nsingle, functional, a, b);
+    return a * J[k] + b * K[k];
+  };
+  if (per <= 64) {
+    for (int part = wave; part < ON_EVAL_PARTS; part += gridDim.x * (NT / 64)) {
+      const long long i = part * per + lane;
+      double s = lane < per && i < total ? term(i) : 0.0;
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+      if (lane == 0) epart[part] = s;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      e += __shfl_down(e, off, 64);
-      s += __shfl_down(s, off, 64);
-    }
-    if (lane == 0) {
-      erow[p] = 2.0 * np_ * Hpp[p] + e;
-      dEdn[p] = 2.0 * Hpp[p] + (is_single(p, npairs, nsingle) ? 0.0 : K[(long long)p * nact + p]) + s;
-      __threadfence();
+  } else {
+    for (int part = blockIdx.x; part < ON_EVAL_PARTS; part += gridDim.x) {
+      double s = 0.0;
+      for (long long i = part * per + t; i < min(total, (part + 1) * per); i += NT) s += term(i);
+      s = block_sum(s);
+      if (t == 0) epart[part] = s;
     }
   }
+  if (lane == 0) __threadfence();
   __syncthreads();
   if (t == 0) s_last = atomicAdd(counter, 1u) == gridDim.x - 1;
   __syncthreads();
   if (!s_last) return;
   __threadfence();
   double e = 0.0;
-  for (int i = t; i < nact; i += NT) e += erow[i];
+  for (int i = t; i < ON_EVAL_PARTS; i += NT) e += epart[i];
   e = block_sum(e);
   if (t == 0) {
     out[0] = e;
@@ -894,7 +903,7 @@ hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v) {
   LAUNCH(fill_u16_k, grid1(n), dim3(NT), p, n, v);
 }
 hipError_t on_eval(hipStream_t s, int kind, int nact, int npairs, int ncwo, int nsingle, int functional, int ngam,
-                   const double* gamma, const double* Hpp, const double* J, const double* K, double* nbuf, double* erow,
+                   const double* gamma, const double* Hpp, const double* J, const double* K, double* nbuf, double* epart,
                    double* dEdn, unsigned* counter, double* out) {
   const size_t lds = sizeof(double) * (size_t)(nact + ngam);
   const bool fits = lds <= 60 * 1024;
@@ -902,8 +911,10 @@ hipError_t on_eval(hipStream_t s, int kind, int nact, int npairs, int ncwo, int 
     const hipError_t e = on_map(s, kind, npairs, ncwo, nsingle, gamma, nbuf, nullptr);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(on_eval_k, dim3((unsigned)cdiv(nact, NT / 64)), dim3(NT), fits ? lds : 0, s, kind, nact, npairs, ncwo,
-                     nsingle, functional, ngam, gamma, fits ? nullptr : nbuf, Hpp, J, K, erow, dEdn, counter, out);
+  // a wave per row of dE/dn, and per range of E
+  const int nb = std::max((int)cdiv(nact, NT / 64), ON_EVAL_PARTS / (NT / 64));
+  hipLaunchKernelGGL(on_eval_k, dim3((unsigned)nb), dim3(NT), fits ? lds : 0, s, kind, nact, npairs, ncwo,
+                     nsingle, functional, ngam, gamma, fits ? nullptr : nbuf, Hpp, J, K, epart, dEdn, counter, out);
   return hipGetLastError();
 }
 hipError_t coeffs(hipStream_t s, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
