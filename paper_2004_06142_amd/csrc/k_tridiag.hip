@@ -53,7 +53,6 @@ namespace {
 constexpr int DC_LEAF = 16;                 // rows of a leaf at most (one wavefront)
 constexpr int DC_LP = DC_LEAF + 1;          // leaf LDS row pitch
 constexpr int DMAX = TRIDIAG_MAX_N;
-constexpr int SQ = DMAX / 64;               // entries per lane of a wavefront over one parent
 constexpr double UEPS = 1.1102230246251565e-16;   // unit roundoff 2^-53
 
 struct DcPar {      // one parent of the current level, written by the deflation kernel
@@ -86,23 +85,36 @@ __device__ __forceinline__ int parent_of(int n, int t, int p) {
   return j;
 }
 
-// Butterfly sums over the 64 lanes: every lane ends with the same bits (each step adds the same
-// two values in either order).
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+// Butterfly reductions over the 64 lanes: every lane ends with the same bits (each step joins the same two values in
+// either order).  Partners within 16 lanes by DPP (l ^ 1, l ^ 2, then the mirrored eight and sixteen), across them by
+// the row swaps: a step costs a few cycles where a shuffle through the LDS crossbar waits about a hundred, and a root
+// of the secular equation takes five sums per iteration.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true));
+}
+template <typename OP>
+__device__ __forceinline__ double wreduce(double v, OP op) {
+  v = op(v, dpp<0xB1>(v));    // l ^ 1
+  v = op(v, dpp<0x4E>(v));    // l ^ 2
+  v = op(v, dpp<0x141>(v));   // 7 - l of each eight
+  v = op(v, dpp<0x140>(v));   // 15 - l of each sixteen
+  {
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    v = op(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+  }
+  {
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    v = op(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+  }
   return v;
 }
-__device__ __forceinline__ double wprod(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v *= __shfl_xor(v, m, 64);
-  return v;
-}
-__device__ __forceinline__ double wmax(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmax(v, __shfl_xor(v, m, 64));
-  return v;
-}
+__device__ __forceinline__ double wsum(double v) { return wreduce(v, [](double a, double b) { return a + b; }); }
+__device__ __forceinline__ double wprod(double v) { return wreduce(v, [](double a, double b) { return a * b; }); }
+__device__ __forceinline__ double wmax(double v) { return wreduce(v, [](double a, double b) { return fmax(a, b); }); }
 
 // Scale by the largest entry, and take each cut's coupling out of the two diagonal entries beside it.
 __global__ __launch_bounds__(1024) void dc_prep_k(DcWs w, const double* __restrict__ d, const double* __restrict__ e) {
@@ -249,12 +261,13 @@ __global__ __launch_bounds__(64) void dc_leaf_k(DcWs w) {
 // Exclusive prefix over the 256 threads of a block of each thread's count v; total in `total`.
 __device__ __forceinline__ int block_scan(int v, int* sh, int& total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
-  }
+  int x = v;   // inclusive over the wavefront: within rows of 16, then the rows' last sums
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
   if (lane == 63) sh[wv] = x;
   __syncthreads();
   int base = 0, tot = 0;
@@ -291,7 +304,7 @@ __global__ __launch_bounds__(256) void dc_deflate_k(DcWs w, int t) {
   const double b = w.es[o + m1 - 1];
   const double rho = 2.0 * fabs(b), sg = b < 0.0 ? -1.0 : 1.0;
   // by place in the merged ascending list
-  __shared__ double sd[DMAX], sz[DMAX];
+  __shared__ double sd[DMAX], sz[DMAX], sch[DMAX];   // sch: the children's values
   __shared__ short ssrc[DMAX];   // local source column
   __shared__ short sl[DMAX];     // survivors of the z test, in order
   __shared__ short sx[DMAX];     // flagged pairs, then the final survivors
@@ -302,18 +315,20 @@ __global__ __launch_bounds__(256) void dc_deflate_k(DcWs w, int t) {
   __shared__ int sh[4];
   __shared__ int snc;
   double md = 0.0, mz = 0.0;
+  for (int j = tid; j < m; j += 256) sch[j] = din[j];
+  __syncthreads();
   for (int j = tid; j < m; j += 256) {
-    const double dj = din[j];
+    const double dj = sch[j];
     double zj = j < m1 ? Z[(long long)(o + j) * n + o + m1 - 1] : sg * Z[(long long)(o + j) * n + o + m1];
     zj *= 0.70710678118654752440;
     int rk;
     if (j < m1) {   // children ascending; the first child's entry goes first on ties
       int lo = 0, hi = m2;
-      while (lo < hi) { const int mid = (lo + hi) >> 1; if (din[m1 + mid] < dj) lo = mid + 1; else hi = mid; }
+      while (lo < hi) { const int mid = (lo + hi) >> 1; if (sch[m1 + mid] < dj) lo = mid + 1; else hi = mid; }
       rk = j + lo;
     } else {
       int lo = 0, hi = m1;
-      while (lo < hi) { const int mid = (lo + hi) >> 1; if (din[mid] <= dj) lo = mid + 1; else hi = mid; }
+      while (lo < hi) { const int mid = (lo + hi) >> 1; if (sch[mid] <= dj) lo = mid + 1; else hi = mid; }
       rk = (j - m1) + lo;
     }
     sd[rk] = dj;
@@ -437,7 +452,8 @@ __global__ __launch_bounds__(256) void dc_deflate_k(DcWs w, int t) {
   }
 }
 
-// Root i of the secular equation of its parent, one wavefront per root.
+// Root i of the secular equation of its parent, one wavefront per root, SQ entries of the parent per lane.
+template <int SQ>
 __global__ __launch_bounds__(256) void dc_secular_k(DcWs w, int t) {
   const int gw = (int)((blockIdx.x * 256u + threadIdx.x) >> 6), lane = threadIdx.x & 63;
   if (gw >= w.n) return;
@@ -756,7 +772,10 @@ hipError_t tridiag_eig_dc(hipStream_t s, int n, double* d, const double* e, doub
   for (int t = w.T - 1; t >= 0; --t) {
     const int np = 1 << t, mmax = cdiv_i(n, np), mcmax = cdiv_i(n, 2 * np);
     hipLaunchKernelGGL(dc_deflate_k, dim3(np), dim3(256), 0, s, w, t);
-    hipLaunchKernelGGL(dc_secular_k, dim3(waves), dim3(256), 0, s, w, t);
+    if (mmax <= 64) hipLaunchKernelGGL(dc_secular_k<1>, dim3(waves), dim3(256), 0, s, w, t);
+    else if (mmax <= 256) hipLaunchKernelGGL(dc_secular_k<4>, dim3(waves), dim3(256), 0, s, w, t);
+    else if (mmax <= 1024) hipLaunchKernelGGL(dc_secular_k<16>, dim3(waves), dim3(256), 0, s, w, t);
+    else hipLaunchKernelGGL(dc_secular_k<DMAX / 64>, dim3(waves), dim3(256), 0, s, w, t);
     const int tiles = cdiv_i(mmax, 64), nrank = np * tiles;
     hipLaunchKernelGGL(dc_post1_k, dim3(nrank + waves), dim3(256), 0, s, w, t, tiles, nrank);
     const int rt = cdiv_i(mmax, 64), ct = cdiv_i(mmax, 32), ngat = np * rt * ct;
