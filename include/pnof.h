@@ -222,7 +222,9 @@ pnof_status pnof_lagrangian_noalloc(pnof_ctx ctx, const pnof_problem* prob, cons
  * signed so that its largest-magnitude entry (lowest index on ties) is positive;
  * C_new = C U.  lambda, C, C_new: nbf x nbf; eps: nbf; S_out (optional): the matrix diagonalised.
  * C_new must not alias C or lambda.  The Householder reduction to tridiagonal form runs on the
- * library's kernels (one launch per column); the library's divide-and-conquer solver solves the
+ * library's kernels (the last 1024 columns in one launch, those before with one launch each; one
+ * launch per column throughout where the device is too busy for the first form); the library's
+ * divide-and-conquer solver solves the
  * tridiagonal problem while a second stream of the context (default priority, forked and joined
  * with events) forms the product of the reflectors in blocks of 128; the eigenvectors are then that
  * product times the tridiagonal solver's.  nbf < 3 or nbf > 2048 use rocSOLVER's dsyevd.  Scratch:

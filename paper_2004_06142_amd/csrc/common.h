@@ -343,9 +343,9 @@ hipError_t df_fp_gemm3(hipStream_t s, int nbf, int nact, int np, int nsplit, con
                        T* Ypart);
 
 // ---------------------------------------------------------------- bf16 split GEMMs (k_gemm_bf16.hip)
-// terms: 1 = hi*hi; 3 = hi*hi + hi*lo + lo*hi.  variant: 0 = 128 x 128 block tiles (two blocks per
-// CU), 1 = 128 x 256 (X) or 256 x 128 (Y) block tiles (one block per CU).  B_P given as bf16 (exact, 2 products against the
-// split Ct) or as a pre-split hi/lo pair (3 products).
+// terms: 1 = hi*hi; 3 = hi*hi + hi*lo + lo*hi.  variant: 1 = 128 x 128 block tiles (two blocks per CU),
+// 2 = 128 x 256 (X) or 256 x 128 (Y), 3 = 256 x 256 (one block per CU).  B_P given as bf16 (exact, 2 products
+// against the split Ct) or as a pre-split hi/lo pair (3 products).
 struct SplitPtr {
   const u16* hi;
   const u16* lo;  // may be null when terms == 1 or the operand is exact

@@ -1,4 +1,5 @@
-// Householder reduction of a symmetric float64 matrix to tridiagonal form, one kernel per column.
+// Householder reduction of a symmetric float64 matrix to tridiagonal form: the last 1024 columns in one
+// launch (trd_reduce_k, below), the columns before them one kernel each (trd_step_k, described here).
 //
 // The orbital step diagonalises an n x n symmetric matrix every iteration (n = 1200 at the largest
 // workload).  The reduction is a chain of n dependent steps, so its cost is per-step latency, not

@@ -9,10 +9,11 @@
 // from bounds, see chunk_scales), multiplied by the fp16 matrix-core instruction; X from a bf16 B
 // multiplies the compact bf16 pair of C by B and writes fp16 pairs.
 //
-// Block tiles BM x BN x 32 (128 x 256 for X, 128 x 128 for the symmetric b, 256 x 128 for Y),
-// 256 threads = 4 waves (2 x 2), each wave owning (BM/2) x (BN/2) in 16 x 16 MFMA blocks.  Operand
-// k-tiles go global -> registers (one tile ahead) -> LDS (two buffers), one barrier per k-tile.  MFMA lane layout (16x16x32): lane l supplies row l%16 and the eight k
-// values 8*(l/16)..+7 of each operand; result element (4*(l/16)+j, l%16) is component j.
+// Block tiles BM x BN x 32: 256 x 256 (8 waves) or 128 x 128 (4 waves, two blocks per compute unit) for X and Y,
+// 128 x 128 for the symmetric b; in 16 x 16 MFMA blocks.  Operand k-tiles go global -> LDS directly through a ring
+// of stages, one barrier per k-tile (where rows are not 16-byte aligned, through registers and two buffers).
+// MFMA lane layout (16x16x32): lane l supplies row l%16 and the eight k values 8*(l/16)..+7 of each operand; result
+// element (4*(l/16)+j, l%16) is component j.
 //
 // Operand storage in global memory:
 //   "row" operand: row r (an output index) is contiguous in k  -> LDS [r][k] (16-byte chunks
