@@ -28,15 +28,15 @@ KSRC = os.path.join(ROOT, "paper_2004_06142_amd", "csrc")
 # once the source changes the figure no longer applies and traffic is reported as null.
 TRAFFIC = {
     # profiles/c5_df1200_hbm_traffic.md: C5, bf16 split, 164-row chunks (read + written bytes per launch)
-    ("gemm1_kernel", 3): {"bytes": 1616331062 + 926146614,
+    ("gemm1_kernel", 3): {"bytes": 1278915712 + 983606467,
                           "plan": {"pchunk": 164, "x_variant": 3},
-                          "sha256": {"k_gemm_bf16.hip": "739a0e927a9a5740758dc869d19722c729b4c658e67bcb213bd4cf4448b56ae8"}},
-    ("gemm2_kernel", 3): {"bytes": 4146286647 + 639393009,
+                          "sha256": {"k_gemm_bf16.hip": "557a1af7cf4674cfb51e8ab77657966c99730bed781145d0f07dd08fb69aca60"}},
+    ("gemm2_kernel", 3): {"bytes": 4925346117 + 712677698,
                           "plan": {"pchunk": 164, "nsplit_b": 18},
-                          "sha256": {"k_gemm_bf16.hip": "739a0e927a9a5740758dc869d19722c729b4c658e67bcb213bd4cf4448b56ae8"}},
-    ("gemm3_kernel", 3): {"bytes": 2586050632 + 57679787,
+                          "sha256": {"k_gemm_bf16.hip": "557a1af7cf4674cfb51e8ab77657966c99730bed781145d0f07dd08fb69aca60"}},
+    ("gemm3_kernel", 3): {"bytes": 2575966956 + 57659388,
                           "plan": {"pchunk": 164, "nsplit_y": 10, "y_variant": 3},
-                          "sha256": {"k_gemm_bf16.hip": "739a0e927a9a5740758dc869d19722c729b4c658e67bcb213bd4cf4448b56ae8"}},
+                          "sha256": {"k_gemm_bf16.hip": "557a1af7cf4674cfb51e8ab77657966c99730bed781145d0f07dd08fb69aca60"}},
 }
 GOLDEN_C5 = os.path.join(ROOT, "tests", "golden", "c5_df1200_expected.json")
 
