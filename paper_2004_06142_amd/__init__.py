@@ -38,7 +38,7 @@ EXPORTS = ["pnof_abi_version", "pnof_last_error", "pnof_check_problem", "pnof_cr
            "pnof_optimize", "pnof_nofmp2_terms", "pnof_batch_plan",
            "pnof_batch_bind", "pnof_batch_run", "pnof_batch_info", "pnof_batch_destroy", "pnof_batch_set_tiles",
            "pnof_batch_get_tiles", "pnof_batch_times", "pnof_batch_set_stall", "pnof_batch_set_dies",
-           "pnof_bind_integrals"]
+           "pnof_bind_integrals", "pnof_set_reduction"]
 STAGES = ("X", "b", "Y", "eig")
 
 
@@ -141,6 +141,7 @@ def lib():
             "pnof_batch_times": ([P, ctypes.POINTER(ctypes.c_double)], S),
             "pnof_batch_set_stall": ([P, ctypes.c_double], S),
             "pnof_batch_set_dies": ([P, I], S),
+            "pnof_set_reduction": ([P, I], S),
         }
         for name, (args, res) in sig.items():
             f = getattr(L, name)
@@ -244,6 +245,10 @@ class Context:
 
     def set_pchunk(self, pc: int):
         _raise(self, lib().pnof_set_pchunk(self.handle, pc))
+
+    def set_reduction(self, form: int = 0):
+        """Form of the orbital step's reduction (pnof_set_reduction; for testing)."""
+        _raise(self, lib().pnof_set_reduction(self.handle, form))
 
     def bind_integrals(self, prob: Optional[Problem] = None, ints: Optional[torch.Tensor] = None):
         """Keep the split mode's row bounds of `ints` for later calls on the same integrals

@@ -54,6 +54,7 @@ struct pnof_ctx_s {
   struct Slot { void* p; size_t bytes; };
   std::vector<Slot> slots;
   size_t slot_top = 0;
+  int reduction = REDUCE_AUTO;   // form of the orbital step's reduction (pnof_set_reduction)
   double* host_on = nullptr;   // pinned: gamma, E and dE/dgamma of one evaluation of the occupation optimisation
   size_t host_on_bytes = 0;
   // integrals bound by pnof_bind_integrals: their per-chunk row bounds (split mode) and the key they
@@ -1504,8 +1505,8 @@ EighWs take_eigh_ws(Arena& a, int n) {
 }
 // Eigenvalues w and column-major eigenvectors U of A (overwritten).  info (device, 2 words): [0] a
 // secular equation did not converge, [1] the one-launch reduction declined (call again with the matrix
-// restored and `launches`).
-pnof_status eigh(pnof_ctx ctx, int n, double* A, double* w, double* U, const EighWs& ws, int* info, bool launches) {
+// restored and REDUCE_LAUNCHES).
+pnof_status eigh(pnof_ctx ctx, int n, double* A, double* w, double* U, const EighWs& ws, int* info, int form) {
   hipStream_t s = ctx->stream;
   if (n < 3 || n > TRIDIAG_MAX_N) {
     rocblas_status rs = rocsolver_dsyevd(ctx->blas, rocblas_evect_original, rocblas_fill_upper, n, A, n, w, ws.e, info);
@@ -1517,7 +1518,7 @@ pnof_status eigh(pnof_ctx ctx, int n, double* A, double* w, double* U, const Eig
   if (!ws.Vh || !ws.p2 || !ws.e || !ws.tau || !ws.T || !ws.Q || !ws.dc)
     return fail(ctx, PNOF_E_ARG, "eigensolver workspace missing");
   RB_CHECK(ensure_aux(ctx));
-  DEV_CHECK(ctx, tridiag_f64(s, n, A, ws.Vh, ws.p2, w, ws.e, ws.tau, info, launches));
+  DEV_CHECK(ctx, tridiag_f64(s, n, A, ws.Vh, ws.p2, w, ws.e, ws.tau, info, form));
   DEV_CHECK(ctx, hipEventRecord(ctx->fork_ev, s));
   DEV_CHECK(ctx, hipStreamWaitEvent(ctx->aux, ctx->fork_ev, 0));
   DEV_CHECK(ctx, form_q_f64(ctx->aux, n, ws.Vh, ws.tau, ws.T, ws.Q));
@@ -1531,6 +1532,13 @@ pnof_status eigh(pnof_ctx ctx, int n, double* A, double* w, double* U, const Eig
   return PNOF_OK;
 }
 }  // namespace
+
+pnof_status pnof_set_reduction(pnof_ctx ctx, int32_t form) {
+  if (!ctx) return fail(nullptr, PNOF_E_ARG, "context is NULL");
+  if (form < REDUCE_AUTO || form > REDUCE_DECLINE) return fail(ctx, PNOF_E_ARG, "unknown form of the reduction");
+  ctx->reduction = form;
+  return PNOF_OK;
+}
 
 pnof_status pnof_orbital_step(pnof_ctx ctx, int32_t nbf, const double* lambda, const double* C,
                               const double* diag_prev, double zeta, double* C_new, double* eps, double* S_out) {
@@ -1547,6 +1555,7 @@ pnof_status pnof_orbital_step(pnof_ctx ctx, int32_t nbf, const double* lambda, c
   probe.take<double>(n2);
   take_eigh_ws(probe, nbf);
   probe.take<int>(4);
+  if (tridiag_may_decline(nbf)) probe.take<double>(n2);
   char* ws = nullptr;
   if ((st = get_ws(ctx, probe.off + 256, &ws)) != PNOF_OK) return st;
   Arena a(ws);
@@ -1554,13 +1563,16 @@ pnof_status pnof_orbital_step(pnof_ctx ctx, int32_t nbf, const double* lambda, c
   double* U = a.take<double>(n2);
   const EighWs ew = take_eigh_ws(a, nbf);
   int* info = a.take<int>(4);
+  // the matrix of a second pass: eps, S_out and C_new may have taken the place of what it was formed from
+  double* keep = tridiag_may_decline(nbf) ? a.take<double>(n2) : nullptr;
   hipStream_t s = ctx->stream;
-  for (int launches = 0; launches < 2; ++launches) {   // again with a launch per column if the reduction declines
-    DEV_CHECK(ctx, build_s(s, nbf, lambda, diag_prev, zeta, A));
-    if (S_out) DEV_CHECK(ctx, hipMemcpyAsync(S_out, A, n2 * sizeof(double), hipMemcpyDeviceToDevice, s));
+  for (int pass = 0; pass < 2; ++pass) {   // again with a launch per column if the reduction declines
+    if (pass == 0) DEV_CHECK(ctx, build_s(s, nbf, lambda, diag_prev, zeta, A, keep));
+    else DEV_CHECK(ctx, hipMemcpyAsync(A, keep, n2 * sizeof(double), hipMemcpyDeviceToDevice, s));
+    if (S_out && pass == 0) DEV_CHECK(ctx, hipMemcpyAsync(S_out, A, n2 * sizeof(double), hipMemcpyDeviceToDevice, s));
     {
       StageTimer t_(ctx, PNOF_STAGE_EIG);
-      if ((st = eigh(ctx, nbf, A, eps, U, ew, info, launches != 0)) != PNOF_OK) return st;
+      if ((st = eigh(ctx, nbf, A, eps, U, ew, info, pass ? REDUCE_LAUNCHES : ctx->reduction)) != PNOF_OK) return st;
     }
     DEV_CHECK(ctx, sign_fix_cols(s, nbf, U));
     // C_new[mu][j] = sum_i C[mu][i] U[i][j], U column-major: U[i][j] = U[j*nbf + i]
@@ -1723,9 +1735,9 @@ pnof_status pnof_optimize(pnof_ctx ctx, const pnof_problem* prob, const double* 
   auto diagonalise = [&]() -> pnof_status {
     // T1 keeps the matrix in case the reduction declines and it is taken again with a launch per column
     DEV_CHECK(ctx, hipMemcpyAsync(T1, S, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
-    for (int launches = 0; launches < 2; ++launches) {
-      if (launches) DEV_CHECK(ctx, hipMemcpyAsync(S, T1, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
-      pnof_status se = eigh(ctx, nbf, S, diag, Ueig, ew, info, launches != 0);
+    for (int pass = 0; pass < 2; ++pass) {
+      if (pass) DEV_CHECK(ctx, hipMemcpyAsync(S, T1, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
+      pnof_status se = eigh(ctx, nbf, S, diag, Ueig, ew, info, pass ? REDUCE_LAUNCHES : ctx->reduction);
       if (se != PNOF_OK) return se;
       DEV_CHECK(ctx, sign_fix_cols(s, nbf, Ueig));
       DEV_CHECK(ctx, gemm_f64(s, nbf, nbf, nbf, 1, 1.0, C, nbf, 1, 0, Ueig, 1, nbf, 0, 0.0, Cn, nbf, 1, 0));

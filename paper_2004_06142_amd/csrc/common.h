@@ -633,17 +633,20 @@ hipError_t on_map(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, co
 hipError_t on_map_vjp(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, const double* gamma,
                       const double* dEdn, double* dEdgamma);
 hipError_t build_s(hipStream_t s, int nbf, const double* lam, const double* diag_prev, double zeta,
-                   double* S);
+                   double* S, double* keep = nullptr);   // keep: a copy of S
 hipError_t sign_fix_cols(hipStream_t s, int nbf, double* Ucm);
 // Householder reduction to tridiagonal form (k_eig.hip): A (n x n symmetric, row-major) may be
 // overwritten; d (n), e (n - 1), tau (n - 1) and the reflectors as rows of Vh (n x n, read column-major:
 // the lower-storage layout of ormtr); ws: tridiag_ws_doubles(n) doubles.  info[1] (device) is set when
 // the one-launch form declined (too few of its workgroups running at once; d, e, tau are then finite but
-// no result): call again with `launches`, one launch per column.
+// no result): call again with REDUCE_LAUNCHES, one launch per column.  REDUCE_DECLINE: the one-launch form asks for
+// more workgroups than there are, so that it declines.
 constexpr int TRIDIAG_MAX_N = 2048;   // three float64 vectors of n in LDS
+enum { REDUCE_AUTO = 0, REDUCE_LAUNCHES = 1, REDUCE_DECLINE = 2 };
 long long tridiag_ws_doubles(int n);
+bool tridiag_may_decline(int n);
 hipError_t tridiag_f64(hipStream_t s, int n, double* A, double* Vh, double* ws, double* d, double* e, double* tau,
-                       int* info, bool launches);
+                       int* info, int form);
 // Q = H_0 ... H_{n-2} (column-major n x n) from the reflectors of tridiag_f64 (Vh, tau), applied in
 // blocks of QNB as float64 GEMMs.  ws: form_q_ws_doubles(n) doubles.  3 <= n <= TRIDIAG_MAX_N.
 constexpr int QNB = 128;

@@ -18,6 +18,7 @@
 // Every block recomputes w_{k-1}, c and v_k identically (same data, same reduction order); block 0
 // stores v_k as row k of Vh, which read column-major is the lower-storage reflector layout that
 // LAPACK-style routines (ormtr) take: Q = H_0 H_1 ... H_{n-2}, H_k = I - tau_k v_k v_k^T, A = Q T Q^T.
+#include <climits>
 #include <type_traits>
 
 #include "common.h"
@@ -393,7 +394,7 @@ __device__ __forceinline__ void trd_pick(int r, F f) {
 }
 
 template <bool MULTI, int NW, int NR, int NJ>
-__global__ __launch_bounds__(64 * NW) void trd_reduce_k(int n, int k0, int want, const double* __restrict__ A,
+__global__ __launch_bounds__(64 * NW) void trd_reduce_k(int n, int k0, int want, int need, const double* __restrict__ A,
                                                     double* __restrict__ Vh, const double* __restrict__ pprev,
                                                     double* __restrict__ d, double* __restrict__ e,
                                                     double* __restrict__ tau, int* ctl, double* xch, int* info) {
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(64 * NW) void trd_reduce_k(int n, int k0, int want,
   const int m0 = n - k0;
   int id = 0, W = 1;
   if constexpr (MULTI) {
-    id = trd_register(ctl, want, (m0 + NW * NR - 1) / (NW * NR), info, W);
+    id = trd_register(ctl, want, need, info, W);
     if (id < 0) return;
     id = __builtin_amdgcn_readfirstlane(id);
     W = __builtin_amdgcn_readfirstlane(W);
@@ -781,15 +782,16 @@ hipError_t form_q_f64(hipStream_t s, int n, const double* Vh, const double* tau,
   return hipGetLastError();
 }
 
+bool tridiag_may_decline(int n) { return n > TRD_SOLO && n <= TRIDIAG_MAX_N; }
 long long tridiag_ws_doubles(int n) { return 2LL * n + TRD_SLOTS * trd_slot(TRD_MMAX) + TRD_CTL; }
 
 hipError_t tridiag_f64(hipStream_t s, int n, double* A, double* Vh, double* ws, double* d, double* e, double* tau,
-                       int* info, bool launches) {
+                       int* info, int form) {
   if (n <= 0 || n > TRIDIAG_MAX_N) return hipErrorInvalidValue;
   double* p2 = ws;                  // two vectors of n by column parity
   double* xch = ws + 2LL * n;
   int* ctl = reinterpret_cast<int*>(xch + TRD_SLOTS * trd_slot(TRD_MMAX));
-  const int kend = std::max(0, n - (launches ? TRD_SOLO : TRD_MMAX));   // columns 0 .. kend-1: a launch each
+  const int kend = std::max(0, n - (form == REDUCE_LAUNCHES ? TRD_SOLO : TRD_MMAX));   // columns 0 .. kend-1: a launch each
   const size_t shm = 3 * (size_t)n * sizeof(double);
   for (int k = 0; k < kend; ++k) {
     const int blocks = std::max(1, (n - 1) / TROWS - trd_group_base(k) + 1);
@@ -799,8 +801,8 @@ hipError_t tridiag_f64(hipStream_t s, int n, double* A, double* Vh, double* ws, 
   const double* pp = p2 + ((kend + 1) & 1) * (long long)n;
   const int m = n - kend;
 #define TRD_REDUCE(MULTI, NW, NR, NJ, grid, want, pad)                                                                 \
-  hipLaunchKernelGGL((trd_reduce_k<MULTI, NW, NR, NJ>), dim3(grid), dim3(64 * NW), pad, s, n, kend, want, A, Vh, pp, d, \
-                     e, tau, ctl, xch, info)
+  hipLaunchKernelGGL((trd_reduce_k<MULTI, NW, NR, NJ>), dim3(grid), dim3(64 * NW), pad, s, n, kend, want,               \
+                     form == REDUCE_DECLINE ? INT_MAX : (int)cdiv(m, NW * NR), A, Vh, pp, d, e, tau, ctl, xch, info)
   if (m <= TRD_SOLO) TRD_REDUCE(false, 8, 4, 1, 1, 1, 0);
   else {
     const int M = m <= 128 ? 128 : m <= 256 ? 256 : m <= 512 ? 512 : m <= 768 ? 768 : 1024, slots = TRD_SLOTS * trd_slot(M);

@@ -790,9 +790,9 @@ __global__ void offdiag_k(int nbf, const double* __restrict__ src, double* __res
   GRID_STRIDE(i, (long long)nbf * nbf) dst[i] = (i / nbf == i % nbf) ? 0.0 : src[i];
 }
 
-// Matrix diagonalised by the orbital step.
+// Matrix diagonalised by the orbital step, and a copy of it in `keep` unless that is null.
 __global__ void build_s_k(int nbf, const double* __restrict__ lam, const double* __restrict__ dprev, double zeta,
-                          double* __restrict__ S) {
+                          double* __restrict__ S, double* __restrict__ keep) {
   GRID_STRIDE(i, (long long)nbf * nbf) {
     const long long p = i / nbf, q = i % nbf;
     const double a = lam[p * nbf + q], b = lam[q * nbf + p];
@@ -805,6 +805,7 @@ __global__ void build_s_k(int nbf, const double* __restrict__ lam, const double*
         while (fabs(v) > zeta) v /= 10.0;
     }
     S[i] = v;
+    if (keep) keep[i] = v;
   }
 }
 
@@ -1087,8 +1088,8 @@ hipError_t on_map_vjp(hipStream_t s, int kind, int npairs, int ncwo, int nsingle
                       const double* dEdn, double* out) {
   LAUNCH(on_map_vjp_k, dim3(cdiv(npairs + nsingle, 64)), dim3(64), kind, npairs, ncwo, nsingle, gamma, dEdn, out);
 }
-hipError_t build_s(hipStream_t s, int nbf, const double* lam, const double* dprev, double zeta, double* S) {
-  LAUNCH(build_s_k, grid1((long long)nbf * nbf), dim3(NT), nbf, lam, dprev, zeta, S);
+hipError_t build_s(hipStream_t s, int nbf, const double* lam, const double* dprev, double zeta, double* S, double* keep) {
+  LAUNCH(build_s_k, grid1((long long)nbf * nbf), dim3(NT), nbf, lam, dprev, zeta, S, keep);
 }
 hipError_t sign_fix_cols(hipStream_t s, int nbf, double* U) {
   LAUNCH(sign_fix_k, dim3(nbf), dim3(NT), nbf, U);

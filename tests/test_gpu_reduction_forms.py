@@ -1,0 +1,89 @@
+"""The orbital step where its one-launch reduction declines (as on a busy device; here the context asks for it)
+and a launch per column follows, at the sizes where the forms change: 32 columns in one workgroup, then the
+register blocks of 128, 256, 512, 768 and 1024 columns, and one launch per column before those.  The results are
+bit for bit those of a launch per column from the start, also where outputs take the place of inputs that the
+first pass has read: eps in diag_prev's buffer, S_out in lambda's.  Bars against the oracle as in
+test_gpu_reduction.py."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import pnof
+
+P = pytest.importorskip("paper_2004_06142_amd")
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda", 0)
+AUTO, LAUNCHES, DECLINE = 0, 1, 2
+SIZES = [3, 32, 33, 34, 128, 129, 145, 256, 257, 513, 769, 1024, 1025, 1057]
+
+
+def t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return P.Context(0)
+
+
+def _case(nbf):
+    rng = np.random.default_rng([nbf, 2])
+    C, _ = np.linalg.qr(rng.standard_normal((nbf, nbf)))
+    return rng.standard_normal((nbf, nbf)), C, np.sort(-20.0 * rng.random(nbf))
+
+
+def _step(ctx, form, lam, C, diag, alias):
+    """(C_new, eps, S_out); with alias, eps and S_out overwrite diag_prev and lambda"""
+    nbf = C.shape[0]
+    l, d, c = t(lam), None if diag is None else t(diag), t(C)
+    Cn = torch.empty_like(c)
+    eps = d if alias and d is not None else torch.empty(nbf, dtype=torch.float64, device=DEV)
+    S = l if alias else torch.empty_like(l)
+    ctx.set_reduction(form)
+    try:
+        P.pnof_orbital_step(ctx, nbf, l, c, d, 0.5 if d is not None else 0.0, Cn, eps, S)
+    finally:
+        ctx.set_reduction(AUTO)
+    torch.cuda.synchronize()
+    return Cn, eps, S
+
+
+@pytest.mark.parametrize("fmode", [False, True])
+@pytest.mark.parametrize("nbf", SIZES)
+def test_declined_reduction(ctx, nbf, fmode):
+    lam, C, diag = _case(nbf)
+    diag = diag if fmode else None
+    ref = _step(ctx, LAUNCHES, lam, C, diag, False)
+    for alias in (False, True):
+        got = _step(ctx, DECLINE, lam, C, diag, alias)
+        for a, b, what in zip(got, ref, ("C_new", "eps", "S")):
+            assert torch.equal(a, b), (what, alias)
+    for Cn, eps, _ in (ref, _step(ctx, AUTO, lam, C, diag, True)):
+        _, eps_r, S = pnof.orbital_step(lam, C, diag, 0.5 if fmode else 0.0)
+        U, e = C.T @ Cn.cpu().numpy(), eps.cpu().numpy()
+        assert np.max(np.abs(e - eps_r)) < 1e-9
+        assert np.max(np.abs(U.T @ U - np.eye(nbf))) < 1e-12
+        assert np.max(np.abs(S @ U - U * e[None, :])) < 1e-9
+
+
+def test_optimisation_with_declined_reduction(ctx):
+    inst = synth.make(synth.Workload("forms", 40, 160, 5, 3, "f64"), 5)
+    prob = P.problem(40, 160, 5, 3, P.PNOF7, P.FP64, P.INTS_DF_F64)
+    out = []
+    for form in (LAUNCHES, DECLINE):
+        ctx.set_reduction(form)
+        try:
+            out.append(ctx.optimize(prob, t(inst.H), t(inst.B), t(inst.C), t(inst.gamma), maxit=2, on_maxiter=10, ndiis=2, zeta=0.5))
+        finally:
+            ctx.set_reduction(AUTO)
+    a, b = out
+    assert torch.equal(a["C"], b["C"]) and torch.equal(a["n"], b["n"]) and a["E"] == b["E"]
+
+
+def test_unknown_form(ctx):
+    with pytest.raises(P.PnofError):
+        ctx.set_reduction(3)
