@@ -697,10 +697,11 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
 
   double* const part = want_e ? b.partials : nullptr;
   DEV_CHECK(ctx, step_tail(s, nbf, nact, pl.npairs, pl.ncwo, pl.nsingle, pl.functional, n, b.Hpp, b.alpha, b.beta, J, K, b.HC,
-                           b.Y2e, C, b.cth, b.ctl, b.Ct32, pl.ldk, corr_terms, part, want_y ? Y : nullptr, r.dEdC, r.dEdn,
-                           r.lam, r.asym));
+                           b.Y2e, C, b.cth, b.ctl, b.Ct32, pl.ldk, corr_terms, part, want_y ? Y : nullptr, r.dEdn, r.lam,
+                           r.asym));
   if (r.lam) RB_CHECK(dprod(ctx, nbf, nact, nbf, C, 1, nbf, Y, nact, 1, r.lam, nbf, 1));
-  DEV_CHECK(ctx, step_end(s, nbf, nact, corr_terms, part, r.E ? r.E : b.E, r.lam, r.lam ? r.asym : nullptr));
+  DEV_CHECK(ctx, step_end(s, nbf, nact, corr_terms, part, r.E ? r.E : b.E, r.lam, r.lam ? r.asym : nullptr, Y,
+                          r.dEdC));
   return PNOF_OK;
 }
 

@@ -620,14 +620,14 @@ hipError_t energy(hipStream_t s, int nbf, int nact, const double* n, const doubl
                   const double* Y2e, const double* C, const u16* Ct_hi, const u16* Ct_lo, const float* Ct32, int ldk,
                   int corr_terms, double* partials, double* E);
 // Everything of the step but lambda's product, before it (step_tail: the partial sums of E unless partials is null,
-// dE/dn, Y, dE/dC, the columns of lambda past nact, each unless null) and after it (step_end: E, max |lambda - lambda^T|).
+// dE/dn, Y, the columns of lambda past nact, each unless null) and after it (step_end: E, max |lambda - lambda^T|,
+// dE/dC).
 hipError_t step_tail(hipStream_t s, int nbf, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                      const double* Hpp, const double* alpha, const double* beta, const double* J, const double* K,
                      const double* HC, const double* Y2e, const double* C, const u16* cth, const u16* ctl, const float* ct32,
-                     int ldk, int corr_terms, double* partials, double* Y, double* dEdC, double* dEdn, double* lam,
-                     double* asym);
+                     int ldk, int corr_terms, double* partials, double* Y, double* dEdn, double* lam, double* asym);
 hipError_t step_end(hipStream_t s, int nbf, int nact, int corr_terms, const double* partials, double* E, const double* lam,
-                    double* asym);
+                    double* asym, const double* Y, double* dEdC);
 hipError_t on_map(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, const double* gamma, double* n,
                   double* jac);
 hipError_t on_map_vjp(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, const double* gamma,

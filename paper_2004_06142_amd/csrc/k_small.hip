@@ -593,13 +593,13 @@ __device__ inline void grad_n_row(int p, int nact, int npairs, int ncwo, int nsi
 }
 
 // What the step forms between the contractions and lambda = C^T Y, in one launch: blocks [0, ne) the partial sums of
-// E; the next ng dE/dn, a wave per orbital; the rest element by element Y = n o (H C_A) + Y2e, dE/dC = 4 Y, the zero
-// columns of dE/dC and lambda past nact, and the zero from which step_end_k raises the asymmetry.
+// E; the next ng dE/dn, a wave per orbital; the rest element by element Y = n o (H C_A) + Y2e, the zero columns of
+// lambda past nact, and the zero from which step_end_k raises the asymmetry.
 struct TailArgs {
   EnergyArgs e;
   int ne, ng, npairs, ncwo, nsingle, functional;
   const double* HC;
-  double *partials, *dEdn, *Y, *dEdC, *lam, *asym;
+  double *partials, *dEdn, *Y, *lam, *asym;
 };
 __global__ void step_tail_k(TailArgs a) {
   const int nbf = a.e.nbf, nact = a.e.nact;
@@ -617,24 +617,22 @@ __global__ void step_tail_k(TailArgs a) {
   }
   b -= a.ng;
   if (b == 0 && threadIdx.x == 0 && a.asym) *a.asym = 0.0;
-  const int w = a.dEdC || a.lam ? nbf : nact;
+  const int w = a.lam ? nbf : nact;
   const long long stride = (long long)(gridDim.x - a.ne - a.ng) * NT;
   for (long long i = (long long)b * NT + threadIdx.x; i < (long long)nbf * w; i += stride) {
     const long long mu = i / w;
     const int q = (int)(i - mu * w);
-    double y = 0.0;
-    if (q < nact) {
-      const long long o = mu * nact + q;
-      y = a.e.n[q] * a.HC[o] + a.e.Y2e[o];
-      a.Y[o] = y;
-    } else if (a.lam) a.lam[i] = 0.0;
-    if (a.dEdC) a.dEdC[i] = 4.0 * y;
+    const long long o = mu * nact + q;
+    if (q < nact) a.Y[o] = a.e.n[q] * a.HC[o] + a.e.Y2e[o];
+    else a.lam[i] = 0.0;
   }
 }
-// After lambda: block 0 adds the partial sums of E, the others raise max |lambda - lambda^T| (not negative, so its bits
-// order as its value).
-__global__ void step_end_k(int ne, const double* __restrict__ partials, double* __restrict__ E, int nbf,
-                           const double* __restrict__ lam, double* __restrict__ asym) {
+// After lambda: block 0 adds the partial sums of E, the next na raise max |lambda - lambda^T| (not negative, so its
+// bits order as its value), the rest write dE/dC = 4 Y, zero past nact (it may take the place of C, which E and
+// lambda are formed from).
+__global__ void step_end_k(int ne, int na, const double* __restrict__ partials, double* __restrict__ E, int nbf, int nact,
+                           const double* __restrict__ lam, double* __restrict__ asym, const double* __restrict__ Y,
+                           double* __restrict__ dEdC) {
   if (blockIdx.x == 0) {
     double s = 0.0;
     for (int i = threadIdx.x; i < ne; i += blockDim.x) s += partials[i];
@@ -642,8 +640,17 @@ __global__ void step_end_k(int ne, const double* __restrict__ partials, double* 
     if (threadIdx.x == 0 && ne > 0) *E = s;
     return;
   }
+  if ((int)blockIdx.x > na) {
+    const long long stride = (long long)(gridDim.x - 1 - na) * NT;
+    for (long long i = (long long)(blockIdx.x - 1 - na) * NT + threadIdx.x; i < (long long)nbf * nbf; i += stride) {
+      const long long mu = i / nbf;
+      const int q = (int)(i - mu * nbf);
+      dEdC[i] = q < nact ? 4.0 * Y[mu * nact + q] : 0.0;
+    }
+    return;
+  }
   double m = 0.0;
-  for (long long i = (long long)(blockIdx.x - 1) * NT + threadIdx.x; i < (long long)nbf * nbf; i += (long long)(gridDim.x - 1) * NT) {
+  for (long long i = (long long)(blockIdx.x - 1) * NT + threadIdx.x; i < (long long)nbf * nbf; i += (long long)na * NT) {
     const long long p = i / nbf, q = i % nbf;
     m = fmax(m, fabs(lam[i] - lam[q * nbf + p]));
   }
@@ -1063,22 +1070,22 @@ static int tail_parts(int nbf, int nact, int corr_terms) {   // 256 blocks at mo
 hipError_t step_tail(hipStream_t s, int nbf, int nact, int npairs, int ncwo, int nsingle, int functional, const double* n,
                      const double* Hpp, const double* alpha, const double* beta, const double* J, const double* K,
                      const double* HC, const double* Y2e, const double* C, const u16* cth, const u16* ctl, const float* ct32,
-                     int ldk, int corr_terms, double* partials, double* Y, double* dEdC, double* dEdn, double* lam,
-                     double* asym) {
+                     int ldk, int corr_terms, double* partials, double* Y, double* dEdn, double* lam, double* asym) {
   TailArgs a{{nbf, nact, n, Hpp, alpha, beta, J, K, Y2e, C, cth, ctl, ct32, ldk, corr_terms}, 0, 0, npairs, ncwo, nsingle,
-             functional, HC, partials, dEdn, Y, dEdC, lam, asym};
+             functional, HC, partials, dEdn, Y, lam, asym};
   a.ne = partials ? tail_parts(nbf, nact, corr_terms) : 0;
   a.ng = dEdn ? cdiv(nact, NT / 64) : 0;
-  const unsigned nel = Y ? grid1((long long)nbf * (dEdC || lam ? nbf : nact)).x : 0;
+  const unsigned nel = Y ? grid1((long long)nbf * (lam ? nbf : nact)).x : 0;
   if (a.ne + a.ng + nel == 0) return hipSuccess;
   LAUNCH(step_tail_k, dim3(a.ne + a.ng + nel), dim3(NT), a);
 }
 hipError_t step_end(hipStream_t s, int nbf, int nact, int corr_terms, const double* partials, double* E, const double* lam,
-                    double* asym) {
+                    double* asym, const double* Y, double* dEdC) {
   const int ne = partials ? tail_parts(nbf, nact, corr_terms) : 0;
   const unsigned na = asym ? (unsigned)std::min(256LL, ((long long)nbf * nbf + NT - 1) / NT) : 0;
-  if (ne == 0 && na == 0) return hipSuccess;
-  LAUNCH(step_end_k, dim3(1 + na), dim3(NT), ne, partials, E, nbf, lam, asym);
+  const unsigned nd = dEdC ? grid1((long long)nbf * nbf).x : 0;
+  if (ne + na + nd == 0) return hipSuccess;
+  LAUNCH(step_end_k, dim3(1 + na + nd), dim3(NT), ne, (int)na, partials, E, nbf, nact, lam, asym, Y, dEdC);
 }
 hipError_t on_map(hipStream_t s, int kind, int npairs, int ncwo, int nsingle, const double* gamma, double* n,
                   double* jac) {
