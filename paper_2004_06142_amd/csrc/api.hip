@@ -192,7 +192,8 @@ struct Plan {
   bool split;   // bf16 family
   bool f32;     // PNOF_FP32: the float64 path's kernels in float32
   int terms;    // 1 or 3
-  int kr;       // split: rows of P that one float32 sum of b^2 covers
+  int ksums;    // split: float32 sums of b^2 of a chunk at least, as far as its rows go (krows)
+  int krows(int np) const { return std::min(8, np / std::min(np, ksums)); }   // rows of one such sum at most
 };
 
 // P-splits of a contraction whose blocks take one tile and the P rows of one split, `slots` blocks resident
@@ -276,10 +277,10 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   const long long auto2 = std::max(1LL, (1024 + ntri - 1) / ntri);
   // b: two (split) or three blocks per compute unit, whole rounds (1200 functions, 55 tiles of 164 rows: 19
   // splits are 4.08 rounds of 256, 42.7 ms over the step; 27 of the present form, 35.1).  The sums of b^2 are
-  // float64, in the split mode over float32 sums of at most kr rows: 8, or the even share of 1024 blocks (K's
-  // distance from float64 arithmetic, 6e-7 to 1e-6 at 200 to 500 functions, is the same to four digits with
-  // 2 or 3 rows; adding to float64 sums that often cost a tenth of b)
-  pl.kr = std::max(8, cdiv(pl.pc, std::min<long long>(pl.pc, auto2)));
+  // float64, in the split mode over float32 sums of krows rows: the even share, rounded down, of a chunk's rows
+  // among 1024 blocks of one sum each, at most 8.  (8 rows whatever the size would take 0.11 ms off the 5.3 ms of
+  // 500 functions with 300 active, which add to the float64 sums every 2 rows, and leave K rounded more often.)
+  pl.ksums = (int)std::min<long long>(auto2, INT_MAX);
   pl.ns2 = tu.nsplit_b > 0 ? tu.nsplit_b
            : pl.split      ? best_splits(pl.pc, ntri, 512, 0.25, 0.1)
                            : best_splits(pl.pc, ntri, 768, 0.25);
@@ -651,7 +652,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
         double* Dc = b.D + (long long)p0 * nact;
         SplitPtr XT{xth_[c & 1], split ? xtl_[c & 1] : nullptr};
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_bf16_gemm2(s, nbf, nact, np, ns2, pl.terms, C16, pl.ldk, XT, pl.ldx,
-                                                               b.beta32, b.Kpart, c == 0, pl.kr, Dc, b.wh, b.wl, pl.ldw, wd, b.bnd, c)));
+                                                               b.beta32, b.Kpart, c == 0, pl.krows(np), Dc, b.wh, b.wl, pl.ldw, wd, b.bnd, c)));
         if (want_y) {
           if (two) {
             DEV_CHECK(ctx, hipEventRecord(ev_b, s));

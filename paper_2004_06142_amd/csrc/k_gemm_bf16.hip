@@ -703,7 +703,7 @@ __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = n
 // other keeps the matrix cores busy.  Against 8 waves and one block, b over the step: 1200 functions 42.7 ->
 // 36.1 ms, 500 functions (300 active, 2000 rows) 1.40 -> 0.91, 413 functions 0.85 -> 0.55 (with the splits that the
 // planner takes for it).
-// The sums of b^2 are float32 over at most krows rows, then float64 in Kpart: each block adds to its own partial
+// The sums of b^2 are float32 over at most krows rows (at most 8), then float64 in Kpart: each block adds to its own partial
 // sums only, with atomics, which need no wait (as loads and stores, 1200 functions in 164 splits 53.0 ms, with
 // atomics 40.0).
 // TT: the square tile (128, or 64 for the short active spaces of batch instances, with 4 waves).
