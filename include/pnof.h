@@ -67,7 +67,7 @@ typedef enum {
   PNOF_E_DEVICE = 5,       /* HIP launch or runtime error (possibly from an earlier call) */
   PNOF_E_NONFINITE = 6,    /* PNOF_CHECK_FINITE found a NaN / Inf in an input           */
   PNOF_E_UNSUPPORTED = 7,  /* valid request that the library does not implement       */
-  PNOF_E_EIG = 8           /* the eigensolver did not converge                          */
+  PNOF_E_EIG = 8           /* the eigensolver did not converge, or its matrix is not finite */
 } pnof_status;
 
 typedef enum { PNOF5 = 5, PNOF7 = 7, PNOF7S = 8 } pnof_functional;
@@ -230,7 +230,8 @@ pnof_status pnof_lagrangian_noalloc(pnof_ctx ctx, const pnof_problem* prob, cons
  * with events) forms the product of the reflectors in blocks of 128; the eigenvectors are then that
  * product times the tridiagonal solver's.  nbf < 3 or nbf > 2048 use rocSOLVER's dsyevd.  Scratch:
  * about 10 nbf^2 doubles from the context's workspace (grown by the context if the lent one is
- * smaller).  PNOF_E_EIG if a secular equation of the tridiagonal solver does not converge. */
+ * smaller).  PNOF_E_EIG if a secular equation of the tridiagonal solver does not converge, or
+ * where lambda or diag_prev is not finite. */
 pnof_status pnof_orbital_step(pnof_ctx ctx, int32_t nbf, const double* lambda, const double* C,
                               const double* diag_prev, double zeta, double* C_new, double* eps,
                               double* S_out);

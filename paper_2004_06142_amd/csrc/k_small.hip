@@ -809,7 +809,7 @@ __global__ void build_s_k(int nbf, const double* __restrict__ lam, const double*
     else {
       v = (p < q) ? (b - a) : (a - b);   // S_pq = lambda_qp - lambda_pq for p < q, mirrored
       if (zeta > 0.0)
-        while (fabs(v) > zeta) v /= 10.0;
+        while (fabs(v) > zeta && isfinite(v)) v /= 10.0;
     }
     S[i] = v;
     if (keep) keep[i] = v;

@@ -116,28 +116,32 @@ __device__ __forceinline__ double wsum(double v) { return wreduce(v, [](double a
 __device__ __forceinline__ double wprod(double v) { return wreduce(v, [](double a, double b) { return a * b; }); }
 __device__ __forceinline__ double wmax(double v) { return wreduce(v, [](double a, double b) { return fmax(a, b); }); }
 
-// Scale by the largest entry, and take each cut's coupling out of the two diagonal entries beside it.
+// Scale by the largest entry, and take each cut's coupling out of the two diagonal entries beside it.  A matrix that is
+// not finite is replaced by zero and reported (info): the merges place entries by comparing them, and none may be NaN.
 __global__ __launch_bounds__(1024) void dc_prep_k(DcWs w, const double* __restrict__ d, const double* __restrict__ e) {
   const int n = w.n, T = w.T, tid = threadIdx.x;
   __shared__ double red[16];
   double mx = 0.0;
+  int bad = 0;
   for (int i = tid; i < n; i += 1024) {
-    mx = fmax(mx, fabs(d[i]));
-    if (i + 1 < n) mx = fmax(mx, fabs(e[i]));
+    const double ei = i + 1 < n ? e[i] : 0.0;
+    mx = fmax(mx, fmax(fabs(d[i]), fabs(ei)));
+    if (!isfinite(d[i]) || !isfinite(ei)) bad = 1;
   }
+  bad = __syncthreads_or(bad);
   mx = wmax(mx);
   if ((tid & 63) == 0) red[tid >> 6] = mx;
   __syncthreads();
   if (tid < 64) {
     double v = tid < 16 ? red[tid] : 0.0;
     v = wmax(v);
-    if (tid == 0) red[0] = v > 0.0 ? v : 1.0;
+    if (tid == 0) red[0] = v > 0.0 && !bad ? fmax(v, 0x1p-1000) : 1.0;   // its reciprocal is finite
   }
   __syncthreads();
   const double sc = red[0], inv = 1.0 / sc;
   if (tid == 0) {
     w.scale[0] = sc;
-    w.info[0] = 0;
+    w.info[0] = bad ? 1 : 0;
   }
   const int nl = 1 << T;
   for (int i = tid; i < n; i += 1024) {
@@ -145,8 +149,8 @@ __global__ __launch_bounds__(1024) void dc_prep_k(DcWs w, const double* __restri
     double v = d[i] * inv;
     if (i == seg_lo(n, T, j) && j > 0) v -= fabs(e[i - 1] * inv);
     if (i == seg_lo(n, T, j + 1) - 1 && j + 1 < nl) v -= fabs(e[i] * inv);
-    w.dS[i] = v;
-    w.es[i] = i + 1 < n ? e[i] * inv : 0.0;
+    w.dS[i] = bad ? 0.0 : v;
+    w.es[i] = i + 1 < n && !bad ? e[i] * inv : 0.0;
   }
 }
 
