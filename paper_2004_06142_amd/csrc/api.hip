@@ -189,10 +189,12 @@ struct Plan {
   int ldk, ldx, ldxx, ldw, nact32;
   int ldb;      // bf16 family: row length of B as X reads it (nbf rounded up to 16 bytes)
   bool packb;   // bf16 B whose rows are not 16-byte aligned: X reads a padded copy of the chunk
+  bool ahead;   // bf16 family: a second buffer of XT, so that X runs one chunk ahead
   bool split;   // bf16 family
   bool f32;     // PNOF_FP32: the float64 path's kernels in float32
   int terms;    // 1 or 3
   int ksums;    // split: float32 sums of b^2 of a chunk at least, as far as its rows go (krows)
+  int ldbeta() const { return split ? nact32 : nact; }   // beta in float32; split: padded
   int krows(int np) const { return std::min(8, np / std::min(np, ksums)); }   // rows of one such sum at most
 };
 
@@ -217,7 +219,15 @@ int best_splits(int np, long long tiles, int slots, double fill, double tail = 0
   return best;
 }
 
-Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
+// Forms of a plan, for regions of memory that the first one does not fit (a workspace lent for an earlier plan, the
+// static array), each smaller than the one before:
+//   PLAN_PLAIN  X reads rows of B that are not 16-byte aligned as they are (register-staged, slower);
+//   PLAN_LEAN   and the partial sums of b and float64 Y of 1024 blocks, float64 chunks of the rows that fill the chip
+//               (with room for B in float64 in the limit on a chunk);
+//   PLAN_LEAST  and one buffer of XT: X of a chunk after Y of the one before.
+enum PlanForm { PLAN_FULL, PLAN_PLAIN, PLAN_LEAN, PLAN_LEAST };
+
+Plan make_plan(const pnof_problem* p, const pnof_tuning& tu, PlanForm form = PLAN_FULL) {
   Plan pl{};
   pl.nbf = p->nbf;
   pl.nact = p->npairs * (p->ncwo + 1) + p->nsingle;
@@ -238,8 +248,9 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   pl.ldxx = (int)round_up(pl.nact, 32);
   pl.ldw = (int)round_up(pl.nact, 32);
   pl.nact32 = (int)round_up(pl.nact, 32);
-  pl.ldb = (int)round_up(pl.nbf, 8);
+  pl.ldb = form == PLAN_FULL ? (int)round_up(pl.nbf, 8) : pl.nbf;
   pl.packb = pl.split && p->ints == PNOF_INTS_DF_BF16 && pl.ldb != pl.nbf;
+  pl.ahead = form != PLAN_LEAST;
   if (!is_df(p->ints)) { pl.pc = pl.ns2 = pl.ns3 = 1; pl.xv = pl.yv = 1; return pl; }
   // block tiles of the split contractions: the 256 x 256 tile (variant 3) halves the LDS and operand
   // traffic per product, and is the automatic choice when it pads the output no more than the 128
@@ -260,14 +271,16 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   long long pc = tu.pchunk > 0 ? tu.pchunk : std::max(64LL, (4096 + t1 - 1) / t1);
   const long long per_p = pl.split ? (long long)(2LL * pl.nact32 * pl.ldx + 2LL * pl.nact32 * pl.ldw) * 2 +
                                          (p->ints == PNOF_INTS_DF_F64 ? 4LL * pl.nbf * pl.nbf : 0)
-                                   : (long long)(pl.nact * pl.ldx + pl.nact * pl.ldw) * (pl.f32 ? 4 : 8);
+                                   : (long long)(pl.nact * pl.ldx + pl.nact * pl.ldw) * (pl.f32 ? 4 : 8) +
+                                         (form >= PLAN_LEAN && !pl.f32 && p->ints == PNOF_INTS_DF_BF16 ? 8LL * pl.nbf * pl.nbf : 0);
   const long long cap = std::max(1LL, (2LL << 30) / std::max(1LL, per_p));
   if (tu.pchunk <= 0) {
     // float64: chunks of equal length of at most 512 rows, or the rows that fill the chip where that is more (a
     // chunk's last blocks leave the chip partly idle: at 500 functions, 300 active, 2000 rows the Lagrangian takes
     // 15.1 ms in chunks of 103 rows, 13.1 of 250, 12.7 of 500; 64 functions, 32 active, 12000 rows 1.61 ms in
     // chunks of 500 rows, 0.91 of 4000)
-    if (!pl.split && !pl.f32) pc = cdiv(pl.naux, cdiv(pl.naux, std::max(1LL, std::min(cap, std::max(pc, 512LL)))));
+    if (!pl.split && !pl.f32 && form < PLAN_LEAN)
+      pc = cdiv(pl.naux, cdiv(pl.naux, std::max(1LL, std::min(cap, std::max(pc, 512LL)))));
     pc = std::min(pc, cap);
   }
   pc = std::min<long long>(pc, pl.naux);
@@ -285,6 +298,7 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
   pl.ns2 = tu.nsplit_b > 0 ? tu.nsplit_b
            : pl.split      ? best_splits(pl.pc, ntri, 512, 0.25, 0.1)
                            : best_splits(pl.pc, ntri, 768, 0.25);
+  if (form >= PLAN_LEAN && tu.nsplit_b <= 0) pl.ns2 = (int)auto2;
   pl.ns2 = std::min(pl.ns2, pl.pc);
   // Y: as many P-splits as fit the chip's resident blocks in one round (MI355X: 256 compute units;
   // the 128 x 128 bf16 tile runs two blocks per unit, the float64 tile of 128 x 64 three); the float32
@@ -294,6 +308,7 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu) {
                           : pl.f32 ? std::max(1LL, (1024 + t3 - 1) / t3)
                                    : best_splits(pl.pc, (long long)cdiv(pl.nbf, 128) * cdiv(pl.nact, 64), 768, 0.25);
   pl.ns3 = tu.nsplit_y > 0 ? tu.nsplit_y : (int)auto3;
+  if (form >= PLAN_LEAN && tu.nsplit_y <= 0 && !pl.split) pl.ns3 = (int)std::max(1LL, (1024 + t3 - 1) / t3);
   pl.ns3 = std::min(pl.ns3, pl.pc);
   return pl;
 }
@@ -323,7 +338,7 @@ Bufs carve(const Plan& pl, char* base) {
   const long long ny = (long long)pl.nbf * pl.nact;
   b.alpha = a.take<double>(n2);
   b.beta = a.take<double>(n2);
-  b.beta32 = a.take<float>((long long)pl.nact32 * pl.nact32);
+  b.beta32 = a.take<float>((long long)pl.ldbeta() * pl.ldbeta());
   b.HC = a.take<double>(ny);
   b.Hpp = a.take<double>(pl.nact);
   b.J = a.take<double>(n2);
@@ -349,7 +364,7 @@ Bufs carve(const Plan& pl, char* base) {
       b.Ypart64 = a.take<double>((long long)pl.ns3 * ny);
     } else {
       b.cth = a.take<u16>((long long)pl.nact32 * pl.ldk);
-      b.ctl = a.take<u16>((long long)pl.nact32 * pl.ldk);
+      if (pl.terms > 1 || pl.ahead) b.ctl = a.take<u16>((long long)pl.nact32 * pl.ldk);
       if (pl.terms > 1) {
         b.ch16 = a.take<u16>((long long)pl.nact32 * pl.ldk);
         b.cl16 = a.take<u16>((long long)pl.nact32 * pl.ldk);
@@ -357,11 +372,11 @@ Bufs carve(const Plan& pl, char* base) {
         b.colb = a.take<float>(4LL * pl.nact);
       }
       b.xth = a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldx);
-      b.xth2 = a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldx);
+      b.xth2 = pl.ahead ? a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldx) : b.xth;
       b.wh = a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldw);
       if (pl.terms > 1) {
         b.xtl = a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldx);
-        b.xtl2 = a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldx);
+        b.xtl2 = pl.ahead ? a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldx) : b.xtl;
         b.wl = a.take<u16>((long long)pl.pc * pl.nact32 * pl.ldw);
       }
       b.Ypart32 = a.take<float>((long long)pl.ns3 * ny);
@@ -378,6 +393,26 @@ Bufs carve(const Plan& pl, char* base) {
   }
   b.bytes = a.off + 256;
   return b;
+}
+
+// The first form of the plan that fits `bytes`; the least one, and false, if none does.
+bool fit_plan(const pnof_problem* prob, const pnof_tuning& tu, size_t bytes, Plan& pl) {
+  for (int f = PLAN_FULL; f <= PLAN_LEAST; ++f) {
+    pl = make_plan(prob, tu, (PlanForm)f);
+    if (carve(pl, nullptr).bytes <= bytes) return true;
+  }
+  return false;
+}
+// Plan for a region of `bytes` and nothing else: fewer rows of B per chunk until one fits.  What PLAN_LEAST saves makes
+// room for beta's padding and no more: the float32 sums of Y grow with the chunk.
+bool region_plan(const pnof_problem* prob, pnof_tuning tu, size_t bytes, Plan& pl) {
+  for (;;) {
+    pl = make_plan(prob, tu, PLAN_LEAN);
+    const long long pad = 4LL * pl.ldbeta() * pl.ldbeta() - round_up(4LL * pl.nact * pl.nact, 256);
+    if (carve(pl, nullptr).bytes <= bytes + std::max(0LL, pad) || pl.pc == 1) break;
+    tu.pchunk = std::max(1, pl.pc / 2);
+  }
+  return fit_plan(prob, tu, bytes, pl);
 }
 
 // Workspace: the caller's if large enough, else the context's own (grow-only).
@@ -445,38 +480,19 @@ pnof_status dprod(pnof_ctx ctx, int M, int N, int K, const double* A, long long 
 
 pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, const double* n,
                      const double* H, const void* ints, Req& r) {
-  Plan pl = make_plan(prob, ctx->tune);
-  Bufs b = carve(pl, nullptr);
-  char* ws = nullptr;
+  Plan pl;
+  char* ws = r.ws;
   pnof_status st = PNOF_OK;
   if (r.ws) {
-    // fit the caller's region: fewer rows of B per chunk until the plan's workspace fits.  The padded
-    // rows of B are not counted (they are an option: X also reads unaligned rows, more slowly), and
-    // used when there is room for them at that chunk length.
-    auto plain = [&](Plan q) {
-      q.packb = false;
-      q.ldb = q.nbf;
-      return q;
-    };
-    pnof_tuning tu = ctx->tune;
-    b = carve(plain(pl), nullptr);
-    while (b.bytes > r.ws_bytes && pl.pc > 1) {
-      tu.pchunk = std::max(1, pl.pc / 2);
-      pl = make_plan(prob, tu);
-      b = carve(plain(pl), nullptr);
-    }
-    const Bufs padded = carve(pl, nullptr);
-    if (padded.bytes <= r.ws_bytes) b = padded;
-    else pl = plain(pl);
-    if (b.bytes > r.ws_bytes)
+    if (!region_plan(prob, ctx->tune, r.ws_bytes, pl))
       return fail(ctx, PNOF_E_UNSUPPORTED,
-                  "the problem needs " + std::to_string(b.bytes) + " bytes of workspace, more than the " +
+                  "the problem needs " + std::to_string(carve(pl, nullptr).bytes) + " bytes of workspace, more than the " +
                       std::to_string(r.ws_bytes) + " available");
-    ws = r.ws;
-  } else if ((st = get_ws(ctx, b.bytes, &ws)) != PNOF_OK) {
-    return st;
+  } else {
+    pl = make_plan(prob, ctx->tune);
+    if ((st = get_ws(ctx, carve(pl, nullptr).bytes, &ws)) != PNOF_OK) return st;
   }
-  b = carve(pl, ws);
+  Bufs b = carve(pl, ws);
   hipStream_t s = ctx->stream;
   const int nbf = pl.nbf, nact = pl.nact;
   const long long n2 = (long long)nact * nact, ny = (long long)nbf * nact;
@@ -499,7 +515,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
   const OccLayout occ{n, pl.npairs, pl.ncwo, pl.nsingle};
 
   if (have_n) DEV_CHECK(ctx, coeffs(s, nact, pl.npairs, pl.ncwo, pl.nsingle, pl.functional, n, b.alpha, b.beta, b.beta32,
-                                pl.nact32));
+                                pl.ldbeta()));
   if (H) {
     // HC = H C_A ; Hpp = diag(C_A^T H C_A)
     RB_CHECK(dprod(ctx, nbf, nact, nbf, H, nbf, 1, C, nbf, 1, b.HC, nact, 1));
@@ -546,7 +562,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
                             : static_cast<const void*>(static_cast<const double*>(ints) + p0 * bsz);
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_X, df_fp_gemm1(s, nbf, nact, np, b.Ct32, pl.ldk, Bc, bb, b.XT32, pl.ldx)));
         DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_B, df_fp_gemm2<float>(s, nbf, nact, np, ns2, b.Ct32, pl.ldk, b.XT32, pl.ldx,
-                                                                    b.beta32, pl.nact32, b.Kpart, p0 == 0, Dc, b.W32, pl.ldw)));
+                                                                    b.beta32, pl.ldbeta(), b.Kpart, p0 == 0, Dc, b.W32, pl.ldw)));
         if (want_y) {
           DEV_CHECK(ctx, add_diag_f32(s, nact, np, Dc, occ, b.dbuf, b.W32, pl.ldw));
           DEV_CHECK(ctx, TIMED(ctx, PNOF_STAGE_Y, df_fp_gemm3(s, nbf, nact, np, ns3, b.XT32, pl.ldx, b.W32, pl.ldw,
@@ -664,7 +680,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
                                        (long long)pl.nact32 * pl.ldw, b.bnd, c));
           if (two) DEV_CHECK(ctx, hipEventRecord(ev_d, sa));
         }
-        if (c + 1 < nchunk) RB_CHECK(run_x(c + 1));
+        if (c + 1 < nchunk && pl.ahead) RB_CHECK(run_x(c + 1));
         if (want_y) {
           if (two) {
             DEV_CHECK(ctx, hipStreamWaitEvent(s, ev_d, 0));
@@ -688,6 +704,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
                                      b.beta, nullptr, nullptr, XT.hi, XT.lo, pl.ldx, (long long)pl.nact32 * pl.ldx, r.Jq,
                                      r.Kq, r.Fq, b.bnd, c, c == 0));
         }
+        if (c + 1 < nchunk && !pl.ahead) RB_CHECK(run_x(c + 1));
       }
       if (want_y && two) DEV_CHECK(ctx, hipStreamWaitEvent(s, ev_r, 0));
     }
