@@ -403,6 +403,13 @@ bool fit_plan(const pnof_problem* prob, const pnof_tuning& tu, size_t bytes, Pla
   }
   return false;
 }
+// Plan of the calls that may allocate: a lent workspace is used if any form fits it, otherwise the full plan
+// takes the context's own.
+Plan call_plan(pnof_ctx ctx, const pnof_problem* prob) {
+  Plan pl;
+  if (ctx->ext_ws && fit_plan(prob, ctx->tune, ctx->ext_bytes, pl)) return pl;
+  return make_plan(prob, ctx->tune);
+}
 // Plan for a region of `bytes` and nothing else: fewer rows of B per chunk until one fits.  What PLAN_LEAST saves makes
 // room for beta's padding and no more: the float32 sums of Y grow with the chunk.
 bool region_plan(const pnof_problem* prob, pnof_tuning tu, size_t bytes, Plan& pl) {
@@ -489,7 +496,7 @@ pnof_status run_step(pnof_ctx ctx, const pnof_problem* prob, const double* C, co
                   "the problem needs " + std::to_string(carve(pl, nullptr).bytes) + " bytes of workspace, more than the " +
                       std::to_string(r.ws_bytes) + " available");
   } else {
-    pl = make_plan(prob, ctx->tune);
+    pl = call_plan(ctx, prob);
     if ((st = get_ws(ctx, carve(pl, nullptr).bytes, &ws)) != PNOF_OK) return st;
   }
   Bufs b = carve(pl, ws);
@@ -1332,7 +1339,7 @@ pnof_status pnof_bind_integrals(pnof_ctx ctx, const pnof_problem* prob, const vo
   if (st != PNOF_OK) return st;
   if ((st = check_ptrs(ctx, {ints}, "pnof_bind_integrals")) != PNOF_OK) return st;
   if ((st = check_ctx(ctx)) != PNOF_OK) return st;
-  const Plan pl = make_plan(prob, ctx->tune);
+  const Plan pl = call_plan(ctx, prob);
   if (!is_df(pl.ints) || pl.terms <= 1) return PNOF_OK;
   const size_t nw = 2 * (size_t)cdiv(pl.naux, pl.pc);
   if (nw > bd.cap) {
@@ -1360,7 +1367,7 @@ pnof_status pnof_get_plan(pnof_ctx ctx, const pnof_problem* prob, pnof_tuning* o
   pnof_status st = check_problem(ctx, prob);
   if (st != PNOF_OK) return st;
   if (!out) return fail(ctx, PNOF_E_ARG, "output is NULL");
-  const Plan pl = make_plan(prob, ctx->tune);
+  const Plan pl = call_plan(ctx, prob);
   *out = pnof_tuning{pl.pc, pl.ns2, pl.ns3, pl.xv, pl.yv};
   return PNOF_OK;
 }

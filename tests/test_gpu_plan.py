@@ -1,4 +1,5 @@
-"""Launch plans: rows of B per chunk, and problems that just fit the static array of
+"""Launch plans: rows of B per chunk, workspaces that were lent at the size of an earlier layout (more partial sums,
+no copy of B's rows, shorter float64 chunks), and problems that just fit the static array of
 pnof_lagrangian_noalloc.  Bars between two plans of one problem, which differ in the order of sums: 1e-11 of the
 largest element in float64; 2e-6 in the split and float32 modes (8 ulp of float32)."""
 import ctypes
@@ -44,6 +45,29 @@ def test_float64_chunk_fills_the_chip(ctx, nbf, naux, npairs, ncwo, pchunk):
     """Blocks of 64 active orbitals and 64 functions: 4096 of them, or 512 rows, in chunks of equal length."""
     prob = P.problem(nbf, naux, npairs, ncwo, P.PNOF7, P.FP64, P.INTS_DF_F64)
     assert ctx.plan(prob)["pchunk"] == pchunk
+
+
+LENT = [(300, 1200, 50, 5, P.FP64, "f64", 340554368), (300, 1200, 50, 5, P.FP64, "bf16", 458634368),
+        (70, 5000, 9, 3, P.FP32, "bf16", 65120768), (213, 900, 25, 4, P.BF16_SPLIT, "bf16", 408425984),
+        (300, 1200, 50, 5, P.BF16_SPLIT, "bf16", 713820160), (213, 900, 25, 4, P.BF16, "bf16", 275598592)]
+
+
+@pytest.mark.parametrize("nbf,naux,npairs,ncwo,prec,b,lent", LENT)
+def test_workspace_lent_at_an_earlier_size(nbf, naux, npairs, ncwo, prec, b, lent):
+    prob, C, n, H, B = _inputs(nbf, naux, npairs, ncwo, prec, b)
+    ref = P.Context(0).lagrangian(prob, C, n, H, B, jk=True)
+    ctx = P.Context(0)
+    ws = torch.empty(lent + 256, dtype=torch.uint8, device=DEV)
+    base = (ws.data_ptr() + 255) // 256 * 256
+    assert P.lib().pnof_set_workspace(ctx.handle, ctypes.c_void_p(base), lent) == 0
+    small = _inputs(24, 96, 3, 3, prec, b)
+    ctx.lagrangian(*small)   # streams and handles of the context
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    out = ctx.lagrangian(prob, C, n, H, B, jk=True)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 32 << 20
+    _same(out, ref, prec)
 
 
 EDGE = [(1655, 151, 3, P.FP64, "f64"), (1784, 172, 3, P.FP32, "bf16"), (2128, 137, 3, P.BF16_SPLIT, "bf16"),
