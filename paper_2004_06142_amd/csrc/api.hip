@@ -412,7 +412,7 @@ Plan call_plan(pnof_ctx ctx, const pnof_problem* prob) {
 }
 // Plan for a region of `bytes` and nothing else: fewer rows of B per chunk until one fits.  What PLAN_LEAST saves makes
 // room for beta's padding and no more: the float32 sums of Y grow with the chunk.  In float64 the rows are raised to
-// the most that fit (413 functions, 246 active in 64 MiB: 12 rows by halving 413, 22 here).
+// the most that fit (413 functions, 246 active in 64 MiB: 12 rows by halving 413, 17.3 ms; 22 rows, 10.7 ms).
 bool region_plan(const pnof_problem* prob, pnof_tuning tu, size_t bytes, Plan& pl) {
   const bool tuned = tu.pchunk > 0;
   int above = make_plan(prob, tu).pc + 1;   // a chunk length that is too long

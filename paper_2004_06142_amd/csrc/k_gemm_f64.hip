@@ -384,13 +384,13 @@ __device__ __forceinline__ int xcd_item(int total) {
   return w < total ? w : -1;
 }
 
-constexpr int XM = 64, XN = 128;   // X: active orbitals x stacked rows (P, mu)
+constexpr int XM = 64;             // X: active orbitals x 128 or 64 stacked rows (P, mu)
 constexpr int BT = 64;             // b: square tiles on and below the diagonal
 constexpr int YN = 64;             // Y: 128 or 64 mu x 64 active orbitals
 
 // gemm1: XT[P][p][mu] = sum_nu Ct[p][nu] B_P[mu][nu] over the stacked rows (P, mu) of the chunk, B read as
 // stored (bf16 or float64) and rounded to T.
-template <typename T, typename SB>
+template <typename T, typename SB, int XN>
 __global__ __launch_bounds__(256, 3) void df_x_kernel(int nbf, int nact, int np, const T* __restrict__ Ct, int ldk,
                                                    const SB* __restrict__ Bc, T* __restrict__ XT, int ldx) {
   __shared__ FpSlab<T, XM> sa[2];
@@ -612,18 +612,24 @@ namespace {
 inline dim3 xcd_grid(long long items) { return dim3((unsigned)(cdiv(items, 8) * 8)); }
 }  // namespace
 
+// float64 B: tiles of 64 rows while those of 128 make at most two blocks per compute unit, of the three that fit (600
+// functions, 300 active, 12 rows of B, which are 285 tiles of 128: 93 us, 71 with tiles of 64).
+constexpr int X_WIDE = 512;
 template <typename T>
 hipError_t df_fp_gemm1(hipStream_t s, int nbf, int nact, int np, const T* Ct, int ldk, const void* Bchunk, int b_is_bf16,
                        T* XT, int ldx) {
   if (np <= 0) return hipSuccess;
   if ((long long)np * nbf >= (1LL << 31)) return hipErrorInvalidValue;
-  const dim3 grid = xcd_grid((long long)cdiv(nact, XM) * cdiv((long long)np * nbf, XN));
+  const long long rows = (long long)np * nbf, wide = cdiv(nact, XM) * (long long)cdiv(rows, 128);
   if (b_is_bf16)
-    hipLaunchKernelGGL((df_x_kernel<T, u16>), grid, dim3(256), 0, s, nbf, nact, np, Ct, ldk, static_cast<const u16*>(Bchunk),
-                       XT, ldx);
-  else
-    hipLaunchKernelGGL((df_x_kernel<T, double>), grid, dim3(256), 0, s, nbf, nact, np, Ct, ldk,
+    hipLaunchKernelGGL((df_x_kernel<T, u16, 128>), xcd_grid(wide), dim3(256), 0, s, nbf, nact, np, Ct, ldk,
+                       static_cast<const u16*>(Bchunk), XT, ldx);
+  else if (wide > X_WIDE)
+    hipLaunchKernelGGL((df_x_kernel<T, double, 128>), xcd_grid(wide), dim3(256), 0, s, nbf, nact, np, Ct, ldk,
                        static_cast<const double*>(Bchunk), XT, ldx);
+  else
+    hipLaunchKernelGGL((df_x_kernel<T, double, 64>), xcd_grid((long long)cdiv(nact, XM) * cdiv(rows, 64)), dim3(256), 0, s, nbf,
+                       nact, np, Ct, ldk, static_cast<const double*>(Bchunk), XT, ldx);
   return hipGetLastError();
 }
 template <typename T>
