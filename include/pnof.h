@@ -85,7 +85,7 @@ typedef enum { PNOF5 = 5, PNOF7 = 7, PNOF7S = 8 } pnof_functional;
  *                    of |B| and |C|; b and Y take 3 fp16 products each (hi*hi, hi*lo, lo*hi).  A
  *                    float64 B is carried as an fp16 pair too (X then takes 3 fp16 products).  K sums
  *                    b^2 in float32 over at most 8 rows (the share of a chunk's rows that each of
- *                    1024 blocks would take, where that is less) and Y its products over the rows of
+ *                    1024 blocks, or of nsplit_b, would take, where that is less) and Y its products over the rows of
  *                    one P-split of one chunk, then in float64; D and J = D^T D are float64.  The energy is corrected to first
  *                    order with 4 <Y_2e, C_A - C~> in float64.
  * Energies, lambda, J = D^T D, the eigensolver and all reductions are float64 in every mode. */

@@ -505,40 +505,6 @@ __device__ __forceinline__ int row1_of(int i) {
   return ((threadIdx.x >> 6) / WGN) * (BM / WGM) + 16 * i + (threadIdx.x & 15);
 }
 
-// The 8 x 8 blocks of 16-bit pairs (hi, lo) over eight consecutive lanes' eight elements, transposed: element e
-// of lane l goes to element l % 8 of lane l - l % 8 + e.
-template <int M>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
-  if constexpr (M == 4)   // l ^ 7, then l ^ 3
-    return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
-  else
-    return __builtin_amdgcn_update_dpp(0, (int)v, M == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
-}
-template <int M>
-__device__ __forceinline__ void transpose_step(uint32_t (&v)[8]) {
-  const bool up = threadIdx.x & M;
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-    if ((r & M) == 0) {
-      const uint32_t other = lane_xor<M>(up ? v[r] : v[r | M]);
-      if (up) v[r] = other;
-      else v[r | M] = other;
-    }
-}
-__device__ __forceinline__ void transpose8(u32x4& hi, u32x4& lo) {
-  uint32_t v[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = __builtin_amdgcn_perm(hi[e >> 1], lo[e >> 1], e & 1 ? 0x07060302 : 0x05040100);
-  transpose_step<1>(v);
-  transpose_step<2>(v);
-  transpose_step<4>(v);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    lo[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x05040100);
-    hi[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x07060302);
-  }
-}
-
 // Lower-triangle tile t of a tt x tt tiling, ordered by column (tiles sharing tn are consecutive,
 // so the blocks an XCD holds at once read few distinct column panels).
 __device__ __forceinline__ void tri_tile(int t, int tt, int& tm, int& tn) {
@@ -698,22 +664,24 @@ __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = n
 // over the successive P-chunks of one call, the first of which stores: kset), D[P][p] = b_pp, W_P = b o beta
 // as a hi/lo pair, written only as the transposed image of each tile: the TT x TT blocks on and above the
 // diagonal, which gemm3 reads.
-// 4 waves of (TT / 2)^2, two blocks per compute unit: a 64 x 64 wave reads 16 KB of LDS per k-tile for 48
-// products, an 8-wave 64 x 32 form 12 KB for 24, which LDS bandwidth bounds, and while one block forms K and W the
-// other keeps the matrix cores busy.  Against 8 waves and one block, b over the step: 1200 functions 42.7 ->
+// 2 x WGN waves.  128 tile, WGN 2: 4 waves of 64 x 64, two blocks per compute unit: such a wave reads 16 KB of LDS per
+// k-tile for 48 products, a 64 x 32 one 12 KB for 24, which LDS bandwidth bounds, and while one block forms K and W
+// the other keeps the matrix cores busy; against 8 waves and one block, b over the step: 1200 functions 42.7 ->
 // 36.1 ms, 500 functions (300 active, 2000 rows) 1.40 -> 0.91, 413 functions 0.85 -> 0.55 (with the splits that the
-// planner takes for it).
-// The sums of b^2 are float32 over at most krows rows (at most 8), then float64 in Kpart: each block adds to its own partial
-// sums only, with atomics, which need no wait (as loads and stores, 1200 functions in 164 splits 53.0 ms, with
+// planner takes for it).  WGN 4: 8 waves of 64 x 32, for launches whose blocks wait rather than compute (G2_FEW).
+// The sums of b^2 are float32 over at most krows rows (at most 8), then float64 in Kpart: each block adds to its own
+// partial sums only, with atomics, which need no wait (as loads and stores, 1200 functions in 164 splits 53.0 ms, with
 // atomics 40.0).
 // TT: the square tile (128, or 64 for the short active spaces of batch instances, with 4 waves).
 // BATCH: one launch covers every P of the problem (K is stored); the blocks on the diagonal hold W[p][q]
-// itself, in place of its image (b_pq and b_qp differ in the last bits), by a transpose between lanes (as 2-byte
-// stores of W[p][q] and its image in every tile, b of 64 problems of 40 to 300 functions took 1.98 ms).
-template <int TERMS, int TT = T2, bool BATCH = false, bool EXT = false, int BUDGET = 0>
+// itself, in place of its image (b_pq and b_qp differ in the last bits): their products are formed transposed, so that
+// a lane holds eight consecutive q (by a transpose between lanes, 4 problems of 30 functions took 206 us, now 172; 64 of
+// 50 functions 244 and 228; as 2-byte stores of W[p][q] and its image in every tile, b of 64 problems of 40 to 300
+// functions took 1.98 ms).
+template <int TERMS, int TT = T2, bool BATCH = false, int WGN = 2, bool EXT = false, int BUDGET = 0>
 __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = nullptr) {
   constexpr bool LO = TERMS >= 3;
-  constexpr int WGN = 2, NI = TT / 32, MI = TT / 32;
+  constexpr int NI = TT / (16 * WGN), MI = TT / 32;
   const int nbf = g.nbf, nact = g.nact, np = g.np, nsplit = g.nsplit, ldw = g.ldw, ldx = g.ldx;
   const int tt = (nact + TT - 1) / TT;
   const int ntri = tt * (tt + 1) / 2;
@@ -729,104 +697,117 @@ __device__ __forceinline__ void gemm2_body(int w, const G2Args& g, void* ext = n
     invB = sc.invB;
     wmul = sc.wmul;
   }
-  // beta (symmetric, nact32 x nact32) of this lane's accumulator positions.  The 64 tile keeps it in registers
-  // for the whole P-range; in the 128 tile, whose sums of b^2 and accumulators fill them, each P reads it anew
-  constexpr bool BREG = TT == 64;
-  auto beta8 = [&](int h, int jn, f32x4(&v)[2]) {
-    const int p0 = m0 + row8_of<TT, 2, WGN>(h), q = n0 + col_of<TT, 2, WGN>(jn);
-    if (p0 < g.ws.nact32 && q < g.ws.nact32) {
-      const f32x4* src = reinterpret_cast<const f32x4*>(g.beta32 + (long long)q * g.ws.nact32 + p0);
-      v[0] = src[0] * wmul;
-      v[1] = src[1] * wmul;
-    } else v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  };
-  f32x4 bet[BREG ? MI / 2 : 1][BREG ? NI : 1][2];
-  if constexpr (BREG)
-#pragma unroll
-    for (int h = 0; h < MI / 2; ++h)
-#pragma unroll
-      for (int jn = 0; jn < NI; ++jn) beta8(h, jn, bet[h][jn]);
-  f32x4 kacc[MI][NI], acc[MI][NI];
-  zero(kacc);
   const bool diag = (tm == tn);
   const int wrows = BATCH ? nact : g.ws.nact32;
-  int kleft = BATCH ? pe - pb : min(g.krows, pe - pb);   // rows of P left for the float32 sums
-  bool kset = BATCH || g.kset;
-  auto epi = [&](int seg, f32x4(&a)[MI][NI]) {
-    const int P = pb + seg;
-    u16* Wh = g.w_hi + (long long)P * g.ws.nact32 * ldw;
-    u16* Wl = LO ? g.w_lo + (long long)P * g.ws.nact32 * ldw : nullptr;
-#pragma unroll
-    for (int h = 0; h < MI / 2; ++h)
-#pragma unroll
-      for (int jn = 0; jn < NI; ++jn) {
-        const int p0 = m0 + row8_of<TT, 2, WGN>(h), q = n0 + col_of<TT, 2, WGN>(jn);
-        float wv[8];
-        f32x4 bv[2];
-        if constexpr (BREG) {
-          bv[0] = bet[h][jn][0];
-          bv[1] = bet[h][jn][1];
-        } else beta8(h, jn, bv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int i = 2 * h + (e >> 2), j = e & 3;
-          const float b = a[i][jn][j] * invB;
-          kacc[i][jn][j] += b * b;
-          wv[e] = a[i][jn][j] * bv[e >> 2][j];
-          if (diag && p0 + e == q && q < nact) g.Dc[(long long)P * nact + q] = (double)b;
-        }
-        u32x4 hi, lo;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          uint32_t x, y = 0;
-          if constexpr (LO) split2_f16(wv[2 * e], wv[2 * e + 1], x, y);
-          else x = cvt2_bf16(wv[2 * e], wv[2 * e + 1]);
-          hi[e] = x;
-          lo[e] = y;
-        }
-        // the transposed image W[q][p0 .. p0 + 7] (rows and columns from nact to nact32 receive zeros; a batch
-        // clears them once, when its plan is made)
-        int wr = q, wc = p0;
-        if (BATCH && diag) {
-          transpose8(hi, lo);
-          const int lane = threadIdx.x & 63;
-          wr = p0 + (lane & 7);
-          wc = q - (lane & 7);
-        }
-        if (wr < wrows && wc < wrows) {
-          const long long o = (long long)wr * ldw + wc;
-          *reinterpret_cast<u32x4*>(Wh + o) = hi;
-          if (LO) *reinterpret_cast<u32x4*>(Wl + o) = lo;
-        }
-      }
-    if (--kleft > 0) return;
-    double* Kp = g.Kpart + (long long)s * nact * nact;
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int jn = 0; jn < NI; ++jn)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int p = m0 + row8_of<TT, 2, WGN>(i >> 1) + 4 * (i & 1) + j, q = n0 + col_of<TT, 2, WGN>(jn);
-          if (p < nact && q <= p) {
-            double* k = Kp + (long long)p * nact + q;
-            if (kset) *k = (double)kacc[i][jn][j];
-            else unsafeAtomicAdd(k, (double)kacc[i][jn][j]);   // nobody else's: an add that needs no wait
-          }
-        }
-    zero(kacc);
-    kset = false;
-    kleft = min(g.krows, pe - 1 - P);
-  };
-  constexpr int S = ring_depth(TT, TT, LO, LO, BUDGET > 0 ? BUDGET : 81920);
+  constexpr int S = ring_depth(TT, TT, LO, LO, BUDGET > 0 ? BUDGET : WGN == 2 ? 81920 : 163840);
   auto& sm = ring_of<Ring<TT, TT, LO, LO, S>, EXT>(ext);
   auto A = [&](int) { return DOpnd{g.ct_hi, g.ct_lo, g.ldk, g.ws.ct_bytes}; };
   auto B = [&](int seg) {
     const long long off = (long long)(pb + seg) * g.ws.nact32 * ldx;
     return DOpnd{g.xt_hi + off, LO ? g.xt_lo + off : nullptr, ldx, g.ws.xt_bytes - 2 * off};
   };
-  mainloop_dl<TT, TT, LO, LO, S, false, false, true, LO, 2, WGN, false, false, 1>(sm, pe - pb, nbf, m0, n0, A, B, acc,
-                                                                                 epi);
+  // LAY as in mainloop_dl: runs (u, v) of eight elements along p (1) or q (2), from r0(u, v) on, at q or p c(u, v)
+  auto run = [&](auto lay) {
+    constexpr int LAY = decltype(lay)::value;
+    constexpr int NU = LAY == 1 ? MI / 2 : MI, NV = LAY == 1 ? NI : NI / 2;
+    auto r0 = [&](int u, int v) { return LAY == 1 ? m0 + row8_of<TT, 2, WGN>(u) : n0 + col8_of<TT, 2, WGN>(v); };
+    auto c = [&](int u, int v) { return LAY == 1 ? n0 + col_of<TT, 2, WGN>(v) : m0 + row1_of<TT, 2, WGN>(u); };
+    auto at = [&](f32x4(&a)[MI][NI], int u, int v, int e) -> f32x4& {
+      return LAY == 1 ? a[2 * u + (e >> 2)][v] : a[u][2 * v + (e >> 2)];
+    };
+    // beta (symmetric, nact32 x nact32) of this lane's runs.  With 32 x 32 and 64 x 32 elements per wave it is kept in
+    // registers for the whole P-range; with 64 x 64, whose sums of b^2 and accumulators fill them, each P reads it anew
+    constexpr bool BREG = MI * NI <= 8;
+    auto beta8 = [&](int u, int v, f32x4(&b)[2]) {
+      const int p0 = r0(u, v), q = c(u, v);
+      if (p0 < g.ws.nact32 && q < g.ws.nact32) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(g.beta32 + (long long)q * g.ws.nact32 + p0);
+        b[0] = src[0] * wmul;
+        b[1] = src[1] * wmul;
+      } else b[0] = b[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    f32x4 bet[BREG ? NU : 1][BREG ? NV : 1][2];
+    if constexpr (BREG)
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) beta8(u, v, bet[u][v]);
+    f32x4 kacc[MI][NI], acc[MI][NI];
+    zero(kacc);
+    bool kset = BATCH || g.kset;
+    auto add_k = [&]() {   // to the block's own partial sums
+      double* Kp = g.Kpart + (long long)s * nact * nact;
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int x = r0(u, v) + e, y = c(u, v), p = LAY == 1 ? x : y, q = LAY == 1 ? y : x;
+            if (p < nact && q <= p) {
+              double* k = Kp + (long long)p * nact + q;
+              const double sum = (double)at(kacc, u, v, e)[e & 3];
+              if (kset) *k = sum;
+              else unsafeAtomicAdd(k, sum);   // nobody else's: an add that needs no wait
+            }
+          }
+    };
+    int kleft = min(g.krows, pe - pb);   // rows of P left for the float32 sums
+    auto epi = [&](int seg, f32x4(&a)[MI][NI]) {
+      const int P = pb + seg;
+      u16* Wh = g.w_hi + (long long)P * g.ws.nact32 * ldw;
+      u16* Wl = LO ? g.w_lo + (long long)P * g.ws.nact32 * ldw : nullptr;
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          const int r = r0(u, v), cc = c(u, v);
+          float wv[8];
+          f32x4 bv[2];
+          if constexpr (BREG) {
+            bv[0] = bet[u][v][0];
+            bv[1] = bet[u][v][1];
+          } else beta8(u, v, bv);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float x = at(a, u, v, e)[e & 3], b = x * invB;
+            at(kacc, u, v, e)[e & 3] += b * b;
+            wv[e] = x * bv[e >> 2][e & 3];
+            if (diag && r + e == cc && cc < nact) g.Dc[(long long)P * nact + cc] = (double)b;
+          }
+          u32x4 hi, lo;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            uint32_t x, y = 0;
+            if constexpr (LO) split2_f16(wv[2 * e], wv[2 * e + 1], x, y);
+            else x = cvt2_bf16(wv[2 * e], wv[2 * e + 1]);
+            hi[e] = x;
+            lo[e] = y;
+          }
+          // rows and columns from nact to nact32 receive zeros; a batch clears them once, when its plan is made
+          if (cc < wrows && r < wrows) {
+            const long long o = (long long)cc * ldw + r;
+            *reinterpret_cast<u32x4*>(Wh + o) = hi;
+            if (LO) *reinterpret_cast<u32x4*>(Wl + o) = lo;
+          }
+        }
+      if (!BATCH && --kleft <= 0) {
+        add_k();
+        zero(kacc);
+        kset = false;
+        kleft = min(g.krows, pe - 1 - P);
+      }
+    };
+    mainloop_dl<TT, TT, LO, LO, S, false, false, true, LO, 2, WGN, false, 0, LAY>(sm, pe - pb, nbf, m0, n0, A, B, acc, epi,
+                                                                               [&](int r) { return n0 + r; });
+    if (BATCH) add_k();
+  };
+  if constexpr (BATCH)
+    if (diag) {
+      run(std::integral_constant<int, 2>{});
+      return;
+    }
+  run(std::integral_constant<int, 1>{});
 }
 
 // gemm3: Ypart[s][mu][q] = sum_{P in s} sum_r XT_P[r][mu] W_P[q][r].  XT is read as a col operand,
@@ -887,11 +868,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm1_kernel(G1Args g) {
   if (w < 0) return;
   gemm1_body<TERMS, BLO, G1M, G1N, WGM, WGN, MINB, VEC>(w, g);
 }
-template <int TERMS>
-__global__ __launch_bounds__(256, 2) void gemm2_kernel(G2Args g) {
+template <int TERMS, int WGN>
+__global__ __launch_bounds__(128 * WGN, WGN == 2 ? 2 : 1) void gemm2_kernel(G2Args g) {
   const int w = xcd_item(g2_items(g, T2));
   if (w < 0) return;
-  gemm2_body<TERMS>(w, g);
+  gemm2_body<TERMS, T2, false, WGN>(w, g);
 }
 template <int TERMS, int G3M, int G3N, int WGM, int WGN, int MINB>
 __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm3_kernel(G3Args g) {
@@ -914,14 +895,14 @@ __global__ __launch_bounds__(256, 2) void gemm1_grouped(const G1Args* __restrict
   const G1Args g = tab[i];
   gemm1_body<TERMS, false, TM, 128, 2, 2, 2, true, true>(w - off[i], g);
 }
-template <int TERMS, int TT>
-__global__ __launch_bounds__(256, 2) void gemm2_grouped(
+template <int TERMS, int TT, int WGN>
+__global__ __launch_bounds__(128 * WGN, WGN == 2 ? 2 : 1) void gemm2_grouped(
     const G2Args* __restrict__ tab, const int* __restrict__ off, int ninst, int total) {
   const int w = xcd_item(total);
   if (w < 0) return;
   const int i = find_instance(off, ninst, w);
   const G2Args g = tab[i];
-  gemm2_body<TERMS, TT, true>(w - off[i], g);
+  gemm2_body<TERMS, TT, true, WGN>(w - off[i], g);
 }
 template <int TERMS, int TN, int WB>
 __global__ __launch_bounds__(256, 2) void gemm3_grouped(const G3Args* __restrict__ tab, const int* __restrict__ off,
@@ -1026,7 +1007,7 @@ __device__ __forceinline__ void persist_item(const PArgs& a, int i, int ph, int 
     case PH_B: {
       const G2Args g = a.g2[i];
       if (idx == 0) bdev::hpp(d, 0, 1);
-      else gemm2_body<3, 64, true, true, PBUDGET>(idx - 1, g, lds);
+      else gemm2_body<3, 64, true, 2, true, PBUDGET>(idx - 1, g, lds);
       break;
     }
     case PH_DA:
@@ -1246,6 +1227,11 @@ hipError_t df_bf16_gemm1(hipStream_t s, int nbf, int nact, int np, int terms, Sp
   return hipGetLastError();
 }
 
+// b's 128 tile: 8 waves and one block per compute unit up to this many blocks (at most one for each unit, bound by the
+// length of a block: a batch of one problem of 40 functions 180 us, 220 with 4 waves) and with one product per term
+// (LDS bounds neither: 500 functions, 300 active 2.67 ms, 2.83 with 4 waves); otherwise 4 waves and two blocks (500
+// functions in the split mode 3.71 ms, 3.75 with 8 waves; 12 problems of 520 functions 11.61 and 11.89 ms).
+constexpr int G2_FEW = 256;
 hipError_t df_bf16_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, int terms, SplitPtr Ct, int ldk,
                          SplitPtr XT, int ldx, const float* beta32, double* Kpart, int kset, int krows, double* Dchunk,
                          u16* W_hi, u16* W_lo, int ldw, const WsDims& d, const uint32_t* bnd, int chunk) {
@@ -1255,9 +1241,11 @@ hipError_t df_bf16_gemm2(hipStream_t s, int nbf, int nact, int np, int nsplit, i
   if (ldk % 32 || ldx % 32 || ldw % 32 || !al16(Ct.hi) || !al16(Ct.lo) || !al16(XT.hi) || !al16(XT.lo) || !al16(W_hi) ||
       !al16(W_lo))
     return hipErrorInvalidValue;
-  const dim3 grid = xcd_grid(g2_items(g, T2)), block(256);
-  if (terms == 1) hipLaunchKernelGGL(gemm2_kernel<1>, grid, block, 0, s, g);
-  else hipLaunchKernelGGL(gemm2_kernel<3>, grid, block, 0, s, g);
+  const int items = g2_items(g, T2);
+  const dim3 grid = xcd_grid(items);
+  if (terms == 1) hipLaunchKernelGGL((gemm2_kernel<1, 4>), grid, dim3(512), 0, s, g);
+  else if (items <= G2_FEW) hipLaunchKernelGGL((gemm2_kernel<3, 4>), grid, dim3(512), 0, s, g);
+  else hipLaunchKernelGGL((gemm2_kernel<3, 2>), grid, dim3(256), 0, s, g);
   return hipGetLastError();
 }
 
@@ -1309,11 +1297,12 @@ hipError_t df_bf16_gemm2_grouped(hipStream_t s, int ninst, int total, int terms,
   if (total <= 0) return hipSuccess;
   const dim3 gr = xcd_grid(total);
   if (tile == 64) {
-    if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
-    else hipLaunchKernelGGL((gemm2_grouped<3, 64>), gr, dim3(256), 0, s, tab, off, ninst, total);
+    if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 64, 2>), gr, dim3(256), 0, s, tab, off, ninst, total);
+    else hipLaunchKernelGGL((gemm2_grouped<3, 64, 2>), gr, dim3(256), 0, s, tab, off, ninst, total);
   } else {
-    if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 128>), gr, dim3(256), 0, s, tab, off, ninst, total);
-    else hipLaunchKernelGGL((gemm2_grouped<3, 128>), gr, dim3(256), 0, s, tab, off, ninst, total);
+    if (terms == 1) hipLaunchKernelGGL((gemm2_grouped<1, 128, 4>), gr, dim3(512), 0, s, tab, off, ninst, total);
+    else if (total <= G2_FEW) hipLaunchKernelGGL((gemm2_grouped<3, 128, 4>), gr, dim3(512), 0, s, tab, off, ninst, total);
+    else hipLaunchKernelGGL((gemm2_grouped<3, 128, 2>), gr, dim3(256), 0, s, tab, off, ninst, total);
   }
   return hipGetLastError();
 }

@@ -1,6 +1,6 @@
 """How many rows of P one float32 sum of b^2 covers in the mixed precision (the sums of those are float64), where
 B_P = a_P 1 and C = 1 make every b exactly a_P: a_P = 2^-13 disappears beside a_P = 1 within a sum, so that K tells
-the rows per sum.  The bound is the even share of a chunk's rows among 1024 blocks, and 8 (500 functions: chunks of 342 rows, 6 tiles).  Exact apart from that:
+the rows per sum.  The bound is the even share of a chunk's rows among 1024 blocks, or among the splits that were set, and 8 (500 functions: chunks of 342 rows, 6 tiles).  Exact apart from that:
 all factors are powers of two."""
 import pytest
 import torch
@@ -12,7 +12,7 @@ DEV = torch.device("cuda", 0)
 
 
 # nbf, naux, npairs, ncwo, tuning, rows per sum at most
-SHAPES = [(200, 800, 20, 4, {}, 1), (300, 1200, 24, 4, {}, 1), (500, 1000, 50, 5, {}, 2), (200, 800, 20, 4, {"nsplit_b": 3}, 1),
+SHAPES = [(200, 800, 20, 4, {}, 1), (300, 1200, 24, 4, {}, 1), (500, 1000, 50, 5, {}, 2), (200, 800, 20, 4, {"nsplit_b": 3}, 8),
           (500, 1000, 50, 5, {"pchunk": 1000}, 5), (520, 1600, 60, 7, {"pchunk": 1600, "nsplit_b": 2}, 8)]
 
 
