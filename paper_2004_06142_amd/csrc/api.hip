@@ -1530,7 +1530,7 @@ namespace {
 // (device) receives the solver's status (0 = converged).
 struct EighWs {
   double* Vh = nullptr;    // n * n
-  double* p2 = nullptr;    // 2n
+  double* p2 = nullptr;    // tridiag_ws_doubles(n): two vectors of n, and the one-launch reduction's exchange
   double* e = nullptr;     // n
   double* tau = nullptr;   // n
   double* T = nullptr;     // form_q_ws_doubles(n): Q's formation

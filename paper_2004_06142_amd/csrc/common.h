@@ -13,6 +13,21 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16;
 
+// ---------------------------------------------------------------- device helpers
+// 1 / sqrt(x) from the hardware estimate and one third-order step (relative error below 2^-60 before the final
+// rounding); x well inside the range of doubles.
+__device__ __forceinline__ double rsqrt_f64(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double r = fma(-x * y, y, 1.0);
+  return fma(y * r, fma(0.375, r, 0.5), y);
+}
+// Block id -> work item, each of the 8 XCDs taking one contiguous range of items (-1: padding block).
+__device__ __forceinline__ int xcd_item(int total) {
+  const int per = (total + 7) / 8;
+  const int w = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  return w < total ? w : -1;
+}
+
 // ---------------------------------------------------------------- orbital layout
 // Strong orbital of pair g is g; the nsingle singly occupied orbitals (Omega_I) follow, each its own
 // subspace; weak k of pair g is npairs + nsingle + ncwo*(npairs-1-g) + k.
@@ -555,7 +570,6 @@ hipError_t batch_persist(hipStream_t s, const PArgs& a, int tx, int ty, int bloc
 
 // ---------------------------------------------------------------- small kernels (k_small.hip)
 hipError_t fill_f64(hipStream_t s, double* p, long long n, double v);
-hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v);
 // E(n(gamma)) and dE/dgamma at fixed H_pp, J, K in one launch: out[0] = E, out[1 ..] = dE/dgamma (ngam of them).
 // out is written by the device and may be pinned host memory; so may gamma, up to ON_EVAL_HOST variables (each
 // block reads them).  nbuf, dEdn: nact doubles each; epart: 256; counter: one word, zero, and zero again afterwards.

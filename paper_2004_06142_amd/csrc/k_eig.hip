@@ -263,7 +263,10 @@ __device__ __forceinline__ int trd_ld(const int* p) { return __hip_atomic_load(p
 __device__ __forceinline__ double trd_ld(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void trd_st(double* p, double v) {   // to the die's L2
+// To the die's L2, where trd_ld of the die's other workgroups finds it: stores at workgroup scope go through the L1 to
+// the L2 that all workgroups of the list share (one die).  The language promises this of stores at agent scope only,
+// which would go past the L2; readers on another die would not see these.
+__device__ __forceinline__ void trd_st(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ bool trd_empty(double v) { return __double_as_longlong(v) == TRD_EMPTY; }
@@ -287,13 +290,7 @@ __global__ __launch_bounds__(256) void trd_reset_k(int n, int k0, int slots, dou
   }
 }
 
-// 1 / sqrt(x) from the hardware estimate and one third-order step (relative error below 2^-60 before the
-// final rounding); x well inside the range of doubles.
-__device__ __forceinline__ double rsqrt_f64(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double r = fma(-x * y, y, 1.0);
-  return fma(y * r, fma(0.375, r, 0.5), y);
-}
+// 1 / x from the hardware estimate and one third-order step.
 __device__ __forceinline__ double rcp_f64(double x) {
   double y = __builtin_amdgcn_rcp(x);
   double r = fma(-x, y, 1.0);

@@ -526,13 +526,6 @@ __device__ __forceinline__ void grouped_tile(int t, int tm_n, int tn_n, int& tm,
   tn = r / rows;
 }
 
-// Block id -> work item, each XCD taking one contiguous range of items (-1: padding block).
-__device__ __forceinline__ int xcd_item(int total) {
-  const int per = (total + NXCD - 1) / NXCD;
-  const int w = (int)(blockIdx.x % NXCD) * per + (int)(blockIdx.x / NXCD);
-  return w < total ? w : -1;
-}
-
 // Shapes of the workspace operands (WsDims): Ct is nact32 x ldk, each XT_P is nact32 x ldx and each
 // W_P is nact32 x ldw (nact32 = nact rounded up to 32), row-major, zero outside the valid block.
 

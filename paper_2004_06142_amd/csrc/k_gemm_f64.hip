@@ -377,13 +377,6 @@ __device__ __forceinline__ void tri_tile(int t, int& tm, int& tn) {
   tm = r;
   tn = t - r * (r + 1) / 2;
 }
-// Block id -> work item, each of the 8 XCDs taking one contiguous range of items (-1: padding block).
-__device__ __forceinline__ int xcd_item(int total) {
-  const int per = (total + 7) / 8;
-  const int w = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  return w < total ? w : -1;
-}
-
 constexpr int XM = 64;             // X: active orbitals x 128 or 64 stacked rows (P, mu)
 constexpr int BT = 64;             // b: square tiles on and below the diagonal
 constexpr int YN = 64;             // Y: 128 or 64 mu x 64 active orbitals

@@ -19,7 +19,6 @@ inline dim3 grid1(long long n, int per = NT) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < (n); i += (long long)gridDim.x * blockDim.x)
 
 __global__ void fill_f64_k(double* p, long long n, double v) { GRID_STRIDE(i, n) p[i] = v; }
-__global__ void fill_u16_k(u16* p, long long n, u16 v) { GRID_STRIDE(i, n) p[i] = v; }
 
 // alpha, beta of E_2 = sum_pq alpha_pq J_pq + beta_pq K_pq (Eqs. Eg, Efg, Efg_s); beta32: ld32 x ld32, zero past
 // nact.
@@ -905,10 +904,6 @@ __global__ void fock_ao_h_k(int nbf, int nq, const int32_t* __restrict__ q_idx, 
 hipError_t fill_f64(hipStream_t s, double* p, long long n, double v) {
   if (n <= 0) return hipSuccess;
   LAUNCH(fill_f64_k, grid1(n), dim3(NT), p, n, v);
-}
-hipError_t fill_u16(hipStream_t s, u16* p, long long n, u16 v) {
-  if (n <= 0) return hipSuccess;
-  LAUNCH(fill_u16_k, grid1(n), dim3(NT), p, n, v);
 }
 hipError_t on_eval(hipStream_t s, int kind, int nact, int npairs, int ncwo, int nsingle, int functional, int ngam,
                    const double* gamma, const double* Hpp, const double* J, const double* K, double* nbuf, double* epart,

@@ -154,14 +154,7 @@ __global__ __launch_bounds__(1024) void dc_prep_k(DcWs w, const double* __restri
   }
 }
 
-// 1 / sqrt(x) from the hardware estimate and one third-order step; x well inside the range of doubles.
-__device__ __forceinline__ double dc_rsqrt(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double r = fma(-x * y, y, 1.0);
-  return fma(y * r, fma(0.375, r, 0.5), y);
-}
-
-// One leaf per wavefront: implicitly shifted QL (each sweep chases the bulge of a shifted step from the
+// One leaf per wavefront: the implicitly shifted QL algorithm of Dubrulle, Martin and Wilkinson 1968 (each sweep chases the bulge of a shifted step from the
 // bottom of the unreduced part to its top, by plane rotations that are applied to the rows of V, one row
 // per lane).  An off-diagonal entry is taken as zero below eps (|d_i| + |d_i+1|) or 1e-3 eps of the
 // leaf's largest entry.  The rotations are one serial chain of about 1.7 m^2 / 2 links, every lane
@@ -209,7 +202,7 @@ __global__ __launch_bounds__(64) void dc_leaf_k(DcWs w) {
         const double q = fma(f, f, g * g);
         double r;
         if (__builtin_expect(q > 1e-280, 1)) {
-          const double y = dc_rsqrt(q);
+          const double y = rsqrt_f64(q);
           r = q * y;
           s = f * y;
           c = g * y;
