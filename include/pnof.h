@@ -219,25 +219,25 @@ pnof_status pnof_lagrangian_noalloc(pnof_ctx ctx, const pnof_problem* prob, cons
 /* diag_prev == NULL: S = (lambda + lambda^T)/2.  Otherwise S_pq = lambda_qp - lambda_pq for p < q
  * (mirrored; the orientation of Eq. Fockian for which the first-order energy change of Eq. ene1
  * is negative when diag_prev increases with the index), S_pp = diag_prev[p], and when zeta > 0
- * every off-diagonal |S_pq| > zeta is divided by ten until it is <= zeta.  (eps, U) = eigh(S) in float64, eps ascending, each column of U
- * signed so that its largest-magnitude entry (lowest index on ties) is positive;
- * C_new = C U.  lambda, C, C_new: nbf x nbf; eps: nbf; S_out (optional): the matrix diagonalised.
- * C_new must not alias C or lambda; eps may take diag_prev's place and S_out lambda's.  The Householder reduction to tridiagonal form runs on the
- * library's kernels (the last 1024 columns in one launch, those before with one launch each; one
- * launch per column throughout where the device is too busy for the first form); the library's
- * divide-and-conquer solver solves the
- * tridiagonal problem while a second stream of the context (default priority, forked and joined
- * with events) forms the product of the reflectors in blocks of 128; the eigenvectors are then that
- * product times the tridiagonal solver's.  nbf < 3 or nbf > 2048 use rocSOLVER's dsyevd.  Scratch:
- * about 10 nbf^2 doubles from the context's workspace (grown by the context if the lent one is
- * smaller).  PNOF_E_EIG if a secular equation of the tridiagonal solver does not converge, or
- * where lambda or diag_prev is not finite. */
+ * every off-diagonal |S_pq| > zeta is divided by ten until it is <= zeta.  (eps, U) = eigh(S) in
+ * float64, eps ascending, each column of U signed so that its largest-magnitude entry (lowest index
+ * on ties) is positive; C_new = C U.  lambda, C, C_new: nbf x nbf; eps: nbf; S_out (optional): the
+ * matrix diagonalised.  C_new must not alias C or lambda; eps may take diag_prev's place and S_out
+ * lambda's.  The Householder reduction to tridiagonal form runs on the library's kernels (the last
+ * 1024 columns in one launch, those before with one launch each; where the device is too busy for the
+ * first form, one launch per column and the last 128 in one workgroup); the library's
+ * divide-and-conquer solver solves the tridiagonal problem while a second stream of the context
+ * (default priority, forked and joined with events) forms the product of the reflectors in blocks of
+ * 128; the eigenvectors are then that product times the tridiagonal solver's.  nbf < 3 or nbf > 2048
+ * use rocSOLVER's dsyevd.  Scratch: about 10 nbf^2 doubles from the context's workspace (grown by the
+ * context if the lent one is smaller).  PNOF_E_EIG if a secular equation of the tridiagonal solver
+ * does not converge, or where lambda or diag_prev is not finite. */
 pnof_status pnof_orbital_step(pnof_ctx ctx, int32_t nbf, const double* lambda, const double* C,
                               const double* diag_prev, double zeta, double* C_new, double* eps,
                               double* S_out);
 /* Form of that reduction, also in pnof_optimize: 0, as described (the default); 1, a launch per column
- * throughout; 2, the one-launch form declines as on a busy device, and the launches per column follow.
- * For testing. */
+ * up to the last 128; 2, as on a busy device: the one-launch form finds too few of its workgroups
+ * running.  For testing. */
 pnof_status pnof_set_reduction(pnof_ctx ctx, int32_t form);
 
 /* ---- NOF-MP2 reference terms (Section 4, Eqs. HFL and Esta) ----------------------------------- */

@@ -653,8 +653,8 @@ hipError_t sign_fix_cols(hipStream_t s, int nbf, double* Ucm);
 // overwritten; d (n), e (n - 1), tau (n - 1) and the reflectors as rows of Vh (n x n, read column-major:
 // the lower-storage layout of ormtr); ws: tridiag_ws_doubles(n) doubles.  info[1] (device) is set when
 // the one-launch form declined (too few of its workgroups running at once; d, e, tau are then finite but
-// no result): call again with REDUCE_LAUNCHES, one launch per column.  REDUCE_DECLINE: the one-launch form asks for
-// more workgroups than there are, so that it declines.
+// no result): call again with REDUCE_LAUNCHES, one launch per column up to the last 128.  REDUCE_DECLINE: the
+// one-launch form asks for more workgroups than there are.
 constexpr int TRIDIAG_MAX_N = 2048;   // three float64 vectors of n in LDS
 enum { REDUCE_AUTO = 0, REDUCE_LAUNCHES = 1, REDUCE_DECLINE = 2 };
 long long tridiag_ws_doubles(int n);

@@ -239,9 +239,13 @@ __global__ __launch_bounds__(TNT) void trd_step_k(int n, int k, double* __restri
 // Which workgroups take part is settled at run time: the first one to start claims its die, those of
 // other dies leave at once, and the first one closes the list when `want` have registered or TRD_WINDOW
 // ticks have passed.  A workgroup on the list is running, so nothing waits for one that is not; with
-// fewer than are needed to hold the rows (a device busy with other work) it declines (info[1] = 1, d, e,
-// tau zero), and the caller takes the launches per column.  A wait that outlasts TRD_STALL ticks ends the
-// same way, so every wavefront ends.
+// fewer than are needed to hold the rows (a device busy with other work) the first one takes all rows of a block of
+// at most 128 itself; otherwise it declines (info[1] = 1, d, e, tau zero), and the caller takes the launches per
+// column, after the rest of the step has run on zeros.  A wait that outlasts TRD_STALL ticks ends the same way, so
+// every wavefront ends.
+// Beside products that fill the chip on another stream (4096^3 in float32, one after the other) the orbital step of 75
+// functions takes 6.5 ms, of 140 16.6, of 300 13.5 (with launches per column and one workgroup for the last 128
+// columns 6.5, 10.3 and 54.8); all 8 x 32 workgroups instead of 8 x `want`, and a decline for 75, took 10.4 there.
 // One workgroup (m0 <= 32): p and the row go through LDS, one barrier per column.
 //
 // What bounds it: the chain of two wavefront sums, a square root and, in MULTI, one exchange per column.
@@ -250,8 +254,10 @@ __global__ __launch_bounds__(TNT) void trd_step_k(int n, int k, double* __restri
 // (2.24 ms); from 1024 on per column 4.6 us in here against 7 us a launch (n = 1200: 6.0 against
 // 6.7 ms).  A column at n = 500: 2.2 us, of it 0.5 waiting for the other workgroups' values.
 constexpr int TRD_SOLO = 32;                 // at most: one workgroup
+constexpr int TRD_SOLO2 = 128;               // and after launches per column
 constexpr int TRD_MMAX = 1024;               // at most: the rows fit one die's registers
-constexpr int TRD_PAD = 82 * 1024;           // LDS request that keeps a second workgroup off a compute unit
+constexpr int TRD_PAD = 82 * 1024;           // LDS request that keeps a second workgroup off a compute unit (blocks over
+                                             // 256: fewer workgroups spread by themselves, and wait less without it)
 constexpr int TRD_WMAX = 64;                 // workgroups that take part at most
 constexpr int TRD_CTL = 32;                  // words: die, registered, closed, abort
 constexpr int TRD_SLOTS = 4;
@@ -298,8 +304,10 @@ __device__ __forceinline__ double rcp_f64(double x) {
   return y;
 }
 
-// Registers this workgroup (MULTI): its index among the W taking part, or -1 to leave.
-__device__ int trd_register(int* ctl, int want, int need, int* info, int& W) {
+// Registers this workgroup (MULTI): its index among the W taking part, TRD_ALONE for the first one if there are too few
+// and it is to go on without the others, or -1 to leave.
+constexpr int TRD_ALONE = -2;
+__device__ int trd_register(int* ctl, int want, int need, bool alone, int* info, int& W) {
   __shared__ int s_id, s_w;
   if (threadIdx.x == 0) {
     int id = -1, w = 0;
@@ -314,7 +322,8 @@ __device__ int trd_register(int* ctl, int want, int need, int* info, int& W) {
           const int cnt = atomicAdd(ctl + 1, 1 << 20);   // late ones see a count past any `want`
           w = cnt < want ? cnt : want;
           if (w < need) {
-            atomicExch(info + 1, 1);
+            if (alone) id = TRD_ALONE;
+            else atomicExch(info + 1, 1);
             w = -1;
           }
           atomicExch(ctl + 2, w);
@@ -322,7 +331,7 @@ __device__ int trd_register(int* ctl, int want, int need, int* info, int& W) {
           while ((w = trd_ld(ctl + 2)) == 0 && wall_clock64() - t0 < TRD_STALL) __builtin_amdgcn_s_sleep(2);
           if (w == 0) atomicExch(info + 1, 1);
         }
-        id = w > 0 && t < w ? t : -1;
+        if (w > 0) id = t < w ? t : -1;
       }
     }
     s_id = id;
@@ -390,26 +399,24 @@ __device__ __forceinline__ void trd_pick(int r, F f) {
   }
 }
 
+template <int NJ>
+struct TrdLds {   // by parity of the column: a slow wavefront may still read one while a fast one fills the other
+  double ps[2][64 * NJ], rs[2][64 * NJ], vs[2][64 * NJ];
+  int stop;
+};
+// The columns, by workgroup id of W.
 template <bool MULTI, int NW, int NR, int NJ>
-__global__ __launch_bounds__(64 * NW) void trd_reduce_k(int n, int k0, int want, int need, const double* __restrict__ A,
-                                                    double* __restrict__ Vh, const double* __restrict__ pprev,
-                                                    double* __restrict__ d, double* __restrict__ e,
-                                                    double* __restrict__ tau, int* ctl, double* xch, int* info) {
+__device__ __forceinline__ void trd_columns(TrdLds<NJ>& sm, int id, int W, int n, int k0, const double* __restrict__ A,
+                                            double* __restrict__ Vh, const double* __restrict__ pprev,
+                                            double* __restrict__ d, double* __restrict__ e, double* __restrict__ tau,
+                                            int* ctl, double* xch, int* info) {
   constexpr int M = 64 * NJ;
   constexpr int NG = NR > 4 ? 8 : NR == 3 ? 4 : NR, NP = (NR + NG - 1) / NG * NG;   // rows summed together
   constexpr int NL = MULTI ? (NJ + NW - 1) / NW : 1;  // values of each kind that a thread reads
-  // by parity of the column: a slow wavefront may still read one while a fast one fills the other
-  __shared__ double ps[2][M], rs[2][M], vs[2][M];
-  __shared__ int s_stop;
+  auto &ps = sm.ps, &rs = sm.rs, &vs = sm.vs;
+  int& s_stop = sm.stop;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int m0 = n - k0;
-  int id = 0, W = 1;
-  if constexpr (MULTI) {
-    id = trd_register(ctl, want, need, info, W);
-    if (id < 0) return;
-    id = __builtin_amdgcn_readfirstlane(id);
-    W = __builtin_amdgcn_readfirstlane(W);
-  }
   double a[NR][NJ], v[NJ];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -634,6 +641,25 @@ __global__ __launch_bounds__(64 * NW) void trd_reduce_k(int n, int k0, int want,
   }
 }
 
+template <bool MULTI, int NW, int NR, int NJ>
+__global__ __launch_bounds__(64 * NW, MULTI && NJ == 2 ? 2 : 1) void trd_reduce_k(int n, int k0, int want, int need, const double* __restrict__ A,
+                                                    double* __restrict__ Vh, const double* __restrict__ pprev,
+                                                    double* __restrict__ d, double* __restrict__ e,
+                                                    double* __restrict__ tau, int* ctl, double* xch, int* info) {
+  __shared__ TrdLds<NJ> sm;
+  if constexpr (MULTI) {
+    constexpr bool ALONE = 64 * NJ == TRD_SOLO2;   // one workgroup can hold the rows
+    int W;
+    const int id = __builtin_amdgcn_readfirstlane(trd_register(ctl, want, need, ALONE, info, W));
+    if constexpr (ALONE)
+      if (id == TRD_ALONE) trd_columns<false, NW, TRD_SOLO2 / NW, NJ>(sm, 0, 1, n, k0, A, Vh, pprev, d, e, tau, ctl, xch, info);
+    if (id < 0) return;
+    trd_columns<true, NW, NR, NJ>(sm, id, __builtin_amdgcn_readfirstlane(W), n, k0, A, Vh, pprev, d, e, tau, ctl, xch, info);
+  } else {
+    trd_columns<false, NW, NR, NJ>(sm, 0, 1, n, k0, A, Vh, pprev, d, e, tau, ctl, xch, info);
+  }
+}
+
 // ---------------------------------------------------------------- back-transformation
 // Q = H_0 ... H_{n-2} formed explicitly (column-major n x n); the eigenvectors are then Q times
 // those of the tridiagonal matrix.  The reflectors are taken in blocks of QNB:
@@ -788,7 +814,7 @@ hipError_t tridiag_f64(hipStream_t s, int n, double* A, double* Vh, double* ws, 
   double* p2 = ws;                  // two vectors of n by column parity
   double* xch = ws + 2LL * n;
   int* ctl = reinterpret_cast<int*>(xch + TRD_SLOTS * trd_slot(TRD_MMAX));
-  const int kend = std::max(0, n - (form == REDUCE_LAUNCHES ? TRD_SOLO : TRD_MMAX));   // columns 0 .. kend-1: a launch each
+  const int kend = std::max(0, n - (form == REDUCE_LAUNCHES ? TRD_SOLO2 : TRD_MMAX));   // columns 0 .. kend-1: a launch each
   const size_t shm = 3 * (size_t)n * sizeof(double);
   for (int k = 0; k < kend; ++k) {
     const int blocks = std::max(1, (n - 1) / TROWS - trd_group_base(k) + 1);
@@ -801,16 +827,18 @@ hipError_t tridiag_f64(hipStream_t s, int n, double* A, double* Vh, double* ws, 
   hipLaunchKernelGGL((trd_reduce_k<MULTI, NW, NR, NJ>), dim3(grid), dim3(64 * NW), pad, s, n, kend, want,               \
                      form == REDUCE_DECLINE ? INT_MAX : (int)cdiv(m, NW * NR), A, Vh, pp, d, e, tau, ctl, xch, info)
   if (m <= TRD_SOLO) TRD_REDUCE(false, 8, 4, 1, 1, 1, 0);
+  else if (form == REDUCE_LAUNCHES) TRD_REDUCE(false, 16, 8, 2, 1, 1, 0);
   else {
     const int M = m <= 128 ? 128 : m <= 256 ? 256 : m <= 512 ? 512 : m <= 768 ? 768 : 1024, slots = TRD_SLOTS * trd_slot(M);
     hipLaunchKernelGGL(trd_reset_k, dim3(cdiv(slots, 1024)), dim3(256), 0, s, n, kend, slots, xch, ctl, info, d, e, tau);
-    // workgroups for 32 compute units on each of 8 dies, TRD_PAD bytes of LDS each: one per compute unit
-    const int grid = 8 * 32;
-    if (M == 128) TRD_REDUCE(true, 4, 2, 2, grid, cdiv(m, 8), TRD_PAD);
-    else if (M == 256) TRD_REDUCE(true, 4, 2, 4, grid, cdiv(m, 8), TRD_PAD);
-    else if (M == 512) TRD_REDUCE(true, 4, 4, 8, grid, cdiv(m, 16), TRD_PAD);
-    else if (M == 768) TRD_REDUCE(true, 8, 3, 12, grid, cdiv(m, 24), TRD_PAD);
-    else TRD_REDUCE(true, 4, 8, 16, grid, cdiv(m, 32), TRD_PAD);
+    // `want` workgroups on each of 8 dies
+#define TRD_MULTI(NW, NR, NJ) TRD_REDUCE(true, NW, NR, NJ, 8 * cdiv(m, NW * NR), cdiv(m, NW * NR), NJ <= 4 ? 0 : TRD_PAD)
+    if (M == 128) TRD_MULTI(4, 2, 2);
+    else if (M == 256) TRD_MULTI(4, 2, 4);
+    else if (M == 512) TRD_MULTI(4, 4, 8);
+    else if (M == 768) TRD_MULTI(8, 3, 12);
+    else TRD_MULTI(4, 8, 16);
+#undef TRD_MULTI
   }
 #undef TRD_REDUCE
   return hipGetLastError();

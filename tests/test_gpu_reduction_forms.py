@@ -1,7 +1,8 @@
-"""The orbital step where its one-launch reduction declines (as on a busy device; here the context asks for it)
-and a launch per column follows, at the sizes where the forms change: 32 columns in one workgroup, then the
-register blocks of 128, 256, 512, 768 and 1024 columns, and one launch per column before those.  The results are
-bit for bit those of a launch per column from the start, also where outputs take the place of inputs that the
+"""The orbital step where its one-launch reduction finds too few of its workgroups running (as on a busy device; here
+the context asks for it), at the sizes where the forms change: 32 columns in one workgroup, then the register blocks
+of 128 (the first workgroup goes on alone), 256, 512, 768 and 1024 columns (a launch per column follows, one workgroup
+for the last 128), and one launch per column before those.  The results are bit for bit those of a launch per column
+from the start, also where outputs take the place of inputs that the
 first pass has read: eps in diag_prev's buffer, S_out in lambda's.  Bars against the oracle as in
 test_gpu_reduction.py."""
 import numpy as np
