@@ -289,11 +289,12 @@ Plan make_plan(const pnof_problem* p, const pnof_tuning& tu, PlanForm form = PLA
   const int tt = cdiv(pl.nact, tile);
   const long long ntri = (long long)tt * (tt + 1) / 2;
   const long long auto2 = std::max(1LL, (1024 + ntri - 1) / ntri);
-  // b: two (split) or three blocks per compute unit, whole rounds (1200 functions, 55 tiles of 164 rows: 19
-  // splits are 4.08 rounds of 256, 42.7 ms over the step; 27 of the present form, 35.1).  The sums of b^2 are
-  // float64, in the split mode over float32 sums of krows rows: the even share, rounded down, of a chunk's rows
-  // among 1024 blocks of one sum each (or among the splits that were set), at most 8.  (8 rows whatever the size would take 0.11 ms off the 5.3 ms of
-  // 500 functions with 300 active, which add to the float64 sums every 2 rows, and leave K rounded more often.)
+  // b: two (split) or three blocks per compute unit at once, the splits by best_splits (1200 functions, 55 tiles of
+  // 164 rows: it takes 33, b 35.4 to 36.8 ms over the step; 18 splits 35.5, 27 34.9, 19, whose last round of 512
+  // is nearly empty, 40.3).  The sums of b^2 are float64, in the split mode over float32 sums of krows rows: the even
+  // share, rounded down, of a chunk's rows among 1024 blocks of one sum each (or among the splits that were set), at
+  // most 8.  (8 rows whatever the size would take 0.11 ms off the 5.3 ms of 500 functions with 300 active, which add
+  // to the float64 sums every 2 rows, and leave K rounded more often.)
   pl.ksums = tu.nsplit_b > 0 ? tu.nsplit_b : (int)std::min<long long>(auto2, INT_MAX);
   pl.ns2 = tu.nsplit_b > 0 ? tu.nsplit_b
            : pl.split      ? best_splits(pl.pc, ntri, 512, 0.25, 0.1)

@@ -660,7 +660,7 @@ __device__ __forceinline__ void gemm1_body(int w, const G1Args& g, void* ext = n
 // 2 x WGN waves.  128 tile, WGN 2: 4 waves of 64 x 64, two blocks per compute unit: such a wave reads 16 KB of LDS per
 // k-tile for 48 products, a 64 x 32 one 12 KB for 24, which LDS bandwidth bounds, and while one block forms K and W
 // the other keeps the matrix cores busy; against 8 waves and one block, b over the step: 1200 functions 42.7 ->
-// 36.1 ms, 500 functions (300 active, 2000 rows) 1.40 -> 0.91, 413 functions 0.85 -> 0.55 (with the splits that the
+// 35.5 ms, 500 functions (300 active, 2000 rows) 1.40 -> 1.05, 413 functions 0.85 -> 0.66 (with the splits that the
 // planner takes for it).  WGN 4: 8 waves of 64 x 32, for launches whose blocks wait rather than compute (G2_FEW).
 // The sums of b^2 are float32 over at most krows rows (at most 8), then float64 in Kpart: each block adds to its own
 // partial sums only, with atomics, which need no wait (as loads and stores, 1200 functions in 164 splits 53.0 ms, with
