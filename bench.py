@@ -28,15 +28,15 @@ KSRC = os.path.join(ROOT, "paper_2004_06142_amd", "csrc")
 # once the source changes the figure no longer applies and traffic is reported as null.
 TRAFFIC = {
     # profiles/c5_df1200_hbm_traffic.md: C5, bf16 split, 164-row chunks (read + written bytes per launch)
-    ("gemm1_kernel", 3): {"bytes": 1278915712 + 983606467,
+    ("gemm1_kernel", 3): {"bytes": 1308260574 + 982350308,
                           "plan": {"pchunk": 164, "x_variant": 3},
-                          "sha256": {"k_gemm_bf16.hip": "557a1af7cf4674cfb51e8ab77657966c99730bed781145d0f07dd08fb69aca60"}},
-    ("gemm2_kernel", 3): {"bytes": 4925346117 + 712677698,
+                          "sha256": {"k_gemm_bf16.hip": "76abe91e801679dc910c1c07514db367d9461b8d53c698552bb09f8d7c7a43fc"}},
+    ("gemm2_kernel", 3): {"bytes": 4737697408 + 808110320,
                           "plan": {"pchunk": 164, "nsplit_b": 18},
-                          "sha256": {"k_gemm_bf16.hip": "557a1af7cf4674cfb51e8ab77657966c99730bed781145d0f07dd08fb69aca60"}},
-    ("gemm3_kernel", 3): {"bytes": 2575966956 + 57659388,
+                          "sha256": {"k_gemm_bf16.hip": "76abe91e801679dc910c1c07514db367d9461b8d53c698552bb09f8d7c7a43fc"}},
+    ("gemm3_kernel", 3): {"bytes": 2583656250 + 57649574,
                           "plan": {"pchunk": 164, "nsplit_y": 10, "y_variant": 3},
-                          "sha256": {"k_gemm_bf16.hip": "557a1af7cf4674cfb51e8ab77657966c99730bed781145d0f07dd08fb69aca60"}},
+                          "sha256": {"k_gemm_bf16.hip": "76abe91e801679dc910c1c07514db367d9461b8d53c698552bb09f8d7c7a43fc"}},
 }
 GOLDEN_C5 = os.path.join(ROOT, "tests", "golden", "c5_df1200_expected.json")
 
