@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 DEV = torch.device("cuda", 0)
 AUTO, LAUNCHES, DECLINE = 0, 1, 2
-SIZES = [3, 32, 33, 34, 128, 129, 145, 256, 257, 513, 769, 1024, 1025, 1057]
+SIZES = [3, 32, 33, 34, 48, 49, 64, 128, 129, 145, 256, 257, 513, 769, 1024, 1025, 1057]
 
 
 def t(a):
